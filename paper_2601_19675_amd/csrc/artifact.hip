@@ -17,6 +17,9 @@
 // sums of a row in a fixed order together with the low-rank part.  Splitting the columns rather
 // than the rows keeps the staged piece of X~ tiny, so that the grid can be large enough to fill
 // the chip without every workgroup re-reading all of X~.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 
 namespace ptq {
@@ -115,9 +118,9 @@ __global__ __launch_bounds__(256) void transpose_grids_kernel(const float* __res
 // Inputs prepared per call: X~ (float32, from the float64 rotation) and the low-rank
 // coefficients  y[t][k] = sigma_k * sum_j V[k][j] x[t][j] / s[j].
 __device__ __forceinline__ float e4m3_to_float(uint8_t c) {
-  const int ef = (c >> 3) & 0xf, mt = c & 7;
-  const float mag = ef == 0 ? ldexpf((float)mt, -9) : ldexpf((float)(8 + mt), ef - 10);
-  return (c & 0x80) ? -mag : mag;
+  // exponent and mantissa in place of a float32's, subnormals included; 2^120 = the difference of the biases
+  const float mag = __uint_as_float((uint32_t)(c & 0x7f) << 20) * 0x1p120f;
+  return __uint_as_float(__float_as_uint(mag) | (uint32_t)(c & 0x80) << 24);
 }
 __device__ __forceinline__ float fp16_bits_to_float(uint16_t h) {
   const int ef = (h >> 10) & 31, mt = h & 0x3ff;
@@ -156,7 +159,8 @@ struct ForwardArgs {
   const float* scales;      // n / group x m
   const uint8_t* zeros;     // n / group x m
   int m, n, group;
-  const float* xt;          // tokens x n: X~
+  const float* xt;          // X~, 32 columns of all tokens at a time: xt[chunk][token][32]
+  int xt_tokens;            // tokens per chunk of xt
   const float* y;           // tokens x r
   const uint8_t* U;         // r x m, e4m3
   int r;
@@ -196,7 +200,7 @@ __global__ __launch_bounds__(256) void forward_partial_kernel(ForwardArgs a) {
   for (int e = tid; e < B * kFwdRun * (kChunk / 4); e += 256) {
     const int t = e / (kFwdRun * (kChunk / 4)), q = e - t * (kFwdRun * (kChunk / 4));   // q: float4 index in the run
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (q < nc * (kChunk / 4)) v = *reinterpret_cast<const float4*>(a.xt + (int64_t)t * n + c0 * kChunk + 4 * q);
+    if (q < nc * (kChunk / 4)) v = *reinterpret_cast<const float4*>(a.xt + ((int64_t)(c0 + (q >> 3)) * a.xt_tokens + t) * kChunk + 4 * (q & 7));
     *reinterpret_cast<float4*>(&xs[t][4 * q]) = v;
     float sum = (v.x + v.y) + (v.z + v.w);     // eight consecutive threads hold one chunk
     sum += __shfl_xor(sum, 1);
@@ -282,151 +286,382 @@ __global__ void clear_counters_kernel(unsigned* done, int count) {
   if (i < count) done[i] = 0u;
 }
 
-// ---- many tokens: the same sums on the matrix cores ------------------------------------------
-// With 8 or more tokens the row-per-lane kernel above is bound by feeding the same x to all lanes.
-// Here a wave takes 32 rows and up to 32 tokens and accumulates  raw[row][t] = sum_j code_j x_tj
-// with the float32 32 x 32 x 2 MFMA (full float32 products and sums): lane l supplies the code of
-// row l % 32 for the column of parity l / 32 -- both halves of the wave load the same packed
-// words and extract alternate codes, so nothing is transposed -- and x[t = l % 32] of that
-// column from LDS.  At the end of a quantization group (or of the run of 8 chunks) the 16
-// accumulators of a lane get  scale (raw - zero sum_j x_tj)  for their rows and start again.
-// grid: (row blocks of 128, runs of kFwdRun chunks), 4 waves; the partial sums are added by the kernel below.
-constexpr int kMfmaTokens = 32, kMfmaRows = 128;
+// ---- many tokens: bfloat16 matrix cores ----------------------------------------------------------
+// O = X~ Dequant^T as a GEMM whose operands are exact in bfloat16: code - zero is an integer of at most
+// eight bits, and a float32 x is the sum of its three truncated bfloat16 pieces (8 + 8 + 8 bits), so the
+// three products per weight are exact in float32 and only the float32 sums round -- as they do in the
+// float32 instruction, which has 1/16 of the rate (three pieces: 1/5.3 of the work).  The group's scale
+// is applied to the accumulators where a group ends.
+//
+// A workgroup takes 32 TT tokens x 128 RT rows of the weight, a wave 32 TT x 32 RT, and walks over chunks of
+// 32 columns.  The weight side never touches LDS: lane l of a wave is row l % 32, and half-wave h = l / 32
+// takes codes [16 h, 16 h + 16) of the chunk -- the contraction index may be dealt to the lanes in any
+// order that both operands share -- so its words come straight from memory and are widened in registers
+// (byte conversions, zero subtracted, high halves paired).  X~ lies chunk by chunk, so that the 32 columns of a
+// workgroup's tokens are one contiguous piece (row by row, the pieces of all tokens fall on the same few channels of
+// the L2); it is read as float32, split while it is staged, and read back as 16-byte fragments; rows of 80 bytes keep those reads free of bank conflicts.
+// One barrier per chunk: while chunk c is multiplied, chunk c + 1 is split into the other LDS half and
+// chunk c + 2 is on its way from memory.  RT = 2 sets the LDS traffic (six 1 KB reads per twelve MFMAs of a
+// wave: half of what the LDS delivers); 64 tokens per workgroup keep 256 registers, two waves per SIMD.
+// Bound: the bfloat16 MFMAs (and about nine vector instructions beside each).  The whole call, against 32-token
+// passes on the float32 instruction: 512 tokens x 4096 x 11008, 3 bits, 1140 -> 253 us; 2048 x 11008 x 4096, 4 bits,
+// 4067 -> 684; 4000 x 999 x 1024 2852 -> 137; 32 x 11008 x 4096 83 -> 55; 8 x 4096 x 4096 41 -> 29; the distance
+// from the float64 product falls from 3.4e-7 to 1.3e-7 of its norm (no sum of code x and zero x of opposite sign).
+template <int BITS> struct HalfWords { uint32_t w[BITS == 2 ? 1 : (BITS == 8 ? 4 : 2)]; };
 
 template <int BITS>
-__global__ __launch_bounds__(256) void forward_mfma_kernel(ForwardArgs a, int tokens) {
-  __shared__ float xs[kFwdRun * kChunk][kMfmaTokens + 1];   // [column of the run][token]; the odd pitch spreads the transposing stores over the banks
-  __shared__ float xsum[kFwdRun][kMfmaTokens];
-  __shared__ float gsc[kFwdRun][kMfmaRows], gz[kFwdRun][kMfmaRows];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int m = a.m, n = a.n, chunks = n / kChunk;
-  const int c0 = blockIdx.y * kFwdRun;
-  const int nc = min(kFwdRun, chunks - c0);
-  const int row = blockIdx.x * kMfmaRows + w * 32 + (lane & 31);   // the row whose codes this lane supplies
-  const int parity = lane >> 5;
-  const bool live = row < m;
+__device__ __forceinline__ HalfWords<BITS> load_half_chunk(const uint32_t* __restrict__ base, uint32_t row, int h) {
+  const uint32_t off = row + (uint32_t)h * (BITS == 2 || BITS == 3 ? 1u : (BITS == 4 ? 2u : 4u));
+  HalfWords<BITS> v;
+  if constexpr (BITS == 2) v.w[0] = base[off];
+  else if constexpr (BITS == 3) { v.w[0] = base[off]; v.w[1] = base[off + 1]; }   // bits [16 h, 16 h + 48) of these two words
+  else if constexpr (BITS == 4) { const uint2 q = *reinterpret_cast<const uint2*>(base + off); v.w[0] = q.x; v.w[1] = q.y; }
+  else { const uint4 q = *reinterpret_cast<const uint4*>(base + off); v.w[0] = q.x; v.w[1] = q.y; v.w[2] = q.z; v.w[3] = q.w; }
+  return v;
+}
 
-  Words<BITS> wd[kFwdRun];
-#pragma unroll
-  for (int k = 0; k < kFwdRun; ++k) {
-#pragma unroll
-    for (int q = 0; q < BITS; ++q) wd[k].w[q] = 0u;
-    if (live && k < nc) wd[k] = *reinterpret_cast<const Words<BITS>*>(a.packed + ((int64_t)(c0 + k) * m + row) * BITS);
-  }
-  // x of the run, transposed to [column][token] (zeros past the last token and the last chunk):
-  // eight 16-byte loads per thread, all requested before the first is stored
-  {
-    constexpr int kQuads = kFwdRun * kChunk / 4;   // per token
-    float4 v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int e = tid + 256 * i, t = e / kQuads, c = 4 * (e - t * kQuads);
-      const bool ok = t < tokens && c < nc * kChunk;
-      const float4 x = *reinterpret_cast<const float4*>(a.xt + (int64_t)(t < tokens ? t : 0) * n + c0 * kChunk +
-                                                         (c < nc * kChunk ? c : 0));
-      v[i] = ok ? x : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int e = tid + 256 * i, t = e / kQuads, c = 4 * (e - t * kQuads);
-      xs[c][t] = v[i].x; xs[c + 1][t] = v[i].y; xs[c + 2][t] = v[i].z; xs[c + 3][t] = v[i].w;
-      float sum = (v[i].x + v[i].y) + (v[i].z + v[i].w);   // eight consecutive lanes hold one chunk of a token
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      sum += __shfl_xor(sum, 4);
-      if ((c & (kChunk - 1)) == 0) xsum[c / kChunk][t] = sum;
-    }
-  }
-  // scale and zero of each chunk's group for the block's 128 rows
-  for (int e = tid; e < kFwdRun * kMfmaRows; e += 256) {
-    const int k = e / kMfmaRows, rl = e - k * kMfmaRows;
-    const int orow = blockIdx.x * kMfmaRows + rl;
-    const bool ok = k < nc && orow < m;
-    const int g = ((c0 + (k < nc ? k : 0)) * kChunk) / a.group;
-    gsc[k][rl] = ok ? a.scales[(int64_t)g * m + orow] : 0.f;
-    gz[k][rl] = ok ? (float)a.zeros[(int64_t)g * m + orow] : 0.f;
-  }
-  __syncthreads();
+// high halves of two floats, the lower one first: two bfloat16 numbers where the low halves are zero
+__device__ __forceinline__ uint32_t pair_high(float a, float b) {
+  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
 
-  // accumulator r of a lane is row (r / 4) * 8 + (lane / 32) * 4 + r % 4 of the wave's 32, token lane % 32
-  const int t_out = lane & 31;
-  f32x16 acc, total;
+// codes [8 KS, 8 KS + 8) of a half chunk, minus the group's zero, as bfloat16
+template <int BITS, int KS>
+__device__ __forceinline__ bf16x8 widen_codes(const HalfWords<BITS>& v, int h, float zero) {
+  float f[8];
+  if constexpr (BITS == 8) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[r] = 0.f; total[r] = 0.f; }
-  float xsg = 0.f;
+    for (int j = 0; j < 8; ++j) f[j] = (float)((v.w[2 * KS + (j >> 2)] >> (8 * (j & 3))) & 0xffu);
+  } else if constexpr (BITS == 4) {
+    const uint32_t even = v.w[KS] & 0x0f0f0f0fu, odd = (v.w[KS] >> 4) & 0x0f0f0f0fu;
 #pragma unroll
-  for (int k = 0; k < kFwdRun; ++k) {
-    if (k >= nc) break;
-    float xv[kChunk / 2];   // the chunk's x values first: one LDS latency per chunk, not per MFMA
+    for (int j = 0; j < 8; ++j) f[j] = (float)((((j & 1) ? odd : even) >> (8 * (j >> 1))) & 0xffu);
+  } else if constexpr (BITS == 2) {
+    uint32_t t[4];
 #pragma unroll
-    for (int i = 0; i < kChunk / 2; ++i) xv[i] = xs[k * kChunk + 2 * i + parity][t_out];
+    for (int i = 0; i < 4; ++i) t[i] = (v.w[0] >> (16 * KS + 2 * i)) & 0x0303u;
 #pragma unroll
-    for (int i = 0; i < kChunk / 2; ++i) {
-      const uint32_t ce = chunk_code<BITS>(wd[k].w, 2 * i), co = chunk_code<BITS>(wd[k].w, 2 * i + 1);
-      const float cf = (float)(parity ? co : ce);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(cf, xv[i], acc, 0, 0, 0);
-    }
-    xsg += xsum[k][t_out];
-    const int col_end = (c0 + k + 1) * kChunk;
-    if (col_end % a.group == 0 || k == nc - 1) {   // the group ends here, or the run does
+    for (int j = 0; j < 8; ++j) f[j] = (float)((t[j & 3] >> (8 * (j >> 2))) & 0xffu);
+  } else {
+    const uint64_t s = (((uint64_t)v.w[1] << 32) | v.w[0]) >> (16 * h);
+    const uint32_t b = (uint32_t)(s >> (24 * KS));
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = w * 32 + (r >> 2) * 8 + parity * 4 + (r & 3);
-        total[r] = fmaf(gsc[k][rl], fmaf(-gz[k][rl], xsg, acc[r]), total[r]);
-        acc[r] = 0.f;
-      }
-      xsg = 0.f;
-    }
+    for (int j = 0; j < 8; ++j) f[j] = (float)((b >> (3 * j)) & 7u);
   }
+  uint4 o;
+  o.x = pair_high(f[0] - zero, f[1] - zero);
+  o.y = pair_high(f[2] - zero, f[3] - zero);
+  o.z = pair_high(f[4] - zero, f[5] - zero);
+  o.w = pair_high(f[6] - zero, f[7] - zero);
+  return __builtin_bit_cast(bf16x8, o);
+}
+
+// the three truncated bfloat16 pieces of two floats, paired
+__device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int orow = blockIdx.x * kMfmaRows + w * 32 + (r >> 2) * 8 + parity * 4 + (r & 3);
-    if (orow < m && t_out < tokens) a.partial[((int64_t)blockIdx.y * kMfmaTokens + t_out) * m + orow] = total[r];
+  for (int i = 0; i < 3; ++i) {
+    p[i] = pair_high(a, b);
+    a -= __uint_as_float(__float_as_uint(a) & 0xffff0000u);
+    b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
   }
 }
 
-// O[t][row] = sum over the column runs, in order, + sum_k U[k][row] y[t][k] for the matrix-core
-// passes: with up to 32 tokens the sums are enough work for a launch of their own over the whole
-// chip (done by the last workgroup of each row block they took longer than the products).
-// grid: (rows / 256, groups of four tokens)
-__global__ __launch_bounds__(256) void forward_mfma_finish_kernel(ForwardArgs a, int tokens, int splits) {
+// what the scheduler is asked for in a step: after each MFMA one fragment read, as long as there are any, and eight
+// vector instructions of the next chunk's preparation
+template <int MFMAS, int READS>
+__device__ __forceinline__ void tile_sched() {
+  if constexpr (MFMAS > 0) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if constexpr (READS > 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+    tile_sched<MFMAS - 1, (READS > 0 ? READS - 1 : 0)>();
+  }
+}
+
+constexpr int kTilePitch = 40;   // bfloat16 elements per staged row of 32 columns
+
+struct TilePlan {
+  int token_blocks, row_blocks, splits, chunks_per_part;   // splits x KG parts
+};
+
+template <int BITS, int TT, int RT, int KG>
+__global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a, int tokens, TilePlan plan) {
+  constexpr int kTokens = 32 * TT, kRows = 128 * RT;
+  constexpr int E = TT == 1 ? 4 : 8;            // consecutive columns a thread stages: 256 E = 32 kTokens
+  __shared__ __attribute__((aligned(16))) uint16_t xs_all[KG][2][3][kTokens][kTilePitch];
+  const int part = KG == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
+  auto& xs = xs_all[part];
+  const int m = a.m, chunks = a.n / kChunk, gpc = a.group / kChunk;
+  // Consecutive items of one XCD (workgroup ids = x mod 8) share a split and neighbouring tiles
+  const int total_items = plan.token_blocks * plan.row_blocks * plan.splits;
+  const int per = (total_items + 7) / 8;
+  const int q = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || q >= total_items) return;
+  const int split = q / (plan.token_blocks * plan.row_blocks);
+  const int rem = q - split * plan.token_blocks * plan.row_blocks;
+  const int rb = rem / plan.token_blocks, tb = rem - rb * plan.token_blocks;
+  const int c_begin = min(chunks, (split * KG + part) * plan.chunks_per_part);
+  const int c_end = min(chunks, c_begin + plan.chunks_per_part);
+
+  const int st_tok = tid / (32 / E), st_col = (tid % (32 / E)) * E;
+  const int tok_src = min(tb * kTokens + st_tok, tokens - 1);   // rows past the last token repeat it; not stored
+  // per lane: 32-bit offsets that never change; per chunk: one scalar base each
+  const uint32_t x_off = (uint32_t)(tok_src - tb * kTokens) * kChunk + (uint32_t)st_col;
+  const float* x_base = a.xt + (int64_t)tb * kTokens * kChunk;
+  uint32_t row[RT];   // within the workgroup's rows; rows past the last one repeat it, not stored
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+    row[rt] = (uint32_t)min((wave * RT + rt) * 32 + (lane & 31), m - 1 - rb * kRows);
+  const uint32_t* packed = a.packed + (int64_t)rb * kRows * BITS;
+  const float* scales = a.scales + (int64_t)rb * kRows;
+  const uint8_t* zeros = a.zeros + (int64_t)rb * kRows;
+  const uint8_t* u_codes = a.U + (int64_t)rb * kRows;
+
+  struct Raw { float x[E]; HalfWords<BITS> w[RT]; float scale[RT]; uint8_t zero[RT]; };
+  auto request = [&](Raw& r, int c) {
+    c = min(c, c_end - 1);   // issued whatever c: no branch
+    const float* xp = x_base + (int64_t)c * a.xt_tokens * kChunk;
+#pragma unroll
+    for (int i = 0; i < E; i += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(xp + x_off + i);
+      r.x[i] = v.x; r.x[i + 1] = v.y; r.x[i + 2] = v.z; r.x[i + 3] = v.w;
+    }
+    const int64_t g = c / gpc;
+    const uint32_t* wp = packed + (int64_t)c * m * BITS;
+    const float* sp = scales + g * m;
+    const uint8_t* zp = zeros + g * m;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      r.w[rt] = load_half_chunk<BITS>(wp, row[rt] * BITS, h);
+      r.scale[rt] = sp[row[rt]];
+      r.zero[rt] = zp[row[rt]];
+    }
+  };
+  auto stage_x = [&](const float (&x)[E], int buf) {
+    uint32_t p[E / 2][3];
+#pragma unroll
+    for (int i = 0; i < E / 2; ++i) split3(x[2 * i], x[2 * i + 1], p[i]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      uint16_t* dst = &xs[buf][k][st_tok][st_col];
+      if constexpr (E == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(p[0][k], p[1][k], p[2][k], p[3][k]);
+      else *reinterpret_cast<uint2*>(dst) = make_uint2(p[0][k], p[1][k]);
+    }
+  };
+
+  f32x16 acc[TT][RT], total[TT][RT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { acc[tt][rt][r] = 0.f; total[tt][rt][r] = 0.f; }
+
+  auto multiply = [&](const bf16x8 (&b)[2][RT], int buf) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int p = 2; p >= 0; --p)   // the smallest piece first
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          const bf16x8 av = *reinterpret_cast<const bf16x8*>(&xs[buf][p][tt * 32 + (lane & 31)][16 * h + 8 * ks]);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[tt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b[ks][rt], acc[tt][rt], 0, 0, 0);
+        }
+  };
+  auto flush = [&](const float (&sc)[RT]) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          total[tt][rt][r] = fmaf(sc[rt], acc[tt][rt][r], total[tt][rt][r]);
+          acc[tt][rt][r] = 0.f;
+        }
+  };
+
+  Raw raw[2];
+  bf16x8 b[2][2][RT];
+  float sc[2][RT];
+  auto prepare = [&](const Raw& r, int c, int buf, bf16x8 (&bb)[2][RT], float (&s)[RT]) {
+    const uint32_t live = c < c_end ? 0xffffffffu : 0u;   // a step past the end multiplies by zero
+    float x[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) x[i] = __uint_as_float(__float_as_uint(r.x[i]) & live);
+    stage_x(x, buf);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const float z = (float)r.zero[rt];
+      bb[0][rt] = widen_codes<BITS, 0>(r.w[rt], h, z);
+      bb[1][rt] = widen_codes<BITS, 1>(r.w[rt], h, z);
+      s[rt] = r.scale[rt];
+    }
+  };
+  request(raw[0], c_begin);
+  request(raw[1], c_begin + 1);
+  prepare(raw[0], c_begin, 0, b[0], sc[0]);
+  int left = gpc - c_begin % gpc;   // chunks until the group ends
+  auto step = [&](auto parity, int c) {
+    constexpr int P = decltype(parity)::value;
+    __syncthreads();
+    request(raw[P], c + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(b[P], P);
+    prepare(raw[P ^ 1], c + 1, P ^ 1, b[P ^ 1], sc[P ^ 1]);
+    // the next chunk's conversions go between this chunk's MFMAs, not after them: kept from sinking past the branch
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(b[P ^ 1][0][rt]), "+v"(b[P ^ 1][1][rt]));
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+    tile_sched<6 * TT * RT, 6 * TT - 4>();
+    if (--left == 0) { flush(sc[P]); left = gpc; }
+  };
+  for (int c = c_begin; c < c_begin + plan.chunks_per_part; c += 2) {   // the same count for all waves
+    step(std::integral_constant<int, 0>{}, c);
+    step(std::integral_constant<int, 1>{}, c + 1);
+  }
+  flush(sc[1]);   // what is left of the last chunk's group
+
+  // The low-rank part, once: coefficients y (tokens x r) against the e4m3 codes of U, 32 ranks at a time; e4m3
+  // is exact in bfloat16, y goes through the same three pieces.
+  if (a.r > 0 && split == plan.splits - 1) {
+#pragma unroll 1
+    for (int k0 = 32 * part; k0 < a.r + 32 * part; k0 += 32 * KG) {   // the same count for all waves
+      float yv[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const int k = k0 + st_col + i;
+        const float v = a.y[(int64_t)tok_src * a.r + min(k, a.r - 1)];
+        yv[i] = k < a.r ? v : 0.f;
+      }
+      __syncthreads();
+      stage_x(yv, 0);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          float u[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int k = k0 + 16 * h + 8 * ks + j;
+            const float v = e4m3_to_float(u_codes[(int64_t)min(k, a.r - 1) * m + row[rt]]);
+            u[j] = k < a.r ? v : 0.f;
+          }
+          const uint4 o = make_uint4(pair_high(u[0], u[1]), pair_high(u[2], u[3]), pair_high(u[4], u[5]), pair_high(u[6], u[7]));
+          b[0][ks][rt] = __builtin_bit_cast(bf16x8, o);
+        }
+      __syncthreads();
+      multiply(b[0], 0);
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) sc[0][rt] = 1.f;
+    flush(sc[0]);
+  }
+
+  if constexpr (KG > 1) {   // the second part's sums go to the first through LDS, a tile at a time
+    static_assert(KG == 2 && sizeof(xs_all) >= 256 * 16 * sizeof(float), "the exchange reuses the staging area");
+    float* ex = reinterpret_cast<float*>(&xs_all[0][0][0][0][0]) + tid;
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        __syncthreads();
+        if (part == 1) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) ex[r * 256] = total[tt][rt][r];
+        }
+        __syncthreads();
+        if (part == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) total[tt][rt][r] += ex[r * 256];
+        }
+      }
+    if (part != 0) return;
+  }
+
+  // accumulator r of a lane is token (r / 4) * 8 + (lane / 32) * 4 + r % 4 of its tile, row lane % 32
+  const bool direct = plan.splits == 1;
+  float* out = direct ? a.O : a.partial + (int64_t)split * tokens * m;
+  const int64_t ld = direct ? a.ldo : m;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int orow = rb * kRows + (wave * RT + rt) * 32 + (lane & 31);
+    if (orow >= m) continue;
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int t = tb * kTokens + tt * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+        if (t < tokens) out[(int64_t)t * ld + orow] = total[tt][rt][r];
+      }
+  }
+}
+
+// O[t][row] = sum over the column splits, in order (the last split holds the low-rank part)
+__global__ __launch_bounds__(256) void forward_tile_finish_kernel(ForwardArgs a, int tokens, int splits) {
   const int row = blockIdx.x * 256 + threadIdx.x;
   const int t0 = blockIdx.y * 4;
   if (row >= a.m) return;
   float out[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int sp0 = 0; sp0 < splits; sp0 += 16) {
-    float v[16][4];
+  for (int sp0 = 0; sp0 < splits; sp0 += 8) {
+    float v[8][4];
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
+    for (int k = 0; k < 8; ++k)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int sp = sp0 + k < splits ? sp0 + k : splits - 1;   // issued whatever sp: no branch, no wait
         const int tt = t0 + t < tokens ? t0 + t : tokens - 1;
-        v[k][t] = a.partial[((int64_t)sp * kMfmaTokens + tt) * a.m + row];
+        v[k][t] = a.partial[((int64_t)sp * tokens + tt) * a.m + row];
       }
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
+    for (int k = 0; k < 8; ++k)
 #pragma unroll
       for (int t = 0; t < 4; ++t) out[t] += sp0 + k < splits ? v[k][t] : 0.f;
-  }
-  for (int k = 0; k < a.r; ++k) {
-    const float u = e4m3_to_float(a.U[(int64_t)k * a.m + row]);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      if (t0 + t < tokens) out[t] = fmaf(u, a.y[(int64_t)(t0 + t) * a.r + k], out[t]);
   }
 #pragma unroll
   for (int t = 0; t < 4; ++t)
     if (t0 + t < tokens) a.O[(int64_t)(t0 + t) * a.ldo + row] = out[t];
 }
 
+constexpr int kPartialTokens = 32;   // the workspace holds partial sums of 32 tokens for every run of 256 columns
+
+template <int BITS, int TT, int KG>
+void launch_forward_tile_as(const ForwardArgs& a, int tokens, TilePlan p, hipStream_t st) {
+  const int chunks = a.n / kChunk;
+  p.chunks_per_part = (int)ceil_div(chunks, p.splits * KG);
+  p.splits = (int)ceil_div(chunks, (int64_t)p.chunks_per_part * KG);
+  const unsigned grid = 8u * (unsigned)ceil_div((int64_t)p.token_blocks * p.row_blocks * p.splits, 8);
+  forward_tile_kernel<BITS, TT, 2, KG><<<grid, 256 * KG, 0, st>>>(a, tokens, p);
+  if (p.splits > 1) {
+    dim3 gf((unsigned)ceil_div(a.m, 256), (unsigned)ceil_div(tokens, 4));
+    forward_tile_finish_kernel<<<gf, 256, 0, st>>>(a, tokens, p.splits);
+  }
+}
+
 template <int BITS>
-void launch_forward_mfma(const ForwardArgs& a, int tokens, hipStream_t st) {
-  const int splits = (int)ceil_div(a.n / kChunk, kFwdRun);
-  dim3 g((unsigned)ceil_div(a.m, kMfmaRows), (unsigned)splits);
-  forward_mfma_kernel<BITS><<<g, 256, 0, st>>>(a, tokens);
-  dim3 gf((unsigned)ceil_div(a.m, 256), (unsigned)ceil_div(tokens, 4));
-  forward_mfma_finish_kernel<<<gf, 256, 0, st>>>(a, tokens, splits);
+void launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st) {
+  const int chunks = a.n / kChunk;
+  const int TT = tokens <= 32 ? 1 : 2;
+  TilePlan p{};
+  p.token_blocks = (int)ceil_div(tokens, 32 * TT);
+  p.row_blocks = (int)ceil_div(a.m, 256);
+  const int64_t tiles = (int64_t)p.token_blocks * p.row_blocks;
+  // Two waves per SIMD hide each other's loads (one alone waits out about a microsecond per chunk: 512 tokens x
+  // 4096 x 11008 272 us for the call, 253 with two): where the tiles alone give every compute unit two workgroups the
+  // columns stay whole; otherwise a workgroup's two halves take half of its columns each, and the columns are
+  // split over workgroups until every compute unit has one, as far as the partial sums fit the workspace and a
+  // part keeps eight chunks.  Up to 32 tokens the codes' stream is the bound and twice as many workgroups keep
+  // more of it in flight (24 x 11008 x 11008: 91 -> 84 us).
+  const bool many = tiles >= 512;
+  int64_t s = many ? 1 : ceil_div(TT == 1 ? 512 : 256, tiles);
+  s = std::min<int64_t>(s, ceil_div(chunks, kFwdRun) * kPartialTokens / tokens);
+  s = std::max<int64_t>(1, std::min<int64_t>(s, chunks / kFwdRun));
+  p.splits = (int)s;
+  const bool halves = !many && chunks / s >= 2;
+  if (TT == 1) halves ? launch_forward_tile_as<BITS, 1, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 1, 1>(a, tokens, p, st);
+  else halves ? launch_forward_tile_as<BITS, 2, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 2, 1>(a, tokens, p, st);
 }
 
 template <int BITS, int B>
@@ -436,21 +671,20 @@ void launch_forward_b(const ForwardArgs& a, hipStream_t st) {
   forward_partial_kernel<BITS, B><<<g, 256, 0, st>>>(a);
 }
 
-// up to 32 tokens per pass over the codes on the matrix cores while 8 or more are left, then
-// four, two or one token per pass
+// eight or more tokens in one launch on the matrix cores (8 x 4096 x 4096: 29 us, as two passes of four 45), fewer in passes of four, two or one over the codes
 template <int BITS>
 void launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
+  if (tokens >= 8) { launch_forward_tile<BITS>(a, tokens, st); return; }
   ForwardArgs b = a;
   int done = 0;
   while (done < tokens) {
     const int left = tokens - done;
     int step;
-    if (left >= 8) { step = left < kMfmaTokens ? left : kMfmaTokens; launch_forward_mfma<BITS>(b, step, st); }
-    else if (left >= 4) { step = 4; launch_forward_b<BITS, 4>(b, st); }
+    if (left >= 4) { step = 4; launch_forward_b<BITS, 4>(b, st); }
     else if (left >= 2) { step = 2; launch_forward_b<BITS, 2>(b, st); }
     else { step = 1; launch_forward_b<BITS, 1>(b, st); }
     done += step;
-    b.xt = a.xt + (int64_t)done * a.n;
+    b.xt = a.xt + (int64_t)done * kChunk;
     b.y = a.y + (int64_t)done * a.r;
     b.O = a.O + (int64_t)done * a.ldo;
   }
@@ -495,7 +729,7 @@ ptq_status unpack_dequant_launch(const uint32_t* packed, int64_t m, int64_t n, i
 }
 
 static size_t forward_partial_bytes(int64_t m, int64_t n) {
-  return align_up((size_t)ceil_div(n / kChunk, kFwdRun) * kMfmaTokens * (size_t)m * sizeof(float), 256);
+  return align_up((size_t)ceil_div(n / kChunk, kFwdRun) * kPartialTokens * (size_t)m * sizeof(float), 256);
 }
 
 static size_t forward_counter_bytes(int64_t m) { return align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256); }
@@ -542,7 +776,7 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
                                             align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256));
   unsigned* done = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(partial) + forward_partial_bytes(m, n));
   // X~ = X P Q: the rows of X go through the same transform as the rows of the residual
-  ptq_status rc = lopro_rotate_input_launch(X, xdt, ldx, tokens, n, perm, b_I, b_H, xt, n, st);
+  ptq_status rc = lopro_rotate_input_launch(X, xdt, ldx, tokens, n, perm, b_I, b_H, xt, st);
   if (rc != PTQ_OK) return rc;
   const int counters = (int)ceil_div(m, 256);
   if (r > 0) {
@@ -556,7 +790,7 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
   } else {
     clear_counters_kernel<<<(unsigned)ceil_div(counters, 256), 256, 0, st>>>(done, counters);
   }
-  ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, y, U, r, partial, done, O, ldo};
+  ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, (int)tokens, y, U, r, partial, done, O, ldo};
   switch (bits) {
     case 2: launch_forward<2>(a, (int)tokens, st); break;
     case 3: launch_forward<3>(a, (int)tokens, st); break;

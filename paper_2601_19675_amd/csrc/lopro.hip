@@ -101,7 +101,8 @@ __global__ __launch_bounds__(256) void rank_kernel(const double* __restrict__ ke
 // One workgroup per row; the row is staged in LDS in its storage type (MODE 0) resp. as float64
 // (MODE 1).  row_perm (MODE 0 only, may be null) picks the source row.
 // (256 threads, or 1024 when the staged row is so large that only one workgroup fits a CU.)
-// OT: float64, or (MODE 0 only) float32 for activations on their way into the stored layer.
+// OT: float64, or (MODE 0 only) float32 for activations on their way into the stored layer: those are written
+// [column / 32][row][column % 32], without a leading dimension (n % 32 == 0).
 template <int DT, int MODE, typename OT>
 __global__ __launch_bounds__(1024) void row_rotate_kernel(const void* __restrict__ in, int64_t ldi, int n,
                                                          const int32_t* __restrict__ perm,
@@ -141,7 +142,9 @@ __global__ __launch_bounds__(1024) void row_rotate_kernel(const void* __restrict
         for (int i = 0; i < 4; ++i) v[i] *= scale;
       }
       if (c < ce) {
-        OT* o = out + (int64_t)row * ldo + c;
+        // float32: 32 columns of all rows at a time (c is a multiple of 4)
+        OT* o = out + (sizeof(OT) == sizeof(double) ? (int64_t)row * ldo + c
+                                                    : ((int64_t)(c >> 5) * gridDim.x + row) * 32 + (c & 31));
         if constexpr (sizeof(OT) == sizeof(double)) {
           *reinterpret_cast<double2*>(o) = double2{v[0], v[1]};
           *reinterpret_cast<double2*>(o + 2) = double2{v[2], v[3]};
@@ -324,9 +327,8 @@ ptq_status lopro_rotate_weight_launch(const void* R, ptq_dtype rdt, int64_t ldr,
 }
 
 ptq_status lopro_rotate_input_launch(const void* X, ptq_dtype xdt, int64_t ldx, int64_t tokens, int64_t n,
-                                     const int32_t* perm, int b_I, int b_H, float* Xout, int64_t ldo,
-                                     hipStream_t st) {
-  return launch_row_rotate<0, float>(X, xdt, ldx, tokens, n, perm, nullptr, b_I, b_H, Xout, ldo, st);
+                                     const int32_t* perm, int b_I, int b_H, float* Xout, hipStream_t st) {
+  return launch_row_rotate<0, float>(X, xdt, ldx, tokens, n, perm, nullptr, b_I, b_H, Xout, 0, st);
 }
 
 ptq_status lopro_unrotate_weight_launch(const double* Rq, int64_t ldq, int64_t m, int64_t n,
