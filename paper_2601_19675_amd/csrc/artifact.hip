@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "rotation.h"
 
 namespace ptq {
 namespace {
@@ -114,9 +115,7 @@ __global__ __launch_bounds__(256) void transpose_grids_kernel(const float* __res
   }
 }
 
-// ---- the layer applied to a few tokens ----------------------------------------------------
-// Inputs prepared per call: X~ (float32, from the float64 rotation) and the low-rank
-// coefficients  y[t][k] = sigma_k * sum_j V[k][j] x[t][j] / s[j].
+// ---- the layer applied to tokens ------------------------------------------------------------
 __device__ __forceinline__ float e4m3_to_float(uint8_t c) {
   // exponent and mantissa in place of a float32's, subnormals included; 2^120 = the difference of the biases
   const float mag = __uint_as_float((uint32_t)(c & 0x7f) << 20) * 0x1p120f;
@@ -130,28 +129,195 @@ __device__ __forceinline__ float fp16_bits_to_float(uint16_t h) {
   return (h & 0x8000) ? -mag : mag;
 }
 
-// one workgroup per (token, rank); the first also clears the counters of the product that follows
-template <int DT>
-__global__ __launch_bounds__(256) void low_rank_coeff_kernel(const void* __restrict__ X, int64_t ldx, int n,
-                                                             const uint8_t* __restrict__ V,
-                                                             const uint16_t* __restrict__ sigma,
-                                                             const double* __restrict__ s, int r,
-                                                             float* __restrict__ y, unsigned* __restrict__ done,
-                                                             int counters) {
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < counters; i += 256) done[i] = 0u;
-  const int t = blockIdx.x / r, k = blockIdx.x - t * r;
-  double acc = 0.0;
-  for (int j = threadIdx.x; j < n; j += 256)
-    acc += (double)e4m3_to_float(V[(int64_t)k * n + j]) * (load_as_f64<DT>(X, (int64_t)t * ldx + j) / s[j]);
-  __shared__ double red[256];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+// ---- what the products read: X~ and the low-rank coefficients, one launch -------------------------
+// X~ = X P Q in float64, written as float32 (xt[chunk][token][32]), and, in float64,
+//   y[t][k] = sigma_k * sum_j V[k][j] x[t][j] / s[j].
+// The first workgroups take TG tokens x RG ranks of y (1 x 4 while there are few tokens, for the latency; 2 x 16
+// from kPrepMany on, where one 1 / s and one conversion of V then serve several products): 2048 columns at a time,
+// four per lane, all loads of a step on their way together; the sums over the 64 lanes are folded by halves, one
+// exchange per value pair and step.  The others rotate: a workgroup stages a token's row in LDS and transforms
+// `segment` of its 256-column chunks (a row goes to several workgroups while there are few tokens).
+// For a token or a few both parts are chains of latencies; as two launches (a workgroup per row; a workgroup per
+// token and rank) the call of one token took 27.0 us at 4096 x 4096, 16 ranks, 53 at 4096 x 11008, now 15.8 and 25.2;
+// at 512 tokens x 4096 x 11008 253, now 169 (the coefficients alone 98 us, mostly divisions and conversions).  The
+// coefficients on the float64 matrix instruction were slower: 16 x 16 tiles of tokens x ranks leave most of
+// the chip idle (194 us; a single token 28).
+struct PrepArgs {
+  const void* X;
+  int64_t ldx;
+  int tokens, n;
+  const int32_t* perm;
+  int b_I, b_H;
+  const uint8_t* V;
+  const uint16_t* sigma;
+  const double* s;
+  int r;
+  float* xt;
+  float* y;
+  unsigned* done;
+  int counters;
+  int coeff_tiles, segments, segment;   // chunks per segment
+};
+
+constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
+constexpr int kPrepMany = 32;   // tokens
+
+// Sums of NV values per lane over the 64 lanes, halving the number of values with every exchange as long as there
+// is more than one: afterwards v[0] is the sum of value (lane / (64 / NV)).
+template <int NV, int MASK>
+__device__ __forceinline__ void fold_lanes(double* v, int lane) {
+  if constexpr (MASK > 0) {
+    constexpr int H = NV > 1 ? NV / 2 : 1;
+    const bool upper = lane & MASK;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double a = v[i], b = NV > 1 ? v[i + H] : v[i];
+      if constexpr (MASK >= 16) {
+        double first, second;
+        lane_pair<MASK == 32>(a, b, first, second);
+        v[i] = first + second;
+      } else {
+        const double keep = upper ? b : a, send = upper ? a : b;
+        double got;
+        if constexpr (MASK == 8) got = dpp_move<kDppRotate8>(send);
+        else if constexpr (MASK == 4) got = dpp_move<kDppReverseQuad>(dpp_move<kDppHalfMirror>(send));
+        else if constexpr (MASK == 2) got = dpp_move<kDppSwapHalfQuads>(send);
+        else got = dpp_move<kDppSwapPairs>(send);
+        v[i] = keep + got;
+      }
+    }
+    fold_lanes<H, MASK / 2>(v, lane);
   }
-  if (threadIdx.x == 0) y[(int64_t)t * r + k] = (float)(red[0] * (double)fp16_bits_to_float(sigma[k]));
+}
+
+template <int DT, bool ALIGNED, int TG, int RG>
+__device__ __forceinline__ void low_rank_coefficients(const PrepArgs& a, double* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rank_tiles = (a.r + RG - 1) / RG;
+  const int t0 = (blockIdx.x / rank_tiles) * TG, k0 = (blockIdx.x % rank_tiles) * RG;
+  using ST = typename StoredType<DT>::type;
+  const ST* xp[TG];   // tokens and ranks past the end repeat the last; not stored
+#pragma unroll
+  for (int t = 0; t < TG; ++t) xp[t] = static_cast<const ST*>(a.X) + (int64_t)min(t0 + t, a.tokens - 1) * a.ldx;
+  const uint8_t* vp[RG];
+#pragma unroll
+  for (int k = 0; k < RG; ++k) vp[k] = a.V + (int64_t)min(k0 + k, a.r - 1) * a.n;
+  double acc[TG * RG];
+#pragma unroll
+  for (int i = 0; i < TG * RG; ++i) acc[i] = 0.0;
+  for (int j = 4 * threadIdx.x; j < a.n; j += 4 * kPrepThreads) {
+    struct alignas(ALIGNED ? 4 * sizeof(ST) : sizeof(ST)) Quad { ST e[4]; };
+    struct alignas(ALIGNED ? 16 : 8) Scale { double e[4]; };
+    struct alignas(ALIGNED ? 4 : 1) Codes { uint8_t e[4]; };
+    Quad x[TG];
+    Codes c[RG];
+    const Scale sc = *reinterpret_cast<const Scale*>(a.s + j);
+#pragma unroll
+    for (int t = 0; t < TG; ++t) x[t] = *reinterpret_cast<const Quad*>(xp[t] + j);
+#pragma unroll
+    for (int k = 0; k < RG; ++k) c[k] = *reinterpret_cast<const Codes*>(vp[k] + j);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double inv = 1.0 / sc.e[i];
+      double xs[TG];
+#pragma unroll
+      for (int t = 0; t < TG; ++t) xs[t] = stored_to_f64<DT>(x[t].e[i]) * inv;
+#pragma unroll
+      for (int k = 0; k < RG; ++k) {
+        const double v = (double)e4m3_to_float(c[k].e[i]);
+#pragma unroll
+        for (int t = 0; t < TG; ++t) acc[t * RG + k] = fma(v, xs[t], acc[t * RG + k]);
+      }
+    }
+  }
+  constexpr int NV = TG * RG;
+  fold_lanes<NV, 32>(acc, lane);
+  if (lane % (64 / NV) == 0) red[wave * NV + lane / (64 / NV)] = acc[0];
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kPrepWaves; ++w) sum += red[w * NV + threadIdx.x];
+    const int t = t0 + (int)threadIdx.x / RG, k = k0 + (int)threadIdx.x % RG;
+    if (t < a.tokens && k < a.r) a.y[(int64_t)t * a.r + k] = (float)(sum * (double)fp16_bits_to_float(a.sigma[k]));
+  }
+}
+
+template <int DT, bool ALIGNED>
+__global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char prep_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0)   // the counters of the few-token product that follows
+    for (int i = tid; i < a.counters; i += kPrepThreads) a.done[i] = 0u;
+  if ((int)blockIdx.x < a.coeff_tiles) {
+    if (a.tokens >= kPrepMany) low_rank_coefficients<DT, ALIGNED, 2, 16>(a, reinterpret_cast<double*>(prep_lds));
+    else low_rank_coefficients<DT, ALIGNED, 1, 4>(a, reinterpret_cast<double*>(prep_lds));
+    return;
+  }
+  const int item = blockIdx.x - a.coeff_tiles;
+  const int token = item / a.segments, seg = item - token * a.segments;
+  using ST = typename StoredType<DT>::type;
+  const ST* src = static_cast<const ST*>(a.X) + (int64_t)token * a.ldx;
+  ST* buf = reinterpret_cast<ST*>(prep_lds);
+  if constexpr (ALIGNED) {   // n is a multiple of 32
+    constexpr int kPer = 16 / (int)sizeof(ST);
+    for (int c = tid * kPer; c < a.n; c += kPrepThreads * kPer)
+      *reinterpret_cast<uint4*>(buf + c) = *reinterpret_cast<const uint4*>(src + c);
+  } else {
+    for (int c = tid; c < a.n; c += kPrepThreads) buf[c] = src[c];
+  }
+  const int nchunk_id = (a.b_I + 255) / 256;                   // chunks of the identity part
+  const int nchunk = nchunk_id + (a.n - a.b_I + 255) / 256;    // ... plus those of the rotated part
+  const int lg = ilog2(a.b_H);
+  const double scale = 1.0 / sqrt((double)a.b_H);
+  const int k_end = min(nchunk, (seg + 1) * a.segment);
+  __syncthreads();
+  for (int k = seg * a.segment + wave; k < k_end; k += kPrepWaves) {
+    const bool ident = k < nchunk_id;
+    const int cs = ident ? 256 * k : a.b_I + 256 * (k - nchunk_id);
+    const int ce = ident ? a.b_I : a.n;
+    const int c = cs + 4 * lane;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (c < ce) {
+      const int4 p = *reinterpret_cast<const int4*>(a.perm + c);
+      v[0] = stored_to_f64<DT>(buf[p.x]);
+      v[1] = stored_to_f64<DT>(buf[p.y]);
+      v[2] = stored_to_f64<DT>(buf[p.z]);
+      v[3] = stored_to_f64<DT>(buf[p.w]);
+    }
+    if (!ident) {
+      fwht_chunk(v, lg, lane);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] *= scale;
+    }
+    if (c < ce)   // c is a multiple of 4
+      *reinterpret_cast<float4*>(a.xt + ((int64_t)(c >> 5) * a.tokens + token) * kChunk + (c & 31)) =
+          make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+  }
+}
+
+template <int DT>
+ptq_status launch_forward_prep(PrepArgs a, hipStream_t st) {
+  using ST = typename StoredType<DT>::type;
+  const size_t row = (size_t)a.n * sizeof(ST);
+  if (row > 160 * 1024) return PTQ_ERR_SHAPE;
+  const int nchunk = (a.b_I + 255) / 256 + (a.n - a.b_I + 255) / 256;
+  a.coeff_tiles = (int)(a.tokens >= kPrepMany ? ceil_div(a.tokens, 2) * ceil_div(a.r, 16) : a.tokens * ceil_div(a.r, 4));
+  // every workgroup of a token stages its whole row: split it only as far as that fills the chip
+  a.segments = (int)std::min<int64_t>(ceil_div(nchunk, kPrepWaves), ceil_div(256, a.tokens));
+  a.segment = (int)ceil_div(nchunk, a.segments);
+  const auto off = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16; };
+  const bool aligned = off(a.X) == 0 && (a.ldx * sizeof(ST)) % 16 == 0 && (a.r == 0 || (off(a.V) % 4 == 0 && off(a.s) == 0));
+  const size_t lds = std::max(row, (size_t)kPrepWaves * 32 * sizeof(double));
+  const unsigned grid = (unsigned)(a.coeff_tiles + (int64_t)a.tokens * a.segments);
+  if (aligned) {
+    if (!lds_opt_in<forward_prep_kernel<DT, true>>(160 * 1024)) return PTQ_ERR_HIP;
+    forward_prep_kernel<DT, true><<<grid, kPrepThreads, lds, st>>>(a);
+  } else {
+    if (!lds_opt_in<forward_prep_kernel<DT, false>>(160 * 1024)) return PTQ_ERR_HIP;
+    forward_prep_kernel<DT, false><<<grid, kPrepThreads, lds, st>>>(a);
+  }
+  return PTQ_OK;
 }
 
 struct ForwardArgs {
@@ -279,11 +445,6 @@ __global__ __launch_bounds__(256) void forward_partial_kernel(ForwardArgs a) {
   }
 #pragma unroll
   for (int t = 0; t < B; ++t) a.O[(int64_t)t * a.ldo + row] = out[t];
-}
-
-__global__ void clear_counters_kernel(unsigned* done, int count) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) done[i] = 0u;
 }
 
 // ---- many tokens: bfloat16 matrix cores ----------------------------------------------------------
@@ -671,7 +832,7 @@ void launch_forward_b(const ForwardArgs& a, hipStream_t st) {
   forward_partial_kernel<BITS, B><<<g, 256, 0, st>>>(a);
 }
 
-// eight or more tokens in one launch on the matrix cores (8 x 4096 x 4096: 29 us, as two passes of four 45), fewer in passes of four, two or one over the codes
+// eight or more tokens in one launch on the matrix cores, fewer in passes of four, two or one over the codes
 template <int BITS>
 void launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
   if (tokens >= 8) { launch_forward_tile<BITS>(a, tokens, st); return; }
@@ -775,21 +936,15 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
   float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(y) +
                                             align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256));
   unsigned* done = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(partial) + forward_partial_bytes(m, n));
-  // X~ = X P Q: the rows of X go through the same transform as the rows of the residual
-  ptq_status rc = lopro_rotate_input_launch(X, xdt, ldx, tokens, n, perm, b_I, b_H, xt, st);
-  if (rc != PTQ_OK) return rc;
-  const int counters = (int)ceil_div(m, 256);
-  if (r > 0) {
-    const unsigned g = (unsigned)(tokens * r);
-    switch (xdt) {
-      case PTQ_F32: low_rank_coeff_kernel<PTQ_F32><<<g, 256, 0, st>>>(X, ldx, (int)n, V, sigma, s, r, y, done, counters); break;
-      case PTQ_BF16: low_rank_coeff_kernel<PTQ_BF16><<<g, 256, 0, st>>>(X, ldx, (int)n, V, sigma, s, r, y, done, counters); break;
-      case PTQ_F64: low_rank_coeff_kernel<PTQ_F64><<<g, 256, 0, st>>>(X, ldx, (int)n, V, sigma, s, r, y, done, counters); break;
-      default: return PTQ_ERR_DTYPE;
-    }
-  } else {
-    clear_counters_kernel<<<(unsigned)ceil_div(counters, 256), 256, 0, st>>>(done, counters);
+  const PrepArgs prep{X, ldx, (int)tokens, (int)n, perm, b_I, b_H, V, sigma, s, r, xt, y, done, (int)ceil_div(m, 256), 0, 0, 0};
+  ptq_status rc;
+  switch (xdt) {
+    case PTQ_F32: rc = launch_forward_prep<PTQ_F32>(prep, st); break;
+    case PTQ_BF16: rc = launch_forward_prep<PTQ_BF16>(prep, st); break;
+    case PTQ_F64: rc = launch_forward_prep<PTQ_F64>(prep, st); break;
+    default: return PTQ_ERR_DTYPE;
   }
+  if (rc != PTQ_OK) return rc;
   ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, (int)tokens, y, U, r, partial, done, O, ldo};
   switch (bits) {
     case 2: launch_forward<2>(a, (int)tokens, st); break;

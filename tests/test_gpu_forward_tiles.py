@@ -20,14 +20,8 @@ def _codes(packed, n, bits):
     return out
 
 
-# one chunk of 32 columns, an odd number of them, more than a split holds; groups of one chunk and of all; the
-# last row / token alone in its tile; ranks over one round of 32; few rows (the columns are split) and many
-@pytest.mark.parametrize("bits,tokens,m,n,group,r,dtype", [
-    (4, 8, 1, 32, 32, 0, torch.float32), (2, 32, 255, 96, 96, 5, torch.bfloat16), (3, 33, 257, 608, 32, 16, torch.float32),
-    (8, 64, 300, 1056, 352, 33, torch.bfloat16), (4, 65, 129, 2048, 128, 16, torch.float64), (3, 130, 513, 4128, 4128, 2, torch.float32),
-    (8, 1025, 70, 288, 32, 1, torch.bfloat16)])
-def test_forward_tiles_match_the_dequantized_product(bits, tokens, m, n, group, r, dtype):
-    g = torch.Generator().manual_seed(1000 * bits + tokens)
+def _random_layer(seed, bits, tokens, m, n, group, r, dtype):
+    g = torch.Generator().manual_seed(seed)
     packed = torch.randint(-2**31, 2**31, (n // 32, m, bits), generator=g, dtype=torch.int64).to(torch.int32)
     scales = 0.002 + 0.05 * torch.rand((n // group, m), generator=g)
     zeros = torch.randint(0, 2**bits, (n // group, m), generator=g).to(torch.uint8)
@@ -37,18 +31,19 @@ def test_forward_tiles_match_the_dequantized_product(bits, tokens, m, n, group, 
     V = torch.randint(0, 0x40, (r, n), generator=g).to(torch.uint8)
     sigma = (torch.rand(r, generator=g) * 0.1).to(torch.float16)
     s = torch.exp(torch.randn(n, generator=g, dtype=torch.float64))
-    d = lambda t: t.cuda()  # noqa: E731
-    low = (d(U), d(V), d(sigma), d(s)) if r else (None,) * 4
-    wide = torch.full((tokens, m + 3), float("nan"), device="cuda")   # an output with a leading dimension of its own
-    ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, *low, wide[:, :m])
-    torch.cuda.synchronize()
-    assert torch.isnan(wide[:, m:]).all()
-    got = wide[:, :m].cpu().double()
+    return packed, scales, zeros, perm, X, U, V, sigma, s
 
+
+def _check(got, layer, bits, group):
+    """Against the dequantized product in float64, unrotated (b_I = n)."""
+    packed, scales, zeros, perm, X, U, V, sigma, s = layer
+    n, r = X.shape[1], U.shape[0]
     X64 = X.double()
     Wt = scales.double().repeat_interleave(group, 0) * (_codes(packed, n, bits) - zeros.double().repeat_interleave(group, 0))
     Xt = X64[:, perm.long()]
     want, mag = Xt @ Wt, Xt.abs() @ Wt.abs()
+    if X.shape[0] < 8:   # the few-token product sums code x and zero x separately
+        mag = mag + 2 * Xt.abs() @ (scales.double() * zeros.double()).repeat_interleave(group, 0)
     if r:
         u, v = U.view(torch.float8_e4m3fn).double(), V.view(torch.float8_e4m3fn).double()
         y, y_mag = ((X64 / s) @ v.T) * sigma.double(), ((X64 / s).abs() @ v.abs().T) * sigma.double()
@@ -60,3 +55,50 @@ def test_forward_tiles_match_the_dequantized_product(bits, tokens, m, n, group, 
     assert (err <= bound * mag + 1e-30).all(), float((err / (bound * mag + 1e-30)).max())
     # and as the roundings fall at random: their square root
     assert float(err.norm() / mag.norm()) <= 4 * bound ** 0.5 * 2.0 ** -12
+
+
+# one chunk of 32 columns, an odd number of them, more than a split holds; groups of one chunk and of all; the
+# last row / token alone in its tile; ranks over one round of 32; few rows (the columns are split) and many
+@pytest.mark.parametrize("bits,tokens,m,n,group,r,dtype", [
+    (4, 8, 1, 32, 32, 0, torch.float32), (2, 32, 255, 96, 96, 5, torch.bfloat16), (3, 33, 257, 608, 32, 16, torch.float32),
+    (8, 64, 300, 1056, 352, 33, torch.bfloat16), (4, 65, 129, 2048, 128, 16, torch.float64), (3, 130, 513, 4128, 4128, 2, torch.float32),
+    (8, 1025, 70, 288, 32, 1, torch.bfloat16)])
+def test_forward_tiles_match_the_dequantized_product(bits, tokens, m, n, group, r, dtype):
+    layer = _random_layer(1000 * bits + tokens, bits, tokens, m, n, group, r, dtype)
+    packed, scales, zeros, perm, X, U, V, sigma, s = layer
+    d = lambda t: t.cuda()  # noqa: E731
+    low = (d(U), d(V), d(sigma), d(s)) if r else (None,) * 4
+    wide = torch.full((tokens, m + 3), float("nan"), device="cuda")   # an output with a leading dimension of its own
+    ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, *low, wide[:, :m])
+    torch.cuda.synchronize()
+    assert torch.isnan(wide[:, m:]).all()
+    _check(wide[:, :m].cpu().double(), layer, bits, group)
+
+
+def _misaligned(t):
+    """The same values on the GPU, one element past an aligned address and with a leading dimension of their own."""
+    if t.dim() == 1:
+        out = torch.empty(t.shape[0] + 1, dtype=t.dtype, device="cuda")[1:]
+    else:
+        out = torch.empty((t.shape[0], t.shape[1] + 3), dtype=t.dtype, device="cuda")[:, 1:1 + t.shape[1]]
+    return out.copy_(t)
+
+
+# rows staged by one workgroup and by several, ranks around the 4 and 16 of a workgroup, tokens around the change of
+# form, each storage type with wide loads and element by element
+@pytest.mark.parametrize("tokens,n,r,dtype", [(1, 4128, 1, torch.bfloat16), (2, 32, 5, torch.float32), (7, 2080, 4, torch.float64),
+                                              (31, 544, 17, torch.bfloat16), (33, 2048, 16, torch.float32), (64, 96, 19, torch.float64)])
+@pytest.mark.parametrize("aligned", [True, False])
+def test_activations_and_coefficients_at_the_edges_of_their_forms(tokens, n, r, dtype, aligned):
+    m, bits, group = 70, 4, 32
+    layer = _random_layer(tokens + n, bits, tokens, m, n, group, r, dtype)
+    packed, scales, zeros, perm, X, U, V, sigma, s = layer
+    d = lambda t: t.cuda()  # noqa: E731
+    Xd, Vd, sd = d(X), d(V), d(s)
+    if not aligned:
+        Xd, sd = _misaligned(X), _misaligned(s)
+        Vd = torch.empty(r * n + 1, dtype=torch.uint8, device="cuda")[1:].view(r, n).copy_(V)
+    O = torch.full((tokens, m), float("nan"), device="cuda")
+    ptq.ptq_lopro_linear_forward(Xd, d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, d(U), Vd, d(sigma), sd, O)
+    torch.cuda.synchronize()
+    _check(O.cpu().double(), layer, bits, group)
