@@ -9,14 +9,8 @@
 // packed[chunk][row][d], and the grids group-major, scale[group][row] and zero[group][row], so
 // that lanes that work on consecutive rows read consecutive memory.
 //
-// The product with the packed residual is bound by the rate at which the codes stream from
-// memory (m n d / 8 bytes; the vectors and grids are a few percent of that).  A lane is a row;
-// a workgroup takes 256 rows and a run of eight chunks (256 columns), whose piece of X~ it
-// stages in LDS (all lanes read the same address: a broadcast), requests its eight chunks at
-// once, and writes one partial sum per row and token; a second small kernel adds the partial
-// sums of a row in a fixed order together with the low-rank part.  Splitting the columns rather
-// than the rows keeps the staged piece of X~ tiny, so that the grid can be large enough to fill
-// the chip without every workgroup re-reading all of X~.
+// The product with the packed residual takes two forms: a few tokens row by row on the vector unit (bound by the
+// codes' stream from memory), more of them in tiles on the bfloat16 matrix cores.
 #include <algorithm>
 #include <type_traits>
 
@@ -154,8 +148,6 @@ struct PrepArgs {
   int r;
   float* xt;
   float* y;
-  unsigned* done;
-  int counters;
   int coeff_tiles, segments, segment;   // chunks per segment
 };
 
@@ -247,8 +239,6 @@ template <int DT, bool ALIGNED>
 __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs a) {
   extern __shared__ __attribute__((aligned(16))) char prep_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (blockIdx.x == 0)   // the counters of the few-token product that follows
-    for (int i = tid; i < a.counters; i += kPrepThreads) a.done[i] = 0u;
   if ((int)blockIdx.x < a.coeff_tiles) {
     if (a.tokens >= kPrepMany) low_rank_coefficients<DT, ALIGNED, 2, 16>(a, reinterpret_cast<double*>(prep_lds));
     else low_rank_coefficients<DT, ALIGNED, 1, 4>(a, reinterpret_cast<double*>(prep_lds));
@@ -330,121 +320,149 @@ struct ForwardArgs {
   const float* y;           // tokens x r
   const uint8_t* U;         // r x m, e4m3
   int r;
-  float* partial;           // splits x B x m
-  unsigned* done;           // one counter per block of 256 rows: zero on entry, left at zero
+  float* partial;           // splits x tokens x m
   float* O;                 // tokens x m
   int64_t ldo;
 };
 
-constexpr int kFwdRun = 8;   // chunks per workgroup: 256 columns
-
+// ---- a few tokens ----------------------------------------------------------------------------
+// Bound by the codes' way from memory.  A lane is a row (R consecutive ones per workgroup) and a slice of the
+// columns: the 256 / R slices of a workgroup take every (256 / R)-th chunk, eight at a time (their words are
+// requested before anything else), X~ of all columns sits in LDS (a slice's lanes read the same address), and the
+// slices are added by lane exchanges and through LDS -- no partial sums in memory and no counting of
+// workgroups.  sum_j scale (code_j - zero) x_j = scale (sum_j code_j x_j - zero sum_j x_j): the second sum does not
+// depend on the row, so a weight costs a conversion and a multiply-add per token (half an instruction to
+// extract).  The ranks of the low-rank part are dealt to the slices like chunks.  One token, 4096 x 4096, 4 bits:
+// 7.5 us for the kernel (11.8 with a workgroup per 256 rows x 256 columns, partial sums in memory and the last
+// workgroup of a row block adding them); 16 rows per workgroup, 8 where that leaves compute units idle.
 template <int BITS>
 struct alignas(BITS == 3 ? 4 : (BITS == 2 ? 8 : 16)) Words { uint32_t w[BITS]; };
 
-// grid: (row blocks of 256, runs of kFwdRun chunks); B tokens.  Requires group % 32 == 0.
-template <int BITS, int B>
-__global__ __launch_bounds__(256) void forward_partial_kernel(ForwardArgs a) {
-  __shared__ float xs[B][kFwdRun * kChunk];
-  __shared__ float xsum[B][kFwdRun];
-  const int tid = threadIdx.x;
-  const int m = a.m, n = a.n, chunks = n / kChunk;
-  const int row = blockIdx.x * 256 + tid;
-  const bool live = row < m;
-  const int c0 = blockIdx.y * kFwdRun;
-  const int nc = min(kFwdRun, chunks - c0);
-
-  // the eight chunks of this row first: they are the long latency
-  Words<BITS> wd[kFwdRun];
+// codes [8 Q, 8 Q + 8) of a chunk
+template <int BITS, int Q>
+__device__ __forceinline__ void codes_to_float(const Words<BITS>& v, float (&f)[8]) {
+  if constexpr (BITS == 8) {
 #pragma unroll
-  for (int k = 0; k < kFwdRun; ++k) {
+    for (int j = 0; j < 8; ++j) f[j] = (float)((v.w[2 * Q + (j >> 2)] >> (8 * (j & 3))) & 0xffu);
+  } else if constexpr (BITS == 4) {
+    const uint32_t even = v.w[Q] & 0x0f0f0f0fu, odd = (v.w[Q] >> 4) & 0x0f0f0f0fu;
 #pragma unroll
-    for (int w = 0; w < BITS; ++w) wd[k].w[w] = 0u;
-    if (live && k < nc) wd[k] = *reinterpret_cast<const Words<BITS>*>(a.packed + ((int64_t)(c0 + k) * m + row) * BITS);
+    for (int j = 0; j < 8; ++j) f[j] = (float)((((j & 1) ? odd : even) >> (8 * (j >> 1))) & 0xffu);
+  } else if constexpr (BITS == 2) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      f[j] = (float)((((v.w[Q >> 1] >> (16 * (Q & 1) + 2 * (j & 3))) & 0x0303u) >> (8 * (j >> 2))) & 0xffu);
+  } else {
+    constexpr int pos = 24 * Q, wi = pos >> 5, sh = pos & 31;
+    uint32_t b = v.w[wi] >> sh;
+    if constexpr (sh + 24 > 32) b |= v.w[wi + 1] << (32 - sh);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] = (float)((b >> (3 * j)) & 7u);
   }
-  // sum_j scale (code_j - zero) x_j = scale (sum_j code_j x_j - zero sum_j x_j): the second sum does
-  // not depend on the row, so a weight costs an extract, a conversion and one multiply-add per token
-  for (int e = tid; e < B * kFwdRun * (kChunk / 4); e += 256) {
-    const int t = e / (kFwdRun * (kChunk / 4)), q = e - t * (kFwdRun * (kChunk / 4));   // q: float4 index in the run
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (q < nc * (kChunk / 4)) v = *reinterpret_cast<const float4*>(a.xt + ((int64_t)(c0 + (q >> 3)) * a.xt_tokens + t) * kChunk + 4 * (q & 7));
-    *reinterpret_cast<float4*>(&xs[t][4 * q]) = v;
-    float sum = (v.x + v.y) + (v.z + v.w);     // eight consecutive threads hold one chunk
-    sum += __shfl_xor(sum, 1);
-    sum += __shfl_xor(sum, 2);
-    sum += __shfl_xor(sum, 4);
-    if ((q & 7) == 0) xsum[t][q >> 3] = sum;
-  }
-  __syncthreads();
+}
 
+constexpr int kRowBatch = 8;             // chunks per lane on their way at a time
+constexpr int kRowLdsFloats = 36 * 1024;  // X~ staged at a time: columns x tokens, plus 1/32 of it for the chunk sums
+
+// B tokens, rows [R q, R q + R) of the weight for item q; `columns` (a multiple of 32) are staged at a time
+template <int BITS, int B, int R>
+__global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int columns, int items) {
+  extern __shared__ __attribute__((aligned(16))) float row_lds[];
+  constexpr int S = 256 / R;
+  const int per = (items + 7) / 8;   // consecutive items on one XCD: neighbouring rows share cache lines
+  const int q = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || q >= items) return;
+  const int tid = threadIdx.x, lane = tid & 63, slice = tid / R;
+  const int m = a.m, chunks = a.n / kChunk;
+  const int row = q * R + tid % R;
+  const int64_t rr = min(row, m - 1);   // a lane past the last row repeats it; not stored
+  const uint32_t* packed = a.packed + rr * BITS;
+  const int stage = columns / kChunk;
+  float* xs = row_lds;                    // [B][columns]
+  float* xsum = row_lds + B * columns;    // [B][stage]
   float acc[B];
 #pragma unroll
   for (int t = 0; t < B; ++t) acc[t] = 0.f;
+  for (int c0 = 0; c0 < chunks; c0 += stage) {
+    const int nc = min(stage, chunks - c0);
+    Words<BITS> wd[kRowBatch];
+    float sc[kRowBatch], zero[kRowBatch];
+    auto request = [&](int i0) {
 #pragma unroll
-  for (int k = 0; k < kFwdRun; ++k) {
-    if (k >= nc) break;
-    const int g = (c0 + k) * kChunk / a.group;
-    const float sc = live ? a.scales[(int64_t)g * m + row] : 0.f;
-    const float z = live ? (float)a.zeros[(int64_t)g * m + row] : 0.f;
-    float raw[B];
+      for (int i = 0; i < kRowBatch; ++i) {
+        const int c = c0 + min(i0 + i * S + slice, nc - 1);   // issued whatever the chunk: no branch
+        wd[i] = *reinterpret_cast<const Words<BITS>*>(packed + (int64_t)c * m * BITS);
+        const int64_t g = c * kChunk / a.group;
+        sc[i] = a.scales[g * m + rr];
+        zero[i] = (float)a.zeros[g * m + rr];
+      }
+    };
+    request(0);
+    if (c0 > 0) __syncthreads();
+    for (int e = tid; e < B * nc * (kChunk / 4); e += 256) {   // eight consecutive threads hold one chunk
+      const int t = e / (nc * (kChunk / 4)), k = e - t * (nc * (kChunk / 4));
+      const float4 v = *reinterpret_cast<const float4*>(a.xt + ((int64_t)(c0 + (k >> 3)) * a.xt_tokens + t) * kChunk + 4 * (k & 7));
+      *reinterpret_cast<float4*>(xs + t * columns + 4 * k) = v;
+      float sum = (v.x + v.y) + (v.z + v.w);
+      sum += __shfl_xor(sum, 1);
+      sum += __shfl_xor(sum, 2);
+      sum += __shfl_xor(sum, 4);
+      if ((k & 7) == 0) xsum[t * stage + (k >> 3)] = sum;
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < nc; i0 += kRowBatch * S) {
+      if (i0 > 0) request(i0);
 #pragma unroll
-    for (int t = 0; t < B; ++t) raw[t] = 0.f;
+      for (int i = 0; i < kRowBatch; ++i) {
+        const int c = i0 + i * S + slice;
+        const int cl = min(c, nc - 1);
+        float raw[B];
 #pragma unroll
-    for (int q = 0; q < kChunk / 4; ++q) {
-      float cf[4];
+        for (int t = 0; t < B; ++t) raw[t] = 0.f;
+        auto eight = [&](auto quarter) {
+          constexpr int Q = decltype(quarter)::value;
+          float f[8];
+          codes_to_float<BITS, Q>(wd[i], f);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cf[j] = (float)chunk_code<BITS>(wd[k].w, 4 * q + j);
+          for (int t = 0; t < B; ++t) {
+            const float4* x = reinterpret_cast<const float4*>(xs + t * columns + cl * kChunk + 8 * Q);
+            const float4 lo = x[0], hi = x[1];
+            raw[t] = fmaf(f[3], lo.w, fmaf(f[2], lo.z, fmaf(f[1], lo.y, fmaf(f[0], lo.x, raw[t]))));
+            raw[t] = fmaf(f[7], hi.w, fmaf(f[6], hi.z, fmaf(f[5], hi.y, fmaf(f[4], hi.x, raw[t]))));
+          }
+        };
+        eight(std::integral_constant<int, 0>{});
+        eight(std::integral_constant<int, 1>{});
+        eight(std::integral_constant<int, 2>{});
+        eight(std::integral_constant<int, 3>{});
+        if (c < nc) {
 #pragma unroll
-      for (int t = 0; t < B; ++t) {
-        const float4 x = *reinterpret_cast<const float4*>(&xs[t][k * kChunk + 4 * q]);
-        raw[t] = fmaf(cf[3], x.w, fmaf(cf[2], x.z, fmaf(cf[1], x.y, fmaf(cf[0], x.x, raw[t]))));
+          for (int t = 0; t < B; ++t) acc[t] = fmaf(sc[i], fmaf(-zero[i], xsum[t * stage + cl], raw[t]), acc[t]);
+        }
       }
     }
-#pragma unroll
-    for (int t = 0; t < B; ++t) acc[t] = fmaf(sc, fmaf(-z, xsum[t][k], raw[t]), acc[t]);
   }
-  // The partial sums go out device-coherently; the workgroup that counts itself last for its
-  // block of rows adds the column runs in order, adds the low-rank part and writes the output:
-  //   O[t][row] = sum over the column runs + sum_k U[k][row] y[t][k]
-  if (live) {
+  for (int k = slice; k < a.r; k += S) {
+    const float u = e4m3_to_float(a.U[(int64_t)k * m + rr]);
 #pragma unroll
-    for (int t = 0; t < B; ++t)
-      __hip_atomic_store(a.partial + ((int64_t)blockIdx.y * B + t) * m + row, acc[t], __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    for (int t = 0; t < B; ++t) acc[t] = fmaf(u, a.y[(int64_t)t * a.r + k], acc[t]);
   }
-  __shared__ int last;
-  __builtin_amdgcn_s_waitcnt(0);   // every wave's stores acknowledged before the workgroup is counted
+  // slices of a wave, then the four waves in order
   __syncthreads();
-  const int splits = gridDim.y;
-  if (tid == 0) last = atomicAdd(a.done + blockIdx.x, 1u) + 1u == (unsigned)splits;
+  float* red = row_lds;   // [4][B][R]
+#pragma unroll
+  for (int t = 0; t < B; ++t) {
+#pragma unroll
+    for (int mask = R; mask < 64; mask <<= 1) acc[t] += __shfl_xor(acc[t], mask);
+    if (lane < R) red[((tid >> 6) * B + t) * R + lane] = acc[t];
+  }
   __syncthreads();
-  if (!last) return;
-  if (tid == 0) __hip_atomic_store(a.done + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (!live) return;
-  float out[B];
-#pragma unroll
-  for (int t = 0; t < B; ++t) out[t] = 0.f;
-  for (int sp0 = 0; sp0 < splits; sp0 += 8) {   // eight loads in flight per token, added in order
-    float v[8][B];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-#pragma unroll
-      for (int t = 0; t < B; ++t) {
-        const int sp = sp0 + k < splits ? sp0 + k : splits - 1;   // issued whatever sp: no branch, no wait
-        v[k][t] = __hip_atomic_load(a.partial + ((int64_t)sp * B + t) * m + row, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT);
-      }
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-#pragma unroll
-      for (int t = 0; t < B; ++t) out[t] += sp0 + k < splits ? v[k][t] : 0.f;
+  if (tid < B * R) {
+    const int t = tid / R, i = tid - t * R;
+    const int orow = q * R + i;
+    if (orow < m)
+      a.O[(int64_t)t * a.ldo + orow] = ((red[t * R + i] + red[(B + t) * R + i]) + red[(2 * B + t) * R + i]) + red[(3 * B + t) * R + i];
   }
-  for (int k = 0; k < a.r; ++k) {
-    const float u = e4m3_to_float(a.U[(int64_t)k * m + row]);
-#pragma unroll
-    for (int t = 0; t < B; ++t) out[t] = fmaf(u, a.y[(int64_t)t * a.r + k], out[t]);
-  }
-#pragma unroll
-  for (int t = 0; t < B; ++t) a.O[(int64_t)t * a.ldo + row] = out[t];
 }
 
 // ---- many tokens: bfloat16 matrix cores ----------------------------------------------------------
@@ -786,6 +804,7 @@ __global__ __launch_bounds__(256) void forward_tile_finish_kernel(ForwardArgs a,
     if (t0 + t < tokens) a.O[(int64_t)(t0 + t) * a.ldo + row] = out[t];
 }
 
+constexpr int kFwdRun = 8;            // chunks: the least a column split keeps
 constexpr int kPartialTokens = 32;   // the workspace holds partial sums of 32 tokens for every run of 256 columns
 
 template <int BITS, int TT, int KG>
@@ -825,29 +844,32 @@ void launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st) {
   else halves ? launch_forward_tile_as<BITS, 2, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 2, 1>(a, tokens, p, st);
 }
 
-template <int BITS, int B>
-void launch_forward_b(const ForwardArgs& a, hipStream_t st) {
-  const int splits = (int)ceil_div(a.n / kChunk, kFwdRun);
-  dim3 g((unsigned)ceil_div(a.m, 256), (unsigned)splits);
-  forward_partial_kernel<BITS, B><<<g, 256, 0, st>>>(a);
+template <int BITS, int B, int R>
+void launch_forward_rows_as(const ForwardArgs& a, hipStream_t st) {
+  const int columns = std::min(a.n, kRowLdsFloats / B / kChunk * kChunk);
+  const int items = (int)ceil_div(a.m, R);
+  const size_t lds = std::max((size_t)B * (columns + columns / kChunk), (size_t)4 * B * R) * sizeof(float);
+  if (!lds_opt_in<forward_rows_kernel<BITS, B, R>>(160 * 1024)) return;
+  forward_rows_kernel<BITS, B, R><<<8u * (unsigned)ceil_div(items, 8), 256, lds, st>>>(a, columns, items);
 }
 
-// eight or more tokens in one launch on the matrix cores, fewer in passes of four, two or one over the codes
+template <int BITS, int B>
+void launch_forward_rows(const ForwardArgs& a, hipStream_t st) {
+  if (a.m > 2048) launch_forward_rows_as<BITS, B, 16>(a, st);
+  else launch_forward_rows_as<BITS, B, 8>(a, st);
+}
+
+// One or two tokens always, three or four while their X~ lets two workgroups share a compute unit, go row by row
+// (4 bits: 2 x 11008 x 8192 38 us for the call, 52 as tiles; 3 x 11008 x 4096 19.4 and 32.9; 4 x 4096 x 4096 18.8 and
+// 19.8; but 4 x 11008 x 5632 55.9 and 40.7, 4 x 4096 x 8192 32.6 and 29.6); all others take the tiles.
 template <int BITS>
 void launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
-  if (tokens >= 8) { launch_forward_tile<BITS>(a, tokens, st); return; }
-  ForwardArgs b = a;
-  int done = 0;
-  while (done < tokens) {
-    const int left = tokens - done;
-    int step;
-    if (left >= 4) { step = 4; launch_forward_b<BITS, 4>(b, st); }
-    else if (left >= 2) { step = 2; launch_forward_b<BITS, 2>(b, st); }
-    else { step = 1; launch_forward_b<BITS, 1>(b, st); }
-    done += step;
-    b.xt = a.xt + (int64_t)done * kChunk;
-    b.y = a.y + (int64_t)done * a.r;
-    b.O = a.O + (int64_t)done * a.ldo;
+  if (tokens > 2 && (tokens > 4 || (int64_t)tokens * a.n > 16384)) { launch_forward_tile<BITS>(a, tokens, st); return; }
+  switch (tokens) {
+    case 1: launch_forward_rows<BITS, 1>(a, st); break;
+    case 2: launch_forward_rows<BITS, 2>(a, st); break;
+    case 3: launch_forward_rows<BITS, 3>(a, st); break;
+    default: launch_forward_rows<BITS, 4>(a, st); break;
   }
 }
 
@@ -893,8 +915,6 @@ static size_t forward_partial_bytes(int64_t m, int64_t n) {
   return align_up((size_t)ceil_div(n / kChunk, kFwdRun) * kPartialTokens * (size_t)m * sizeof(float), 256);
 }
 
-static size_t forward_counter_bytes(int64_t m) { return align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256); }
-
 // ---- scratch for callers that cannot allocate -----------------------------------------------
 // One array per GPU, part of the library's code object: the device memory the forward call needs
 // beyond its inputs and outputs (the rotated input, the low-rank coefficients, the partial sums of
@@ -922,7 +942,7 @@ ptq_status linear_forward_static_scratch(void** ptr) {
 size_t linear_forward_workspace_bytes(int64_t tokens, int64_t m, int64_t n, int64_t r) {
   return align_up((size_t)tokens * n * sizeof(float), 256) +
          align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256) + forward_partial_bytes(m, n) +
-         forward_counter_bytes(m);
+         align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256);   // unused; which sizes fit the static array stays as it is
 }
 
 ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int64_t tokens, int64_t m, int64_t n,
@@ -935,8 +955,7 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
   float* y = reinterpret_cast<float*>(reinterpret_cast<char*>(xt) + align_up((size_t)tokens * n * sizeof(float), 256));
   float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(y) +
                                             align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256));
-  unsigned* done = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(partial) + forward_partial_bytes(m, n));
-  const PrepArgs prep{X, ldx, (int)tokens, (int)n, perm, b_I, b_H, V, sigma, s, r, xt, y, done, (int)ceil_div(m, 256), 0, 0, 0};
+  const PrepArgs prep{X, ldx, (int)tokens, (int)n, perm, b_I, b_H, V, sigma, s, r, xt, y, 0, 0, 0};
   ptq_status rc;
   switch (xdt) {
     case PTQ_F32: rc = launch_forward_prep<PTQ_F32>(prep, st); break;
@@ -945,7 +964,7 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
     default: return PTQ_ERR_DTYPE;
   }
   if (rc != PTQ_OK) return rc;
-  ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, (int)tokens, y, U, r, partial, done, O, ldo};
+  ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, (int)tokens, y, U, r, partial, O, ldo};
   switch (bits) {
     case 2: launch_forward<2>(a, (int)tokens, st); break;
     case 3: launch_forward<3>(a, (int)tokens, st); break;

@@ -42,7 +42,7 @@ def _check(got, layer, bits, group):
     Wt = scales.double().repeat_interleave(group, 0) * (_codes(packed, n, bits) - zeros.double().repeat_interleave(group, 0))
     Xt = X64[:, perm.long()]
     want, mag = Xt @ Wt, Xt.abs() @ Wt.abs()
-    if X.shape[0] < 8:   # the few-token product sums code x and zero x separately
+    if X.shape[0] <= 4:   # the few-token product sums code x and zero x separately
         mag = mag + 2 * Xt.abs() @ (scales.double() * zeros.double()).repeat_interleave(group, 0)
     if r:
         u, v = U.view(torch.float8_e4m3fn).double(), V.view(torch.float8_e4m3fn).double()
@@ -62,7 +62,7 @@ def _check(got, layer, bits, group):
 @pytest.mark.parametrize("bits,tokens,m,n,group,r,dtype", [
     (4, 8, 1, 32, 32, 0, torch.float32), (2, 32, 255, 96, 96, 5, torch.bfloat16), (3, 33, 257, 608, 32, 16, torch.float32),
     (8, 64, 300, 1056, 352, 33, torch.bfloat16), (4, 65, 129, 2048, 128, 16, torch.float64), (3, 130, 513, 4128, 4128, 2, torch.float32),
-    (8, 1025, 70, 288, 32, 1, torch.bfloat16)])
+    (8, 1025, 70, 288, 32, 1, torch.bfloat16), (3, 5, 300, 4096, 128, 4, torch.float32)])
 def test_forward_tiles_match_the_dequantized_product(bits, tokens, m, n, group, r, dtype):
     layer = _random_layer(1000 * bits + tokens, bits, tokens, m, n, group, r, dtype)
     packed, scales, zeros, perm, X, U, V, sigma, s = layer
@@ -100,5 +100,21 @@ def test_activations_and_coefficients_at_the_edges_of_their_forms(tokens, n, r, 
         Vd = torch.empty(r * n + 1, dtype=torch.uint8, device="cuda")[1:].view(r, n).copy_(V)
     O = torch.full((tokens, m), float("nan"), device="cuda")
     ptq.ptq_lopro_linear_forward(Xd, d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, d(U), Vd, d(sigma), sd, O)
+    torch.cuda.synchronize()
+    _check(O.cpu().double(), layer, bits, group)
+
+
+# row by row: the last row alone, eight and sixteen rows a workgroup, one chunk, a second batch of a lane's chunks, columns
+# staged in two pieces (two tokens beyond 18432 columns), more ranks than slices, and the token counts around the change of form
+@pytest.mark.parametrize("bits,tokens,m,n,group,r", [(2, 1, 1, 32, 32, 0), (3, 1, 2049, 1056, 96, 16), (4, 2, 4100, 320, 64, 3),
+                                                     (8, 3, 17, 5440, 32, 40), (4, 4, 33, 4096, 4096, 5), (3, 4, 33, 4128, 32, 5),
+                                                     (8, 2, 9, 18496, 32, 1)])
+def test_forward_rows_match_the_dequantized_product(bits, tokens, m, n, group, r):
+    layer = _random_layer(77 * bits + tokens, bits, tokens, m, n, group, r, torch.float32)
+    packed, scales, zeros, perm, X, U, V, sigma, s = layer
+    d = lambda t: t.cuda()  # noqa: E731
+    low = (d(U), d(V), d(sigma), d(s)) if r else (None,) * 4
+    O = torch.full((tokens, m), float("nan"), device="cuda")
+    ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, *low, O)
     torch.cuda.synchronize()
     _check(O.cpu().double(), layer, bits, group)
