@@ -13,7 +13,9 @@
 // Products of two bf16 numbers are exact in float32.  A workgroup accumulates
 // its 128 x 128 tile in float32 over at most 8192 tokens and stores that
 // partial tile; a second kernel adds the partial tiles into H in float64 in a
-// fixed order, so the result is bit-reproducible from run to run.
+// fixed order, so the result is bit-reproducible from run to run.  (Layers from 2048
+// channels on: a 256 x 256-tile kernel, which adds to H by itself where the tokens
+// are few enough for one split.)
 //
 // float32 activations: hessian_f32.hip (float64 matrix cores, 64 x 64 or 128 x 128 tiles), same
 // partial scheme with float64 partial tiles.
@@ -170,10 +172,9 @@ __global__ __launch_bounds__(256) void hessian_bf16_kernel(const uint16_t* __res
 constexpr int kBT = 256;
 constexpr int kBKS = 32;                          // tokens per stage
 constexpr int kBRing = 4;                         // stages in LDS
-constexpr int kBRow = kBT * 2;                    // bytes per token row of a part
-constexpr int kBPart = kBKS * kBRow;              // 16 KB
-constexpr int kBStage = 2 * kBPart;               // 32 KB
-constexpr size_t kBigLdsBytes = (size_t)kBRing * kBStage;  // 128 KB
+constexpr int kBRow = kBT * 2;                    // bytes per token row of the A part
+constexpr int kBPart = kBKS * kBRow;              // A part: 16 KB
+constexpr size_t kBigLdsBytes = (size_t)kBRing * 2 * kBPart;  // 128 KB
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
@@ -206,6 +207,10 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
 
+// rows of MFMA tiles that a wave of big_tile has in this role
+template <int ROLE>
+constexpr int role_rows = ROLE == 2 ? 2 : (ROLE == 3 ? 0 : 4);
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
 template <class F, int... Is>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
@@ -216,32 +221,42 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <bool diag>
+// A wave's tile is 128 x 32 NB: NB = 4, the 256 x 256 tile; NB = 2, one half (`half_tile`, 128 columns) of an
+// off-diagonal 256 x 256 tile, with a B part of half the size.  On a diagonal tile both operands come from the A part;
+// waves 0 and 3 take its two diagonal quadrants (ten of sixteen MFMA tiles) and wave 1 the off-diagonal one, which
+// keeps the workgroup in step with those of whole tiles beside it (they share their operands in the L2: shared out
+// evenly, n = 11008 took 25.2 ms instead of 24.5); SHARED, beside half tiles: waves 1 and 2 take half of it each.
+template <bool diag, int NB, bool SHARED = false>
 __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t ldx, int64_t t, int n,
-                                         int64_t tok0, int chunk, int I, int J, int split,
-                                         float* __restrict__ out, uint16_t* hs) {
+                                         int64_t tok0, int chunk, int I, int J, int half_tile, int split,
+                                         float* __restrict__ out, double* __restrict__ H, int64_t ldh, uint16_t* hs) {
+  static_assert(NB == 4 || (NB == 2 && !diag), "");
+  constexpr int kBRowB = 128 * NB;                  // bytes per token row of the B part
+  constexpr int kBStage = kBPart + kBKS * kBRowB;   // 32 or 24 KB
   typedef __attribute__((address_space(3))) char lds_char;
   typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
   lds_char* lds = (lds_char*)hs;
   const uint32_t lbase = (uint32_t)(uintptr_t)lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wi = wave >> 1, wj = wave & 1;
+  // rows 128 wi + 64 * low .., columns 32 NB wj of the tile (low: the second half of a shared quadrant)
+  const int wi = SHARED ? wave == 3 : wave >> 1, wj = SHARED ? wave != 0 : wave & 1;
+  const int low = SHARED && wave == 2;
   const int64_t kbeg = tok0 + (int64_t)split * chunk;
   const int64_t kend = (kbeg + chunk < t) ? kbeg + chunk : t;
   const int64_t len = kend - kbeg;
 
-  f32x16 acc[4][4];
+  f32x16 acc[4][NB];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
   if (len > 0) {
     const int nstage = (int)((len + kBKS - 1) / kBKS);
-    constexpr int L = diag ? 4 : 8;  // DMA instructions per stage and wave
+    constexpr int L = diag ? 4 : 4 + NB;  // DMA instructions per stage and wave
 
     // descriptor over the chunk's tokens (uniform, kept in scalar registers)
     const uint64_t gb0 = (uint64_t)(X + kbeg * ldx);
@@ -251,38 +266,45 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
                 0x00020000};
     const uint32_t stage_step = __builtin_amdgcn_readfirstlane((uint32_t)(kBKS * ldx * 2));
 
-    // per-lane byte offsets of the four DMA instructions of a part, inside a stage (the descriptor advances)
-    uint32_t voA[4], voB[4];
-    {
-      const int pos = lane & 31;
+    // per-lane byte offsets of the DMA instructions of a part, inside a stage (the descriptor advances): one brings
+    // two token rows of 32 chunks, or four of 16
+    uint32_t voA[4], voB[NB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 8 * i + 2 * wave + (lane >> 5);
-        const int c = pos ^ swz(row);
-        int colA = I * kBT + 8 * c, colB = J * kBT + 8 * c;
-        if (colA >= n) colA = I * kBT;
-        if (colB >= n) colB = J * kBT;
-        voA[i] = (uint32_t)((row * ldx + colA) * 2);
-        voB[i] = (uint32_t)((row * ldx + colB) * 2);
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int row = 8 * i + 2 * wave + (lane >> 5);
+      int col = I * kBT + 8 * ((lane & 31) ^ swz(row));
+      if (col >= n) col = I * kBT;
+      voA[i] = (uint32_t)((row * ldx + col) * 2);
+    }
+    const int col0 = J * kBT + (NB == 2 ? 128 * half_tile : 0);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      constexpr int kPerRow = 8 * NB;   // chunks
+      const int row = (32 / NB) * i + (8 / NB) * wave + lane / kPerRow;
+      int col = col0 + 8 * ((lane % kPerRow) ^ swz(row));
+      if (col >= n) col = J * kBT;
+      voB[i] = (uint32_t)((row * ldx + col) * 2);
     }
     // per-lane LDS read addresses inside a stage, one per MFMA tile of the wave's strips
-    uint32_t adA[4], adB[4];
+    uint32_t adA[4], adB[NB];
     {
       const int g = lane >> 4, h = g & 1, kg = g >> 1, j = lane & 15, r = j >> 2, q = j & 3;
       const int row = kg * 8 + r;
 #pragma unroll
       for (int T = 0; T < 4; ++T) {
-        const int cA = wi * 16 + T * 4 + 2 * h + (q >> 1);
-        const int cB = wj * 16 + T * 4 + 2 * h + (q >> 1);
-        adA[T] = row * kBRow + ((cA ^ swz(r)) * 16) + (q & 1) * 8;
-        adB[T] = (diag ? 0 : kBPart) + row * kBRow + ((cB ^ swz(r)) * 16) + (q & 1) * 8;
+        const int c = wi * 16 + low * 8 + (T & (low ? 1 : 3)) * 4 + 2 * h + (q >> 1);
+        adA[T] = row * kBRow + ((c ^ swz(r)) * 16) + (q & 1) * 8;
+      }
+#pragma unroll
+      for (int T = 0; T < NB; ++T) {
+        const int c = wj * 4 * NB + T * 4 + 2 * h + (q >> 1);
+        adB[T] = (diag ? 0 : kBPart) + row * kBRowB + ((c ^ swz(r)) * 16) + (q & 1) * 8;
       }
     }
-    // fragment of eight tokens: rows +0..3 and +4..7 relative to the lane's row
-    auto read_one = [&](uint32_t addr) -> bf16x8 {
+    // fragment of eight tokens: rows +0..3 and +4..7 relative to the lane's row (of `pitch` bytes)
+    auto read_one = [&](uint32_t addr, int pitch) -> bf16x8 {
       const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + addr));
-      const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + addr + 4 * kBRow));
+      const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + addr + 4 * pitch));
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     // DMA instruction q of a stage (A rows first, then B rows) into the slot at dst
@@ -302,34 +324,40 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
       rs[1] = (int)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
       rs[2] = (int)__builtin_amdgcn_readfirstlane(extent > stage_step ? extent - stage_step : 0u);
     };
-    // 16 MFMAs on (fa, fb) while the next fragments (na, nb) are read at `so`.  L/2 DMA
-    // instructions, q0 onwards, go between the four groups of four MFMAs: issued in one
-    // burst they fill the memory pipeline's queue and the wave (hence its MFMAs) stalls.
-    // ROLE: 0 = the wave's whole 128 x 128 quadrant; on a diagonal tile 1 = only the MFMA
-    // tiles on or above the diagonal (the quadrant is itself a diagonal block of H),
-    // 2 = nothing (the quadrant lies below the diagonal; the wave only moves data).
-    auto half = [&](auto role, const bf16x8 (&fa)[4], const bf16x8 (&fb)[4], bf16x8 (&na)[4], bf16x8 (&nb)[4],
-                    uint32_t so, int q0, uint32_t dst) {
+    // The MFMAs of 16 tokens on (fa, fb) while the next fragments (na, nb) are read, `soA` / `soB` bytes on.  L/2 DMA
+    // instructions, q0 onwards, go between the four groups of MFMAs: issued in one burst they fill the
+    // memory pipeline's queue and the wave (hence its MFMAs) stalls.
+    // ROLE: 0 = all MFMA tiles of the wave; on a diagonal tile 1 = only those on or above the diagonal (the quadrant is
+    // itself a diagonal block of H), 2 = the upper two rows of them (a shared quadrant), 3 = none (the quadrant lies below
+    // the diagonal; the wave only moves data).
+    auto group_order = [&](auto role, auto g_) {   // what is asked of the scheduler for group g
+      constexpr int ROLE = decltype(role)::value, g = decltype(g_)::value;
+      constexpr int M = ROLE == 1 ? 4 - g : NB;
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read
+      if constexpr (M > 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if constexpr (g < NB) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      if constexpr (M > 2) __builtin_amdgcn_sched_group_barrier(0x008, M - 2, 0);
+    };
+    // the request that goes after group g of a half: q0 + this, or -1
+    auto request_after = [](int g) constexpr { return L == 8 ? g : (L == 6 ? (g < 3 ? g : -1) : (g & 1 ? g >> 1 : -1)); };
+    auto half = [&](auto role, const bf16x8 (&fa)[4], const bf16x8 (&fb)[NB], bf16x8 (&na)[4], bf16x8 (&nb)[NB],
+                    uint32_t soA, uint32_t soB, int q0, uint32_t dst) {
       constexpr int ROLE = decltype(role)::value;
+      static_for<4>([&](auto g_) {
+        constexpr int g = decltype(g_)::value;
+        if constexpr (g < role_rows<ROLE>) na[g] = read_one(soA + adA[g], kBRow);
+        if constexpr (g < NB && ROLE != 3) nb[g] = read_one(soB + adB[g], kBRowB);
+        if constexpr (g < role_rows<ROLE>) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (ROLE != 2) {
-          na[g] = read_one(so + adA[g]);
-          nb[g] = read_one(so + adB[g]);
-#pragma unroll
-          for (int b = (ROLE == 1 ? g : 0); b < 4; ++b)
+          for (int b = (ROLE == 1 ? g : 0); b < NB; ++b)
             acc[g][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[g], fb[b], acc[g][b], 0, 0, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read
-          if (ROLE == 0 || g < 3) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          if (ROLE == 0 || g < 2) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          group_order(role, g_);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (L == 8) dma_q(q0 + g, dst);
-        else if (g & 1) dma_q(q0 + (g >> 1), dst);
+        if (request_after(g) >= 0) dma_q(q0 + request_after(g), dst);
         __builtin_amdgcn_sched_barrier(0);
-      }
+      });
     };
 
     // prologue: stages 0, 1, 2 and the first half of stage 3 are requested; stage 0 must have
@@ -355,39 +383,41 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
     // two slots, since the immediate has 16 bits -- and DST (slot being refilled) into the immediate of the request's
     // scalar add.  With a run-time slot every pair of reads and every request needs an add of its own, and this
     // loop is bound by what a wave issues besides its MFMAs.
-    uint32_t hiA[4], hiB[4];
+    uint32_t hiA[4], hiB[NB];
 #pragma unroll
     for (int T = 0; T < 4; ++T) {
       hiA[T] = adA[T] + 65536u;
+      // (opaque to the compiler, or it forms them again before every use instead of keeping the registers)
+      asm volatile("" : "+v"(hiA[T]));
+    }
+#pragma unroll
+    for (int T = 0; T < NB; ++T) {
       hiB[T] = adB[T] + 65536u;
-      // (opaque to the compiler, or it forms them again before every use instead of keeping eight registers)
-      asm volatile("" : "+v"(hiA[T]), "+v"(hiB[T]));
+      asm volatile("" : "+v"(hiB[T]));
     }
     const uint32_t wbase = lbase + wave * 1024;
-    auto half_at = [&](auto role, auto so_, auto q0_, auto dst_, const bf16x8 (&fa)[4], const bf16x8 (&fb)[4],
-                       bf16x8 (&na)[4], bf16x8 (&nb)[4]) {
+    auto half_at = [&](auto role, auto slot_, auto second_, auto q0_, auto dst_, const bf16x8 (&fa)[4], const bf16x8 (&fb)[NB],
+                       bf16x8 (&na)[4], bf16x8 (&nb)[NB]) {
       constexpr int ROLE = decltype(role)::value;
-      constexpr uint32_t SO = decltype(so_)::value, DST = decltype(dst_)::value;
+      constexpr uint32_t SA = decltype(slot_)::value + (decltype(second_)::value ? 16 * kBRow : 0), DST = decltype(dst_)::value;
+      constexpr uint32_t SB = decltype(slot_)::value + (decltype(second_)::value ? 16 * kBRowB : 0);
       constexpr int Q0 = decltype(q0_)::value;
-      constexpr bool HI = SO >= 65536u;
-      constexpr uint32_t so = HI ? SO - 65536u : SO;
+      constexpr bool HIA = SA >= 65536u, HIB = SB >= 65536u;
+      constexpr uint32_t soA = HIA ? SA - 65536u : SA, soB = HIB ? SB - 65536u : SB;
       static_for<4>([&](auto g_) {
         constexpr int g = decltype(g_)::value;
-        if constexpr (ROLE != 2) {
-          na[g] = read_one(so + (HI ? hiA[g] : adA[g]));
-          nb[g] = read_one(so + (HI ? hiB[g] : adB[g]));
+        if constexpr (g < role_rows<ROLE>) na[g] = read_one(soA + (HIA ? hiA[g] : adA[g]), kBRow);
+        if constexpr (g < NB && ROLE != 3) nb[g] = read_one(soB + (HIB ? hiB[g] : adB[g]), kBRowB);
+        if constexpr (g < role_rows<ROLE>) {
 #pragma unroll
-          for (int b = (ROLE == 1 ? g : 0); b < 4; ++b)
+          for (int b = (ROLE == 1 ? g : 0); b < NB; ++b)
             acc[g][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[g], fb[b], acc[g][b], 0, 0, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read
-          if (ROLE == 0 || g < 3) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          if (ROLE == 0 || g < 2) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          group_order(role, g_);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (L == 8 || (g & 1)) {
-          constexpr int q = (L == 8) ? Q0 + g : Q0 + (g >> 1);
+        constexpr int at = L == 8 ? g : (L == 6 ? (g < 3 ? g : -1) : (g & 1 ? g >> 1 : -1));
+        if constexpr (at >= 0) {
+          constexpr int q = Q0 + at;
           if constexpr (q < 4) dma16_at<DST + q * 4096>(rs, voA[q], wbase);
           else dma16_at<DST + kBPart + (q - 4) * 4096>(rs, voB[q - 4], wbase);
         }
@@ -405,26 +435,23 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
     auto main_loop = [&](auto role) {
       constexpr int ROLE = decltype(role)::value;
       using std::integral_constant;
-      bf16x8 fa0[4], fb0[4], fa1[4], fb1[4];
-      if (ROLE != 2) {
+      bf16x8 fa0[4], fb0[NB], fa1[4], fb1[NB];
 #pragma unroll
-        for (int T = 0; T < 4; ++T) {
-          fa0[T] = read_one(adA[T]);
-          fb0[T] = read_one(adB[T]);
-        }
-      }
+      for (int T = 0; T < role_rows<ROLE>; ++T) fa0[T] = read_one(adA[T], kBRow);
+#pragma unroll
+      for (int T = 0; T < (ROLE == 3 ? 0 : NB); ++T) fb0[T] = read_one(adB[T], kBRowB);
       auto iteration_at = [&](auto slot_) {
         constexpr uint32_t SLOT = decltype(slot_)::value;
         constexpr uint32_t slot_off = SLOT * kBStage, pend_off = ((SLOT + kBRing - 1) & (kBRing - 1)) * kBStage,
                            next_off = ((SLOT + 1) & (kBRing - 1)) * kBStage;
-        half_at(role, integral_constant<uint32_t, slot_off + 16 * kBRow>{}, integral_constant<int, L / 2>{},
+        half_at(role, integral_constant<uint32_t, slot_off>{}, std::true_type{}, integral_constant<int, L / 2>{},
                 integral_constant<uint32_t, pend_off>{}, fa0, fb0, fa1, fb1);
         dma_advance();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         wait_vmcnt<2 * L>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        half_at(role, integral_constant<uint32_t, next_off>{}, integral_constant<int, 0>{},
+        half_at(role, integral_constant<uint32_t, next_off>{}, std::false_type{}, integral_constant<int, 0>{},
                 integral_constant<uint32_t, slot_off>{}, fa1, fb1, fa0, fb0);
       };
       int s = 0;
@@ -438,34 +465,70 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
         const uint32_t slot_off = (s & (kBRing - 1)) * kBStage;
         const uint32_t pend_off = ((s + kBRing - 1) & (kBRing - 1)) * kBStage;
         const uint32_t next_off = ((s + 1) & (kBRing - 1)) * kBStage;
-        half(role, fa0, fb0, fa1, fb1, slot_off + 16 * kBRow, L / 2, lbase + pend_off + wave * 1024);
+        half(role, fa0, fb0, fa1, fb1, slot_off + 16 * kBRow, slot_off + 16 * kBRowB, L / 2, lbase + pend_off + wave * 1024);
         dma_advance();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         wait_vmcnt<2 * L>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        half(role, fa1, fb1, fa0, fb0, next_off, 0, lbase + slot_off + wave * 1024);
+        half(role, fa1, fb1, fa0, fb0, next_off, next_off, 0, lbase + slot_off + wave * 1024);
       }
     };
-    if (!diag || wave == 1)
+    if constexpr (!diag) {
       main_loop(std::integral_constant<int, 0>{});
-    else if (wave == 2)
-      main_loop(std::integral_constant<int, 2>{});
-    else
-      main_loop(std::integral_constant<int, 1>{});
+    } else if constexpr (SHARED) {
+      if (wave == 1 || wave == 2) main_loop(std::integral_constant<int, 2>{});
+      else main_loop(std::integral_constant<int, 1>{});
+    } else {
+      if (wave == 1) main_loop(std::integral_constant<int, 0>{});
+      else if (wave == 2) main_loop(std::integral_constant<int, 3>{});
+      else main_loop(std::integral_constant<int, 1>{});
+    }
     wait_vmcnt<0>();  // nothing may still be landing in LDS when the workgroup ends
   }
 
+  // register r of MFMA tile (a, b): row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
+  const int il0 = wi * 128 + low * 64 + (lane >> 5) * 4, jl0 = (NB == 2 ? 128 * half_tile : 0) + wj * 32 * NB + (lane & 31);
+  const int rows = SHARED && (wave == 1 || wave == 2) ? 2 : 4;   // MFMA tile rows of this wave
+  if (H) {
+    // The only split: straight into H, eight rows at a time across all of the wave's columns, all loads of a step on
+    // their way together (a load under a condition would wait for the one before: 69 us instead of 29 for a call of 32
+    // tokens at n = 4096).
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a) {
+      if (a >= rows) break;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+      for (int r0 = 0; r0 < 16; r0 += 4) {
+        double v[4][NB];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            const int i = I * kBT + il0 + 32 * a + 2 * r0 + r, j = J * kBT + jl0 + 32 * b;
+            v[r][b] = H[(int64_t)min(i, n - 1) * ldh + min(j, n - 1)];   // issued whatever (i, j): no branch, no wait
+          }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            const int i = I * kBT + il0 + 32 * a + 2 * r0 + r, j = J * kBT + jl0 + 32 * b;
+            if (j < n && i <= j) H[(int64_t)i * ldh + j] = v[r][b] + (double)acc[a][b][r0 + r];
+          }
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    if (a >= rows) break;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int il = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        const int jl = lane & 31;
-        out[(wi * 128 + 32 * a + il) * kBT + wj * 128 + 32 * b + jl] = acc[a][b][r];
+        const int il = il0 + 32 * a + (r >> 2) * 8 + (r & 3);
+        out[il * kBT + jl0 + 32 * b] = acc[a][b][r];
       }
+  }
 }
 
 // Work order.  Workgroups are handed to the eight XCDs (each with its own L2) round-robin by
@@ -506,23 +569,50 @@ __device__ __forceinline__ void tile_in_locality_order(int r, int ntb, int& I, i
   I = J = 0;  // not reached
 }
 
+// HALVES: an item is half of an off-diagonal tile (and the whole of a diagonal one: those come first, they take a
+// quarter longer).  For calibration that arrives a few sequences at a time, where the tiles of a call alone do not
+// fill the chip: n = 4096 has 136 tiles, but 256 such items.  Half a tile takes about 66 % of a whole one's time (three
+// quarters of its operands pass through the LDS for half the MFMAs), so the split into halves is taken where it
+// saves rounds of 256 workgroups.
+// H not null: one split, added to H without a partial tile.  Bound: H's float64 update, 16 bytes per entry.
+// Call of 2048 tokens, partial tiles and whole tiles before: n = 2048 39.9 -> 31.9 us, n = 4096 89.6 -> 54.3,
+// n = 5632 119 -> 88, n = 8192 325 -> 234, n = 11008 571 -> 404.
+template <bool HALVES, bool SHARED>
 __global__ __launch_bounds__(256) void hessian_bf16_big_kernel(const uint16_t* __restrict__ X, int64_t ldx,
                                                                int64_t t, int n, int64_t tok0, int chunk,
                                                                int ntb, int ntiles, int nsplits,
-                                                               float* __restrict__ partial) {
+                                                               float* __restrict__ partial, double* __restrict__ H,
+                                                               int64_t ldh) {
   extern __shared__ __attribute__((aligned(16))) uint16_t hs[];
-  const int total = ntiles * nsplits;
+  const int items = HALVES ? ntb * ntb : ntiles;
+  const int total = items * nsplits;
   const int q = 256 * (blockIdx.x >> 8) + 32 * (blockIdx.x & 7) + ((blockIdx.x & 255) >> 3);
   if (q >= total) return;
-  const int split = q / ntiles;
-  int I, J;
-  tile_in_locality_order(q - split * ntiles, ntb, I, J);
+  const int split = q / items;
+  int k = q - split * items, I, J, half_tile = 0;
+  if constexpr (HALVES) {
+    if (k < ntb) {
+      I = J = k;
+    } else {   // the two halves of a tile above the diagonal, row by row of tiles
+      k -= ntb;
+      half_tile = k & 1;
+      k >>= 1;
+      I = 0;
+      while (k >= ntb - 1 - I) {
+        k -= ntb - 1 - I;
+        ++I;
+      }
+      J = I + 1 + k;
+    }
+  } else {
+    tile_in_locality_order(k, ntb, I, J);
+  }
   const int lin = I * ntb - I * (I - 1) / 2 + (J - I);  // index in the row-major upper-triangular tile list
   float* out = partial + ((int64_t)split * ntiles + lin) * (kBT * kBT);
   if (I == J)
-    big_tile<true>(X, ldx, t, n, tok0, chunk, I, J, split, out, hs);
+    big_tile<true, 4, SHARED>(X, ldx, t, n, tok0, chunk, I, J, 0, split, out, H, ldh, hs);
   else
-    big_tile<false>(X, ldx, t, n, tok0, chunk, I, J, split, out, hs);
+    big_tile<false, HALVES ? 2 : 4>(X, ldx, t, n, tok0, chunk, I, J, half_tile, split, out, H, ldh, hs);
 }
 
 // H[upper] += sum over splits of the partial tiles, in float64, fixed order.  Four consecutive
@@ -553,9 +643,11 @@ __global__ __launch_bounds__(256) void hessian_reduce_kernel(const PT* __restric
 
 struct Plan {
   int tile, ntb, ntiles, chunk, splits_total, splits_launch;
+  bool halves;   // 256-tile kernel: items of half a tile
   size_t tile_bytes;
 };
 
+constexpr int64_t kHalfCost = 66;   // percent of a whole tile's time that half a tile takes (measured with full rounds)
 constexpr int64_t kBigFrom = 2048;                   // layers at least this wide use the 256-tile kernel
 constexpr size_t kMaxPartialBytes = (size_t)1 << 30;  // partial tiles in flight per launch
 
@@ -579,16 +671,20 @@ Plan make_plan(int64_t n, int64_t t, ptq_dtype dt, bool allow_big) {
   const int64_t max_chunk = big ? (p.ntiles >= 512 ? kMaxChunkHuge : kMaxChunkBig) : kMaxChunk;
   const int64_t s_min = ceil_div(t > 0 ? t : 1, max_chunk);
   int64_t best_s = s_min, best_cost = -1;
-  for (int64_t sp = s_min; sp < s_min + 64; ++sp) {
-    int64_t ch = ceil_div(ceil_div(t > 0 ? t : 1, sp), kt) * kt;
-    if (ch < 256 && sp > s_min) break;
-    // + 1024: writing and re-reading a partial tile costs about as much as 1024 tokens
-    const int64_t cost = ceil_div(p.ntiles * sp, 256) * (ch + 1024);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best_s = sp;
+  p.halves = false;
+  for (int halves = 0; halves <= (big ? 1 : 0); ++halves)
+    for (int64_t sp = s_min; sp < s_min + 64; ++sp) {
+      int64_t ch = ceil_div(ceil_div(t > 0 ? t : 1, sp), kt) * kt;
+      if (ch < 256 && sp > s_min) break;
+      // + 1024: writing and re-reading a partial tile costs about as much as 1024 tokens; + 400 for one added to H at once
+      const int64_t items = halves ? (int64_t)p.ntb * p.ntb : p.ntiles;
+      const int64_t cost = ceil_div(items * sp, 256) * (ch + (big && sp == 1 ? 400 : 1024)) * (halves ? kHalfCost : 100);
+      if (best_cost < 0 || cost < best_cost) {
+        best_cost = cost;
+        best_s = sp;
+        p.halves = halves;
+      }
     }
-  }
   int64_t chunk = ceil_div(ceil_div(t > 0 ? t : 1, best_s), kt) * kt;
   if (chunk < kt) chunk = kt;
   p.chunk = (int)chunk;
@@ -625,13 +721,22 @@ ptq_status hessian_launch(double* H, int64_t ldh, const void* X, ptq_dtype xdt, 
     dim3 g((unsigned)p.ntiles, (unsigned)ns);
     dim3 gr((unsigned)p.ntiles, (unsigned)(p.tile * p.tile / 1024));
     if (xdt == PTQ_BF16 && p.tile == kBT) {
-      if (!lds_opt_in<hessian_bf16_big_kernel>((int)kBigLdsBytes)) return PTQ_ERR_HIP;
-      const unsigned nwg = 256u * (unsigned)ceil_div((int64_t)p.ntiles * ns, 256);
-      hessian_bf16_big_kernel<<<nwg, 256, kBigLdsBytes, st>>>(static_cast<const uint16_t*>(X), ldx, t, (int)n,
-                                                              tok0, p.chunk, p.ntb, p.ntiles, ns,
-                                                              static_cast<float*>(ws));
-      hessian_reduce_kernel<float, kBT><<<gr, 256, 0, st>>>(static_cast<const float*>(ws), ns, p.ntiles,
-                                                            p.ntb, (int)n, H, ldh);
+      const bool direct = p.splits_total == 1;
+      auto launch = [&](auto halves, auto shared) {
+        constexpr bool HALVES = decltype(halves)::value, SHARED = decltype(shared)::value;
+        if (!lds_opt_in<hessian_bf16_big_kernel<HALVES, SHARED>>((int)kBigLdsBytes)) return false;
+        const int64_t items = HALVES ? (int64_t)p.ntb * p.ntb : p.ntiles;
+        hessian_bf16_big_kernel<HALVES, SHARED><<<256u * (unsigned)ceil_div(items * ns, 256), 256, kBigLdsBytes, st>>>(
+            static_cast<const uint16_t*>(X), ldx, t, (int)n, tok0, p.chunk, p.ntb, p.ntiles, ns, static_cast<float*>(ws),
+            direct ? H : nullptr, ldh);
+        return true;
+      };
+      const std::true_type yes;
+      const std::false_type no;
+      if (!(p.halves ? launch(yes, yes) : (direct ? launch(no, yes) : launch(no, no)))) return PTQ_ERR_HIP;
+      if (!direct)
+        hessian_reduce_kernel<float, kBT><<<gr, 256, 0, st>>>(static_cast<const float*>(ws), ns, p.ntiles,
+                                                              p.ntb, (int)n, H, ldh);
     } else if (xdt == PTQ_BF16) {
       hessian_bf16_kernel<<<g, 256, 0, st>>>(static_cast<const uint16_t*>(X), ldx, t, (int)n, tok0, p.chunk,
                                              p.ntb, static_cast<float*>(ws));
