@@ -9,10 +9,15 @@
 // sum_i e_i^2 with e = (w - c) T^-1 taken by forward substitution (the errors the scalar walk would
 // make column by column); the entry with the smallest loss is assigned, the lowest index among exactly
 // equal ones.  Half a wave works for one row: a lane keeps K / 32 entries in registers for the whole
-// walk, evaluates their losses, and the 32 lanes agree on the minimum by exchanging (loss, index)
-// pairs; every lane then knows the group's errors and applies them to the later columns of the
+// walk, evaluates their losses, and the 32 lanes agree on the minimum by data-parallel exchanges (the
+// smallest loss first, then the lowest index that has it); the assigned entry comes from a copy of the
+// codebook in LDS.  Every lane then knows the group's errors and applies them to the later columns of the
 // mini-block itself, so the eight waves walk their two rows each without a barrier between groups.
-#include "common.h"
+// Bound: float64 vector instructions of the losses (18 and a selection per entry of 4 weights) and the
+// chain from a group's losses to the next group's values.  4096 x 4096, 256 x 4: 4.13 -> 3.75 ms; 64 x 2: 4.12 -> 2.78
+// (before: lane permutes through the LDS crossbar, the entry taken out of registers, and room for 256
+// entries in every lane whatever K).
+#include "rotation.h"
 
 namespace ptq {
 namespace {
@@ -21,7 +26,7 @@ constexpr int kRows = 16;       // rows per workgroup
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kRowAlign = 96;   // row padding of the error matrix (the scalar solve's workspace layout)
-constexpr int kSlots = 8;       // codebook entries per lane: K <= 32 * kSlots
+constexpr int kMaxEntries = 256;  // a lane holds SLOTS of them: K <= 32 * SLOTS
 
 struct VqArgs {
   const void* W;
@@ -45,21 +50,27 @@ __global__ void vq_inv_diag_kernel(const double* __restrict__ U, int64_t ldu, in
   if (j < n) invd[j] = 1.0 / U[(int64_t)j * ldu + j];
 }
 
-// (loss, index) of lane ^ MASK, by two 32-bit lane permutes per double
-template <int MASK>
-__device__ __forceinline__ void take_smaller(double& loss, int& idx) {
-  const int lane = threadIdx.x & 63;
-  const int src = (lane ^ MASK) << 2;
-  const int lo = __builtin_amdgcn_ds_bpermute(src, __double2loint(loss));
-  const int hi = __builtin_amdgcn_ds_bpermute(src, __double2hiint(loss));
-  const int oi = __builtin_amdgcn_ds_bpermute(src, idx);
-  const double ol = __hiloint2double(hi, lo);
-  const bool take = (ol < loss) || (ol == loss && oi < idx);
-  loss = take ? ol : loss;
-  idx = take ? oi : idx;
+// Smallest value over the 32 lanes of a half-wave, in every one of them.
+__device__ __forceinline__ double half_wave_min(double v) {
+  v = fmin(v, dpp_move<kDppSwapPairs>(v));
+  v = fmin(v, dpp_move<kDppSwapHalfQuads>(v));
+  v = fmin(v, dpp_move<kDppHalfMirror>(v));
+  v = fmin(v, dpp_move<kDppMirror>(v));
+  double even, odd;
+  lane_pair<false>(v, v, even, odd);
+  return fmin(even, odd);
+}
+__device__ __forceinline__ int half_wave_min(int v) {
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppSwapPairs, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppSwapHalfQuads, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xf, 0xf, false));
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 p = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  return min((int)p[0], (int)p[1]);
 }
 
-template <int DT, int NT, int D>
+template <int DT, int NT, int D, int SLOTS>
 __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   extern __shared__ double lds[];
   const int tid = threadIdx.x;
@@ -79,7 +90,8 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   double* Qm = Em + 256;                            // [16 k][17] assigned values of the mini-block
   double* Ud = Qm + 272;                            // [2][16][16] diagonal block of U
   double* Id = Ud + 512;                            // [2][16] reciprocal pivots
-  uint8_t* It = reinterpret_cast<uint8_t*>(Id + 32);  // [16][bw / D] indices of the block
+  double* Cb = Id + 32;                             // [32 SLOTS][D] the codebook
+  uint8_t* It = reinterpret_cast<uint8_t*>(Cb + kMaxEntries * D);  // [16][bw / D] indices of the block
 
   // ---- phase 1: acc = E[rows, 0:i1] * U[0:i1, block], k split over the waves
   f64x4 acc[NT];
@@ -186,6 +198,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
     }
     if (tid < 256) Ud[tid] = U[(int64_t)(a.i1 + (tid >> 4)) * a.ldu + a.i1 + (tid & 15)];
     if (tid < 16) Id[tid] = invd[a.i1 + tid];
+    for (int e = tid; e < 32 * SLOTS * D; e += kThreads) Cb[e] = e < a.K * D ? (double)a.codebook[e] : 0.0;
   }
   __syncthreads();
 
@@ -193,13 +206,11 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   // this lane's codebook entries, k = l32 + 32 s, in registers from here on (after the lazy update, whose
   // accumulators need the room)
   const int l32 = lane & 31;
-  double cb[kSlots][D];
+  double cb[SLOTS][D];
 #pragma unroll
-  for (int s = 0; s < kSlots; ++s) {
-    const int k = l32 + 32 * s;
+  for (int s = 0; s < SLOTS; ++s)
 #pragma unroll
-    for (int i = 0; i < D; ++i) cb[s][i] = k < a.K ? (double)a.codebook[k * D + i] : 0.0;
-  }
+    for (int i = 0; i < D; ++i) cb[s][i] = Cb[(l32 + 32 * s) * D + i];
   const int r = 2 * wave + (lane >> 5);   // the row of this half-wave
   double err2 = 0.0;
   constexpr int kUpd = (NT + kWaves - 1) / kWaves;
@@ -229,6 +240,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
       for (int j = 0; j < 16; ++j) w[j] = S[r * sp + c0 + j];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
+        __builtin_amdgcn_sched_barrier(0);   // a group's LDS reads stay in it: all groups' together do not fit the registers
         // the group's triangle of U and its reciprocal pivots
         double T[D][D], inv[D];
 #pragma unroll
@@ -241,7 +253,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
         double best = __builtin_inf();
         int bidx = 0x7fffffff;
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
+        for (int s = 0; s < SLOTS; ++s) {
           const int k = l32 + 32 * s;
           double rem[D], loss = 0.0;
 #pragma unroll
@@ -257,24 +269,16 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
           best = take ? loss : best;
           bidx = take ? k : bidx;
         }
-        take_smaller<1>(best, bidx);
-        take_smaller<2>(best, bidx);
-        take_smaller<4>(best, bidx);
-        take_smaller<8>(best, bidx);
-        take_smaller<16>(best, bidx);
-        // every lane of the half-wave now holds the assigned index; its entry comes from the lane that owns it
+        {
+          const double smallest = half_wave_min(best);
+          bidx = half_wave_min(best == smallest ? bidx : 0x7fffffff);
+        }
+        // every lane of the half-wave now holds the assigned index (one past the codebook if no loss was a number)
         double q[D], e[D];
         {
-          const int owner = ((lane & 32) | (bidx & 31)) << 2, slot = bidx >> 5;
+          const int entry = bidx < 32 * SLOTS ? bidx : 31;
 #pragma unroll
-          for (int i = 0; i < D; ++i) {
-            double mine = cb[0][i];
-#pragma unroll
-            for (int s = 1; s < kSlots; ++s) mine = (slot == s) ? cb[s][i] : mine;
-            const int lo = __builtin_amdgcn_ds_bpermute(owner, __double2loint(mine));
-            const int hi = __builtin_amdgcn_ds_bpermute(owner, __double2hiint(mine));
-            q[i] = __hiloint2double(hi, lo);
-          }
+          for (int i = 0; i < D; ++i) q[i] = Cb[entry * D + i];
         }
         {
           double rem[D];
@@ -350,26 +354,31 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   }
 }
 
-size_t vq_lds_bytes(int bw) {
-  return (size_t)(4 * kRows * bw + 256 + 272 + 512 + 32) * sizeof(double) + (size_t)kRows * bw;
+size_t vq_lds_bytes(int bw, int d) {
+  return (size_t)(4 * kRows * bw + 256 + 272 + 512 + 32 + kMaxEntries * d) * sizeof(double) + (size_t)kRows * bw;
 }
 
-template <int DT, int NT, int D>
+template <int DT, int NT, int D, int SLOTS>
 ptq_status vq_launch_block(const VqArgs& a, hipStream_t st) {
-  if (!lds_opt_in<vq_block_kernel<DT, NT, D>>((int)vq_lds_bytes(16 * NT))) return PTQ_ERR_HIP;
-  vq_block_kernel<DT, NT, D><<<(unsigned)ceil_div(a.m, kRows), kThreads, vq_lds_bytes(a.bw), st>>>(a);
+  if (!lds_opt_in<vq_block_kernel<DT, NT, D, SLOTS>>((int)vq_lds_bytes(16 * NT, D))) return PTQ_ERR_HIP;
+  vq_block_kernel<DT, NT, D, SLOTS><<<(unsigned)ceil_div(a.m, kRows), kThreads, vq_lds_bytes(a.bw, D), st>>>(a);
+  return PTQ_OK;
+}
+
+template <int DT, int D, int SLOTS>
+ptq_status vq_run_blocks_with(VqArgs a, int block, hipStream_t st) {
+  for (int i1 = 0; i1 < a.n; i1 += block) {
+    a.i1 = i1;
+    a.bw = (a.n - i1 < block) ? a.n - i1 : block;
+    const ptq_status rc = (a.bw <= 128) ? vq_launch_block<DT, 8, D, SLOTS>(a, st) : vq_launch_block<DT, 16, D, SLOTS>(a, st);
+    if (rc != PTQ_OK) return rc;
+  }
   return PTQ_OK;
 }
 
 template <int DT, int D>
-ptq_status vq_run_blocks(VqArgs a, int block, hipStream_t st) {
-  for (int i1 = 0; i1 < a.n; i1 += block) {
-    a.i1 = i1;
-    a.bw = (a.n - i1 < block) ? a.n - i1 : block;
-    const ptq_status rc = (a.bw <= 128) ? vq_launch_block<DT, 8, D>(a, st) : vq_launch_block<DT, 16, D>(a, st);
-    if (rc != PTQ_OK) return rc;
-  }
-  return PTQ_OK;
+ptq_status vq_run_blocks(const VqArgs& a, int block, hipStream_t st) {
+  return a.K <= 64 ? vq_run_blocks_with<DT, D, 2>(a, block, st) : vq_run_blocks_with<DT, D, 8>(a, block, st);
 }
 
 template <int DT>
