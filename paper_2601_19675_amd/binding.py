@@ -106,7 +106,8 @@ def ptq_workspace_bytes(op: int, m: int = 0, n: int = 0, t: int = 0, block: int 
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the raw handle of torch.cuda.current_stream(), without the Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t) -> int | None:
@@ -129,9 +130,11 @@ def _check_dev(*ts):
             raise ValueError("libptq takes device tensors only")
 
 
-def _ws(ws: torch.Tensor | None, need: int, like: torch.Tensor) -> torch.Tensor:
+def _ws(ws: torch.Tensor | None, like: torch.Tensor, op: int, m: int = 0, n: int = 0, t: int = 0,
+        block: int = 0) -> torch.Tensor:
+    """The caller's workspace (the library checks its size), or a new one of the size the call needs."""
     if ws is None:
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=like.device)
+        ws = torch.empty(max(ptq_workspace_bytes(op, m, n, t, block), 256), dtype=torch.uint8, device=like.device)
     return ws
 
 
@@ -140,7 +143,7 @@ def ptq_hessian_accumulate(H: torch.Tensor, X: torch.Tensor, ws: torch.Tensor | 
     _check_dev(H, X)
     t, n = X.shape
     assert H.dtype == torch.float64 and H.shape == (n, n) and H.stride(1) == 1 and X.stride(1) == 1
-    ws = _ws(ws, ptq_workspace_bytes(OP_HESSIAN, 0, n, t), H)
+    ws = _ws(ws, H, OP_HESSIAN, 0, n, t)
     rc = load_library().ptq_hessian_accumulate(H.data_ptr(), H.stride(0), X.data_ptr(), _dtype_code(X), t,
                                                n, X.stride(0), ws.data_ptr(), ws.numel(), _stream())
     if rc:
@@ -156,7 +159,7 @@ def ptq_damped_cholesky_inv(H: torch.Tensor, damp: float, U: torch.Tensor,
     assert H.dtype == torch.float64 and U.dtype == torch.float64 and info.dtype == torch.int32
     assert H.stride(1) == 1 and U.stride(1) == 1 and U.shape == (n, n) and info.numel() >= 2
     assert dead_mask is None or (dead_mask.dtype == torch.uint8 and dead_mask.numel() >= n)
-    ws = _ws(ws, ptq_workspace_bytes(OP_CHOLESKY_INV, 0, n), H)
+    ws = _ws(ws, H, OP_CHOLESKY_INV, 0, n)
     rc = load_library().ptq_damped_cholesky_inv(H.data_ptr(), H.stride(0), n, float(damp), U.data_ptr(),
                                                 U.stride(0), _ptr(dead_mask), info.data_ptr(),
                                                 ws.data_ptr(), ws.numel(), _stream())
@@ -179,7 +182,7 @@ def ptq_quantize_layer(W: torch.Tensor, U: torch.Tensor, dead_mask: torch.Tensor
         assert zeros.dtype == torch.uint8 and zeros.is_contiguous() and zeros.shape == (m, n // group)
     assert Wq is None or (Wq.dtype == torch.float64 and Wq.is_contiguous() and Wq.shape == (m, n))
     assert row_err2 is None or (row_err2.dtype == torch.float64 and row_err2.numel() >= m)
-    ws = _ws(ws, ptq_workspace_bytes(OP_QUANTIZE, m, n), W)
+    ws = _ws(ws, W, OP_QUANTIZE, m, n)
     rc = getattr(load_library(), _entry)(W.data_ptr(), _dtype_code(W), W.stride(0), m, n, U.data_ptr(),
                                          U.stride(0), _ptr(dead_mask), bits, group, block,
                                          codes.data_ptr(), scales.data_ptr(), zeros.data_ptr(), _ptr(Wq),
@@ -210,7 +213,7 @@ def ptq_quantize_layer_vq(W: torch.Tensor, U: torch.Tensor, dead_mask: torch.Ten
         assert indices.dtype == torch.uint8 and indices.is_contiguous() and indices.shape == (m, n // dim)
     assert Wq is None or (Wq.dtype == torch.float64 and Wq.is_contiguous() and Wq.shape == (m, n))
     assert row_err2 is None or (row_err2.dtype == torch.float64 and row_err2.numel() >= m)
-    ws = _ws(ws, ptq_workspace_bytes(OP_QUANTIZE, m, n), W)
+    ws = _ws(ws, W, OP_QUANTIZE, m, n)
     rc = load_library().ptq_quantize_layer_vq(W.data_ptr(), _dtype_code(W), W.stride(0), m, n, U.data_ptr(), U.stride(0),
                                               _ptr(dead_mask), codebook.data_ptr(), entries, dim, block,
                                               indices.data_ptr(), _ptr(Wq), _ptr(row_err2), ws.data_ptr(), ws.numel(),
@@ -226,7 +229,7 @@ def ptq_layer_error(W: torch.Tensor, Wq: torch.Tensor, H: torch.Tensor, out: tor
     m, n = W.shape
     assert Wq.dtype == torch.float64 and Wq.is_contiguous() and Wq.shape == (m, n)
     assert H.dtype == torch.float64 and H.stride(1) == 1 and out.dtype == torch.float64 and out.numel() >= 3
-    ws = _ws(ws, ptq_workspace_bytes(OP_LAYER_ERROR, m, n), W)
+    ws = _ws(ws, W, OP_LAYER_ERROR, m, n)
     rc = load_library().ptq_layer_error(W.data_ptr(), _dtype_code(W), W.stride(0), Wq.data_ptr(), m, n,
                                         H.data_ptr(), H.stride(0), out.data_ptr(), ws.data_ptr(),
                                         ws.numel(), _stream())
@@ -242,7 +245,7 @@ def ptq_lopro_column_order(R: torch.Tensor, H: torch.Tensor, perm: torch.Tensor,
     assert R.stride(1) == 1 and H.dtype == torch.float64 and H.stride(1) == 1
     assert perm.dtype == torch.int32 and perm.is_contiguous() and perm.numel() >= n
     assert keys is None or (keys.dtype == torch.float64 and keys.is_contiguous() and keys.numel() >= n)
-    ws = _ws(ws, ptq_workspace_bytes(OP_LOPRO_ORDER, m, n), R)
+    ws = _ws(ws, R, OP_LOPRO_ORDER, m, n)
     rc = load_library().ptq_lopro_column_order(R.data_ptr(), _dtype_code(R), R.stride(0), m, n, H.data_ptr(),
                                                H.stride(0), int(bool(descending)), perm.data_ptr(),
                                                _ptr(keys), ws.data_ptr(), ws.numel(), _stream())
@@ -281,7 +284,7 @@ def ptq_lopro_rotate_hessian(H: torch.Tensor, perm: torch.Tensor, b_I: int, b_H:
     n = H.shape[0]
     assert H.dtype == torch.float64 and H.stride(1) == 1 and perm.dtype == torch.int32 and perm.is_contiguous()
     assert Hout.dtype == torch.float64 and Hout.stride(1) == 1 and Hout.shape == (n, n)
-    ws = _ws(ws, ptq_workspace_bytes(OP_LOPRO_ROTATE_HESSIAN, 0, n), H)
+    ws = _ws(ws, H, OP_LOPRO_ROTATE_HESSIAN, 0, n)
     rc = load_library().ptq_lopro_rotate_hessian(H.data_ptr(), H.stride(0), n, perm.data_ptr(), b_I, b_H,
                                                  Hout.data_ptr(), Hout.stride(0), ws.data_ptr(), ws.numel(),
                                                  _stream())
@@ -294,7 +297,7 @@ def ptq_activation_abs_sum(asum: torch.Tensor, X: torch.Tensor, ws: torch.Tensor
     _check_dev(asum, X)
     t, n = X.shape
     assert X.stride(1) == 1 and asum.dtype == torch.float64 and asum.is_contiguous() and asum.numel() >= n
-    ws = _ws(ws, ptq_workspace_bytes(OP_ACTIVATION_ABS_SUM, 0, n), X)
+    ws = _ws(ws, X, OP_ACTIVATION_ABS_SUM, 0, n)
     rc = load_library().ptq_activation_abs_sum(asum.data_ptr(), X.data_ptr(), _dtype_code(X), t, n, X.stride(0),
                                                ws.data_ptr(), ws.numel(), _stream())
     if rc:
@@ -325,7 +328,7 @@ def ptq_scaled_r1svd(W: torch.Tensor, s: torch.Tensor, S: torch.Tensor, it: int,
     assert V.dtype == torch.uint8 and V.is_contiguous() and V.shape == (r, n)
     assert sigma.dtype == torch.float16 and sigma.is_contiguous() and sigma.numel() == r
     assert R.dtype == torch.float32 and R.stride(1) == 1 and R.shape == (m, n)
-    ws = _ws(ws, ptq_workspace_bytes(OP_SCALED_R1SVD, m, n), W)
+    ws = _ws(ws, W, OP_SCALED_R1SVD, m, n)
     rc = load_library().ptq_scaled_r1svd(W.data_ptr(), _dtype_code(W), W.stride(0), m, n, s.data_ptr(),
                                          S.data_ptr(), S.stride(0) if r else n, r, int(it), U.data_ptr(),
                                          V.data_ptr(), sigma.data_ptr(), R.data_ptr(), R.stride(0),
@@ -406,7 +409,7 @@ def ptq_lopro_linear_forward(X: torch.Tensor, packed: torch.Tensor, bits: int, s
         if rc:
             raise PtqError(rc, "ptq_lopro_linear_forward_static")
         return
-    ws = _ws(ws, ptq_workspace_bytes(OP_LINEAR_FORWARD, m, n, tokens, r), X)
+    ws = _ws(ws, X, OP_LINEAR_FORWARD, m, n, tokens, r)
     rc = load_library().ptq_lopro_linear_forward(*args, ws.data_ptr(), ws.numel(), _stream())
     if rc:
         raise PtqError(rc, "ptq_lopro_linear_forward")
