@@ -169,33 +169,34 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   }
   __syncthreads();
 
-  // ---- state tile S = W - (p0 + p1 + p2 + p3), dead channels read as zero
+  // ---- state tile S = W - (p0 + p1 + p2 + p3), dead channels read as zero; what comes from memory is requested all at
+  //      once and whatever the row (loads under a condition wait for each other)
   {
     constexpr int NP = (kRows * 16 * NT + kThreads - 1) / kThreads;
+    typename StoredType<DT>::type wraw[NP];
+    uint8_t draw[NP];
+    int at[NP];   // row * 256 + column of the block
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int e = min(tid + kThreads * p, kRows * a.bw - 1);
+      const int r = e / a.bw, c = e - r * a.bw;
+      at[p] = r << 8 | c;
+      wraw[p] = load_stored<DT>(a.W, (int64_t)min(row0 + r, a.m - 1) * a.ldw + a.i1 + c);
+      draw[p] = a.dead ? a.dead[a.i1 + c] : (uint8_t)0;
+    }
     double sv[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const int e = tid + kThreads * p;
-      sv[p] = 0.0;
-      if (e < kRows * a.bw) {
-        const int r = e / a.bw, c = e - r * a.bw;
-        double w = 0.0;
-        if (row0 + r < a.m && !(a.dead && a.dead[a.i1 + c]))
-          w = load_as_f64<DT>(a.W, (int64_t)(row0 + r) * a.ldw + a.i1 + c);
-        const double s01 = P[(0 * kRows + r) * a.bw + c] + P[(1 * kRows + r) * a.bw + c];
-        const double s23 = P[(2 * kRows + r) * a.bw + c] + P[(3 * kRows + r) * a.bw + c];
-        sv[p] = w - (s01 + s23);
-      }
+      const int r = at[p] >> 8, c = at[p] & 255;
+      const double w = (row0 + r < a.m && draw[p] == 0) ? stored_to_f64<DT>(wraw[p]) : 0.0;
+      const double s01 = P[(0 * kRows + r) * a.bw + c] + P[(1 * kRows + r) * a.bw + c];
+      const double s23 = P[(2 * kRows + r) * a.bw + c] + P[(3 * kRows + r) * a.bw + c];
+      sv[p] = w - (s01 + s23);
     }
     __syncthreads();
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int e = tid + kThreads * p;
-      if (e < kRows * a.bw) {
-        const int r = e / a.bw, c = e - r * a.bw;
-        S[r * sp + c] = sv[p];
-      }
-    }
+    for (int p = 0; p < NP; ++p)
+      if (tid + kThreads * p < kRows * a.bw) S[(at[p] >> 8) * sp + (at[p] & 255)] = sv[p];
     if (tid < 256) Ud[tid] = U[(int64_t)(a.i1 + (tid >> 4)) * a.ldu + a.i1 + (tid & 15)];
     if (tid < 16) Id[tid] = invd[a.i1 + tid];
     for (int e = tid; e < 32 * SLOTS * D; e += kThreads) Cb[e] = e < a.K * D ? (double)a.codebook[e] : 0.0;
