@@ -14,9 +14,10 @@
 // codebook in LDS.  Every lane then knows the group's errors and applies them to the later columns of the
 // mini-block itself, so the eight waves walk their two rows each without a barrier between groups.
 // Bound: float64 vector instructions of the losses (18 and a selection per entry of 4 weights) and the
-// chain from a group's losses to the next group's values.  4096 x 4096, 256 x 4: 4.13 -> 3.75 ms; 64 x 2: 4.12 -> 2.78
-// (before: lane permutes through the LDS crossbar, the entry taken out of registers, and room for 256
+// chain from a group's losses to the next group's values.  4096 x 4096, 256 x 4: 4.13 -> 3.39 ms; 64 x 2: 4.12 -> 2.49
+// (before: lane permutes through the LDS crossbar, the entry taken out of registers, conditional loads, and room for 256
 // entries in every lane whatever K).
+#include "lazy_update.h"
 #include "rotation.h"
 
 namespace ptq {
@@ -95,59 +96,9 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
 
   // ---- phase 1: acc = E[rows, 0:i1] * U[0:i1, block], k split over the waves
   f64x4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-  // 16-byte loads need 16-byte alignment here (plain loads): an even ldu and U itself aligned
-  const bool paired = (nt % 2 == 0) && (a.ldu % 2 == 0) && ((reinterpret_cast<uintptr_t>(U) & 15) == 0);
+  const bool paired = lazy_update_paired(nt, a.n, a.ldu, a.mpad);
   auto column_of = [&](int t, int cl) { return paired ? 32 * (t >> 1) + 2 * cl + (t & 1) : 16 * t + cl; };
-  {
-    constexpr int kDepth = (NT >= 16) ? 2 : 4;
-    const int kl = lane >> 4, cl = lane & 15;
-    int coff[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) coff[t] = 16 * (t < nt ? t : nt - 1);
-    const int niter = (a.i1 - 4 * wv + 4 * kWaves - 1) / (4 * kWaves);
-    double av[kDepth], bv[kDepth][NT];
-    auto mfmas = [&](int d) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[d], bv[d][t], acc[t], 0, 0, 0);
-    };
-    const double* ep = a.errT + (int64_t)(4 * wv + kl) * a.mpad + row0 + cl;
-    const double* up = U + (int64_t)(4 * wv + kl) * a.ldu + a.i1 + cl;
-    // (with a whole number of tile pairs a lane fetches two neighbouring columns of U at once, one for each
-    //  tile of a pair -- tile 2p + q then works on columns 32 p + 2 cl + q; see the scalar solve for why)
-    typedef double f64x2 __attribute__((ext_vector_type(2)));
-    const double* up2 = U + (int64_t)(4 * wv + kl) * a.ldu + a.i1 + 2 * cl;
-    auto issue = [&](int slot, int it) {
-      av[slot] = ep[(int64_t)it * (4 * kWaves) * a.mpad];
-      if (paired) {
-        const double* u = up2 + (int64_t)it * (4 * kWaves) * a.ldu;
-#pragma unroll
-        for (int p = 0; p < NT / 2; ++p) {
-          const f64x2 two = *reinterpret_cast<const f64x2*>(u + (coff[2 * p] & ~31));
-          bv[slot][2 * p] = two[0];
-          bv[slot][2 * p + 1] = two[1];
-        }
-      } else {
-        const double* u = up + (int64_t)it * (4 * kWaves) * a.ldu;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) bv[slot][t] = u[coff[t]];
-      }
-    };
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d)
-      if (d < niter) issue(d, d);
-    for (int it = 0; it < niter; it += kDepth) {
-#pragma unroll
-      for (int d = 0; d < kDepth; ++d) {
-        if (it + d < niter) {
-          mfmas(d);
-          if (it + d + kDepth < niter) issue(d, it + d + kDepth);
-        }
-      }
-    }
-  }
+  lazy_update<NT, kWaves>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, acc);
   if (wave >= 4) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
