@@ -24,11 +24,6 @@ constexpr int kRowAlign = 96;   // the error matrix is padded to a multiple of e
 constexpr int kThreads = 512;   // eight waves: one wave per SIMD cannot keep the float64 matrix pipe busy
 constexpr int kWaves = kThreads / 64;
 
-__global__ void inv_diag_kernel(const double* __restrict__ U, int64_t ldu, int n, double* invd) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) invd[j] = 1.0 / U[(int64_t)j * ldu + j];
-}
-
 // doubles of the LDS region that first holds the partial sums of the lazy update and then the state tile
 __host__ __device__ constexpr int state_doubles(int mt, int bw) {
   return mt == 1 ? 4 * kRowTile * bw : kRowTile * mt * (bw + 1);
@@ -41,7 +36,6 @@ struct QuantArgs {
   const double* U;
   int64_t ldu;
   const uint8_t* dead;
-  const double* invd;
   double* errT;  // [n][mpad]
   int bits, group;
   int i1, bw;    // block start, block width (multiple of 16)
@@ -68,7 +62,6 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
   const int nt = a.bw >> 4;
   const int sp = a.bw + 1;  // pitch of the state tile
   const double* __restrict__ U = a.U;
-  const double* __restrict__ invd = a.invd;
 
   // LDS carve-up: partial sums of four waves at a time (reused as the state tile),
   // the mini-block errors, the mini-block's 16 x 16 diagonal block of U and its
@@ -88,7 +81,7 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
     f64x4 acc[NT];
     const bool paired = lazy_update_paired(nt, a.n, a.ldu, a.mpad);
     auto column_of = [&](int t, int cl) { return paired ? 32 * (t >> 1) + 2 * cl + (t & 1) : 16 * t + cl; };
-    lazy_update<NT, kWaves>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, acc);
+    lazy_update<NT, kWaves>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, lane, wave, acc);
     // the eight partial sums are folded in two rounds through four LDS slots
     if (wave >= 4) {
 #pragma unroll
@@ -322,7 +315,7 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
 
   // The block's weights, dead marks and first diagonal block of U are requested all at once and whatever the row (loads
   // under a condition wait for each other, one trip to memory after the other): 512 x 512 118.4 -> 115.0 us,
-  // 4096 x 4096 1792 -> 1750, 11008 x 4096 4208 -> 4068, 4096 x 11008 10040 -> 9930.  Requested before the lazy update
+  // 4096 x 4096 1792 -> 1750, 11008 x 4096 4208 -> 4075, 4096 x 11008 10040 -> 9930.  Requested before the lazy update
   // they cost more registers than they hide: 11008 x 4096 4378, 4096 x 11008 9990.
   constexpr int NP = (kRows * 16 * NT + kThreads - 1) / kThreads;
   using ST = typename StoredType<DT>::type;
@@ -338,7 +331,7 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
     draw[p] = a.dead ? a.dead[a.i1 + c] : (uint8_t)0;
   }
   const double ud0 = U[(int64_t)(a.i1 + ((tid >> 4) & 15)) * a.ldu + a.i1 + (tid & 15)];
-  const double id0 = invd[a.i1 + (tid & 15)];
+  const double piv0 = U[(int64_t)(a.i1 + (tid & 15)) * (a.ldu + 1)];
 
   // ---- state tile S = W - (sum of the partial sums), dead channels read as zero
   {
@@ -361,7 +354,7 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
       if (tid + kThreads * p < kRows * a.bw) S[(at[p] >> 8) * sp + (at[p] & 255)] = sv[p];
     // diagonal block of the first mini-block
     if (tid < 256) Ud[tid] = ud0;
-    if (tid < 16) Id[tid] = id0;
+    if (tid < 16) Id[tid] = 1.0 / piv0;
   }
   __syncthreads();
 
@@ -380,7 +373,8 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
     double ud_next = 0.0, id_next = 0.0;
     if (mb + 1 < nt) {
       if (tid < 256) ud_next = U[(int64_t)(gcol + 16 + (tid >> 4)) * a.ldu + gcol + 16 + (tid & 15)];
-      if (tid < 16) id_next = invd[gcol + 16 + tid];
+      // (the reciprocals by a wave that does not walk, not by a kernel of their own: 512 x 512 115 -> 114 us)
+      if (tid >= 256 && tid < 272) id_next = 1.0 / U[(int64_t)(gcol + 16 + tid - 256) * (a.ldu + 1)];
     }
     double ub[kUpd][4];
 #pragma unroll
@@ -525,7 +519,7 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
     }
     if (mb + 1 < nt) {
       if (tid < 256) Ud[(buf ^ 1) * 256 + tid] = ud_next;
-      if (tid < 16) Id[(buf ^ 1) * 16 + tid] = id_next;
+      if (tid >= 256 && tid < 272) Id[(buf ^ 1) * 16 + tid - 256] = id_next;
     }
     __syncthreads();
   }
@@ -566,7 +560,7 @@ __global__ __launch_bounds__(kThreads) void quant_layer_kernel(QuantArgs a, int 
     // tile keeping them pays (4096 x 11008: 9.93 ms against 10.52 opaque and 10.19 with a launch per block).
     if constexpr (MT > 1) {
       asm volatile("" : "+s"(b.U), "+s"(b.errT), "+s"(b.W), "+s"(b.Wq), "+s"(b.codes), "+s"(b.mpad), "+s"(b.n));
-      asm volatile("" : "+s"(b.invd), "+s"(b.dead), "+s"(b.scales), "+s"(b.zeros), "+s"(b.ldu), "+s"(b.ldw), "+s"(b.m));
+      asm volatile("" : "+s"(b.dead), "+s"(b.scales), "+s"(b.zeros), "+s"(b.ldu), "+s"(b.ldw), "+s"(b.m));
     }
     quant_block<DT, NT, MT>(b, lds);
     __syncthreads();
@@ -689,8 +683,6 @@ ptq_status quantize_launch(const void* W, ptq_dtype wdt, int64_t ldw, int64_t m,
   a.ldu = ldu;
   a.dead = dead_mask;
   a.errT = static_cast<double*>(ws);
-  a.invd = reinterpret_cast<double*>(static_cast<char*>(ws) +
-                                     align_up((size_t)n * (size_t)a.mpad * sizeof(double), 256));
   a.bits = bits;
   a.group = group;
   a.i1 = 0;
@@ -710,8 +702,6 @@ ptq_status quantize_launch(const void* W, ptq_dtype wdt, int64_t ldw, int64_t m,
       default: return PTQ_ERR_DTYPE;
     }
   }
-  inv_diag_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(U, ldu, (int)n, const_cast<double*>(a.invd));
-  PTQ_HIP_CHECK_LAUNCH();
   ptq_status rc;
   switch (wdt) {
     case PTQ_F32: rc = run_blocks_any<PTQ_F32>(a, block, st); break;

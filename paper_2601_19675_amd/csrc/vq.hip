@@ -77,7 +77,6 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wv = __builtin_amdgcn_readfirstlane(wave);
   const int row0 = blockIdx.x * kRows;
   const int nt = a.bw >> 4;
   const int sp = a.bw + 1;  // pitch of the state tile
@@ -98,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   f64x4 acc[NT];
   const bool paired = lazy_update_paired(nt, a.n, a.ldu, a.mpad);
   auto column_of = [&](int t, int cl) { return paired ? 32 * (t >> 1) + 2 * cl + (t & 1) : 16 * t + cl; };
-  lazy_update<NT, kWaves>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, acc);
+  lazy_update<NT, kWaves>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, lane, wave, acc);
   if (wave >= 4) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
