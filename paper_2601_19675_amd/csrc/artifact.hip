@@ -38,9 +38,42 @@ __device__ __forceinline__ void unpack_chunk(const uint32_t* __restrict__ words,
   for (int j = 0; j < kChunk; ++j) code[j] = (uint8_t)chunk_code<BITS>(words, j);
 }
 
+// scale[row][group] -> scale[group][row], the same for the zero-points: 32 x 32 tiles through LDS
+struct GridTranspose {
+  const float* scales;
+  const uint8_t* zeros;
+  int ng;
+  float* scales_t;
+  uint8_t* zeros_t;
+  int row_tiles, tiles;   // tiles = 0: nothing to do
+};
+
+__device__ __forceinline__ void transpose_grids_tile(const GridTranspose& a, int m, int tile) {
+  __shared__ float ts[32][33];
+  __shared__ uint8_t tz[32][33];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int r0 = (tile % a.row_tiles) * 32, g0 = (tile / a.row_tiles) * 32;
+  for (int k = ty; k < 32; k += 8) {
+    const int row = r0 + k, g = g0 + tx;
+    if (row < m && g < a.ng) { ts[k][tx] = a.scales[(int64_t)row * a.ng + g]; tz[k][tx] = a.zeros[(int64_t)row * a.ng + g]; }
+  }
+  __syncthreads();
+  for (int k = ty; k < 32; k += 8) {
+    const int g = g0 + k, row = r0 + tx;
+    if (row < m && g < a.ng) { a.scales_t[(int64_t)g * m + row] = ts[tx][k]; a.zeros_t[(int64_t)g * m + row] = tz[tx][k]; }
+  }
+}
+
+// The last grids.tiles workgroups bring the grids into their order (one launch instead of two: a call of 512 x 512 codes
+// 11.3 -> 6.6 us, of 11008 x 4096 31.3 -> 29.5).
 template <int BITS>
 __global__ __launch_bounds__(256) void pack_kernel(const uint8_t* __restrict__ codes, int64_t ldc, int m, int n,
-                                                   uint32_t* __restrict__ packed) {
+                                                   uint32_t* __restrict__ packed, GridTranspose grids) {
+  const int pack_blocks = (int)gridDim.x - grids.tiles;
+  if ((int)blockIdx.x >= pack_blocks) {
+    transpose_grids_tile(grids, m, blockIdx.x - pack_blocks);
+    return;
+  }
   const int chunks = n / kChunk;
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= (int64_t)m * chunks) return;
@@ -86,26 +119,6 @@ __global__ __launch_bounds__(256) void unpack_dequant_kernel(const uint32_t* __r
     const double sc = (double)scales[(int64_t)g * m + row];
     const double z = (double)zeros[(int64_t)g * m + row];
     dst[j] = sc * ((double)code[j] - z);
-  }
-}
-
-// scale[row][group] -> scale[group][row], the same for the zero-points (32 x 32 tiles through LDS)
-__global__ __launch_bounds__(256) void transpose_grids_kernel(const float* __restrict__ scales,
-                                                              const uint8_t* __restrict__ zeros, int m, int ng,
-                                                              float* __restrict__ scales_t,
-                                                              uint8_t* __restrict__ zeros_t) {
-  __shared__ float ts[32][33];
-  __shared__ uint8_t tz[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int r0 = blockIdx.x * 32, g0 = blockIdx.y * 32;
-  for (int k = ty; k < 32; k += 8) {
-    const int row = r0 + k, g = g0 + tx;
-    if (row < m && g < ng) { ts[k][tx] = scales[(int64_t)row * ng + g]; tz[k][tx] = zeros[(int64_t)row * ng + g]; }
-  }
-  __syncthreads();
-  for (int k = ty; k < 32; k += 8) {
-    const int g = g0 + k, row = r0 + tx;
-    if (row < m && g < ng) { scales_t[(int64_t)g * m + row] = ts[tx][k]; zeros_t[(int64_t)g * m + row] = tz[tx][k]; }
   }
 }
 
@@ -875,22 +888,17 @@ void launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
 
 }  // namespace
 
-ptq_status pack_grids_launch(const float* scales, const uint8_t* zeros, int64_t m, int64_t ng, float* scales_t,
-                             uint8_t* zeros_t, hipStream_t st) {
-  dim3 g((unsigned)ceil_div(m, 32), (unsigned)ceil_div(ng, 32));
-  transpose_grids_kernel<<<g, 256, 0, st>>>(scales, zeros, (int)m, (int)ng, scales_t, zeros_t);
-  PTQ_HIP_CHECK_LAUNCH();
-  return PTQ_OK;
-}
-
 ptq_status pack_codes_launch(const uint8_t* codes, int64_t ldc, int64_t m, int64_t n, int bits, uint32_t* packed,
+                             const float* scales, const uint8_t* zeros, int64_t ng, float* scales_t, uint8_t* zeros_t,
                              hipStream_t st) {
-  const unsigned grid = (unsigned)ceil_div(m * (n / kChunk), 256);
+  const int64_t row_tiles = ceil_div(m, 32), tiles = scales ? row_tiles * ceil_div(ng, 32) : 0;
+  const GridTranspose t{scales, zeros, (int)ng, scales_t, zeros_t, (int)row_tiles, (int)tiles};
+  const unsigned grid = (unsigned)(ceil_div(m * (n / kChunk), 256) + tiles);
   switch (bits) {
-    case 2: pack_kernel<2><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed); break;
-    case 3: pack_kernel<3><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed); break;
-    case 4: pack_kernel<4><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed); break;
-    case 8: pack_kernel<8><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed); break;
+    case 2: pack_kernel<2><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed, t); break;
+    case 3: pack_kernel<3><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed, t); break;
+    case 4: pack_kernel<4><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed, t); break;
+    case 8: pack_kernel<8><<<grid, 256, 0, st>>>(codes, ldc, (int)m, (int)n, packed, t); break;
     default: return PTQ_ERR_ARG;
   }
   PTQ_HIP_CHECK_LAUNCH();

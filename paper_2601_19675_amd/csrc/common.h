@@ -143,12 +143,12 @@ ptq_status r1svd_launch(const void* W, ptq_dtype wdt, int64_t ldw, int64_t m, in
                         float* Rout, int64_t ldr, void* ws, hipStream_t st);
 
 
+// scales may be null: the codes alone
 ptq_status pack_codes_launch(const uint8_t* codes, int64_t ldc, int64_t m, int64_t n, int bits, uint32_t* packed,
+                             const float* scales, const uint8_t* zeros, int64_t ng, float* scales_t, uint8_t* zeros_t,
                              hipStream_t st);
 ptq_status unpack_dequant_launch(const uint32_t* packed, int64_t m, int64_t n, int bits, const float* scales,
                                  const uint8_t* zeros, int group, double* Wq, int64_t ldq, hipStream_t st);
-ptq_status pack_grids_launch(const float* scales, const uint8_t* zeros, int64_t m, int64_t ng, float* scales_t,
-                             uint8_t* zeros_t, hipStream_t st);
 size_t linear_forward_workspace_bytes(int64_t tokens, int64_t m, int64_t n, int64_t r);
 // the per-GPU static scratch of ptq_lopro_linear_forward_static: its size, and its address on the current device
 size_t linear_forward_static_scratch_bytes();

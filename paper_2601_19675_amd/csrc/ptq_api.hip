@@ -245,9 +245,8 @@ ptq_status ptq_pack_codes(const uint8_t* codes, int64_t ldc, int64_t m, int64_t 
   if (!codes || !packed || misaligned(codes, 16) || misaligned(packed, 16)) return PTQ_ERR_ARG;
   if (grids && (!scales || !zeros || !scales_t || !zeros_t || scales == scales_t || zeros == zeros_t))
     return PTQ_ERR_ARG;
-  ptq_status rc = pack_codes_launch(codes, ldc, m, n, bits, packed, static_cast<hipStream_t>(stream));
-  if (rc != PTQ_OK || !grids) return rc;
-  return pack_grids_launch(scales, zeros, m, n / group, scales_t, zeros_t, static_cast<hipStream_t>(stream));
+  return pack_codes_launch(codes, ldc, m, n, bits, packed, grids ? scales : nullptr, zeros, grids ? n / group : 0, scales_t,
+                           zeros_t, static_cast<hipStream_t>(stream));
 }
 
 ptq_status ptq_unpack_dequantize(const uint32_t* packed, int64_t m, int64_t n, int bits, const float* scales,

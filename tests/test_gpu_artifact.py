@@ -166,3 +166,17 @@ def test_forward_full_size_attention_projection(tokens):
     X_t = _dev(rng.standard_normal((tokens, n)).astype(np.float32)).to(torch.bfloat16)
     got, packed = _forward(X_t, *layer, bits, group, bI, bH)
     _check_forward(X_t.to(torch.float64).cpu().numpy(), got, packed, *layer, bits, group, bI, bH)
+
+
+@pytest.mark.parametrize("m,ng", [(1, 1), (31, 33), (32, 32), (33, 31), (257, 65)])
+def test_pack_grids_at_the_edges_of_their_tiles(m, ng):
+    rng = np.random.default_rng(m)
+    n = 32 * ng
+    codes, zeros = (_dev(rng.integers(0, 16, size=(m, k), dtype=np.uint8)) for k in (n, ng))
+    scales = _dev(rng.uniform(0.001, 0.2, size=(m, ng)).astype(np.float32))
+    packed = torch.full((ng, m, 4), -1, dtype=torch.int32, device="cuda")
+    st = torch.full((ng, m), float("nan"), dtype=torch.float32, device="cuda")
+    zt = torch.full((ng, m), 0xEE, dtype=torch.uint8, device="cuda")
+    ptq.ptq_pack_codes(codes, 4, packed, scales, zeros, 32, st, zt)
+    assert torch.equal(st, scales.T) and torch.equal(zt, zeros.T)
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), ao.pack_codes(codes.cpu().numpy(), 4))
