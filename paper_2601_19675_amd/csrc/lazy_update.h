@@ -15,11 +15,13 @@ __device__ __forceinline__ bool lazy_update_paired(int nt, int n, int64_t ldu, i
 // acc[t] = this wave's share of E[row0 .. row0 + 15, 0:i1] * U[0:i1, tile t of the block at i1]: k = 4 (kWaves it + wave)
 // + lane / 16, operands of the next kDepth steps in flight while the MFMAs run.  Tile t's columns in the
 // block: 16 t + lane % 16, or 32 (t / 2) + 2 (lane % 16) + t % 2 where `paired`.  i1 is a multiple of 16.
+// RAGGED: the last of the nt tiles ends at column bw of the block; what lies past it repeats column bw - 1 (not `paired`).
 // (lane and wave are the caller's own values: formed here once more, the loop was scheduled differently and the 4096 x 4096
 // scalar solve took 1775 us against 1723.)
-template <int NT, int kWaves>
+template <int NT, int kWaves, bool RAGGED = false>
 __device__ __forceinline__ void lazy_update(const double* __restrict__ U, int64_t ldu, const double* __restrict__ errT, int mpad,
-                                            int n, int i1, int nt, int row0, bool paired, int lane, int wave, f64x4 (&acc)[NT]) {
+                                            int n, int i1, int nt, int row0, bool paired, int lane, int wave, f64x4 (&acc)[NT],
+                                            int bw = 0) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
   constexpr int kDepth = (NT >= 16) ? 2 : 4;
@@ -27,7 +29,10 @@ __device__ __forceinline__ void lazy_update(const double* __restrict__ U, int64_
   const int wv = __builtin_amdgcn_readfirstlane(wave);   // uniform: scalar loop control
   int coff[NT];  // tiles beyond the block re-read its last tile (result unused)
 #pragma unroll
-  for (int t = 0; t < NT; ++t) coff[t] = 16 * (t < nt ? t : nt - 1);
+  for (int t = 0; t < NT; ++t) {
+    coff[t] = 16 * (t < nt ? t : nt - 1);
+    if constexpr (RAGGED) coff[t] = min(coff[t] + cl, bw - 1) - cl;
+  }
   const int niter = (i1 - 4 * wv + 4 * kWaves - 1) / (4 * kWaves);  // k = 32 it + 4 wave + kl < i1 (a multiple of 16)
   double av[kDepth], bv[kDepth][NT];
   auto mfmas = [&](int d) {

@@ -71,22 +71,26 @@ __device__ __forceinline__ int half_wave_min(int v) {
   return min((int)p[0], (int)p[1]);
 }
 
-template <int DT, int NT, int D, int SLOTS>
+// RAGGED: a last block whose width is no multiple of 16 (n need only be one of D).  Its last mini-block is walked as far as the
+// groups go; nothing past column n of U, the pivots, W or the outputs is read or written, the tiles in LDS are whole.
+template <int DT, int NT, int D, int SLOTS, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   extern __shared__ double lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int row0 = blockIdx.x * kRows;
-  const int nt = a.bw >> 4;
-  const int sp = a.bw + 1;  // pitch of the state tile
+  const int nt = RAGGED ? (a.bw + 15) >> 4 : a.bw >> 4;
+  const int pw = RAGGED ? 16 * nt : a.bw;   // columns of the tiles in LDS
+  const int sp = pw + 1;  // pitch of the state tile
+  auto in_layer = [&](int col) { return RAGGED ? min(col, a.n - 1) : col; };   // a column or row of U past the last: unused
   const double* __restrict__ U = a.U;
   const double* __restrict__ invd = a.invd;
   constexpr int G = 16 / D;  // groups per mini-block
 
-  double* P = lds;                                  // [4][16][bw] partial sums of the lazy update
-  double* S = lds;                                  // [16][bw + 1] state tile (aliases P)
-  double* Em = lds + 4 * kRows * a.bw;              // [16 k][16 rows] errors of the mini-block
+  double* P = lds;                                  // [4][16][pw] partial sums of the lazy update
+  double* S = lds;                                  // [16][pw + 1] state tile (aliases P)
+  double* Em = lds + 4 * kRows * pw;                // [16 k][16 rows] errors of the mini-block
   double* Qm = Em + 256;                            // [16 k][17] assigned values of the mini-block
   double* Ud = Qm + 272;                            // [2][16][16] diagonal block of U
   double* Id = Ud + 512;                            // [2][16] reciprocal pivots
@@ -95,16 +99,16 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
 
   // ---- phase 1: acc = E[rows, 0:i1] * U[0:i1, block], k split over the waves
   f64x4 acc[NT];
-  const bool paired = lazy_update_paired(nt, a.n, a.ldu, a.mpad);
+  const bool paired = !RAGGED && lazy_update_paired(nt, a.n, a.ldu, a.mpad);
   auto column_of = [&](int t, int cl) { return paired ? 32 * (t >> 1) + 2 * cl + (t & 1) : 16 * t + cl; };
-  lazy_update<NT, kWaves>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, lane, wave, acc);
+  lazy_update<NT, kWaves, RAGGED>(U, a.ldu, a.errT, a.mpad, a.n, a.i1, nt, row0, paired, lane, wave, acc, a.bw);
   if (wave >= 4) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
       if (t < nt) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          P[((wave - 4) * kRows + 4 * r + (lane >> 4)) * a.bw + column_of(t, lane & 15)] = acc[t][r];
+          P[((wave - 4) * kRows + 4 * r + (lane >> 4)) * pw + column_of(t, lane & 15)] = acc[t][r];
       }
   }
   __syncthreads();
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
       if (t < nt) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          P[(wave * kRows + 4 * r + (lane >> 4)) * a.bw + column_of(t, lane & 15)] += acc[t][r];
+          P[(wave * kRows + 4 * r + (lane >> 4)) * pw + column_of(t, lane & 15)] += acc[t][r];
       }
   }
   __syncthreads();
@@ -139,16 +143,16 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
     for (int p = 0; p < NP; ++p) {
       const int r = at[p] >> 8, c = at[p] & 255;
       const double w = (row0 + r < a.m && draw[p] == 0) ? stored_to_f64<DT>(wraw[p]) : 0.0;
-      const double s01 = P[(0 * kRows + r) * a.bw + c] + P[(1 * kRows + r) * a.bw + c];
-      const double s23 = P[(2 * kRows + r) * a.bw + c] + P[(3 * kRows + r) * a.bw + c];
+      const double s01 = P[(0 * kRows + r) * pw + c] + P[(1 * kRows + r) * pw + c];
+      const double s23 = P[(2 * kRows + r) * pw + c] + P[(3 * kRows + r) * pw + c];
       sv[p] = w - (s01 + s23);
     }
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < NP; ++p)
       if (tid + kThreads * p < kRows * a.bw) S[(at[p] >> 8) * sp + (at[p] & 255)] = sv[p];
-    if (tid < 256) Ud[tid] = U[(int64_t)(a.i1 + (tid >> 4)) * a.ldu + a.i1 + (tid & 15)];
-    if (tid < 16) Id[tid] = invd[a.i1 + tid];
+    if (tid < 256) Ud[tid] = U[(int64_t)in_layer(a.i1 + (tid >> 4)) * a.ldu + in_layer(a.i1 + (tid & 15))];
+    if (tid < 16) Id[tid] = invd[in_layer(a.i1 + tid)];
     for (int e = tid; e < 32 * SLOTS * D; e += kThreads) Cb[e] = e < a.K * D ? (double)a.codebook[e] : 0.0;
   }
   __syncthreads();
@@ -172,8 +176,8 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
     const int buf = mb & 1;
     double ud_next = 0.0, id_next = 0.0;
     if (mb + 1 < nt) {
-      if (tid < 256) ud_next = U[(int64_t)(gcol + 16 + (tid >> 4)) * a.ldu + gcol + 16 + (tid & 15)];
-      if (tid < 16) id_next = invd[gcol + 16 + tid];
+      if (tid < 256) ud_next = U[(int64_t)in_layer(gcol + 16 + (tid >> 4)) * a.ldu + in_layer(gcol + 16 + (tid & 15))];
+      if (tid < 16) id_next = invd[in_layer(gcol + 16 + tid)];
     }
     double ub[kUpd][4];
 #pragma unroll
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
       const int tc = t < nt ? t : nt - 1;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
-        ub[q][kk] = U[(int64_t)(gcol + 4 * kk + (lane >> 4)) * a.ldu + a.i1 + 16 * tc + (lane & 15)];
+        ub[q][kk] = U[(int64_t)in_layer(gcol + 4 * kk + (lane >> 4)) * a.ldu + in_layer(a.i1 + 16 * tc + (lane & 15))];
     }
     {
       const double* ud = Ud + buf * 256;
@@ -191,6 +195,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
       for (int j = 0; j < 16; ++j) w[j] = S[r * sp + c0 + j];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
+        if (RAGGED && c0 + g * D >= a.bw) continue;
         __builtin_amdgcn_sched_barrier(0);   // a group's LDS reads stay in it: all groups' together do not fit the registers
         // the group's triangle of U and its reciprocal pivots
         double T[D][D], inv[D];
@@ -280,9 +285,9 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
     }
     if (tid >= 256) {
       const int e = tid - 256;
-      a.errT[(int64_t)(gcol + (e >> 4)) * a.mpad + row0 + (e & 15)] = Em[e];
+      if (!RAGGED || gcol + (e >> 4) < a.n) a.errT[(int64_t)(gcol + (e >> 4)) * a.mpad + row0 + (e & 15)] = Em[e];
       const int rr = e >> 4, j = e & 15;
-      if (a.Wq && row0 + rr < a.m) a.Wq[(int64_t)(row0 + rr) * a.n + gcol + j] = Qm[j * 17 + rr];
+      if (a.Wq && row0 + rr < a.m && (!RAGGED || gcol + j < a.n)) a.Wq[(int64_t)(row0 + rr) * a.n + gcol + j] = Qm[j * 17 + rr];
     }
     if (mb + 1 < nt) {
       if (tid < 256) Ud[(buf ^ 1) * 256 + tid] = ud_next;
@@ -309,10 +314,11 @@ size_t vq_lds_bytes(int bw, int d) {
   return (size_t)(4 * kRows * bw + 256 + 272 + 512 + 32 + kMaxEntries * d) * sizeof(double) + (size_t)kRows * bw;
 }
 
-template <int DT, int NT, int D, int SLOTS>
+template <int DT, int NT, int D, int SLOTS, bool RAGGED = false>
 ptq_status vq_launch_block(const VqArgs& a, hipStream_t st) {
-  if (!lds_opt_in<vq_block_kernel<DT, NT, D, SLOTS>>((int)vq_lds_bytes(16 * NT, D))) return PTQ_ERR_HIP;
-  vq_block_kernel<DT, NT, D, SLOTS><<<(unsigned)ceil_div(a.m, kRows), kThreads, vq_lds_bytes(a.bw, D), st>>>(a);
+  if (!lds_opt_in<vq_block_kernel<DT, NT, D, SLOTS, RAGGED>>((int)vq_lds_bytes(16 * NT, D))) return PTQ_ERR_HIP;
+  const size_t lds = vq_lds_bytes((a.bw + 15) / 16 * 16, D);
+  vq_block_kernel<DT, NT, D, SLOTS, RAGGED><<<(unsigned)ceil_div(a.m, kRows), kThreads, lds, st>>>(a);
   return PTQ_OK;
 }
 
@@ -321,7 +327,10 @@ ptq_status vq_run_blocks_with(VqArgs a, int block, hipStream_t st) {
   for (int i1 = 0; i1 < a.n; i1 += block) {
     a.i1 = i1;
     a.bw = (a.n - i1 < block) ? a.n - i1 : block;
-    const ptq_status rc = (a.bw <= 128) ? vq_launch_block<DT, 8, D, SLOTS>(a, st) : vq_launch_block<DT, 16, D, SLOTS>(a, st);
+    // (one form of the ragged kernel, for all widths and codebooks: it takes a layer's last block only)
+    const ptq_status rc = a.bw % 16 != 0 ? vq_launch_block<DT, 16, D, kMaxEntries / 32, true>(a, st)
+                          : a.bw <= 128  ? vq_launch_block<DT, 8, D, SLOTS>(a, st)
+                                         : vq_launch_block<DT, 16, D, SLOTS>(a, st);
     if (rc != PTQ_OK) return rc;
   }
   return PTQ_OK;
