@@ -575,8 +575,8 @@ __device__ __forceinline__ void tile_in_locality_order(int r, int ntb, int& I, i
 // quarters of its operands pass through the LDS for half the MFMAs), so the split into halves is taken where it
 // saves rounds of 256 workgroups.
 // H not null: one split, added to H without a partial tile.  Bound: H's float64 update, 16 bytes per entry.
-// Call of 2048 tokens, partial tiles and whole tiles before: n = 2048 39.9 -> 31.9 us, n = 4096 89.6 -> 54.3,
-// n = 5632 119 -> 88, n = 8192 325 -> 234, n = 11008 571 -> 404.
+// Call of 2048 tokens, partial tiles and whole tiles before: n = 4096 90.1 -> 53.6 us, n = 5376 111 -> 86,
+// n = 8192 325 -> 218, n = 11008 564 -> 399; n = 2048, seven splits either way, 40.0 and 40.7.
 template <bool HALVES, bool SHARED>
 __global__ __launch_bounds__(256) void hessian_bf16_big_kernel(const uint16_t* __restrict__ X, int64_t ldx,
                                                                int64_t t, int n, int64_t tok0, int chunk,
@@ -671,24 +671,27 @@ Plan make_plan(int64_t n, int64_t t, ptq_dtype dt, bool allow_big) {
   const int64_t max_chunk = big ? (p.ntiles >= 512 ? kMaxChunkHuge : kMaxChunkBig) : kMaxChunk;
   const int64_t s_min = ceil_div(t > 0 ? t : 1, max_chunk);
   int64_t best_s = s_min, best_cost = -1;
-  p.halves = false;
-  for (int halves = 0; halves <= (big ? 1 : 0); ++halves)
-    for (int64_t sp = s_min; sp < s_min + 64; ++sp) {
-      int64_t ch = ceil_div(ceil_div(t > 0 ? t : 1, sp), kt) * kt;
-      if (ch < 256 && sp > s_min) break;
-      // + 1024: writing and re-reading a partial tile costs about as much as 1024 tokens; + 400 for one added to H at once
-      const int64_t items = halves ? (int64_t)p.ntb * p.ntb : p.ntiles;
-      const int64_t cost = ceil_div(items * sp, 256) * (ch + (big && sp == 1 ? 400 : 1024)) * (halves ? kHalfCost : 100);
-      if (best_cost < 0 || cost < best_cost) {
-        best_cost = cost;
-        best_s = sp;
-        p.halves = halves;
-      }
+  for (int64_t sp = s_min; sp < s_min + 64; ++sp) {
+    int64_t ch = ceil_div(ceil_div(t > 0 ? t : 1, sp), kt) * kt;
+    if (ch < 256 && sp > s_min) break;
+    // + 1024: writing and re-reading a partial tile costs about as much as 1024 tokens
+    const int64_t cost = ceil_div(p.ntiles * sp, 256) * (ch + 1024);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best_s = sp;
     }
+  }
   int64_t chunk = ceil_div(ceil_div(t > 0 ? t : 1, best_s), kt) * kt;
   if (chunk < kt) chunk = kt;
   p.chunk = (int)chunk;
   p.splits_total = (int)ceil_div(t > 0 ? t : 1, chunk);
+  // Whole tiles alone decide how many tokens a float32 sum takes, and a split that is added to H directly or made of
+  // halves keeps that number: weighed at their own, lower cost (a direct split as + 400) fewer and longer splits win, up
+  // to five times the tokens in one float32 sum, for less time but a larger distance from the float64 Gram matrix
+  // (n = 4096, 16384 tokens: 312 and 250 us, 8.7e-8 and 7.1e-7; n = 9472, 40000: 2881 and 2820 us, 1.8e-7 and 1.2e-6;
+  // n = 2048, 2048: 40.7 and 32.2 us, 3.0e-8 and 5.3e-8).
+  p.halves = big && ceil_div((int64_t)p.ntb * p.ntb * p.splits_total, 256) * kHalfCost <
+                        ceil_div((int64_t)p.ntiles * p.splits_total, 256) * 100;
   p.tile_bytes = (size_t)p.tile * p.tile * ((dt == PTQ_BF16) ? sizeof(float) : sizeof(double));
   int64_t sl = big ? (int64_t)(kMaxPartialBytes / (p.tile_bytes * p.ntiles)) : ceil_div(2048, p.ntiles);
   if (sl > p.splits_total) sl = p.splits_total;

@@ -1,0 +1,26 @@
+"""How the bfloat16 Hessian splits its tokens, from the launches that the host would make (no GPU)."""
+import pytest
+
+from launch_recorder import PTR, record
+
+BIG = {"hessian_bf16_big": {"chunk": (5, "i"), "splits": (8, "i"), "direct": (10, "q")}}
+
+
+def plan(n, t):
+    """Launches of one call on bfloat16 activations."""
+    (rc, launches), = record([("ptq_hessian_accumulate", [PTR, n, PTR, 1, t, n, n, PTR, 1 << 40, 0])], BIG)
+    assert rc == 0
+    return launches
+
+
+# tokens that one float32 sum may take: what whole tiles with partial sums in memory take, also where a split is added to
+# H directly or made of half tiles
+@pytest.mark.parametrize("n,t,tokens", [(2048, 2048, 320), (2048, 4096, 608), (4096, 2048, 2048), (4096, 16384, 3296), (5632, 2048, 2048),
+                                        (8192, 16384, 5472), (9472, 40000, 10016), (11008, 2048, 2048), (11008, 50000, 12512),
+                                        (11008, 65536, 16384), (11008, 262144, 65536)])
+def test_tokens_of_a_float32_sum(n, t, tokens):
+    main = [k for k in plan(n, t) if "hessian_bf16_big" in k["kernel"]]
+    assert main and all(k["chunk"] == tokens for k in main)
+    assert sum(k["splits"] for k in main) == -(-t // tokens)
+    # added to H by the kernel itself exactly where there is one split
+    assert all((k["direct"] != 0) == (t <= tokens) for k in main)
