@@ -226,7 +226,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // waves 0 and 3 take its two diagonal quadrants (ten of sixteen MFMA tiles) and wave 1 the off-diagonal one, which
 // keeps the workgroup in step with those of whole tiles beside it (they share their operands in the L2: shared out
 // evenly, n = 11008 took 25.2 ms instead of 24.5); SHARED, beside half tiles: waves 1 and 2 take half of it each.
-template <bool diag, int NB, bool SHARED = false>
+template <bool diag, int NB, bool SHARED, bool DIRECT>
 __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t ldx, int64_t t, int n,
                                          int64_t tok0, int chunk, int I, int J, int half_tile, int split,
                                          float* __restrict__ out, double* __restrict__ H, int64_t ldh, uint16_t* hs) {
@@ -490,7 +490,7 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
   // register r of MFMA tile (a, b): row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
   const int il0 = wi * 128 + low * 64 + (lane >> 5) * 4, jl0 = (NB == 2 ? 128 * half_tile : 0) + wj * 32 * NB + (lane & 31);
   const int rows = SHARED && (wave == 1 || wave == 2) ? 2 : 4;   // MFMA tile rows of this wave
-  if (H) {
+  if constexpr (DIRECT) {
     // The only split: straight into H, eight rows at a time across all of the wave's columns, all loads of a step on
     // their way together (a load under a condition would wait for the one before: 69 us instead of 29 for a call of 32
     // tokens at n = 4096).
@@ -574,10 +574,10 @@ __device__ __forceinline__ void tile_in_locality_order(int r, int ntb, int& I, i
 // fill the chip: n = 4096 has 136 tiles, but 256 such items.  Half a tile takes about 66 % of a whole one's time (three
 // quarters of its operands pass through the LDS for half the MFMAs), so the split into halves is taken where it
 // saves rounds of 256 workgroups.
-// H not null: one split, added to H without a partial tile.  Bound: H's float64 update, 16 bytes per entry.
+// DIRECT: one split, added to H without a partial tile.  Bound: H's float64 update, 16 bytes per entry.
 // Call of 2048 tokens, partial tiles and whole tiles before: n = 4096 90.1 -> 53.6 us, n = 5376 111 -> 86,
 // n = 8192 325 -> 218, n = 11008 564 -> 399; n = 2048, seven splits either way, 40.0 and 40.7.
-template <bool HALVES, bool SHARED>
+template <bool HALVES, bool SHARED, bool DIRECT>
 __global__ __launch_bounds__(256) void hessian_bf16_big_kernel(const uint16_t* __restrict__ X, int64_t ldx,
                                                                int64_t t, int n, int64_t tok0, int chunk,
                                                                int ntb, int ntiles, int nsplits,
@@ -610,9 +610,9 @@ __global__ __launch_bounds__(256) void hessian_bf16_big_kernel(const uint16_t* _
   const int lin = I * ntb - I * (I - 1) / 2 + (J - I);  // index in the row-major upper-triangular tile list
   float* out = partial + ((int64_t)split * ntiles + lin) * (kBT * kBT);
   if (I == J)
-    big_tile<true, 4, SHARED>(X, ldx, t, n, tok0, chunk, I, J, 0, split, out, H, ldh, hs);
+    big_tile<true, 4, SHARED, DIRECT>(X, ldx, t, n, tok0, chunk, I, J, 0, split, out, H, ldh, hs);
   else
-    big_tile<false, HALVES ? 2 : 4>(X, ldx, t, n, tok0, chunk, I, J, half_tile, split, out, H, ldh, hs);
+    big_tile<false, HALVES ? 2 : 4, false, DIRECT>(X, ldx, t, n, tok0, chunk, I, J, half_tile, split, out, H, ldh, hs);
 }
 
 // H[upper] += sum over splits of the partial tiles, in float64, fixed order.  Four consecutive
@@ -725,18 +725,19 @@ ptq_status hessian_launch(double* H, int64_t ldh, const void* X, ptq_dtype xdt, 
     dim3 gr((unsigned)p.ntiles, (unsigned)(p.tile * p.tile / 1024));
     if (xdt == PTQ_BF16 && p.tile == kBT) {
       const bool direct = p.splits_total == 1;
-      auto launch = [&](auto halves, auto shared) {
-        constexpr bool HALVES = decltype(halves)::value, SHARED = decltype(shared)::value;
-        if (!lds_opt_in<hessian_bf16_big_kernel<HALVES, SHARED>>((int)kBigLdsBytes)) return false;
+      auto launch = [&](auto halves, auto shared, auto direct_) {
+        constexpr bool HALVES = decltype(halves)::value, SHARED = decltype(shared)::value, DIRECT = decltype(direct_)::value;
+        if (!lds_opt_in<hessian_bf16_big_kernel<HALVES, SHARED, DIRECT>>((int)kBigLdsBytes)) return false;
         const int64_t items = HALVES ? (int64_t)p.ntb * p.ntb : p.ntiles;
-        hessian_bf16_big_kernel<HALVES, SHARED><<<256u * (unsigned)ceil_div(items * ns, 256), 256, kBigLdsBytes, st>>>(
-            static_cast<const uint16_t*>(X), ldx, t, (int)n, tok0, p.chunk, p.ntb, p.ntiles, ns, static_cast<float*>(ws),
-            direct ? H : nullptr, ldh);
+        hessian_bf16_big_kernel<HALVES, SHARED, DIRECT><<<256u * (unsigned)ceil_div(items * ns, 256), 256, kBigLdsBytes, st>>>(
+            static_cast<const uint16_t*>(X), ldx, t, (int)n, tok0, p.chunk, p.ntb, p.ntiles, ns, static_cast<float*>(ws), H, ldh);
         return true;
       };
       const std::true_type yes;
       const std::false_type no;
-      if (!(p.halves ? launch(yes, yes) : (direct ? launch(no, yes) : launch(no, no)))) return PTQ_ERR_HIP;
+      const bool ok = p.halves ? (direct ? launch(yes, yes, yes) : launch(yes, yes, no))
+                               : (direct ? launch(no, yes, yes) : launch(no, no, no));
+      if (!ok) return PTQ_ERR_HIP;
       if (!direct)
         hessian_reduce_kernel<float, kBT><<<gr, 256, 0, st>>>(static_cast<const float*>(ws), ns, p.ntiles,
                                                               p.ntb, (int)n, H, ldh);

@@ -1,15 +1,24 @@
 """How the bfloat16 Hessian splits its tokens, from the launches that the host would make (no GPU)."""
+import os
+import re
+import subprocess
+
 import pytest
 
+from paper_2601_19675_amd import build
 from launch_recorder import PTR, record
 
-BIG = {"hessian_bf16_big": {"chunk": (5, "i"), "splits": (8, "i"), "direct": (10, "q")}}
+BIG = {"hessian_bf16_big": {"chunk": (5, "i"), "splits": (8, "i")}}
 
 
 def plan(n, t):
     """Launches of one call on bfloat16 activations."""
     (rc, launches), = record([("ptq_hessian_accumulate", [PTR, n, PTR, 1, t, n, n, PTR, 1 << 40, 0])], BIG)
     assert rc == 0
+    for k in launches:
+        form = re.search(r"hessian_bf16_big_kernelILb(\d)ELb(\d)ELb(\d)E", k["kernel"])
+        if form:
+            k["halves"], k["shared"], k["direct"] = (f == "1" for f in form.groups())
     return launches
 
 
@@ -19,8 +28,18 @@ def plan(n, t):
                                         (8192, 16384, 5472), (9472, 40000, 10016), (11008, 2048, 2048), (11008, 50000, 12512),
                                         (11008, 65536, 16384), (11008, 262144, 65536)])
 def test_tokens_of_a_float32_sum(n, t, tokens):
-    main = [k for k in plan(n, t) if "hessian_bf16_big" in k["kernel"]]
+    main = [k for k in plan(n, t) if "direct" in k]
     assert main and all(k["chunk"] == tokens for k in main)
     assert sum(k["splits"] for k in main) == -(-t // tokens)
     # added to H by the kernel itself exactly where there is one split
-    assert all((k["direct"] != 0) == (t <= tokens) for k in main)
+    assert all(k["direct"] == (t <= tokens) for k in main)
+
+
+def test_main_kernels_keep_their_accumulators_in_registers():
+    """No form of the 256 x 256-tile kernel spills: each has only the epilogue that it runs."""
+    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
+    r = subprocess.run([build._hipcc(), *flags, "-S", "--cuda-device-only", os.path.join(build.CSRC, "hessian.hip"), "-o", "-"],
+                       capture_output=True, text=True, check=True)
+    spills = re.findall(r"\.name:\s+(\S*hessian_bf16_big_kernel\S*)\n(?:.*\n)*?\s+\.private_segment_fixed_size: (\d+)\n"
+                        r"(?:.*\n)*?\s+\.vgpr_spill_count: (\d+)", r.stdout)
+    assert len(spills) == 4 and all(s[1:] == ("0", "0") for s in spills), spills
