@@ -224,8 +224,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // A wave's tile is 128 x 32 NB: NB = 4, the 256 x 256 tile; NB = 2, one half (`half_tile`, 128 columns) of an
 // off-diagonal 256 x 256 tile, with a B part of half the size.  On a diagonal tile both operands come from the A part;
 // waves 0 and 3 take its two diagonal quadrants (ten of sixteen MFMA tiles) and wave 1 the off-diagonal one, which
-// keeps the workgroup in step with those of whole tiles beside it (they share their operands in the L2: shared out
-// evenly, n = 11008 took 25.2 ms instead of 24.5); SHARED, beside half tiles: waves 1 and 2 take half of it each.
+// keeps the workgroup in step with those of whole tiles beside it (they share their operands in the L2); SHARED: waves 1
+// and 2 take half of it each, for half tiles and for short splits (kSharedTokens).
 template <bool diag, int NB, bool SHARED, bool DIRECT>
 __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t ldx, int64_t t, int n,
                                          int64_t tok0, int chunk, int I, int J, int half_tile, int split,
@@ -648,6 +648,12 @@ struct Plan {
 };
 
 constexpr int64_t kHalfCost = 66;   // percent of a whole tile's time that half a tile takes (measured with full rounds)
+// Tokens of a split up to which whole tiles added to H share the off-diagonal quadrant of a diagonal tile: a short split ends
+// with the update of H, which such a workgroup then starts earlier; in a long one the workgroups should keep in step.
+// Shared and not: n = 16384 with 2048 tokens 862 and 883 us, 4096 1237 and 1267; n = 11008 with 2048 402 and 405, 4096
+// 580 and 586, 16384 1675 and 1677, 20480 2047 and 2034, 46016 4428 and 4392; n = 9728 with 65536 4904 and 4865; n = 5632
+// with 2048 to 20480 the same.  (Partial tiles are never shared: 262144 tokens x 11008 took 25.2 ms instead of 24.5.)
+constexpr int kSharedTokens = 16384;
 constexpr int64_t kBigFrom = 2048;                   // layers at least this wide use the 256-tile kernel
 constexpr size_t kMaxPartialBytes = (size_t)1 << 30;  // partial tiles in flight per launch
 
@@ -736,7 +742,8 @@ ptq_status hessian_launch(double* H, int64_t ldh, const void* X, ptq_dtype xdt, 
       const std::true_type yes;
       const std::false_type no;
       const bool ok = p.halves ? (direct ? launch(yes, yes, yes) : launch(yes, yes, no))
-                               : (direct ? launch(no, yes, yes) : launch(no, no, no));
+                    : !direct  ? launch(no, no, no)
+                    : p.chunk <= kSharedTokens ? launch(no, yes, yes) : launch(no, no, yes);
       if (!ok) return PTQ_ERR_HIP;
       if (!direct)
         hessian_reduce_kernel<float, kBT><<<gr, 256, 0, st>>>(static_cast<const float*>(ws), ns, p.ntiles,

@@ -1,4 +1,5 @@
-"""How the bfloat16 Hessian splits its tokens, from the launches that the host would make (no GPU)."""
+"""How the bfloat16 Hessian splits its tokens and which form of the main kernel it takes, from the launches that the host would
+make (no GPU)."""
 import os
 import re
 import subprocess
@@ -35,6 +36,14 @@ def test_tokens_of_a_float32_sum(n, t, tokens):
     assert all(k["direct"] == (t <= tokens) for k in main)
 
 
+# where a diagonal tile's off-diagonal quadrant is shared by two waves: half tiles, and whole ones in short direct splits
+@pytest.mark.parametrize("n,t,halves,shared", [(4096, 2048, True, True), (6144, 2048, True, True), (5632, 2048, False, True), (11008, 16384, False, True),
+                                               (11008, 16416, False, False), (11008, 46016, False, False), (11008, 262144, False, False)])
+def test_forms_of_the_main_kernel(n, t, halves, shared):
+    main = [k for k in plan(n, t) if "direct" in k]
+    assert main and all((k["halves"], k["shared"]) == (halves, shared) for k in main)
+
+
 def test_main_kernels_keep_their_accumulators_in_registers():
     """No form of the 256 x 256-tile kernel spills: each has only the epilogue that it runs."""
     flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
@@ -42,4 +51,4 @@ def test_main_kernels_keep_their_accumulators_in_registers():
                        capture_output=True, text=True, check=True)
     spills = re.findall(r"\.name:\s+(\S*hessian_bf16_big_kernel\S*)\n(?:.*\n)*?\s+\.private_segment_fixed_size: (\d+)\n"
                         r"(?:.*\n)*?\s+\.vgpr_spill_count: (\d+)", r.stdout)
-    assert len(spills) == 4 and all(s[1:] == ("0", "0") for s in spills), spills
+    assert len(spills) == 5 and all(s[1:] == ("0", "0") for s in spills), spills
