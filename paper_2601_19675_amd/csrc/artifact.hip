@@ -548,13 +548,19 @@ __device__ __forceinline__ bf16x8 widen_codes(const HalfWords<BITS>& v, int h, f
   return __builtin_bit_cast(bf16x8, o);
 }
 
-// the three truncated bfloat16 pieces of two floats, paired
+// The three truncated bfloat16 pieces of two floats, paired.  KEEP_INF: an infinity is its first piece alone, so that its
+// products are those of the float32 (otherwise the others are NaN, and so is every sum that it enters).
+template <bool KEEP_INF>
 __device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
+  auto rest = [](float v) {
+    const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
+    return KEEP_INF && __builtin_isinf(v) ? 0.f : r;
+  };
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     p[i] = pair_high(a, b);
-    a -= __uint_as_float(__float_as_uint(a) & 0xffff0000u);
-    b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
+    a = rest(a);
+    b = rest(b);
   }
 }
 
@@ -630,10 +636,10 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
       r.zero[rt] = zp[row[rt]];
     }
   };
-  auto stage_x = [&](const float (&x)[E], int buf) {
+  auto stage_x = [&](auto keep_inf, const float (&x)[E], int buf) {
     uint32_t p[E / 2][3];
 #pragma unroll
-    for (int i = 0; i < E / 2; ++i) split3(x[2 * i], x[2 * i + 1], p[i]);
+    for (int i = 0; i < E / 2; ++i) split3<decltype(keep_inf)::value>(x[2 * i], x[2 * i + 1], p[i]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       uint16_t* dst = &xs[buf][k][st_tok][st_col];
@@ -683,7 +689,8 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
     float x[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) x[i] = __uint_as_float(__float_as_uint(r.x[i]) & live);
-    stage_x(x, buf);
+    // (an infinite x makes all outputs of its token NaN either way: a row's sum of zero x, were it 0 x, is NaN)
+    stage_x(std::false_type{}, x, buf);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       const float z = (float)r.zero[rt];
@@ -729,7 +736,7 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
         yv[i] = k < a.r ? v : 0.f;
       }
       __syncthreads();
-      stage_x(yv, 0);
+      stage_x(std::true_type{}, yv, 0);   // a coefficient past the float32 range makes its products infinite
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll

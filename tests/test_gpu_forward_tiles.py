@@ -118,3 +118,31 @@ def test_forward_rows_match_the_dequantized_product(bits, tokens, m, n, group, r
     ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, *low, O)
     torch.cuda.synchronize()
     _check(O.cpu().double(), layer, bits, group)
+
+
+# a coefficient beyond float32: its products with U are infinite (NaN with a zero of U), whatever form the product takes
+@pytest.mark.parametrize("bits,tokens,m,n,r", [(4, 1, 40, 96, 2), (4, 4, 40, 4096, 3), (3, 5, 300, 608, 1), (8, 33, 70, 288, 35), (2, 64, 4100, 512, 2),
+                                               (4, 1100, 4352, 64, 33)])
+def test_an_infinite_coefficient_stays_infinite(bits, tokens, m, n, r):
+    layer = list(_random_layer(31 * bits + tokens, bits, tokens, m, n, 32, r, torch.float32))
+    packed, scales, zeros, perm, X, U, V, sigma, s = layer
+    U[:, ::7], U[:, 1::7] = 0, 0x80                       # zeros of either sign
+    s.clamp_(min=0.1)
+    s[3], X[:, 3] = 1e-20, 0.0
+    hit = torch.arange(tokens) % 3 == 0
+    X[hit, 3] = torch.where(torch.arange(tokens)[hit] % 2 == 0, 1e30, -1e30)
+    last = torch.arange(r) == r - 1
+    V[:, 3] = torch.where(last, 0x38, 0).to(torch.uint8)   # 1 or 0: the other coefficients stay finite
+    sigma.fill_(1.0)
+    d = lambda t: t.cuda()  # noqa: E731
+    O = torch.full((tokens, m), float("nan"), device="cuda")
+    ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), 32, d(perm), n, 16, d(U), d(V), d(sigma), d(s), O)
+    torch.cuda.synchronize()
+    got = O.cpu()
+    u, v = U.view(torch.float8_e4m3fn).float(), V.view(torch.float8_e4m3fn).double()
+    y = ((X.double() / s) @ v.T).float()
+    assert torch.equal(torch.isinf(y), hit[:, None] & last[None, :])
+    low = (y[:, :, None] * u[None]).sum(1)                # infinite or NaN where it is decided by infinite coefficients
+    assert torch.equal(torch.isnan(got), torch.isnan(low)) and torch.isnan(low).any()
+    assert torch.equal(torch.isinf(got), torch.isinf(low)) and torch.isinf(low).any()
+    assert torch.equal(got[torch.isinf(low)], low[torch.isinf(low)]) and torch.isfinite(got[~hit]).all()
