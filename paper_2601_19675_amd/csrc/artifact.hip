@@ -140,7 +140,7 @@ __device__ __forceinline__ float fp16_bits_to_float(uint16_t h) {
 // X~ = X P Q in float64, written as float32 (xt[chunk][token][32]), and, in float64,
 //   y[t][k] = sigma_k * sum_j V[k][j] x[t][j] / s[j].
 // The first workgroups take TG tokens x RG ranks of y (1 x 4 while there are few tokens, for the latency; 2 x 16
-// from kPrepMany on, where one 1 / s and one conversion of V then serve several products): 2048 columns at a time,
+// from kPrepMany on, where one conversion of V and one quotient x / s then serve several products): 2048 columns at a time,
 // four per lane, all loads of a step on their way together; the sums over the 64 lanes are folded by halves, one
 // exchange per value pair and step.  The others rotate: a workgroup stages a token's row in LDS and transforms
 // `segment` of its 256-column chunks (a row goes to several workgroups while there are few tokens).
@@ -223,10 +223,9 @@ __device__ __forceinline__ void low_rank_coefficients(const PrepArgs& a, double*
     for (int k = 0; k < RG; ++k) c[k] = *reinterpret_cast<const Codes*>(vp[k] + j);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const double inv = 1.0 / sc.e[i];
       double xs[TG];
 #pragma unroll
-      for (int t = 0; t < TG; ++t) xs[t] = stored_to_f64<DT>(x[t].e[i]) * inv;
+      for (int t = 0; t < TG; ++t) xs[t] = stored_to_f64<DT>(x[t].e[i]) / sc.e[i];
 #pragma unroll
       for (int k = 0; k < RG; ++k) {
         const double v = (double)e4m3_to_float(c[k].e[i]);

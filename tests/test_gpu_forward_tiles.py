@@ -146,3 +146,20 @@ def test_an_infinite_coefficient_stays_infinite(bits, tokens, m, n, r):
     assert torch.equal(torch.isnan(got), torch.isnan(low)) and torch.isnan(low).any()
     assert torch.equal(torch.isinf(got), torch.isinf(low)) and torch.isinf(low).any()
     assert torch.equal(got[torch.isinf(low)], low[torch.isinf(low)]) and torch.isfinite(got[~hit]).all()
+
+
+# x / s, not x times a rounded 1 / s: a scale whose reciprocal is past the float64 range, under an activation of zero and
+# under one of its own size
+@pytest.mark.parametrize("tokens,r", [(1, 3), (33, 16)])
+def test_the_smallest_scales_divide(tokens, r):
+    m, n, bits = 40, 96, 4
+    layer = list(_random_layer(5 + tokens, bits, tokens, m, n, 32, r, torch.float64))
+    packed, scales, zeros, perm, X, U, V, sigma, s = layer
+    s[3], X[:, 3] = 1e-310, 0.0
+    s[40], X[:, 40] = 2e-309, 4e-309
+    V[:, 40] = 0x38                                       # 1: the quotient counts
+    d = lambda t: t.cuda()  # noqa: E731
+    O = torch.full((tokens, m), float("nan"), device="cuda")
+    ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), 32, d(perm), n, 16, d(U), d(V), d(sigma), d(s), O)
+    torch.cuda.synchronize()
+    _check(O.cpu().double(), layer, bits, 32)
