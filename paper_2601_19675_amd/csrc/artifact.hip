@@ -864,31 +864,34 @@ void launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st) {
 }
 
 template <int BITS, int B, int R>
-void launch_forward_rows_as(const ForwardArgs& a, hipStream_t st) {
+ptq_status launch_forward_rows_as(const ForwardArgs& a, hipStream_t st) {
   const int columns = std::min(a.n, kRowLdsFloats / B / kChunk * kChunk);
   const int items = (int)ceil_div(a.m, R);
   const size_t lds = std::max((size_t)B * (columns + columns / kChunk), (size_t)4 * B * R) * sizeof(float);
-  if (!lds_opt_in<forward_rows_kernel<BITS, B, R>>(160 * 1024)) return;
+  if (!lds_opt_in<forward_rows_kernel<BITS, B, R>>(160 * 1024)) return PTQ_ERR_HIP;
   forward_rows_kernel<BITS, B, R><<<8u * (unsigned)ceil_div(items, 8), 256, lds, st>>>(a, columns, items);
+  return PTQ_OK;
 }
 
 template <int BITS, int B>
-void launch_forward_rows(const ForwardArgs& a, hipStream_t st) {
-  if (a.m > 2048) launch_forward_rows_as<BITS, B, 16>(a, st);
-  else launch_forward_rows_as<BITS, B, 8>(a, st);
+ptq_status launch_forward_rows(const ForwardArgs& a, hipStream_t st) {
+  return a.m > 2048 ? launch_forward_rows_as<BITS, B, 16>(a, st) : launch_forward_rows_as<BITS, B, 8>(a, st);
 }
 
 // One or two tokens always, three or four while their X~ lets two workgroups share a compute unit, go row by row
 // (4 bits: 2 x 11008 x 8192 38 us for the call, 52 as tiles; 3 x 11008 x 4096 19.4 and 32.9; 4 x 4096 x 4096 18.8 and
 // 19.8; but 4 x 11008 x 5632 55.9 and 40.7, 4 x 4096 x 8192 32.6 and 29.6); all others take the tiles.
 template <int BITS>
-void launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
-  if (tokens > 2 && (tokens > 4 || (int64_t)tokens * a.n > 16384)) { launch_forward_tile<BITS>(a, tokens, st); return; }
+ptq_status launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
+  if (tokens > 2 && (tokens > 4 || (int64_t)tokens * a.n > 16384)) {
+    launch_forward_tile<BITS>(a, tokens, st);
+    return PTQ_OK;
+  }
   switch (tokens) {
-    case 1: launch_forward_rows<BITS, 1>(a, st); break;
-    case 2: launch_forward_rows<BITS, 2>(a, st); break;
-    case 3: launch_forward_rows<BITS, 3>(a, st); break;
-    default: launch_forward_rows<BITS, 4>(a, st); break;
+    case 1: return launch_forward_rows<BITS, 1>(a, st);
+    case 2: return launch_forward_rows<BITS, 2>(a, st);
+    case 3: return launch_forward_rows<BITS, 3>(a, st);
+    default: return launch_forward_rows<BITS, 4>(a, st);
   }
 }
 
@@ -980,12 +983,13 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
   if (rc != PTQ_OK) return rc;
   ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, (int)tokens, y, U, r, partial, O, ldo};
   switch (bits) {
-    case 2: launch_forward<2>(a, (int)tokens, st); break;
-    case 3: launch_forward<3>(a, (int)tokens, st); break;
-    case 4: launch_forward<4>(a, (int)tokens, st); break;
-    case 8: launch_forward<8>(a, (int)tokens, st); break;
+    case 2: rc = launch_forward<2>(a, (int)tokens, st); break;
+    case 3: rc = launch_forward<3>(a, (int)tokens, st); break;
+    case 4: rc = launch_forward<4>(a, (int)tokens, st); break;
+    case 8: rc = launch_forward<8>(a, (int)tokens, st); break;
     default: return PTQ_ERR_ARG;
   }
+  if (rc != PTQ_OK) return rc;
   PTQ_HIP_CHECK_LAUNCH();
   return PTQ_OK;
 }
