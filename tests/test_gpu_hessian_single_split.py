@@ -6,12 +6,19 @@ import paper_2601_19675_amd as ptq
 
 pytestmark = pytest.mark.gpu
 
+# (n, tokens of the calls in a row), by the form that every call takes (tests/test_hessian_plan.py holds them to it).
+# Halves of tiles with the smallest width, a last tile of 8 and of 136 channels, an odd and an even number of tiles, tokens
+# around the 32 of a stage and the ring of four.
+HALVES = [(2048, (1,)), (2056, (31, 33)), (2184, (129, 96, 1)), (2304, (256,)), (4096, (64, 160)), (5640, (65, 32)), (6144, (130,))]
+# Whole tiles, the diagonal ones shared: a last tile of 8, 136 and 248 channels, one, two and three rounds of workgroups.
+WHOLE = [(4360, (1, 33)), (5512, (65, 32)), (7176, (130,)), (8440, (31,))]
+# Whole tiles in long splits, nothing shared; a last tile of 136 channels.
+LONG = [(5512, (16416,))]
+# Halves of tiles in several splits, by way of partial tiles.
+SPLIT_HALVES = [(2304, (700,)), (2056, (512,))]
 
-# halves of tiles with the smallest width, a last tile of 8 and of 136 channels, an odd and an even number of tiles, tokens
-# around the 32 of a stage and the ring of four; whole tiles (5640 = 22 tiles + 8 channels); three calls in a row
-@pytest.mark.parametrize("n,chunks", [(2048, (1,)), (2056, (31, 33)), (2184, (129, 96, 1)), (2304, (700,)), (4096, (64, 160)),
-                                      (5640, (65, 32)), (6144, (130,))])
-def test_single_split_adds_the_gram_matrix_to_the_upper_triangle(n, chunks):
+
+def _check(n, chunks, on):
     g = torch.Generator().manual_seed(n)
     t = sum(chunks)
     X = (torch.randn((t, n), generator=g) * torch.exp(torch.randn(n, generator=g))).to(torch.bfloat16)
@@ -22,11 +29,21 @@ def test_single_split_adds_the_gram_matrix_to_the_upper_triangle(n, chunks):
         ptq.ptq_hessian_accumulate(H, Xd[a:a + c])
         a += c
     torch.cuda.synchronize()
-    x = X.double()
+    x = X.to(on).double()
     want, mag = x.T @ x, x.abs().T @ x.abs()
-    got = wide.cpu()
-    assert (got[:, n:] == 0.5).all() and (torch.tril(got[:, :n], -1) == torch.tril(torch.full((n, n), 0.5), -1)).all()
+    got = wide.to(on)
+    assert (got[:, n:] == 0.5).all() and (torch.tril(got[:, :n], -1) == torch.tril(torch.full((n, n), 0.5, device=on), -1)).all()
     # float32 sums of exact products, at worst one after the other
     err = (torch.triu(got[:, :n] - 0.5) - torch.triu(want)).abs()
     bound = t * 2.0 ** -24 * mag + 1e-12 * mag.max()
     assert (err <= bound).all(), float((err / bound).max())
+
+
+@pytest.mark.parametrize("n,chunks", HALVES + WHOLE + SPLIT_HALVES)
+def test_single_split_adds_the_gram_matrix_to_the_upper_triangle(n, chunks):
+    _check(n, chunks, "cpu")
+
+
+@pytest.mark.parametrize("n,chunks", LONG)
+def test_a_long_split_adds_the_gram_matrix_to_the_upper_triangle(n, chunks):
+    _check(n, chunks, "cuda")   # the float64 reference is a plain library product

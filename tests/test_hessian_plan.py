@@ -8,6 +8,7 @@ import pytest
 
 from paper_2601_19675_amd import build
 from launch_recorder import PTR, record
+import test_gpu_hessian_single_split as single
 
 BIG = {"hessian_bf16_big": {"chunk": (5, "i"), "splits": (8, "i")}}
 
@@ -42,6 +43,16 @@ def test_tokens_of_a_float32_sum(n, t, tokens):
 def test_forms_of_the_main_kernel(n, t, halves, shared):
     main = [k for k in plan(n, t) if "direct" in k]
     assert main and all((k["halves"], k["shared"]) == (halves, shared) for k in main)
+
+
+# the sizes at which the forms are compared with the Gram matrix take the forms that they are listed for
+@pytest.mark.parametrize("cases,form", [(single.HALVES, (True, True, True)), (single.WHOLE, (False, True, True)), (single.LONG, (False, False, True)),
+                                        (single.SPLIT_HALVES, (True, True, False))], ids=["halves", "whole", "long", "split halves"])
+def test_sizes_of_the_single_split_tests(cases, form):
+    for n, chunks in cases:
+        for t in chunks:
+            main = [k for k in plan(n, t) if "direct" in k]
+            assert main and all((k["halves"], k["shared"], k["direct"]) == form for k in main), (n, t, main)
 
 
 def test_main_kernels_keep_their_accumulators_in_registers():
