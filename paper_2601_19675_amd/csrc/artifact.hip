@@ -144,9 +144,9 @@ __device__ __forceinline__ float fp16_bits_to_float(uint16_t h) {
 // four per lane, all loads of a step on their way together; the sums over the 64 lanes are folded by halves, one
 // exchange per value pair and step.  The others rotate: a workgroup stages a token's row in LDS and transforms
 // `segment` of its 256-column chunks (a row goes to several workgroups while there are few tokens).
-// For a token or a few both parts are chains of latencies; as two launches (a workgroup per row; a workgroup per
-// token and rank) the call of one token took 27.0 us at 4096 x 4096, 16 ranks, 53 at 4096 x 11008, now 15.8 and 25.2;
-// at 512 tokens x 4096 x 11008 253, now 169 (the coefficients alone 98 us, mostly divisions and conversions).  The
+// For a token or a few both parts are chains of latencies: one token, 4096 x 4096, 16 ranks 3.8 us for the launch, 7.3 +
+// 7.2 as two (a workgroup per row; a workgroup per token and rank).  512 tokens x 4096 x 11008 29.5 us, 29.9 + 132 as
+// two (the coefficients mostly divisions and conversions, one of each for every product).  The
 // coefficients on the float64 matrix instruction were slower: 16 x 16 tiles of tokens x ranks leave most of
 // the chip idle (194 us; a single token 28).
 struct PrepArgs {
@@ -345,7 +345,7 @@ struct ForwardArgs {
 // workgroups.  sum_j scale (code_j - zero) x_j = scale (sum_j code_j x_j - zero sum_j x_j): the second sum does not
 // depend on the row, so a weight costs a conversion and a multiply-add per token (half an instruction to
 // extract).  The ranks of the low-rank part are dealt to the slices like chunks.  One token, 4096 x 4096, 4 bits:
-// 7.5 us for the kernel (11.8 with a workgroup per 256 rows x 256 columns, partial sums in memory and the last
+// 7.6 us for the kernel (11.8 with a workgroup per 256 rows x 256 columns, partial sums in memory and the last
 // workgroup of a row block adding them); 16 rows per workgroup, 8 where that leaves compute units idle.
 template <int BITS>
 struct alignas(BITS == 3 ? 4 : (BITS == 2 ? 8 : 16)) Words { uint32_t w[BITS]; };
@@ -494,9 +494,10 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int co
 // One barrier per chunk: while chunk c is multiplied, chunk c + 1 is split into the other LDS half and
 // chunk c + 2 is on its way from memory.  RT = 2 sets the LDS traffic (six 1 KB reads per twelve MFMAs of a
 // wave: half of what the LDS delivers); 64 tokens per workgroup keep 256 registers, two waves per SIMD.
-// Bound: the bfloat16 MFMAs (and about nine vector instructions beside each).  The whole call, against 32-token
-// passes on the float32 instruction: 512 tokens x 4096 x 11008, 3 bits, 1140 -> 253 us; 2048 x 11008 x 4096, 4 bits,
-// 4067 -> 684; 4000 x 999 x 1024 2852 -> 137; 32 x 11008 x 4096 83 -> 55; 8 x 4096 x 4096 41 -> 29; the distance
+// Bound: the bfloat16 MFMAs (and about nine vector instructions beside each).  The whole call with 16 ranks, against 32-token
+// passes on the float32 instruction and an input of two launches: 512 tokens x 4096 x 11008, 3 bits, 1131 -> 167 us;
+// 2048 x 11008 x 4096, 4 bits, 4045 -> 540; 4000 x 999 x 1024 2859 -> 65; 32 x 11008 x 4096 82 -> 44; 8 x 4096 x 4096
+// 39 -> 20; the distance
 // from the float64 product falls from 3.4e-7 to 1.3e-7 of its norm (no sum of code x and zero x of opposite sign).
 template <int BITS> struct HalfWords { uint32_t w[BITS == 2 ? 1 : (BITS == 8 ? 4 : 2)]; };
 
@@ -847,12 +848,14 @@ void launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st) {
   p.token_blocks = (int)ceil_div(tokens, 32 * TT);
   p.row_blocks = (int)ceil_div(a.m, 256);
   const int64_t tiles = (int64_t)p.token_blocks * p.row_blocks;
-  // Two waves per SIMD hide each other's loads (one alone waits out about a microsecond per chunk: 512 tokens x
-  // 4096 x 11008 272 us for the call, 253 with two): where the tiles alone give every compute unit two workgroups the
-  // columns stay whole; otherwise a workgroup's two halves take half of its columns each, and the columns are
-  // split over workgroups until every compute unit has one, as far as the partial sums fit the workspace and a
-  // part keeps eight chunks.  Up to 32 tokens the codes' stream is the bound and twice as many workgroups keep
-  // more of it in flight (24 x 11008 x 11008: 91 -> 84 us).
+  // Two waves per SIMD hide each other's loads (one alone waits out about a microsecond per chunk): where the tiles
+  // alone give every compute unit two workgroups the columns stay whole; otherwise a workgroup's two halves take half of
+  // its columns each (whole call, 16 ranks, 4 bits: 512 tokens x 4096 x 11008 162 us, 177 without; 4000 x 999 x 1024 65 and
+  // 68; not at 32 tokens or fewer: 32 x 11008 x 4096 44 and 37, 24 x 11008 x 11008 66 and 54, 8 x 4096 x 4096 19.8 and 19.4),
+  // and the columns are split over workgroups until every compute unit has one, as far as the partial sums fit the
+  // workspace and a part keeps eight chunks.  Up to 32 tokens the codes' stream is the bound and twice as many
+  // workgroups keep more of it in flight (24 x 11008 x 11008 78 -> 66 us, 32 x 11008 x 4096 47 -> 44; 4 x 4096 x 8192
+  // loses, 25 -> 29).
   const bool many = tiles >= 512;
   int64_t s = many ? 1 : ceil_div(TT == 1 ? 512 : 256, tiles);
   s = std::min<int64_t>(s, ceil_div(chunks, kFwdRun) * kPartialTokens / tokens);
@@ -879,8 +882,9 @@ ptq_status launch_forward_rows(const ForwardArgs& a, hipStream_t st) {
 }
 
 // One or two tokens always, three or four while their X~ lets two workgroups share a compute unit, go row by row
-// (4 bits: 2 x 11008 x 8192 38 us for the call, 52 as tiles; 3 x 11008 x 4096 19.4 and 32.9; 4 x 4096 x 4096 18.8 and
-// 19.8; but 4 x 11008 x 5632 55.9 and 40.7, 4 x 4096 x 8192 32.6 and 29.6); all others take the tiles.
+// (whole call, 4 bits, 16 ranks: 2 x 11008 x 8192 39 us, 54 as tiles; 3 x 11008 x 4096 20.0 and 33.3; 4 x 4096 x 4096
+// 18.9 and 19.8; beyond that line 4 x 11008 x 5632 56.3 and 40.5, 4 x 4096 x 8192 32.7 and 29.3, and, three tokens just past
+// it, 3 x 11008 x 5632 35.3 and 39.2, 3 x 4096 x 8192 26.5 and 29.3); all others take the tiles.
 template <int BITS>
 ptq_status launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
   if (tokens > 2 && (tokens > 4 || (int64_t)tokens * a.n > 16384)) {
@@ -935,7 +939,7 @@ static size_t forward_partial_bytes(int64_t m, int64_t n) {
 // ---- scratch for callers that cannot allocate -----------------------------------------------
 // One array per GPU, part of the library's code object: the device memory the forward call needs
 // beyond its inputs and outputs (the rotated input, the low-rank coefficients, the partial sums of
-// the column runs and the row-block counters).  Its name is a host-side stand-in, not a device
+// the column splits).  Its name is a host-side stand-in, not a device
 // address: the address on the current device comes from hipGetSymbolAddress, once per device.
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -959,7 +963,7 @@ ptq_status linear_forward_static_scratch(void** ptr) {
 size_t linear_forward_workspace_bytes(int64_t tokens, int64_t m, int64_t n, int64_t r) {
   return align_up((size_t)tokens * n * sizeof(float), 256) +
          align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256) + forward_partial_bytes(m, n) +
-         align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256);   // unused; which sizes fit the static array stays as it is
+         align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256);   // no kernel uses these: which sizes fit the static array is part of the contract
 }
 
 ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int64_t tokens, int64_t m, int64_t n,

@@ -60,6 +60,10 @@ def record(calls, read=None, failing=""):
     """[(status, [{"kernel", "grid", **arguments}])] for every (function, arguments).  `read`: arguments to note,
     {part of a kernel's name: {key: (position, "i" for 32 bits or "q" for 64)}}; `failing`: part of a kernel's name whose
     hipFuncSetAttribute fails."""
+    if not os.path.exists(LIB):
+        sys.path.insert(0, ROOT)
+        from paper_2601_19675_amd import build
+        build.build(verbose=False)
     with tempfile.TemporaryDirectory() as tmp:
         src, shim = os.path.join(tmp, "shim.c"), os.path.join(tmp, "shim.so")
         with open(src, "w") as f:
