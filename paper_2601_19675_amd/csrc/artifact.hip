@@ -10,9 +10,11 @@
 // that lanes that work on consecutive rows read consecutive memory.
 //
 // The product with the packed residual takes two forms: a few tokens row by row on the vector unit (bound by the
-// codes' stream from memory), more of them in tiles on the bfloat16 matrix cores.
+// codes' stream from memory), more of them in tiles on the 16-bit matrix cores.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "rotation.h"
@@ -137,18 +139,15 @@ __device__ __forceinline__ float fp16_bits_to_float(uint16_t h) {
 }
 
 // ---- what the products read: X~ and the low-rank coefficients, one launch -------------------------
-// X~ = X P Q in float64, written as float32 (xt[chunk][token][32]), and, in float64,
+// X~ = X P Q in float64, written as float32 (xt[chunk][token][32]) for the few-token product, as two float16 pieces
+// ([2][32] in the same place) for the tiles, and, in float64,
 //   y[t][k] = sigma_k * sum_j V[k][j] x[t][j] / s[j].
-// The first workgroups take TG tokens x RG ranks of y (1 x 4 while there are few tokens, for the latency; 2 x 16
-// from kPrepMany on, where one conversion of V and one quotient x / s then serve several products): 2048 columns at a time,
-// four per lane, all loads of a step on their way together; the sums over the 64 lanes are folded by halves, one
-// exchange per value pair and step.  The others rotate: a workgroup stages a token's row in LDS and transforms
-// `segment` of its 256-column chunks (a row goes to several workgroups while there are few tokens).
-// For a token or a few both parts are chains of latencies: one token, 4096 x 4096, 16 ranks 3.8 us for the launch, 7.3 +
-// 7.2 as two (a workgroup per row; a workgroup per token and rank).  512 tokens x 4096 x 11008 29.5 us, 29.9 + 132 as
-// two (the coefficients mostly divisions and conversions, one of each for every product).  The
-// coefficients on the float64 matrix instruction were slower: 16 x 16 tiles of tokens x ranks leave most of
-// the chip idle (194 us; a single token 28).
+// The first workgroups take y: a token and four ranks each, or 16 tokens x 16 ranks on the float64 matrix instruction from
+// kPrepMany tokens on.  The others rotate: a workgroup stages the rows of a token (several, where they are narrow and many)
+// in LDS and transforms 256-column chunks, a wave each (a row goes to several workgroups while there are few tokens).
+// For a few tokens both parts are chains of latencies; for many the rotation is vector instructions (some 200 per
+// chunk).  512 tokens x 11008 columns, 16 ranks: 30 us as float32 with 2 tokens x 16 ranks of y per workgroup on the vector
+// unit (the rotation alone 15), now 24 with the pieces (18); 4000 x 1024 34 -> 22.
 struct PrepArgs {
   const void* X;
   int64_t ldx;
@@ -161,11 +160,22 @@ struct PrepArgs {
   int r;
   float* xt;
   float* y;
-  int coeff_tiles, segments, segment;   // chunks per segment
+  double* y_parts;      // null: y; else coeff_splits x tokens x r, without sigma
+  int coeff_tiles, coeff_splits;
+  int run_lg, segments, segment;   // 2^run_lg tokens a rotating workgroup; workgroups per token (run_lg = 0) and chunks of each
+  uint64_t order;   // 0: X~ as float32; otherwise as two float16 pieces, position p of 16 holds column (order >> 4 p) & 15
+  int* exponents;   // tokens: X~ is 2^exponents[token] times the pieces' sum
+  bool roomy;       // LDS beyond the row: kPrepWaves x 256 words
+  int lg;           // b_H = 2^lg
+  double scale;     // 1 / sqrt(b_H)
 };
 
 constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
-constexpr int kPrepMany = 32;   // tokens
+// From here on 16 tokens share a wave's quotients and conversions (whole call, 16 ranks: 200 x 4096 x 11008 75 us, 76 without;
+// 512 x 4096 x 11008 120 and 139; 1000 x 777 x 512 27 and 37).  Below it the chip is not full that way (128 x 4096 x 11008 57
+// and 52 us, 160 x 11008 x 4096 91 and 87).
+constexpr int kPrepMany = 192;   // tokens
+constexpr int kCoeffSplits = 4;  // workgroups that share the columns of 16 tokens x 16 ranks
 
 // Sums of NV values per lane over the 64 lanes, halving the number of values with every exchange as long as there
 // is more than one: afterwards v[0] is the sum of value (lane / (64 / NV)).
@@ -247,54 +257,264 @@ __device__ __forceinline__ void low_rank_coefficients(const PrepArgs& a, double*
   }
 }
 
+__device__ __host__ __forceinline__ int align16(int bytes) { return (bytes + 15) & ~15; }
+
+// low halves of two words, the lower one first, and their high halves
+__device__ __forceinline__ uint32_t pair_low(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t pair_high(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// A number below 2^15 as the sum of two float16: each rounded to nearest, the second of what the first leaves
+__device__ __forceinline__ uint32_t split2(double x) {
+  // by way of float32, kept apart: as one conversion from float64 it is some forty instructions
+  auto narrow = [](double v) {
+    float f = (float)v;
+    asm("" : "+v"(f));
+    return (_Float16)f;
+  };
+  const _Float16 first = narrow(x);
+  const _Float16 second = narrow(x - (double)first);
+  return (uint32_t)__builtin_bit_cast(uint16_t, second) << 16 | __builtin_bit_cast(uint16_t, first);
+}
+
+// Many tokens: 16 of them x 16 ranks on the float64 matrix instruction, the columns dealt to the waves of coeff_splits
+// workgroups, 32 at a time: lane l is token (rank) l % 16 and takes columns 8 (l / 16) .. + 7.  A column's reciprocal
+// 1 / s serves all tokens; the quotient x / s it gives is corrected by its remainder, x - q s being exact, and
+// is right to an ulp of float64.  Where that fails (x infinite, s beyond 2^500 or below 2^-500) the remainder is NaN, and the
+// division itself is done.
 template <int DT, bool ALIGNED>
+__device__ __forceinline__ void low_rank_coefficients_many(const PrepArgs& a, char* lds) {
+  using ST = typename StoredType<DT>::type;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = (lane >> 4) * 8;
+  const int rank_tiles = (a.r + 15) / 16;
+  const int split = blockIdx.x % a.coeff_splits, tile = blockIdx.x / a.coeff_splits;
+  const int t0 = (tile / rank_tiles) * 16, k0 = (tile % rank_tiles) * 16;
+  // tokens and ranks past the end repeat the last; not stored
+  const ST* xp = static_cast<const ST*>(a.X) + (int64_t)min(t0 + (lane & 15), a.tokens - 1) * a.ldx + col;
+  const uint8_t* vp = a.V + (int64_t)min(k0 + (lane & 15), a.r - 1) * a.n + col;
+  struct Column { double s, inverse; };
+  Column* table = reinterpret_cast<Column*>(lds) + 32 * wave;
+  struct alignas(ALIGNED ? 16 : sizeof(ST)) Eight { ST e[8]; };
+  struct alignas(ALIGNED ? 4 : 1) Codes { uint8_t e[8]; };
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  const int blocks = a.n / 32, stride = kPrepWaves * a.coeff_splits;
+  int b = split * kPrepWaves + wave;
+  Eight x;
+  Codes c;
+  double sv = 1.0;
+  auto request = [&](int at) {
+    at = min(at, blocks - 1) * 32;   // issued whatever the block: no branch
+    x = *reinterpret_cast<const Eight*>(xp + at);
+    c = *reinterpret_cast<const Codes*>(vp + at);
+    sv = a.s[at + (lane & 31)];
+  };
+  request(b);
+  for (; b < blocks; b += stride) {
+    const double mag = fabs(sv);
+    const bool safe = DT != PTQ_F64 && mag > 0x1p-500 && mag < 0x1p500;
+    table[lane & 31] = Column{sv, safe ? 1.0 / sv : __builtin_nan("")};
+    __builtin_amdgcn_wave_barrier();
+    const Eight xb = x;
+    const Codes cb = c;
+    request(b + stride);
+    double q[8], v[8], sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const Column t = table[col + i];
+      const double xv = stored_to_f64<DT>(xb.e[i]), q0 = xv * t.inverse;
+      q[i] = fma(fma(-q0, t.s, xv), t.inverse, q0);
+      sum += q[i];
+    }
+    if (__builtin_isnan(sum)) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (__builtin_isnan(q[i])) q[i] = stored_to_f64<DT>(xb.e[i]) / table[col + i].s;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {   // e4m3 in place of a float16's upper bits: 2^-8 of its value
+      const uint32_t two = (uint32_t)cb.e[i] | (uint32_t)cb.e[i + 1] << 16;
+      const uint32_t h = (two & 0x007f007fu) << 7 | (two & 0x00800080u) << 8;
+      typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+      const f16x2 f = __builtin_bit_cast(f16x2, h);
+      v[i] = (double)(float)f.x;
+      v[i + 1] = (double)(float)f.y;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(q[i], v[i], acc, 0, 0, 0);
+    __builtin_amdgcn_wave_barrier();
+  }
+  // accumulator k of a lane is token 4 k + lane / 16, rank lane % 16; the waves' sums in order
+  __syncthreads();
+  double* red = reinterpret_cast<double*>(lds);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) red[wave * 256 + k * 64 + lane] = acc[k];
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kPrepWaves; ++w) sum += red[w * 256 + threadIdx.x];
+    sum *= 0x1p8;
+    const int t = t0 + 4 * wave + (lane >> 4), k = k0 + (lane & 15);
+    if (t < a.tokens && k < a.r) {
+      if (a.y_parts) a.y_parts[((int64_t)split * a.tokens + t) * a.r + k] = sum;
+      else a.y[(int64_t)t * a.r + k] = (float)(sum * (double)fp16_bits_to_float(a.sigma[k]));
+    }
+  }
+}
+
+// the part of a stored number that orders magnitudes: float32 bits, the upper half of a float64
+template <int DT>
+__device__ __forceinline__ uint32_t magnitude(typename StoredType<DT>::type v) {
+  if constexpr (DT == PTQ_F64) return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32) & 0x7fffffffu;
+  else if constexpr (DT == PTQ_F32) return __float_as_uint(v) & 0x7fffffffu;
+  else return ((uint32_t)v << 16) & 0x7fffffffu;
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  auto with = [&](auto ctrl) { v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, false)); };
+  with(std::integral_constant<int, kDppSwapPairs>{});
+  with(std::integral_constant<int, kDppSwapHalfQuads>{});
+  with(std::integral_constant<int, kDppHalfMirror>{});
+  with(std::integral_constant<int, kDppMirror>{});
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  return max(max(a, b), max(c, d));
+}
+
+template <int DT, bool ALIGNED, bool PIECES>
 __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs a) {
   extern __shared__ __attribute__((aligned(16))) char prep_lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
+  // all arguments at once: fetched where they are used, one after the other, they cost a few tokens' launch half a microsecond
+  asm volatile("" ::"s"(a.X), "s"(a.ldx), "s"(a.tokens), "s"(a.n), "s"(a.perm), "s"(a.b_I), "s"(a.xt), "s"(a.run_lg), "s"(a.segments),
+               "s"(a.segment), "s"(a.order), "s"((int)a.roomy), "s"(a.lg), "s"(a.scale), "s"(a.V), "s"(a.s), "s"(a.r), "s"(a.y), "s"(a.coeff_tiles));
   if ((int)blockIdx.x < a.coeff_tiles) {
-    if (a.tokens >= kPrepMany) low_rank_coefficients<DT, ALIGNED, 2, 16>(a, reinterpret_cast<double*>(prep_lds));
+    if (PIECES && a.tokens >= kPrepMany) low_rank_coefficients_many<DT, ALIGNED>(a, prep_lds);
     else low_rank_coefficients<DT, ALIGNED, 1, 4>(a, reinterpret_cast<double*>(prep_lds));
     return;
   }
-  const int item = blockIdx.x - a.coeff_tiles;
-  const int token = item / a.segments, seg = item - token * a.segments;
   using ST = typename StoredType<DT>::type;
-  const ST* src = static_cast<const ST*>(a.X) + (int64_t)token * a.ldx;
-  ST* buf = reinterpret_cast<ST*>(prep_lds);
-  if constexpr (ALIGNED) {   // n is a multiple of 32
-    constexpr int kPer = 16 / (int)sizeof(ST);
-    for (int c = tid * kPer; c < a.n; c += kPrepThreads * kPer)
-      *reinterpret_cast<uint4*>(buf + c) = *reinterpret_cast<const uint4*>(src + c);
-  } else {
-    for (int c = tid; c < a.n; c += kPrepThreads) buf[c] = src[c];
+  const int item = blockIdx.x - a.coeff_tiles, run_lg = a.run_lg;
+  const int unit = a.segments == 1 ? item : item / a.segments;
+  const int token0 = unit << run_lg, seg = item - unit * a.segments;
+  const int run = min(1 << run_lg, a.tokens - token0);
+  const int row = align16(a.n * (int)sizeof(ST));
+  // A wave stages a share of one token's row and keeps its largest magnitude
+  const int my = wave & ((1 << run_lg) - 1), shares = kPrepWaves >> run_lg;
+  uint32_t top = 0;
+  if (my < run) {
+    const ST* src = static_cast<const ST*>(a.X) + (int64_t)(token0 + my) * a.ldx;
+    ST* dst = reinterpret_cast<ST*>(prep_lds + my * row);
+    constexpr int kPer = ALIGNED ? 16 / (int)sizeof(ST) : 1;   // n is a multiple of 32
+    struct alignas(ALIGNED ? 16 : sizeof(ST)) Piece { ST e[kPer]; };
+    for (int c = ((wave >> run_lg) * 64 + lane) * kPer; c < a.n; c += shares * 64 * kPer) {
+      const Piece p = *reinterpret_cast<const Piece*>(src + c);
+      *reinterpret_cast<Piece*>(dst + c) = p;
+      if constexpr (PIECES) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) top = max(top, magnitude<DT>(p.e[i]));
+      }
+    }
+  }
+  uint32_t* tops = reinterpret_cast<uint32_t*>(prep_lds + (row << run_lg));   // with pieces and where there is room: of each wave
+  uint32_t* swap = tops + kPrepWaves + 256 * wave;                            // ... and a wave's own 256 words
+  if (PIECES && a.roomy) {
+    top = wave_max(top);
+    if (lane == 0) tops[wave] = top;
   }
   const int nchunk_id = (a.b_I + 255) / 256;                   // chunks of the identity part
   const int nchunk = nchunk_id + (a.n - a.b_I + 255) / 256;    // ... plus those of the rotated part
-  const int lg = ilog2(a.b_H);
-  const double scale = 1.0 / sqrt((double)a.b_H);
-  const int k_end = min(nchunk, (seg + 1) * a.segment);
+  const int lg = a.lg;
+  const int k_begin = seg * a.segment, items = (min(nchunk, k_begin + a.segment) - k_begin) << run_lg;
+  // item i: token i % 2^run_lg of chunk k_begin + i / 2^run_lg, its columns first .. first + 255 as far as they lie below `end`
+  struct Chunk { int first, end; bool rotated; };
+  auto chunk_of = [&](int i) {
+    const int k = k_begin + (i >> run_lg);
+    const bool rotated = k >= nchunk_id;
+    return Chunk{rotated ? a.b_I + 256 * (k - nchunk_id) : 256 * k, rotated ? a.n : a.b_I, rotated};
+  };
+  auto places = [&](int i) {
+    return *reinterpret_cast<const int4*>(a.perm + min(chunk_of(i).first + 4 * lane, a.n - 4));
+  };
+  int4 next = places(min(wave, items - 1));
   __syncthreads();
-  for (int k = seg * a.segment + wave; k < k_end; k += kPrepWaves) {
-    const bool ident = k < nchunk_id;
-    const int cs = ident ? 256 * k : a.b_I + 256 * (k - nchunk_id);
-    const int ce = ident ? a.b_I : a.n;
-    const int c = cs + 4 * lane;
+  // X~ 2^up stays below 2^15: 2^e <= max |x| < 2^(e + 1) (numbers below the normal range, rows of zeros and rows with an
+  // infinity or a NaN, whose outputs are NaN, go as they are), and a rotation makes it sqrt(b_H) times as large at most.
+  // Lane tl holds token tl's.
+  int ups = 0;
+  uint32_t from[4];   // where a lane's four positions of 16 come from
+  if constexpr (PIECES) {
+    uint32_t largest = 0;
+    if (a.roomy) {
+      static_assert(kPrepWaves == 8, "two reads");
+      const uint4 lo = reinterpret_cast<const uint4*>(tops)[0], hi = reinterpret_cast<const uint4*>(tops)[1];
+      const uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int w = 0; w < 8; ++w) largest = max(largest, ((w ^ lane) & ((1 << run_lg) - 1)) == 0 ? t[w] : 0u);
+    } else {   // one row
+      for (int q = lane; q < a.n; q += 64) largest = max(largest, magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]));
+      largest = wave_max(largest);
+    }
+    constexpr int kMantissa = DT == PTQ_F64 ? 20 : 23, kBias = DT == PTQ_F64 ? 1023 : 127;
+    const int field = (int)(largest >> kMantissa);
+    ups = field == 0 || field == 2 * kBias + 1 ? 0 : min(14 - (field - kBias) - (lg + 1) / 2, 1000);
+    if (seg == 0 && tid < run) a.exponents[token0 + tid] = -ups;
+    const uint32_t mine = (uint32_t)(a.order >> (16 * (lane & 3)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) from[q] = 4 * (lane & ~3) + ((mine >> (4 * q)) & 15);
+  }
+  for (int i = wave; i < items; i += kPrepWaves) {
+    const int tl = i & ((1 << run_lg) - 1), token = token0 + tl;
+    const Chunk ch = chunk_of(i);
+    const int4 p = next;
+    if (i + kPrepWaves < items) next = places(i + kPrepWaves);
+    if (tl >= run) continue;
+    const int c = ch.first + 4 * lane;
+    const bool live = c < ch.end;
+    const ST* buf = reinterpret_cast<const ST*>(prep_lds + tl * row);
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (c < ce) {
-      const int4 p = *reinterpret_cast<const int4*>(a.perm + c);
+    if (live) {
       v[0] = stored_to_f64<DT>(buf[p.x]);
       v[1] = stored_to_f64<DT>(buf[p.y]);
       v[2] = stored_to_f64<DT>(buf[p.z]);
       v[3] = stored_to_f64<DT>(buf[p.w]);
     }
-    if (!ident) {
-      fwht_chunk(v, lg, lane);
+    if (ch.rotated) fwht_chunk(v, lg, lane);
+    if (PIECES || ch.rotated) {
+      const double factor = ch.rotated ? a.scale : 1.0, unit = PIECES ? ldexp(factor, __builtin_amdgcn_readlane(ups, tl)) : factor;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] *= scale;
+      for (int q = 0; q < 4; ++q) v[q] *= unit;
     }
-    if (c < ce)   // c is a multiple of 4
-      *reinterpret_cast<float4*>(a.xt + ((int64_t)(c >> 5) * a.tokens + token) * kChunk + (c & 31)) =
-          make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+    // of the token's 128 bytes in each of the 32-column pieces c / 32; c is a multiple of 4
+    char* const base = reinterpret_cast<char*>(a.xt) + (int64_t)token * (kChunk * 4);
+    const uint32_t at = (uint32_t)(c >> 5) * ((uint32_t)a.tokens * (kChunk * 4));
+    if constexpr (!PIECES) {
+      if (live) *reinterpret_cast<float4*>(base + (at + 4 * (c & 31))) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+      continue;
+    }
+    uint32_t both[4];   // the second piece above the first
+#pragma unroll
+    for (int q = 0; q < 4; ++q) both[q] = split2(v[q]);
+    if (a.roomy) {   // a group of 16 columns is whole: b_I and n are multiples of 16
+      *reinterpret_cast<uint4*>(swap + 4 * lane) = make_uint4(both[0], both[1], both[2], both[3]);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) both[q] = swap[from[q]];
+      __builtin_amdgcn_wave_barrier();
+      if (live) {
+        char* dst = base + (at + 2 * (c & 31));
+        *reinterpret_cast<uint2*>(dst) = make_uint2(pair_low(both[0], both[1]), pair_low(both[2], both[3]));
+        *reinterpret_cast<uint2*>(dst + 2 * kChunk) = make_uint2(pair_high(both[0], both[1]), pair_high(both[2], both[3]));
+      }
+    } else if (live) {
+      for (int q = 0; q < 16; ++q) {
+        const int j = (int)(a.order >> (4 * q)) & 15;
+        if ((j >> 2) != (lane & 3)) continue;
+        const uint32_t w = (j & 2) ? ((j & 1) ? both[3] : both[2]) : ((j & 1) ? both[1] : both[0]);
+        uint16_t* dst = reinterpret_cast<uint16_t*>(base + at) + (c & 16) + q;
+        dst[0] = (uint16_t)w;
+        dst[kChunk] = (uint16_t)(w >> 16);
+      }
+    }
   }
 }
 
@@ -304,22 +524,32 @@ ptq_status launch_forward_prep(PrepArgs a, hipStream_t st) {
   const size_t row = (size_t)a.n * sizeof(ST);
   if (row > 160 * 1024) return PTQ_ERR_SHAPE;
   const int nchunk = (a.b_I + 255) / 256 + (a.n - a.b_I + 255) / 256;
-  a.coeff_tiles = (int)(a.tokens >= kPrepMany ? ceil_div(a.tokens, 2) * ceil_div(a.r, 16) : a.tokens * ceil_div(a.r, 4));
-  // every workgroup of a token stages its whole row: split it only as far as that fills the chip
+  const bool many = a.tokens >= kPrepMany;
+  a.coeff_tiles = (int)(many ? ceil_div(a.tokens, 16) * ceil_div(a.r, 16) * a.coeff_splits : a.tokens * ceil_div(a.r, 4));
+  // every workgroup of a token stages its whole row: split it only as far as that fills the chip.  Narrow rows of many
+  // tokens go several to a workgroup, until its waves have two chunks each.
   a.segments = (int)std::min<int64_t>(ceil_div(nchunk, kPrepWaves), ceil_div(256, a.tokens));
   a.segment = (int)ceil_div(nchunk, a.segments);
+  constexpr size_t extra = (kPrepWaves + (size_t)kPrepWaves * 256) * sizeof(uint32_t);   // behind the rows, with pieces
+  a.run_lg = 0;
+  while (a.run_lg < 3 && a.segments == 1 && (nchunk << a.run_lg) < 2 * kPrepWaves && a.tokens >> (a.run_lg + 1) >= 512 &&
+         2 * row << a.run_lg <= 32 * 1024)
+    ++a.run_lg;
+  const size_t rows = (size_t)align16((int)row) << a.run_lg;
+  a.roomy = rows + extra <= 160 * 1024;
   const auto off = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16; };
   const bool aligned = off(a.X) == 0 && (a.ldx * sizeof(ST)) % 16 == 0 && (a.r == 0 || (off(a.V) % 4 == 0 && off(a.s) == 0));
-  const size_t lds = std::max(row, (size_t)kPrepWaves * 32 * sizeof(double));
-  const unsigned grid = (unsigned)(a.coeff_tiles + (int64_t)a.tokens * a.segments);
-  if (aligned) {
-    if (!lds_opt_in<forward_prep_kernel<DT, true>>(160 * 1024)) return PTQ_ERR_HIP;
-    forward_prep_kernel<DT, true><<<grid, kPrepThreads, lds, st>>>(a);
-  } else {
-    if (!lds_opt_in<forward_prep_kernel<DT, false>>(160 * 1024)) return PTQ_ERR_HIP;
-    forward_prep_kernel<DT, false><<<grid, kPrepThreads, lds, st>>>(a);
-  }
-  return PTQ_OK;
+  const size_t coeff = many ? (size_t)kPrepWaves * 256 * sizeof(double) : (size_t)kPrepWaves * 4 * sizeof(double);
+  const size_t lds = std::max(a.order && a.roomy ? rows + extra : std::max(rows, row), a.r ? coeff : 0);
+  const unsigned grid = (unsigned)(a.coeff_tiles + ceil_div(a.tokens, (int64_t)1 << a.run_lg) * a.segments);
+  const auto launch = [&](auto is_aligned, auto pieces) {
+    constexpr auto kernel = forward_prep_kernel<DT, decltype(is_aligned)::value, decltype(pieces)::value>;
+    if (!lds_opt_in<kernel>(160 * 1024)) return PTQ_ERR_HIP;
+    kernel<<<grid, kPrepThreads, lds, st>>>(a);
+    return PTQ_OK;
+  };
+  if (a.order) return aligned ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
+  return aligned ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
 }
 
 struct ForwardArgs {
@@ -327,12 +557,16 @@ struct ForwardArgs {
   const float* scales;      // n / group x m
   const uint8_t* zeros;     // n / group x m
   int m, n, group;
-  const float* xt;          // X~, 32 columns of all tokens at a time: xt[chunk][token][32]
+  const float* xt;          // X~, 32 columns of all tokens at a time: xt[chunk][token][32], or two float16 pieces [2][32] in its place
   int xt_tokens;            // tokens per chunk of xt
   const float* y;           // tokens x r
+  const double* y_parts;    // null: y; else y_splits x tokens x r, to be added and multiplied by sigma
+  int y_splits;
+  const uint16_t* sigma;
   const uint8_t* U;         // r x m, e4m3
   int r;
-  float* partial;           // splits x tokens x m
+  const int* exponents;     // tokens: with pieces, X~ is 2^exponent times their sum
+  float* partial;           // (splits - 1) x tokens x m: the first split's sums go to O
   float* O;                 // tokens x m
   int64_t ldo;
 };
@@ -477,84 +711,112 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int co
   }
 }
 
-// ---- many tokens: bfloat16 matrix cores ----------------------------------------------------------
-// O = X~ Dequant^T as a GEMM whose operands are exact in bfloat16: code - zero is an integer of at most
-// eight bits, and a float32 x is the sum of its three truncated bfloat16 pieces (8 + 8 + 8 bits), so the
-// three products per weight are exact in float32 and only the float32 sums round -- as they do in the
-// float32 instruction, which has 1/16 of the rate (three pieces: 1/5.3 of the work).  The group's scale
-// is applied to the accumulators where a group ends.
+// ---- many tokens: 16-bit matrix cores -----------------------------------------------------------
+// O = X~ Dequant^T as a GEMM on the float16 matrix instruction.  code - zero is an integer of at most eight bits and a
+// sign: exact in float16.  X~ comes from float64 as the sum of two float16, each rounded to nearest, of a token's own power
+// of two: it is off by at most 2^-23 of itself, or 2^-35 of the token's largest |x| where that is more.  The products are exact
+// in float32 and only its sums round; with two of them per weight fewer do than with the three truncated bfloat16
+// pieces that hold a float32 exactly, and the distance from the float64 product is smaller everywhere it was measured
+// (512 to 11008 columns, groups of 64 and 128, 2 to 8 bits: 0.63 to 1.35e-7 of its norm, 0.65 to 1.50e-7 with three
+// pieces): the second pieces' products, 2^-11 of the others, go first.  The group's scale is applied to the
+// accumulators where a group ends, the token's power of two at the end.
 //
 // A workgroup takes 32 TT tokens x 128 RT rows of the weight, a wave 32 TT x 32 RT, and walks over chunks of
-// 32 columns.  The weight side never touches LDS: lane l of a wave is row l % 32, and half-wave h = l / 32
-// takes codes [16 h, 16 h + 16) of the chunk -- the contraction index may be dealt to the lanes in any
-// order that both operands share -- so its words come straight from memory and are widened in registers
-// (byte conversions, zero subtracted, high halves paired).  X~ lies chunk by chunk, so that the 32 columns of a
-// workgroup's tokens are one contiguous piece (row by row, the pieces of all tokens fall on the same few channels of
-// the L2); it is read as float32, split while it is staged, and read back as 16-byte fragments; rows of 80 bytes keep those reads free of bank conflicts.
-// One barrier per chunk: while chunk c is multiplied, chunk c + 1 is split into the other LDS half and
-// chunk c + 2 is on its way from memory.  RT = 2 sets the LDS traffic (six 1 KB reads per twelve MFMAs of a
-// wave: half of what the LDS delivers); 64 tokens per workgroup keep 256 registers, two waves per SIMD.
-// Bound: the bfloat16 MFMAs (and about nine vector instructions beside each).  The whole call with 16 ranks, against 32-token
-// passes on the float32 instruction and an input of two launches: 512 tokens x 4096 x 11008, 3 bits, 1131 -> 167 us;
-// 2048 x 11008 x 4096, 4 bits, 4045 -> 540; 4000 x 999 x 1024 2859 -> 65; 32 x 11008 x 4096 82 -> 44; 8 x 4096 x 4096
-// 39 -> 20; the distance
-// from the float64 product falls from 3.4e-7 to 1.3e-7 of its norm (no sum of code x and zero x of opposite sign).
+// 32 columns.  A lane of a wave is row l % 32, and half-wave h = l / 32 takes codes [16 h, 16 h + 16) of the chunk, in the
+// order in which they leave their words two at a time (code_order): the contraction index may be dealt out in any order that
+// both operands share, and the input's launch writes X~ in that one.  A pair costs an and-or and a packed multiply-add.
+// One barrier per chunk, in the middle of its MFMAs; what a chunk needs was requested four chunks before, straight into LDS.
+// Between two MFMAs a wave issues a pair or two of the next chunk's codes, a fragment read or a request, in the order
+// written down: 2 waves per SIMD, 64 tokens, at most 250 registers.
+// Bound: MFMA and what a wave issues beside it (16 MFMAs, about 65 other instructions and, every group, 128).
+// Kernel alone, 512 tokens x 4096 x 11008, 4 bits: 92 us (three bfloat16 pieces, split where they were staged: 150).
+// Whole calls with 16 ranks, three pieces -> now: 512 x 4096 x 11008 173 -> 121 us, 2048 x 11008 x 4096 580 -> 385,
+// 4000 x 999 x 1024 71 -> 50, 128 x 4096 x 4096 45 -> 38, 32 x 11008 x 4096 44 -> 28, 8 x 4096 x 4096 21 -> 18.7.
 template <int BITS> struct HalfWords { uint32_t w[BITS == 2 ? 1 : (BITS == 8 ? 4 : 2)]; };
 
+// two bfloat16 numbers from floats whose low halves are zero (or are to be dropped)
+__device__ __forceinline__ uint32_t pair_high(float a, float b) { return pair_high(__float_as_uint(a), __float_as_uint(b)); }
+
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// The order in which a lane's 16 codes of a half chunk leave the words that hold them, two at a time: codes 16 bits apart
+// (3 bits: after one shift) need one operation for the pair.  Position p holds code (order >> 4 p) & 15.
 template <int BITS>
-__device__ __forceinline__ HalfWords<BITS> load_half_chunk(const uint32_t* __restrict__ base, uint32_t row, int h) {
-  const uint32_t off = row + (uint32_t)h * (BITS == 2 || BITS == 3 ? 1u : (BITS == 4 ? 2u : 4u));
-  HalfWords<BITS> v;
-  if constexpr (BITS == 2) v.w[0] = base[off];
-  else if constexpr (BITS == 3) { v.w[0] = base[off]; v.w[1] = base[off + 1]; }   // bits [16 h, 16 h + 48) of these two words
-  else if constexpr (BITS == 4) { const uint2 q = *reinterpret_cast<const uint2*>(base + off); v.w[0] = q.x; v.w[1] = q.y; }
-  else { const uint4 q = *reinterpret_cast<const uint4*>(base + off); v.w[0] = q.x; v.w[1] = q.y; v.w[2] = q.z; v.w[3] = q.w; }
-  return v;
-}
-
-// high halves of two floats, the lower one first: two bfloat16 numbers where the low halves are zero
-__device__ __forceinline__ uint32_t pair_high(float a, float b) {
-  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
-}
-
-// codes [8 KS, 8 KS + 8) of a half chunk, minus the group's zero, as bfloat16
-template <int BITS, int KS>
-__device__ __forceinline__ bf16x8 widen_codes(const HalfWords<BITS>& v, int h, float zero) {
-  float f[8];
-  if constexpr (BITS == 8) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) f[j] = (float)((v.w[2 * KS + (j >> 2)] >> (8 * (j & 3))) & 0xffu);
-  } else if constexpr (BITS == 4) {
-    const uint32_t even = v.w[KS] & 0x0f0f0f0fu, odd = (v.w[KS] >> 4) & 0x0f0f0f0fu;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) f[j] = (float)((((j & 1) ? odd : even) >> (8 * (j >> 1))) & 0xffu);
-  } else if constexpr (BITS == 2) {
-    uint32_t t[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = (v.w[0] >> (16 * KS + 2 * i)) & 0x0303u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) f[j] = (float)((t[j & 3] >> (8 * (j >> 2))) & 0xffu);
-  } else {
-    const uint64_t s = (((uint64_t)v.w[1] << 32) | v.w[0]) >> (16 * h);
-    const uint32_t b = (uint32_t)(s >> (24 * KS));
-#pragma unroll
-    for (int j = 0; j < 8; ++j) f[j] = (float)((b >> (3 * j)) & 7u);
+constexpr uint64_t code_order() {
+  uint64_t o = 0;
+  for (int q = 0; q < 8; ++q) {
+    uint64_t a = 0, b = 0;
+    if (BITS == 2) { a = q; b = a + 8; }
+    else if (BITS == 3) { a = q < 5 ? q : q + 5; b = q < 5 ? q + 5 : q + 8; }
+    else if (BITS == 4) { a = (q & 3) + 8 * (q >> 2); b = a + 4; }
+    else { a = 2 * q; b = a + 1; }
+    o |= (a | b << 4) << (8 * q);
   }
-  uint4 o;
-  o.x = pair_high(f[0] - zero, f[1] - zero);
-  o.y = pair_high(f[2] - zero, f[3] - zero);
-  o.z = pair_high(f[4] - zero, f[5] - zero);
-  o.w = pair_high(f[6] - zero, f[7] - zero);
-  return __builtin_bit_cast(bf16x8, o);
+  return o;
 }
 
-// The three truncated bfloat16 pieces of two floats, paired.  KEEP_INF: an infinity is its first piece alone, so that its
-// products are those of the float32 (otherwise the others are NaN, and so is every sum that it enters).
-template <bool KEEP_INF>
+// Two codes at bit S of a word's halves, minus the zero, as float16: put into the mantissa of 1024 (unit 2^-S of it), then one
+// multiply-add; every value on the way is exact.  offset = -(2^(10 - S) + zero).
+template <int S, int BITS>
+__device__ __forceinline__ f16x2 code_pair(uint32_t w, uint32_t magic, f16x2 offset) {
+  constexpr uint32_t one = ((1u << BITS) - 1u) << S, both = one | one << 16;
+  const f16x2 v = __builtin_bit_cast(f16x2, (w & both) | magic);
+  if constexpr (S == 0) return v + offset;
+  constexpr _Float16 unit = (_Float16)(1.0f / (1 << S));
+  return __builtin_elementwise_fma(v, f16x2{unit, unit}, offset);
+}
+
+// a half chunk's words with codes 16 bits apart
+template <int BITS>
+__device__ __forceinline__ void align_codes(HalfWords<BITS>& v, int h) {
+  if constexpr (BITS == 3) {
+    const uint32_t top = v.w[1] >> (16 * h), low = __builtin_amdgcn_alignbit(v.w[1], v.w[0], 16 * h);   // 48 bits
+    const uint32_t r = __builtin_amdgcn_alignbit(top, low, 30);
+    v.w[0] = (low & 0x7fffu) | ((low << 1) & ~0x7fffu);   // codes 0 .. 4 and, from bit 16, 5 .. 9
+    v.w[1] = (r & 0x1ffu) | ((r << 7) & ~0x1ffu);         // codes 10 .. 12 and, from bit 16, 13 .. 15
+  }
+}
+
+// what a group's zero makes of the offsets of code_pair, for the places that codes take
+template <int BITS> struct Offsets { f16x2 o[BITS == 8 ? 1 : (BITS == 4 ? 2 : 3)]; };
+template <int BITS>
+__device__ __forceinline__ Offsets<BITS> code_offsets(uint32_t zero) {
+  constexpr int kStep = BITS == 3 ? 3 : (BITS == 4 ? 4 : 2), kCount = sizeof(Offsets<BITS>) / sizeof(f16x2);
+  const _Float16 z1 = (_Float16)(uint16_t)zero;
+  const f16x2 z = {z1, z1};
+  Offsets<BITS> out;
+#pragma unroll
+  for (int i = 0; i < kCount; ++i) {
+    const _Float16 base = (_Float16)(float)(1 << (10 - kStep * i));
+    out.o[i] = -(f16x2{base, base} + z);
+  }
+  return out;
+}
+
+// pair q of a half chunk's codes in their order, minus the zero
+template <int BITS, int Q>
+__device__ __forceinline__ f16x2 widen_pair(const HalfWords<BITS>& v, uint32_t magic, const Offsets<BITS>& o) {
+  if constexpr (BITS == 8) {   // bytes 2 (q % 2) and the next of a word, 0x64 above each
+    return __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(magic, v.w[Q >> 1], Q & 1 ? 0x05030502u : 0x05010500u)) + o.o[0];
+  } else if constexpr (BITS == 4) {
+    constexpr int k = Q >> 2, i = Q & 3;
+    return code_pair<4 * (i & 1), 4>(i & 2 ? v.w[k] >> 8 : v.w[k], magic, o.o[i & 1]);
+  } else if constexpr (BITS == 2) {
+    return code_pair<2 * (Q % 3), 2>(v.w[0] >> (6 * (Q / 3)), magic, o.o[Q % 3]);
+  } else if constexpr (Q < 5) {
+    return code_pair<3 * (Q % 3), 3>(v.w[0] >> (9 * (Q / 3)), magic, o.o[Q % 3]);
+  } else {
+    return code_pair<3 * (Q - 5), 3>(v.w[1], magic, o.o[Q - 5]);
+  }
+}
+
+// The three truncated bfloat16 pieces of two floats, paired.  An infinity is its first piece alone, so that its
+// products are those of the float32.
 __device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
   auto rest = [](float v) {
     const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
-    return KEEP_INF && __builtin_isinf(v) ? 0.f : r;
+    return __builtin_isinf(v) ? 0.f : r;
   };
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -564,19 +826,68 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
   }
 }
 
-// what the scheduler is asked for in a step: after each MFMA one fragment read, as long as there are any, and eight
-// vector instructions of the next chunk's preparation
-template <int MFMAS, int READS>
-__device__ __forceinline__ void tile_sched() {
-  if constexpr (MFMAS > 0) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if constexpr (READS > 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-    tile_sched<MFMAS - 1, (READS > 0 ? READS - 1 : 0)>();
-  }
+// What a chunk needs goes from memory straight into LDS (buffer_load ... lds), into a ring of kTileRing chunks for each
+// half of a workgroup: the tokens' rows of X~, 128 bytes each, [piece][32], whose 16-byte slot k lies at k ^ (token % 8), so that the
+// fragment reads of eight neighbouring lanes cover all banks; and, a wave's own 64 rows of the weight at a time, the
+// codes' words as they lie in memory, the scales and the zeros (a dword each).  These requests are issued by inline assembly
+// and waited for by count: the compiler would wait for all of them before each LDS read.
+constexpr int kTileRing = 4;
+constexpr int kTileRow = 2 * kChunk * (int)sizeof(uint16_t);
+constexpr int kYPitch = 40;   // bfloat16 elements per staged row of 32 ranks
+
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
+
+// 64 lanes x 16, 4 or 1 bytes from descriptor base + voff + soff to LDS address ldsaddr + 16 or 4 lane; lanes past the
+// descriptor's end deliver zeros
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int BYTES>
+__device__ __forceinline__ void request_to_lds(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t ldsaddr) {
+  if constexpr (BYTES == 16)
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+  else if constexpr (BYTES == 4)
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ubyte %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+template <int N>
+__device__ __forceinline__ void wait_requests() {   // until N requests to memory are on their way; other counters: no wait
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
 
-constexpr int kTilePitch = 40;   // bfloat16 elements per staged row of 32 columns
+// a buffer of `bytes` at p; p and bytes the same for a wave
+__device__ __forceinline__ i32x4 buffer_at(const void* p, int64_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  return i32x4{(int)__builtin_amdgcn_readfirstlane((uint32_t)a), (int)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
+               (int)__builtin_amdgcn_readfirstlane((uint32_t)(bytes > 0 ? bytes : 0)), 0x00020000};
+}
+__device__ __forceinline__ void buffer_advance(i32x4& b, uint64_t bytes) {
+  const uint64_t a = (((uint64_t)(uint32_t)b[1] << 32) | (uint32_t)b[0]) + bytes;
+  b[0] = (int)__builtin_amdgcn_readfirstlane((uint32_t)a);
+  b[1] = (int)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+}
+
+// LDS of one half of a workgroup, in bytes: rows of X~, words, scales, zeros
+template <int BITS, int TT>
+struct TileLds {
+  static constexpr int kX = 32 * TT * kTileRow, kW = 256 * 4 * BITS, kGrid = 256 * 4;   // of one chunk
+  static constexpr int w = kTileRing * kX, scale = w + kTileRing * kW, zero = scale + kTileRing * kGrid, all = zero + kTileRing * kGrid;
+};
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <class F, int... Is>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
+  (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 struct TilePlan {
   int token_blocks, row_blocks, splits, chunks_per_part;   // splits x KG parts
@@ -585,11 +896,11 @@ struct TilePlan {
 template <int BITS, int TT, int RT, int KG>
 __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a, int tokens, TilePlan plan) {
   constexpr int kTokens = 32 * TT, kRows = 128 * RT;
-  constexpr int E = TT == 1 ? 4 : 8;            // consecutive columns a thread stages: 256 E = 32 kTokens
-  __shared__ __attribute__((aligned(16))) uint16_t xs_all[KG][2][3][kTokens][kTilePitch];
+  using Lds = TileLds<BITS, TT>;
+  extern __shared__ __attribute__((aligned(16))) char tile_lds[];
+  typedef __attribute__((address_space(3))) char lds_char;
   const int part = KG == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
-  auto& xs = xs_all[part];
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5;
   const int m = a.m, chunks = a.n / kChunk, gpc = a.group / kChunk;
   // Consecutive items of one XCD (workgroup ids = x mod 8) share a split and neighbouring tiles
   const int total_items = plan.token_blocks * plan.row_blocks * plan.splits;
@@ -602,50 +913,94 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
   const int c_begin = min(chunks, (split * KG + part) * plan.chunks_per_part);
   const int c_end = min(chunks, c_begin + plan.chunks_per_part);
 
-  const int st_tok = tid / (32 / E), st_col = (tid % (32 / E)) * E;
-  const int tok_src = min(tb * kTokens + st_tok, tokens - 1);   // rows past the last token repeat it; not stored
-  // per lane: 32-bit offsets that never change; per chunk: one scalar base each
-  const uint32_t x_off = (uint32_t)(tok_src - tb * kTokens) * kChunk + (uint32_t)st_col;
-  const float* x_base = a.xt + (int64_t)tb * kTokens * kChunk;
+  static_assert(RT == 2, "a wave's rows are 64: a request's lanes");
   uint32_t row[RT];   // within the workgroup's rows; rows past the last one repeat it, not stored
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
     row[rt] = (uint32_t)min((wave * RT + rt) * 32 + (lane & 31), m - 1 - rb * kRows);
-  const uint32_t* packed = a.packed + (int64_t)rb * kRows * BITS;
-  const float* scales = a.scales + (int64_t)rb * kRows;
-  const uint8_t* zeros = a.zeros + (int64_t)rb * kRows;
   const uint8_t* u_codes = a.U + (int64_t)rb * kRows;
 
-  struct Raw { float x[E]; HalfWords<BITS> w[RT]; float scale[RT]; uint8_t zero[RT]; };
-  auto request = [&](Raw& r, int c) {
-    c = min(c, c_end - 1);   // issued whatever c: no branch
-    const float* xp = x_base + (int64_t)c * a.xt_tokens * kChunk;
+  const int exponent = a.exponents[min(tb * kTokens + lane, tokens - 1)];   // a token's per lane
+
+  // Batch j of requests: X~ of chunk j (counted from c_begin), words and grids of chunk j + 1.  What lies past the part's
+  // end is its last chunk again.
+  const int count = max(c_end - c_begin, 1);                  // chunks that can be asked for
+  const int c_first = min(c_begin, chunks - 1);
+  const int row0 = rb * kRows + wave * 64, rows_left = min(max(m - row0, 0), 64);
+  const int row_at = min(row0, m - 1);                        // a base inside the arrays
+  const uint32_t x_step = (uint32_t)(a.xt_tokens * kTileRow);
+  const uint64_t w_step = (uint64_t)m * (4 * BITS);
+  const i32x4 x_src = buffer_at(reinterpret_cast<const char*>(a.xt) + (int64_t)tb * kTokens * kTileRow,
+                                ((int64_t)chunks * a.xt_tokens - tb * kTokens) * kTileRow);
+  i32x4 w_src = buffer_at(a.packed + ((int64_t)c_first * m + row_at) * BITS, rows_left * (4 * BITS));
+  i32x4 scale_src = buffer_at(a.scales + (int64_t)(c_first / gpc) * m + row_at, rows_left * 4);
+  i32x4 zero_src = buffer_at(a.zeros + (int64_t)(c_first / gpc) * m + row_at, rows_left);
+  uint32_t x_at_chunk = (uint32_t)c_first * x_step;
+  int x_count = 1, w_count = 1, w_left = gpc - c_first % gpc;
+  uint32_t x_off[TT];
 #pragma unroll
-    for (int i = 0; i < E; i += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(xp + x_off + i);
-      r.x[i] = v.x; r.x[i + 1] = v.y; r.x[i + 2] = v.z; r.x[i + 3] = v.w;
-    }
-    const int64_t g = c / gpc;
-    const uint32_t* wp = packed + (int64_t)c * m * BITS;
-    const float* sp = scales + g * m;
-    const uint8_t* zp = zeros + g * m;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      r.w[rt] = load_half_chunk<BITS>(wp, row[rt] * BITS, h);
-      r.scale[rt] = sp[row[rt]];
-      r.zero[rt] = zp[row[rt]];
+  for (int i = 0; i < TT; ++i) {   // 8 tokens a request; tokens past the last repeat it, not stored
+    const int t = (wave * TT + i) * 8 + (lane >> 3);
+    x_off[i] = (uint32_t)(min(t, tokens - 1 - tb * kTokens) * kTileRow + (((lane & 7) ^ (lane >> 3)) << 4));
+  }
+  const uint32_t lane4 = (uint32_t)lane * 4, lane16 = (uint32_t)lane * 16;
+  const int part_at = part * Lds::all;
+  const uint32_t lbase = (uint32_t)(uintptr_t)(lds_char*)tile_lds + (uint32_t)part_at;
+  const uint32_t x_dst = lbase + (uint32_t)(wave * TT * 1024), w_dst = lbase + (uint32_t)(Lds::w + wave * (256 * BITS)),
+                 grid_dst = lbase + (uint32_t)(Lds::scale + wave * 256);
+  constexpr int kWide = BITS % 4 == 0 ? 16 : 4, kWordRequests = 256 * BITS / (64 * kWide);
+  constexpr int kBatch = TT + kWordRequests + 2;
+  // A request of a batch, the words last.  words: where they go, relative to the ring
+  auto request = [&](auto index, auto slot_x, auto slot_grid, uint32_t words) {
+    constexpr int I = decltype(index)::value, S = decltype(slot_grid)::value;
+    if constexpr (I < TT) {
+      request_to_lds<16>(x_src, x_off[I], x_at_chunk, x_dst + decltype(slot_x)::value * Lds::kX + I * 1024);
+    } else if constexpr (I == TT) {
+      request_to_lds<4>(scale_src, lane4, 0, grid_dst + S * Lds::kGrid);
+    } else if constexpr (I == TT + 1) {
+      request_to_lds<1>(zero_src, (uint32_t)lane, 0, grid_dst + (Lds::zero - Lds::scale) + S * Lds::kGrid);
+    } else {
+      constexpr int k = I - TT - 2;
+      request_to_lds<kWide>(w_src, (kWide == 16 ? lane16 : lane4) + k * 64 * kWide, 0, w_dst + words + k * 64 * kWide);
     }
   };
-  auto stage_x = [&](auto keep_inf, const float (&x)[E], int buf) {
-    uint32_t p[E / 2][3];
+  auto advance_x = [&]() {
+    if (x_count < count) x_at_chunk += x_step;
+    ++x_count;
+  };
+  auto advance_w = [&]() {
+    const bool more = w_count < count;
+    buffer_advance(w_src, more ? w_step : 0);
+    const bool next_group = more && --w_left == 0;
+    buffer_advance(scale_src, next_group ? 4u * (uint32_t)m : 0u);
+    buffer_advance(zero_src, next_group ? (uint32_t)m : 0u);
+    if (next_group) w_left = gpc;
+    ++w_count;
+  };
+
+  // what is read back: fragments of X~ (piece p, step ks: its place in a token's row), words, scales and zeros
+  uint32_t x_at[2][2];
 #pragma unroll
-    for (int i = 0; i < E / 2; ++i) split3<decltype(keep_inf)::value>(x[2 * i], x[2 * i + 1], p[i]);
+  for (int p = 0; p < 2; ++p)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      uint16_t* dst = &xs[buf][k][st_tok][st_col];
-      if constexpr (E == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(p[0][k], p[1][k], p[2][k], p[3][k]);
-      else *reinterpret_cast<uint2*>(dst) = make_uint2(p[0][k], p[1][k]);
-    }
+    for (int ks = 0; ks < 2; ++ks)
+      x_at[p][ks] = (uint32_t)(part_at + (lane & 31) * kTileRow + (((4 * p + 2 * h + ks) ^ (lane & 7)) << 4));
+  const uint32_t w_at = (uint32_t)(part_at + Lds::w + wave * (256 * BITS) + (lane & 31) * (4 * BITS) + h * (BITS <= 3 ? 4 : 2 * BITS));
+  const uint32_t grid_at = (uint32_t)(part_at + Lds::scale + wave * 256 + (lane & 31) * 4);
+  auto lds_at = [&](uint32_t at) { return (const lds_char*)tile_lds + at; };
+  auto lds_word = [&](uint32_t at) { return *(const __attribute__((address_space(3))) uint32_t*)lds_at(at); };
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  struct Raw { HalfWords<BITS> w[RT]; float scale[RT]; uint32_t zero[RT]; };
+  auto read_raw = [&](Raw& r, auto slot_, uint32_t words, auto rt_) {
+    constexpr int slot = decltype(slot_)::value, rt = decltype(rt_)::value;
+    const uint32_t at = w_at + words + rt * 32 * (4 * BITS);
+    if constexpr (BITS == 2) r.w[rt].w[0] = lds_word(at);
+    else if constexpr (BITS == 3) { r.w[rt].w[0] = lds_word(at); r.w[rt].w[1] = lds_word(at + 4); }
+    else if constexpr (BITS == 4) { const u32x2 q = *(const __attribute__((address_space(3))) u32x2*)lds_at(at); r.w[rt].w[0] = q.x; r.w[rt].w[1] = q.y; }
+    else { const u32x4 q = *(const __attribute__((address_space(3))) u32x4*)lds_at(at); r.w[rt].w[0] = q.x; r.w[rt].w[1] = q.y; r.w[rt].w[2] = q.z; r.w[rt].w[3] = q.w; }
+    r.scale[rt] = __uint_as_float(lds_word(grid_at + slot * Lds::kGrid + rt * 128));
+    r.zero[rt] = lds_word(grid_at + (Lds::zero - Lds::scale) + slot * Lds::kGrid + rt * 128);
   };
 
   f32x16 acc[TT][RT], total[TT][RT];
@@ -656,19 +1011,6 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
 #pragma unroll
       for (int r = 0; r < 16; ++r) { acc[tt][rt][r] = 0.f; total[tt][rt][r] = 0.f; }
 
-  auto multiply = [&](const bf16x8 (&b)[2][RT], int buf) {
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int p = 2; p >= 0; --p)   // the smallest piece first
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-          const bf16x8 av = *reinterpret_cast<const bf16x8*>(&xs[buf][p][tt * 32 + (lane & 31)][16 * h + 8 * ks]);
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            acc[tt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b[ks][rt], acc[tt][rt], 0, 0, 0);
-        }
-  };
   auto flush = [&](const float (&sc)[RT]) {
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
@@ -681,87 +1023,216 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
         }
   };
 
+  constexpr int kHalf = 2 * TT * RT;   // MFMAs of one piece
   Raw raw[2];
-  bf16x8 b[2][2][RT];
-  float sc[2][RT];
-  auto prepare = [&](const Raw& r, int c, int buf, bf16x8 (&bb)[2][RT], float (&s)[RT]) {
-    const uint32_t live = c < c_end ? 0xffffffffu : 0u;   // a step past the end multiplies by zero
-    float x[E];
-#pragma unroll
-    for (int i = 0; i < E; ++i) x[i] = __uint_as_float(__float_as_uint(r.x[i]) & live);
-    // (an infinite x makes all outputs of its token NaN either way: a row's sum of zero x, were it 0 x, is NaN)
-    stage_x(std::false_type{}, x, buf);
+  f16x8 fr[2][2][TT];    // [piece][16 columns]
+  struct Codes { f16x2 pair[RT][8]; float scale[RT]; } codes[2];
+  uint32_t magic = 0x64006400u;
+  asm volatile("" : "+v"(magic));   // in a vector register, so that mask and 1024 go into one instruction
+  Offsets<BITS> off[RT];
+  auto start_codes = [&](Raw& r, Codes& to) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      const float z = (float)r.zero[rt];
-      bb[0][rt] = widen_codes<BITS, 0>(r.w[rt], h, z);
-      bb[1][rt] = widen_codes<BITS, 1>(r.w[rt], h, z);
-      s[rt] = r.scale[rt];
+      off[rt] = code_offsets<BITS>(r.zero[rt]);
+      align_codes<BITS>(r.w[rt], h);
+      to.scale[rt] = r.scale[rt];
     }
   };
-  request(raw[0], c_begin);
-  request(raw[1], c_begin + 1);
-  prepare(raw[0], c_begin, 0, b[0], sc[0]);
-  int left = gpc - c_begin % gpc;   // chunks until the group ends
-  auto step = [&](auto parity, int c) {
-    constexpr int P = decltype(parity)::value;
-    __syncthreads();
-    request(raw[P], c + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(b[P], P);
-    prepare(raw[P ^ 1], c + 1, P ^ 1, b[P ^ 1], sc[P ^ 1]);
-    // the next chunk's conversions go between this chunk's MFMAs, not after them: kept from sinking past the branch
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(b[P ^ 1][0][rt]), "+v"(b[P ^ 1][1][rt]));
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-    tile_sched<6 * TT * RT, 6 * TT - 4>();
-    if (--left == 0) { flush(sc[P]); left = gpc; }
+  auto widen = [&](Raw& r, Codes& to, auto index) {   // pair by pair, index < 8 RT
+    constexpr int I = decltype(index)::value, q = I / RT, rt = I % RT;
+    to.pair[rt][q] = widen_pair<BITS, q>(r.w[rt], magic, off[rt]);
+    uint32_t bits = __builtin_bit_cast(uint32_t, to.pair[rt][q]);
+    asm volatile("" : "+v"(bits));   // here, not where the next step uses it
+    to.pair[rt][q] = __builtin_bit_cast(f16x2, bits);
   };
-  for (int c = c_begin; c < c_begin + plan.chunks_per_part; c += 2) {   // the same count for all waves
-    step(std::integral_constant<int, 0>{}, c);
-    step(std::integral_constant<int, 1>{}, c + 1);
+  auto read_x = [&](auto slot_, auto piece, auto index) {   // index < 2 TT
+    constexpr int p = decltype(piece)::value, ks = decltype(index)::value / TT, tt = decltype(index)::value % TT;
+    fr[p][ks][tt] = *(const __attribute__((address_space(3))) f16x8*)lds_at(x_at[p][ks] + decltype(slot_)::value * Lds::kX + tt * 32 * kTileRow);
+  };
+  auto mfma = [&](const Codes& b, auto piece, auto index) {   // index < kHalf
+    constexpr int I = decltype(index)::value, p = decltype(piece)::value;
+    constexpr int ks = I / (TT * RT), tt = I / RT % TT, rt = I % RT;
+    struct Quad { f16x2 e[4]; };
+    const f16x8 bv = __builtin_bit_cast(f16x8, Quad{{b.pair[rt][4 * ks], b.pair[rt][4 * ks + 1], b.pair[rt][4 * ks + 2], b.pair[rt][4 * ks + 3]}});
+    acc[tt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[p][ks][tt], bv, acc[tt][rt], 0, 0, 0);
+  };
+  using std::integral_constant;
+  typedef integral_constant<int, 0> Zero;
+  typedef integral_constant<int, 1> One;
+
+  // chunk 0's words and grids, batches 0 and 1; when those words are read, batches 2 and 3
+  auto batch = [&](auto index, auto from) {
+    constexpr int J = decltype(index)::value, F = decltype(from)::value;
+    static_for<kBatch - F>([&](auto k) {
+      request(integral_constant<int, F + decltype(k)::value>{}, integral_constant<int, (J < 0 ? 0 : J)>{},
+              integral_constant<int, (J + 1) % kTileRing>{}, (J + 1) % kTileRing * Lds::kW);
+    });
+    if constexpr (J >= 0) advance_x();
+    advance_w();
+  };
+  batch(integral_constant<int, -1>{}, integral_constant<int, TT>{});
+  batch(Zero{}, Zero{});
+  batch(One{}, Zero{});
+  wait_requests<kBatch>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  static_for<RT>([&](auto rt) { read_raw(raw[0], Zero{}, 0u, rt); });
+  static_for<RT>([&](auto rt) { read_raw(raw[1], One{}, (uint32_t)Lds::kW, rt); });
+  static_for<2 * TT>([&](auto k) { read_x(Zero{}, One{}, k); });
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  batch(integral_constant<int, 2>{}, Zero{});
+  batch(integral_constant<int, 3>{}, Zero{});
+  start_codes(raw[0], codes[0]);
+  static_for<8 * RT>([&](auto k) { widen(raw[0], codes[0], k); });
+
+  // Step j: the MFMAs of chunk j's second pieces (the smaller ones first) | barrier | those of the first.  At the barrier every wave has read
+  // all it needs of chunk j's rows and of chunk j + 1's words, whose places batch j + 4 takes, and batch j + 1 has
+  // landed: the newest requests are those of batches j + 2 and j + 3.  Beside the MFMAs, chunk j + 1's codes are widened and
+  // what comes next is read from LDS, in the order written down here (a step is one basic block; left to the
+  // scheduler, the MFMAs follow each other and the vector instructions follow them).
+  int left = gpc - c_begin % gpc;   // chunks until the group ends
+  auto step = [&](auto slot_, int c) {
+    constexpr int Q = decltype(slot_)::value, P = Q & 1;
+    typedef integral_constant<int, Q> Here;
+    typedef integral_constant<int, (Q + 1) % kTileRing> Next;
+    typedef integral_constant<int, (Q + 2) % kTileRing> After;
+    constexpr int kPairs = 8 * RT / (2 * kHalf);   // widened per MFMA
+    start_codes(raw[P ^ 1], codes[P ^ 1]);
+    static_for<kHalf>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      mfma(codes[P], One{}, i_);
+      if constexpr (i < 2 * TT) read_x(Here{}, Zero{}, i_);
+      static_for<kPairs>([&](auto k) { widen(raw[P ^ 1], codes[P ^ 1], integral_constant<int, kPairs * i + decltype(k)::value>{}); });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wait_requests<(kTileRing - 2) * kBatch>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<kHalf>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      mfma(codes[P], Zero{}, i_);
+      if constexpr (i < 2 * TT) read_x(Next{}, One{}, i_);
+      if constexpr (i < RT) read_raw(raw[P], After{}, After::value * Lds::kW, i_);
+      static_for<kPairs>([&](auto k) { widen(raw[P ^ 1], codes[P ^ 1], integral_constant<int, kPairs * (kHalf + i) + decltype(k)::value>{}); });
+      static_for<(kBatch + kHalf - 1) / kHalf>([&](auto k) {
+        constexpr int r = i * ((kBatch + kHalf - 1) / kHalf) + decltype(k)::value;
+        if constexpr (r < kBatch) request(integral_constant<int, r>{}, Here{}, Next{}, Next::value * Lds::kW);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    advance_x();
+    advance_w();
+    if (c < c_end && (--left == 0 || c + 1 == c_end)) { flush(codes[P].scale); left = gpc; }   // the same for a wave
+  };
+  // the same count for all waves; past c_end a part adds what is never used
+  int c = c_begin;
+  const int stop = c_begin + plan.chunks_per_part;
+  for (; c + kTileRing <= stop; c += kTileRing) {
+    step(integral_constant<int, 0>{}, c);
+    step(integral_constant<int, 1>{}, c + 1);
+    step(integral_constant<int, 2>{}, c + 2);
+    step(integral_constant<int, 3>{}, c + 3);
   }
-  flush(sc[1]);   // what is left of the last chunk's group
+  if (c < stop) {
+    step(integral_constant<int, 0>{}, c);
+    if (c + 1 < stop) {
+      step(integral_constant<int, 1>{}, c + 1);
+      if (c + 2 < stop) step(integral_constant<int, 2>{}, c + 2);
+    }
+  }
+  wait_requests<0>();
+  __syncthreads();   // the ring's space is used for other things from here on
+
+  // back from the pieces' unit: accumulator r of a lane is token (r / 4) * 8 + (lane / 32) * 4 + r % 4 of its tile
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int e = __shfl(exponent, tt * 32 + (r >> 2) * 8 + h * 4 + (r & 3));
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) total[tt][rt][r] = ldexpf(total[tt][rt][r], e);
+    }
 
   // The low-rank part, once: coefficients y (tokens x r) against the e4m3 codes of U, 32 ranks at a time; e4m3
-  // is exact in bfloat16, y goes through the same three pieces.
+  // is exact in bfloat16, y goes through three pieces of it (exact in float32, and their range is its range).
   if (a.r > 0 && split == plan.splits - 1) {
+    constexpr int E = TT == 1 ? 4 : 8;   // consecutive ranks a thread stages: 256 E = 32 kTokens
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[tt][rt][r] = 0.f;
+    auto ys = reinterpret_cast<uint16_t(*)[kTokens][kYPitch]>(tile_lds) + 3 * part;
+    const int y_tok = tid / (32 / E), y_col = (tid % (32 / E)) * E;
+    const int64_t y_row = (int64_t)min(tb * kTokens + y_tok, tokens - 1) * a.r;
 #pragma unroll 1
     for (int k0 = 32 * part; k0 < a.r + 32 * part; k0 += 32 * KG) {   // the same count for all waves
       float yv[E];
 #pragma unroll
       for (int i = 0; i < E; ++i) {
-        const int k = k0 + st_col + i;
-        const float v = a.y[(int64_t)tok_src * a.r + min(k, a.r - 1)];
-        yv[i] = k < a.r ? v : 0.f;
+        const int k = min(k0 + y_col + i, a.r - 1);
+        float v;
+        if (a.y_parts) {
+          double part[kCoeffSplits], sum = 0.0;
+#pragma unroll
+          for (int q = 0; q < kCoeffSplits; ++q)   // issued whatever the split: no wait between them
+            part[q] = a.y_parts[(int64_t)min(q, a.y_splits - 1) * tokens * a.r + y_row + k];
+#pragma unroll
+          for (int q = 0; q < kCoeffSplits; ++q) sum += q < a.y_splits ? part[q] : 0.0;
+          v = (float)(sum * (double)fp16_bits_to_float(a.sigma[k]));
+        } else {
+          v = a.y[y_row + k];
+        }
+        yv[i] = k0 + y_col + i < a.r ? v : 0.f;
       }
       __syncthreads();
-      stage_x(std::true_type{}, yv, 0);   // a coefficient past the float32 range makes its products infinite
+#pragma unroll
+      for (int i = 0; i < E; i += 4) {
+        uint32_t lo[3], hi[3];   // a coefficient past the float32 range makes its products infinite
+        split3(yv[i], yv[i + 1], lo);
+        split3(yv[i + 2], yv[i + 3], hi);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(&ys[k][y_tok][y_col + i]) = make_uint2(lo[k], hi[k]);
+      }
+      bf16x8 u[2][RT];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          float u[8];
+          float f[8];
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const int k = k0 + 16 * h + 8 * ks + j;
             const float v = e4m3_to_float(u_codes[(int64_t)min(k, a.r - 1) * m + row[rt]]);
-            u[j] = k < a.r ? v : 0.f;
+            f[j] = k < a.r ? v : 0.f;
           }
-          const uint4 o = make_uint4(pair_high(u[0], u[1]), pair_high(u[2], u[3]), pair_high(u[4], u[5]), pair_high(u[6], u[7]));
-          b[0][ks][rt] = __builtin_bit_cast(bf16x8, o);
+          const uint4 o = make_uint4(pair_high(f[0], f[1]), pair_high(f[2], f[3]), pair_high(f[4], f[5]), pair_high(f[6], f[7]));
+          u[ks][rt] = __builtin_bit_cast(bf16x8, o);
         }
       __syncthreads();
-      multiply(b[0], 0);
-    }
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) sc[0][rt] = 1.f;
-    flush(sc[0]);
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int p = 2; p >= 0; --p)   // the smallest piece first
+#pragma unroll
+          for (int tt = 0; tt < TT; ++tt) {
+            const bf16x8 av = *reinterpret_cast<const bf16x8*>(&ys[p][tt * 32 + (lane & 31)][16 * h + 8 * ks]);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              acc[tt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, u[ks][rt], acc[tt][rt], 0, 0, 0);
+          }
+    }
+    const float one[RT] = {1.f, 1.f};
+    flush(one);
   }
 
   if constexpr (KG > 1) {   // the second part's sums go to the first through LDS, a tile at a time
-    static_assert(KG == 2 && sizeof(xs_all) >= 256 * 16 * sizeof(float), "the exchange reuses the staging area");
-    float* ex = reinterpret_cast<float*>(&xs_all[0][0][0][0][0]) + tid;
+    static_assert(KG == 2, "");
+    float* ex = reinterpret_cast<float*>(tile_lds) + tid;
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
@@ -780,9 +1251,8 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
     if (part != 0) return;
   }
 
-  // accumulator r of a lane is token (r / 4) * 8 + (lane / 32) * 4 + r % 4 of its tile, row lane % 32
-  const bool direct = plan.splits == 1;
-  float* out = direct ? a.O : a.partial + (int64_t)split * tokens * m;
+  const bool direct = split == 0;
+  float* out = direct ? a.O : a.partial + (int64_t)(split - 1) * tokens * m;
   const int64_t ld = direct ? a.ldo : m;
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
@@ -798,26 +1268,26 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
   }
 }
 
-// O[t][row] = sum over the column splits, in order (the last split holds the low-rank part)
+// O[t][row] = sum over the column splits, in order: the first is in O, the last holds the low-rank part
 __global__ __launch_bounds__(256) void forward_tile_finish_kernel(ForwardArgs a, int tokens, int splits) {
   const int row = blockIdx.x * 256 + threadIdx.x;
   const int t0 = blockIdx.y * 4;
   if (row >= a.m) return;
-  float out[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int sp0 = 0; sp0 < splits; sp0 += 8) {
+  float out[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) out[t] = a.O[(int64_t)min(t0 + t, tokens - 1) * a.ldo + row];
+  const int more = splits - 1;
+  for (int sp0 = 0; sp0 < more; sp0 += 8) {
     float v[8][4];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int sp = sp0 + k < splits ? sp0 + k : splits - 1;   // issued whatever sp: no branch, no wait
-        const int tt = t0 + t < tokens ? t0 + t : tokens - 1;
-        v[k][t] = a.partial[((int64_t)sp * tokens + tt) * a.m + row];
-      }
+      for (int t = 0; t < 4; ++t)   // issued whatever the split: no branch, no wait
+        v[k][t] = a.partial[((int64_t)min(sp0 + k, more - 1) * tokens + min(t0 + t, tokens - 1)) * a.m + row];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) out[t] += sp0 + k < splits ? v[k][t] : 0.f;
+      for (int t = 0; t < 4; ++t) out[t] += sp0 + k < more ? v[k][t] : 0.f;
   }
 #pragma unroll
   for (int t = 0; t < 4; ++t)
@@ -828,42 +1298,44 @@ constexpr int kFwdRun = 8;            // chunks: the least a column split keeps
 constexpr int kPartialTokens = 32;   // the workspace holds partial sums of 32 tokens for every run of 256 columns
 
 template <int BITS, int TT, int KG>
-void launch_forward_tile_as(const ForwardArgs& a, int tokens, TilePlan p, hipStream_t st) {
+ptq_status launch_forward_tile_as(const ForwardArgs& a, int tokens, TilePlan p, hipStream_t st) {
   const int chunks = a.n / kChunk;
   p.chunks_per_part = (int)ceil_div(chunks, p.splits * KG);
   p.splits = (int)ceil_div(chunks, (int64_t)p.chunks_per_part * KG);
   const unsigned grid = 8u * (unsigned)ceil_div((int64_t)p.token_blocks * p.row_blocks * p.splits, 8);
-  forward_tile_kernel<BITS, TT, 2, KG><<<grid, 256 * KG, 0, st>>>(a, tokens, p);
+  constexpr int ring = KG * TileLds<BITS, TT>::all, ys = KG * 3 * 32 * TT * kYPitch * (int)sizeof(uint16_t);
+  constexpr int lds = std::max(std::max(ring, ys), KG > 1 ? 256 * 16 * (int)sizeof(float) : 0);
+  if (!lds_opt_in<forward_tile_kernel<BITS, TT, 2, KG>>(lds)) return PTQ_ERR_HIP;
+  forward_tile_kernel<BITS, TT, 2, KG><<<grid, 256 * KG, lds, st>>>(a, tokens, p);
   if (p.splits > 1) {
     dim3 gf((unsigned)ceil_div(a.m, 256), (unsigned)ceil_div(tokens, 4));
     forward_tile_finish_kernel<<<gf, 256, 0, st>>>(a, tokens, p.splits);
   }
+  return PTQ_OK;
 }
 
 template <int BITS>
-void launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st) {
+ptq_status launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st) {
   const int chunks = a.n / kChunk;
   const int TT = tokens <= 32 ? 1 : 2;
   TilePlan p{};
   p.token_blocks = (int)ceil_div(tokens, 32 * TT);
   p.row_blocks = (int)ceil_div(a.m, 256);
   const int64_t tiles = (int64_t)p.token_blocks * p.row_blocks;
-  // Two waves per SIMD hide each other's loads (one alone waits out about a microsecond per chunk): where the tiles
-  // alone give every compute unit two workgroups the columns stay whole; otherwise a workgroup's two halves take half of
-  // its columns each (whole call, 16 ranks, 4 bits: 512 tokens x 4096 x 11008 162 us, 177 without; 4000 x 999 x 1024 65 and
-  // 68; not at 32 tokens or fewer: 32 x 11008 x 4096 44 and 37, 24 x 11008 x 11008 66 and 54, 8 x 4096 x 4096 19.8 and 19.4),
-  // and the columns are split over workgroups until every compute unit has one, as far as the partial sums fit the
-  // workspace and a part keeps eight chunks.  Up to 32 tokens the codes' stream is the bound and twice as many
-  // workgroups keep more of it in flight (24 x 11008 x 11008 78 -> 66 us, 32 x 11008 x 4096 47 -> 44; 4 x 4096 x 8192
-  // loses, 25 -> 29).
+  // Two waves per SIMD hide each other's waits: where the tiles alone give every compute unit two workgroups the columns
+  // stay whole; otherwise a workgroup's two halves take half of its columns each (64 tokens a tile: 512 x 4096 x 11008, 4 bits, 162
+  // us and 177 without, with the bfloat16 pieces), and the columns are split over workgroups until every compute unit has
+  // one, as far as the partial sums fit the workspace and a part keeps eight chunks.  Up to 32 tokens the codes' stream is
+  // the bound and twice as many workgroups, without halves, keep more of it in flight (whole call, 16 ranks: 32 x 11008 x 4096
+  // 27.5 us, 31.6 with halves; 8 x 4096 x 4096 18.7 and 19.5; 5 x 777 x 512 16.1 and 16.8).
   const bool many = tiles >= 512;
   int64_t s = many ? 1 : ceil_div(TT == 1 ? 512 : 256, tiles);
   s = std::min<int64_t>(s, ceil_div(chunks, kFwdRun) * kPartialTokens / tokens);
   s = std::max<int64_t>(1, std::min<int64_t>(s, chunks / kFwdRun));
   p.splits = (int)s;
-  const bool halves = !many && chunks / s >= 2;
-  if (TT == 1) halves ? launch_forward_tile_as<BITS, 1, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 1, 1>(a, tokens, p, st);
-  else halves ? launch_forward_tile_as<BITS, 2, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 2, 1>(a, tokens, p, st);
+  const bool halves = TT == 2 && !many && chunks / s >= 2;
+  if (TT == 1) return halves ? launch_forward_tile_as<BITS, 1, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 1, 1>(a, tokens, p, st);
+  return halves ? launch_forward_tile_as<BITS, 2, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 2, 1>(a, tokens, p, st);
 }
 
 template <int BITS, int B, int R>
@@ -881,16 +1353,14 @@ ptq_status launch_forward_rows(const ForwardArgs& a, hipStream_t st) {
   return a.m > 2048 ? launch_forward_rows_as<BITS, B, 16>(a, st) : launch_forward_rows_as<BITS, B, 8>(a, st);
 }
 
-// One or two tokens always, three or four while their X~ lets two workgroups share a compute unit, go row by row
-// (whole call, 4 bits, 16 ranks: 2 x 11008 x 8192 39 us, 54 as tiles; 3 x 11008 x 4096 20.0 and 33.3; 4 x 4096 x 4096
-// 18.9 and 19.8; beyond that line 4 x 11008 x 5632 56.3 and 40.5, 4 x 4096 x 8192 32.7 and 29.3, and, three tokens just past
-// it, 3 x 11008 x 5632 35.3 and 39.2, 3 x 4096 x 8192 26.5 and 29.3); all others take the tiles.
+// One token always, up to four while X~ has at most 16384 values go row by row (whole call, 4 bits, 16 ranks, rows and
+// tiles: 2 x 4096 x 4096 14.2 and 18.1 us, 2 x 11008 x 11008 69 and 37, 3 x 11008 x 4096 20.5 and 22.7, 3 x 4096 x 8192 30 and 23,
+// 4 x 11008 x 2048 15.5 and 19.1; on the line 2 x 4096 x 8192 22.1 and 22.9, 4 x 4096 x 4096 19.3 and 17.9).
+bool takes_tiles(int64_t tokens, int64_t n) { return tokens > 1 && (tokens > 4 || tokens * n > 16384); }
+
 template <int BITS>
 ptq_status launch_forward(const ForwardArgs& a, int tokens, hipStream_t st) {
-  if (tokens > 2 && (tokens > 4 || (int64_t)tokens * a.n > 16384)) {
-    launch_forward_tile<BITS>(a, tokens, st);
-    return PTQ_OK;
-  }
+  if (takes_tiles(tokens, a.n)) return launch_forward_tile<BITS>(a, tokens, st);
   switch (tokens) {
     case 1: return launch_forward_rows<BITS, 1>(a, st);
     case 2: return launch_forward_rows<BITS, 2>(a, st);
@@ -936,6 +1406,8 @@ static size_t forward_partial_bytes(int64_t m, int64_t n) {
   return align_up((size_t)ceil_div(n / kChunk, kFwdRun) * kPartialTokens * (size_t)m * sizeof(float), 256);
 }
 
+static size_t forward_tail_bytes(int64_t m) { return align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256); }
+
 // ---- scratch for callers that cannot allocate -----------------------------------------------
 // One array per GPU, part of the library's code object: the device memory the forward call needs
 // beyond its inputs and outputs (the rotated input, the low-rank coefficients, the partial sums of
@@ -963,7 +1435,7 @@ ptq_status linear_forward_static_scratch(void** ptr) {
 size_t linear_forward_workspace_bytes(int64_t tokens, int64_t m, int64_t n, int64_t r) {
   return align_up((size_t)tokens * n * sizeof(float), 256) +
          align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256) + forward_partial_bytes(m, n) +
-         align_up((size_t)ceil_div(m, 256) * sizeof(unsigned), 256);   // no kernel uses these: which sizes fit the static array is part of the contract
+         forward_tail_bytes(m);   // which sizes fit the static array is part of the contract
 }
 
 ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int64_t tokens, int64_t m, int64_t n,
@@ -976,24 +1448,51 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
   float* y = reinterpret_cast<float*>(reinterpret_cast<char*>(xt) + align_up((size_t)tokens * n * sizeof(float), 256));
   float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(y) +
                                             align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256));
-  const PrepArgs prep{X, ldx, (int)tokens, (int)n, perm, b_I, b_H, V, sigma, s, r, xt, y, 0, 0, 0};
-  ptq_status rc;
-  switch (xdt) {
-    case PTQ_F32: rc = launch_forward_prep<PTQ_F32>(prep, st); break;
-    case PTQ_BF16: rc = launch_forward_prep<PTQ_BF16>(prep, st); break;
-    case PTQ_F64: rc = launch_forward_prep<PTQ_F64>(prep, st); break;
-    default: return PTQ_ERR_DTYPE;
+  // behind the partial sums, which leave a split's room: the tokens' exponents, where X~ is in pieces.  A layer of
+  // a few rows and more tokens than its workspace has exponents for goes by runs of tokens.
+  const size_t behind = forward_partial_bytes(m, n) + forward_tail_bytes(m);
+  int64_t run = tokens;
+  int* exponents = nullptr;
+  const bool pieces = takes_tiles(tokens, n);
+  if (pieces) {
+    run = std::min<int64_t>(tokens, (int64_t)(behind / sizeof(int)));
+    exponents = reinterpret_cast<int*>(reinterpret_cast<char*>(partial) + behind) - run;
   }
-  if (rc != PTQ_OK) return rc;
-  ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, (int)tokens, y, U, r, partial, O, ldo};
-  switch (bits) {
-    case 2: rc = launch_forward<2>(a, (int)tokens, st); break;
-    case 3: rc = launch_forward<3>(a, (int)tokens, st); break;
-    case 4: rc = launch_forward<4>(a, (int)tokens, st); break;
-    case 8: rc = launch_forward<8>(a, (int)tokens, st); break;
-    default: return PTQ_ERR_ARG;
+  for (int64_t t0 = 0; t0 < tokens; t0 += run) {
+    const int part = (int)std::min(run, tokens - t0);
+    const char* x0 = static_cast<const char*>(X) + t0 * ldx * (xdt == PTQ_F64 ? 8 : (xdt == PTQ_F32 ? 4 : 2));
+    const bool tiles = pieces && takes_tiles(part, n);
+    PrepArgs prep{x0, ldx, part, (int)n, perm, b_I, b_H, V, sigma, s, r, xt, y, nullptr, 0, 1, 0, 1, 1, 0, exponents, false, 0, 1.0 / std::sqrt((double)b_H)};
+    while (1 << prep.lg < b_H) ++prep.lg;
+    // the coefficients of many tokens, where the room that the partial sums leave (a split's) holds them: by several workgroups
+    if (tiles && r > 0 && part >= kPrepMany) {
+      const int64_t wanted = std::min<int64_t>(std::min<int64_t>(n / 1024, kCoeffSplits), 128 / (ceil_div(part, 16) * ceil_div(r, 16)));
+      const int64_t held = ceil_div(n / kChunk, kFwdRun) * kPartialTokens;   // tokens times splits
+      const int64_t free = (int64_t)behind - std::max<int64_t>(held / part - 1, 0) * part * m * 4;
+      const int64_t room = part == tokens ? (free - part * 4 - 8) / (part * r * 8) : 0;
+      prep.coeff_splits = (int)std::max<int64_t>(1, std::min(wanted, room));
+      if (prep.coeff_splits > 1)
+        prep.y_parts = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(exponents) & ~(uintptr_t)7)) - (int64_t)prep.coeff_splits * part * r;
+    }
+    if (tiles) prep.order = bits == 2 ? code_order<2>() : (bits == 3 ? code_order<3>() : (bits == 4 ? code_order<4>() : code_order<8>()));
+    ptq_status rc;
+    switch (xdt) {
+      case PTQ_F32: rc = launch_forward_prep<PTQ_F32>(prep, st); break;
+      case PTQ_BF16: rc = launch_forward_prep<PTQ_BF16>(prep, st); break;
+      case PTQ_F64: rc = launch_forward_prep<PTQ_F64>(prep, st); break;
+      default: return PTQ_ERR_DTYPE;
+    }
+    if (rc != PTQ_OK) return rc;
+    ForwardArgs a{packed, scales, zeros, (int)m, (int)n, group, xt, part, y, prep.y_parts, prep.coeff_splits, sigma, U, r, exponents, partial, O + t0 * ldo, ldo};
+    switch (bits) {
+      case 2: rc = launch_forward<2>(a, part, st); break;
+      case 3: rc = launch_forward<3>(a, part, st); break;
+      case 4: rc = launch_forward<4>(a, part, st); break;
+      case 8: rc = launch_forward<8>(a, part, st); break;
+      default: return PTQ_ERR_ARG;
+    }
+    if (rc != PTQ_OK) return rc;
   }
-  if (rc != PTQ_OK) return rc;
   PTQ_HIP_CHECK_LAUNCH();
   return PTQ_OK;
 }
