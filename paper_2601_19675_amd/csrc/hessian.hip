@@ -491,31 +491,38 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
   const int il0 = wi * 128 + low * 64 + (lane >> 5) * 4, jl0 = (NB == 2 ? 128 * half_tile : 0) + wj * 32 * NB + (lane & 31);
   const int rows = SHARED && (wave == 1 || wave == 2) ? 2 : 4;   // MFMA tile rows of this wave
   if constexpr (DIRECT) {
-    // The only split: straight into H, eight rows at a time across all of the wave's columns, all loads of a step on
-    // their way together (a load under a condition would wait for the one before: 69 us instead of 29 for a call of 32
-    // tokens at n = 4096).
+    // The only split: straight into H, 16 entries of a lane at a time (8 or 4 rows of an MFMA tile across all of the wave's
+    // columns) while the next 16 are on their way; entries outside the matrix or below the diagonal are loaded from some valid
+    // place and not stored (a load under a condition would wait for the one before).  With each 16 waiting for their own
+    // loads a workgroup pays the way to memory 8 or 16 times: calls of 2048 tokens n = 4096 54 -> 51 us, n = 8192 224 -> 182,
+    // n = 11008 405 -> 350.  32 entries at a time spill.
+    constexpr int kRows = 16 / NB, kSteps = 64 / kRows;
+    double v[2][kRows][NB];
+    auto load = [&](auto step) {
+      constexpr int S = decltype(step)::value, a = S * kRows / 16, r0 = S * kRows % 16;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      if (a >= rows) break;
+      for (int r = 0; r < kRows; ++r)
 #pragma unroll
-      for (int r0 = 0; r0 < 16; r0 += 4) {
-        double v[4][NB];
+        for (int b = 0; b < NB; ++b) {
+          const int i = I * kBT + il0 + 32 * a + ((r0 + r) >> 2) * 8 + (r & 3), j = J * kBT + jl0 + 32 * b;
+          v[S & 1][r][b] = H[(int64_t)min(i, n - 1) * ldh + min(j, n - 1)];
+        }
+    };
+    load(std::integral_constant<int, 0>{});
+    static_for<kSteps>([&](auto step) {
+      constexpr int S = decltype(step)::value, a = S * kRows / 16, r0 = S * kRows % 16;
+      if (a >= rows) return;
+      if constexpr (S + 1 < kSteps) load(std::integral_constant<int, S + 1>{});
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+      for (int r = 0; r < kRows; ++r)
 #pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const int i = I * kBT + il0 + 32 * a + 2 * r0 + r, j = J * kBT + jl0 + 32 * b;
-            v[r][b] = H[(int64_t)min(i, n - 1) * ldh + min(j, n - 1)];   // issued whatever (i, j): no branch, no wait
-          }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const int i = I * kBT + il0 + 32 * a + 2 * r0 + r, j = J * kBT + jl0 + 32 * b;
-            if (j < n && i <= j) H[(int64_t)i * ldh + j] = v[r][b] + (double)acc[a][b][r0 + r];
-          }
-      }
-    }
+        for (int b = 0; b < NB; ++b) {
+          const int i = I * kBT + il0 + 32 * a + ((r0 + r) >> 2) * 8 + (r & 3), j = J * kBT + jl0 + 32 * b;
+          if (j < n && i <= j) H[(int64_t)i * ldh + j] = v[S & 1][r][b] + (double)acc[a][b][r0 + r];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    });
     return;
   }
 #pragma unroll
@@ -575,8 +582,8 @@ __device__ __forceinline__ void tile_in_locality_order(int r, int ntb, int& I, i
 // quarters of its operands pass through the LDS for half the MFMAs), so the split into halves is taken where it
 // saves rounds of 256 workgroups.
 // DIRECT: one split, added to H without a partial tile.  Bound: H's float64 update, 16 bytes per entry.
-// Call of 2048 tokens, partial tiles and whole tiles before: n = 4096 90.1 -> 53.6 us, n = 5376 111 -> 86,
-// n = 8192 325 -> 218, n = 11008 564 -> 399; n = 2048, seven splits either way, 40.0 and 40.7.
+// Call of 2048 tokens, partial tiles and whole tiles before: n = 4096 90.1 -> 51 us, n = 5376 111 -> 83,
+// n = 8192 325 -> 182, n = 11008 564 -> 350; n = 2048, seven splits either way, 40.0 and 40.7.
 template <bool HALVES, bool SHARED, bool DIRECT>
 __global__ __launch_bounds__(256) void hessian_bf16_big_kernel(const uint16_t* __restrict__ X, int64_t ldx,
                                                                int64_t t, int n, int64_t tok0, int chunk,
