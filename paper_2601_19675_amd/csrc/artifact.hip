@@ -827,13 +827,15 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
 }
 
 // What a chunk needs goes from memory straight into LDS (buffer_load ... lds), into a ring of kTileRing chunks for each
-// half of a workgroup: the tokens' rows of X~, 128 bytes each, [piece][32], whose 16-byte slot k lies at k ^ (token % 8), so that the
-// fragment reads of eight neighbouring lanes cover all banks; and, a wave's own 64 rows of the weight at a time, the
-// codes' words as they lie in memory, the scales and the zeros (a dword each).  These requests are issued by inline assembly
+// half of a workgroup: the tokens' rows of X~, 128 bytes each, [piece][32], whose 16-byte slot k lies at k ^ (token / 2 % 8), so
+// that the fragment reads of sixteen neighbouring lanes cover the 64 banks; and, a wave's own 64 rows of the weight at a time,
+// the codes' words as they lie in memory, the scales and the zeros (a dword each).  These requests are issued by inline assembly
 // and waited for by count: the compiler would wait for all of them before each LDS read.
 constexpr int kTileRing = 4;
 constexpr int kTileRow = 2 * kChunk * (int)sizeof(uint16_t);
 constexpr int kYPitch = 40;   // bfloat16 elements per staged row of 32 ranks
+
+__device__ __forceinline__ int tile_key(int token) { return (token >> 1) & 7; }
 
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 
@@ -941,7 +943,7 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
 #pragma unroll
   for (int i = 0; i < TT; ++i) {   // 8 tokens a request; tokens past the last repeat it, not stored
     const int t = (wave * TT + i) * 8 + (lane >> 3);
-    x_off[i] = (uint32_t)(min(t, tokens - 1 - tb * kTokens) * kTileRow + (((lane & 7) ^ (lane >> 3)) << 4));
+    x_off[i] = (uint32_t)(min(t, tokens - 1 - tb * kTokens) * kTileRow + (((lane & 7) ^ tile_key(t)) << 4));
   }
   const uint32_t lane4 = (uint32_t)lane * 4, lane16 = (uint32_t)lane * 16;
   const int part_at = part * Lds::all;
@@ -984,7 +986,7 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
   for (int p = 0; p < 2; ++p)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
-      x_at[p][ks] = (uint32_t)(part_at + (lane & 31) * kTileRow + (((4 * p + 2 * h + ks) ^ (lane & 7)) << 4));
+      x_at[p][ks] = (uint32_t)(part_at + (lane & 31) * kTileRow + (((4 * p + 2 * h + ks) ^ tile_key(lane & 31)) << 4));
   const uint32_t w_at = (uint32_t)(part_at + Lds::w + wave * (256 * BITS) + (lane & 31) * (4 * BITS) + h * (BITS <= 3 ? 4 : 2 * BITS));
   const uint32_t grid_at = (uint32_t)(part_at + Lds::scale + wave * 256 + (lane & 31) * 4);
   auto lds_at = [&](uint32_t at) { return (const lds_char*)tile_lds + at; };
