@@ -18,6 +18,7 @@
 #include "dgemm.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace ptq {
 namespace {
@@ -125,6 +126,31 @@ struct SplitArgs {
   int mp, np;
   double* partial;     // [2][tiles]: the tile sums of tr(D H D^T), then those of tr(W H W^T)
 };
+
+constexpr int kWideM = 256;   // rows of a tile of the wide form
+constexpr int64_t kWideFrom = 384;   // tiles
+constexpr int kSlab = 16;            // rows of tiles that are worked on together; a multiple of 8
+
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
+
+// 64 lanes x 16 bytes from descriptor base + voff + soff to LDS address ldsaddr + 16 lane; lanes past the end deliver zeros
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void request_to_lds(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t ldsaddr) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <class F, int... Is>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
+  (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 // D and W as bfloat16 pieces, four consecutive k per thread
 template <int DT, int P>
@@ -374,6 +400,206 @@ __global__ __launch_bounds__(256) void quad_form_split_kernel(SplitArgs a) {
   }
 }
 
+// The same products in tiles of 256 x 128 for layers that have enough of them: eight waves, two per SIMD, 64 x 64 each.
+// The pieces go from memory straight into LDS (buffer_load ... lds, inline assembly, waited for by count: the
+// compiler would wait for all of them before each LDS read), two k-tiles of 32, rows of 64 bytes whose 16-byte slot s lies at
+// s ^ (row / 4 % 4): the fragment reads of sixteen neighbouring lanes cover the 64 banks.  Step j: the first 16
+// k of tile j | barrier | the others; at the barrier every wave has read tile j, whose place tile j + 2 takes, and tile
+// j + 1 has landed.  What goes between the MFMAs is written down in order.  A workgroup of the 128 x 128 kernel has one wave per
+// SIMD, which waits out the barrier, the first fragments and the LDS stores of each k-tile by itself.
+// Bound: MFMA (five piece products of 11008 x 4096 in about 770 us: 1.2 PFLOP/s; the 128 x 128 kernel 1091).
+template <int ND, int NW, int NH>
+__global__ __launch_bounds__(512, 2) void quad_form_wide_kernel(SplitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char wide_lds[];
+  __shared__ double red[2][8];
+  typedef __attribute__((address_space(3))) char lds_char;
+  constexpr int NA = ND + NW, kRow = 64, kPieceA = kWideM * kRow, kPieceB = kT * kRow, kStage = NA * kPieceA + NH * kPieceB;
+  constexpr int kRequestsA = NA * kWideM / 16, kRequests = kRequestsA + NH * kT / 16, kOwn = kRequests / 8;   // of 16 rows
+  static_assert(kRequests % 8 == 0, "the same number for each wave");
+  // Up to kSlab rows of tiles at a time, the widest column tiles first: the 256 workgroups in flight walk along k together
+  // and read 16 strips of D and W and 16 of Hu (all rows of tiles at a time, 43 strips and 6: 1348 us for 11008 x 4096 instead of
+  // 967).  Sixteen or eight rows put a strip on one XCD (workgroup ids = x mod 8) and its L2; fifteen do not:
+  // 1262 us.  What is left over comes first, so that the narrow tiles of many rows are the last to start (2504 x 6971 with
+  // its last two rows of tiles at the end: 894 us).
+  const int rts = (a.mp + kWideM - 1) / kWideM, cts = a.np / kT;
+  int row = 0, height = rts % 8 ? rts % 8 : (rts % kSlab ? rts % kSlab : kSlab), at = blockIdx.x;
+  while (at >= height * cts) {
+    at -= height * cts;
+    row += height;
+    height = (rts - row) % kSlab ? 8 : kSlab;
+  }
+  const int rt = row + at % height, ct = cts - 1 - at / height;
+  const int i0 = rt * kWideM, j0 = ct * kT;
+  const int ktiles = (j0 + kT) / kSK;   // beyond them Hu is zero; a multiple of four
+  const int lane = threadIdx.x & 63, wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int64_t planeA = (int64_t)a.mp * a.np, planeB = (int64_t)a.np * a.np;
+  const uint16_t* first = NW == 0 && blockIdx.z ? a.W : a.D;
+
+  // a wave's requests: 16 rows of a piece each; rows past mp deliver zeros
+  const uint32_t lbase = (uint32_t)(uintptr_t)(lds_char*)wide_lds;
+  const uint32_t voff = (uint32_t)((lane >> 2) * a.np * 2 + (((lane & 3) ^ (lane >> 4)) << 4));
+  i32x4 src[kOwn];
+  uint32_t dst[kOwn];
+#pragma unroll
+  for (int r = 0; r < kOwn; ++r) {
+    const int q = wave * kOwn + r;
+    const bool is_a = q < kRequestsA;
+    const int p = is_a ? q / (kWideM / 16) : (q - kRequestsA) / (kT / 16);
+    const int row = (is_a ? q % (kWideM / 16) : (q - kRequestsA) % (kT / 16)) * 16;
+    const uint16_t* plane = is_a ? (p < ND ? first + p * planeA : a.W + (p - ND) * planeA) : a.HuT + p * planeB;
+    const int at = is_a ? i0 + row : j0 + row;
+    const bool there = !is_a || at < a.mp;
+    const uint64_t base = (uint64_t)(plane + (int64_t)(there ? at : 0) * a.np);
+    src[r] = i32x4{(int)__builtin_amdgcn_readfirstlane((uint32_t)base), (int)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)),
+                   (int)__builtin_amdgcn_readfirstlane(there ? (uint32_t)a.np * 32u : 0u), 0x00020000};
+    dst[r] = (uint32_t)__builtin_amdgcn_readfirstlane(lbase + (is_a ? p * kPieceA : NA * kPieceA + p * kPieceB) + row * kRow);
+  }
+  auto request = [&](auto r_, auto stage_, int tile) {
+    constexpr int r = decltype(r_)::value;
+    request_to_lds(src[r], voff, (uint32_t)min(tile, ktiles - 1) * (kSK * 2), dst[r] + decltype(stage_)::value * kStage);
+  };
+
+  f32x16 acc[1 + (NW > 0)][2][2];
+#pragma unroll
+  for (int f = 0; f < 1 + (NW > 0); ++f)
+#pragma unroll
+    for (int tm = 0; tm < 2; ++tm)
+#pragma unroll
+      for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[f][tm][tn][r] = 0.f;
+
+  // fragment of a 32-row strip: lane l holds row l % 32, k = 8 (l / 32) .. + 7 of the 16-wide k-step
+  uint32_t at_a[2][2], at_b[2][2];   // [stage][k-step]
+#pragma unroll
+  for (int st = 0; st < 2; ++st)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const uint32_t in_row = (uint32_t)((lane & 31) * kRow + (((2 * ks + (lane >> 5)) ^ ((lane >> 2) & 3)) << 4));
+      at_a[st][ks] = st * kStage + wm * 64 * kRow + in_row;
+      at_b[st][ks] = st * kStage + NA * kPieceA + wn * 64 * kRow + in_row;
+      asm volatile("" : "+v"(at_a[st][ks]), "+v"(at_b[st][ks]));   // kept, not formed again before every read
+    }
+  constexpr int kReads = 2 * (NA + NH);
+  bf16x8 fa[2][NA][2], fb[2][NH][2];   // [k-step][piece][strip]
+  auto read = [&](auto stage_, auto ks_, auto index) {   // in the order of their first use: the last pieces of Hu and the first of D
+    constexpr int ks = decltype(ks_)::value, st = decltype(stage_)::value, t = decltype(index)::value & 1, k = decltype(index)::value >> 1;
+    if constexpr (k < NH) {
+      constexpr int p = NH - 1 - k;
+      fb[ks][p][t] = *(const __attribute__((address_space(3))) bf16x8*)((const lds_char*)wide_lds + (at_b[st][ks] + p * kPieceB + t * 32 * kRow));
+    } else {
+      constexpr int p = k - NH;
+      fa[ks][p][t] = *(const __attribute__((address_space(3))) bf16x8*)((const lds_char*)wide_lds + (at_a[st][ks] + p * kPieceA + t * 32 * kRow));
+    }
+  };
+  // piece pa of an operand with piece pb of Hu for pa + pb < NH, the smallest products first; MFMA I of a k-step
+  constexpr int kFull = NH * (NH + 1) / 2, kProducts = kFull + (NW == 0 ? 0 : (NW == 1 ? NH : kFull)), kMfma = 4 * kProducts;
+  static_assert(NW <= 1 && ND == NH, "");
+  auto mfma = [&](auto ks_, auto index) {
+    constexpr int ks = decltype(ks_)::value, I = decltype(index)::value;
+    constexpr auto product = [](int want) constexpr {   // order, piece of A
+      int n = 0;
+      for (int order = NH - 1; order >= 0; --order)
+        for (int p = 0; p < NA; ++p) {
+          const int pa = p < ND ? p : p - ND, pb = order - pa;
+          if (pb < 0 || pb >= NH) continue;
+          if (n++ == want) return p * 16 + pb;
+        }
+      return -1;
+    };
+    constexpr int code = product(I / 4), p = code / 16, pb = code % 16, f = p >= ND ? 1 : 0, tm = I >> 1 & 1, tn = I & 1;
+    static_assert(code >= 0, "");
+    acc[f][tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][p][tm], fb[ks][pb][tn], acc[f][tm][tn], 0, 0, 0);
+  };
+  using std::integral_constant;
+  typedef integral_constant<int, 0> Zero;
+  typedef integral_constant<int, 1> One;
+  // per MFMA of a half at most one fragment read and, in the second half, one request
+  static_assert(kReads <= kMfma && kOwn <= kMfma, "");
+  auto step = [&](auto stage_, int tile) {
+    constexpr int S = decltype(stage_)::value;
+    typedef integral_constant<int, S ^ 1> Other;
+    static_for<kMfma>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      mfma(Zero{}, i_);
+      if constexpr (i < kReads) read(stage_, One{}, i_);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): tile + 1, requested a step ago
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<kMfma>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      mfma(One{}, i_);
+      if constexpr (i < kReads) read(Other{}, Zero{}, i_);
+      if constexpr (i < kOwn) request(i_, stage_, tile + 2);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  static_for<kOwn>([&](auto r) { request(r, Zero{}, 0); });
+  static_for<kOwn>([&](auto r) { request(r, One{}, 1); });
+  __builtin_amdgcn_s_waitcnt((kOwn & 15) | ((kOwn >> 4) << 14) | 0x0f70);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  static_for<kReads>([&](auto i) { read(Zero{}, Zero{}, i); });
+  for (int tile = 0; tile < ktiles; tile += 2) {
+    step(Zero{}, tile);
+    step(One{}, tile + 1);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // nothing may still be landing in LDS when the workgroup ends
+
+  // sum_ij A_ij T_ij of the tile in float64; accumulator r of a lane is row (r / 4) * 8 + (lane / 32) * 4 + r % 4,
+  // column lane % 32 of its 32 x 32 tile; rows and columns beyond m x n hold zeros, rows beyond mp are not there
+  double sums[1 + (NW > 0)];
+#pragma unroll
+  for (int f = 0; f < 1 + (NW > 0); ++f) {
+    const uint16_t* P = f == 1 ? a.W : first;
+    constexpr int kMost = ND;
+    const int np_ = f == 1 ? NW : ND;
+    sums[f] = 0.0;
+    if (i0 + wm * 64 < a.mp) {
+#pragma unroll
+      for (int tm = 0; tm < 2; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < 2; ++tn) {
+          uint16_t v[16][kMost];
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int p = 0; p < kMost; ++p) {
+              const int i = wm * 64 + tm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+              const int j = wn * 64 + tn * 32 + (lane & 31);
+              v[r][p] = p < np_ ? P[p * planeA + (int64_t)(i0 + i) * a.np + j0 + j] : (uint16_t)0;
+            }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            double x = (double)bf16_val(v[r][0]);
+#pragma unroll
+            for (int p = 1; p < kMost; ++p) x += (double)bf16_val(v[r][p]);
+            sums[f] = fma((double)acc[f][tm][tn][r], x, sums[f]);
+          }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sums[f] += __shfl_xor(sums[f], off);
+    if (lane == 0) red[f][wave] = sums[f];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int64_t tile = (int64_t)rt * cts + ct, tiles = (int64_t)rts * cts;
+#pragma unroll
+    for (int f = 0; f < 1 + (NW > 0); ++f) {
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) sum += red[f][w];
+      a.partial[(f == 1 || blockIdx.z ? tiles : 0) + tile] = sum;
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void finish_kernel(const double* __restrict__ partial, int tiles,
                                                      double* out) {
   __shared__ double red[2][256];
@@ -429,6 +655,15 @@ size_t layer_error_workspace_bytes(int64_t m, int64_t n) {
 }
 
 template <int ND, int NW, int NH>
+static bool launch_wide(const SplitArgs& a, hipStream_t st) {
+  constexpr int lds = 2 * ((ND + NW) * kWideM + NH * kT) * 64;
+  if (!lds_opt_in<quad_form_wide_kernel<ND, NW, NH>>(lds)) return false;
+  const dim3 g((unsigned)(ceil_div(a.mp, kWideM) * (a.np / kT)), 1, NW == 0 ? 2u : 1u);
+  quad_form_wide_kernel<ND, NW, NH><<<g, 512, lds, st>>>(a);
+  return true;
+}
+
+template <int ND, int NW, int NH>
 static bool launch_split(const SplitArgs& a, hipStream_t st) {
   const int lds = 2 * (ND + NW + NH) * kT * kSP * (int)sizeof(uint16_t);
   if (!lds_opt_in<quad_form_split_kernel<ND, NW, NH>>(lds)) return false;
@@ -447,8 +682,14 @@ static ptq_status launch_split_form(const void* W, ptq_dtype wdt, int64_t ldw, c
   uint16_t* HuT = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(Wp) + pieces_bytes(mp, np));
   const unsigned ga = (unsigned)ceil_div(mp * np / 4, 256);
   const dim3 gh((unsigned)(np / 32), (unsigned)(np / 32));
-  const int tiles = (int)((mp / kT) * (np / kT));
+  int tiles = (int)((mp / kT) * (np / kT));
   SplitArgs a{Dp, Wp, HuT, (int)mp, (int)np, partial};
+  // 256 x 128 tiles where they fill the chip one and a half times and little of them lies past the last row (whole call, 128 x 128
+  // and 256 x 128: bfloat16 11008 x 4096 1187 and 967 us, 4096 x 4096 429 and 384, 1100 x 6000 (235 tiles) 312 and 406;
+  // float32 4096 x 11008 3548 and 3091, 1100 x 6000 403 and 387, 2048 x 2048 (256) 91 and 100, 300 x 11008 (344) 660 and 752)
+  const int64_t wide_tiles = ceil_div(mp, kWideM) * (np / kT);
+  const bool wide = m * n >= kTwoPiecesFrom && wide_tiles * (wdt == PTQ_BF16 ? 1 : 2) >= kWideFrom && (mp % kWideM == 0 || mp > 4 * kWideM);
+  if (wide) tiles = (int)wide_tiles;
   auto run = [&](auto pieces) -> bool {
     constexpr int P = decltype(pieces)::value;
     if (wdt == PTQ_F32)
@@ -456,6 +697,9 @@ static ptq_status launch_split_form(const void* W, ptq_dtype wdt, int64_t ldw, c
     else
       split_weights_kernel<PTQ_BF16, P><<<ga, 256, 0, st>>>(W, ldw, Wq, (int)m, (int)n, (int)mp, (int)np, Dp, Wp);
     split_hu_kernel<P><<<gh, 256, 0, st>>>(H, ldh, (int)n, (int)np, HuT);
+    if constexpr (P == 2) {
+      if (wide) return wdt == PTQ_BF16 ? launch_wide<P, 1, P>(a, st) : launch_wide<P, 0, P>(a, st);
+    }
     if (wdt == PTQ_BF16) return launch_split<P, 1, P>(a, st);
     return launch_split<P, 0, P>(a, st);   // both traces in one launch (float32 512 x 512: 38.4 us for the call as two, now 24.8; 320 x 2856 148 and 87)
   };
