@@ -615,6 +615,9 @@ template <int BITS, int B, int R>
 __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int columns, int items) {
   extern __shared__ __attribute__((aligned(16))) float row_lds[];
   constexpr int S = 256 / R;
+  // all arguments at once, not one after the other where they are used
+  asm volatile("" ::"s"(a.packed), "s"(a.scales), "s"(a.zeros), "s"(a.m), "s"(a.n), "s"(a.group), "s"(a.xt), "s"(a.xt_tokens), "s"(a.y),
+               "s"(a.U), "s"(a.r), "s"(a.O), "s"(a.ldo), "s"(columns), "s"(items));
   const int per = (items + 7) / 8;   // consecutive items on one XCD: neighbouring rows share cache lines
   const int q = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= per || q >= items) return;
