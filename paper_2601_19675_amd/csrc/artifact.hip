@@ -153,7 +153,7 @@ struct PrepArgs {
   int64_t ldx;
   int tokens, n;
   const int32_t* perm;
-  int b_I, b_H;
+  int b_I;
   const uint8_t* V;
   const uint16_t* sigma;
   const double* s;
@@ -733,8 +733,8 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int co
 // written down: 2 waves per SIMD, 64 tokens, at most 250 registers.
 // Bound: MFMA and what a wave issues beside it (16 MFMAs, about 65 other instructions and, every group, 128).
 // Kernel alone, 512 tokens x 4096 x 11008, 4 bits: 92 us (three bfloat16 pieces, split where they were staged: 150).
-// Whole calls with 16 ranks, three pieces -> now: 512 x 4096 x 11008 173 -> 121 us, 2048 x 11008 x 4096 580 -> 385,
-// 4000 x 999 x 1024 71 -> 50, 128 x 4096 x 4096 45 -> 38, 32 x 11008 x 4096 44 -> 28, 8 x 4096 x 4096 21 -> 18.7.
+// Whole calls with 16 ranks, three pieces -> now: 512 x 4096 x 11008 171 -> 119 us, 2048 x 11008 x 4096 564 -> 363,
+// 4000 x 999 x 1024 71 -> 50, 128 x 4096 x 4096 45 -> 37, 32 x 11008 x 4096 45 -> 28, 8 x 4096 x 4096 21 -> 18.4.
 template <int BITS> struct HalfWords { uint32_t w[BITS == 2 ? 1 : (BITS == 8 ? 4 : 2)]; };
 
 // two bfloat16 numbers from floats whose low halves are zero (or are to be dropped)
@@ -1467,7 +1467,7 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
     const int part = (int)std::min(run, tokens - t0);
     const char* x0 = static_cast<const char*>(X) + t0 * ldx * (xdt == PTQ_F64 ? 8 : (xdt == PTQ_F32 ? 4 : 2));
     const bool tiles = pieces && takes_tiles(part, n);
-    PrepArgs prep{x0, ldx, part, (int)n, perm, b_I, b_H, V, sigma, s, r, xt, y, nullptr, 0, 1, 0, 1, 1, 0, exponents, false, 0, 1.0 / std::sqrt((double)b_H)};
+    PrepArgs prep{x0, ldx, part, (int)n, perm, b_I, V, sigma, s, r, xt, y, nullptr, 0, 1, 0, 1, 1, 0, exponents, false, 0, 1.0 / std::sqrt((double)b_H)};
     while (1 << prep.lg < b_H) ++prep.lg;
     // the coefficients of many tokens, where the room that the partial sums leave (a split's) holds them: by several workgroups
     if (tiles && r > 0 && part >= kPrepMany) {
