@@ -67,6 +67,73 @@ def check_dpp_wait_states(asm_text: str) -> int:
     return seen
 
 
+def check_lds_dma_wait_states(asm_text: str) -> int:
+    """lds_dma.h issues its loads into LDS from inline assembly, where the compiler does not count wait states: such a
+    load needs one after a scalar instruction wrote m0.  Walks the generated assembly back from every such load, into all predecessors at a label, and raises if
+    something stands closer.  Returns the number of loads seen."""
+    import re
+
+    lines = [l.split(";")[0].strip() for l in asm_text.splitlines()]
+    lines = [l for l in lines if l and (not l.startswith(".") or re.match(r"\.\w+:$", l))]
+    jumps = {}   # label -> the branches to it
+    for i, l in enumerate(lines):
+        m = re.match(r"s_c?branch\S* (\S+)$", l)
+        if m:
+            jumps.setdefault(m.group(1), []).append(i)
+
+    def walk(i, left, load):
+        """From line i back while `left` wait states are missing."""
+        while left > 0 and i >= 0:
+            l = lines[i]
+            if l.endswith(":"):
+                for j in jumps.get(l[:-1], []):
+                    walk(j, left, load)
+                if i > 0 and re.match(r"s_(branch|endpgm|setpc)", lines[i - 1]):
+                    return
+                i -= 1
+                continue
+            toks = re.split(r"[ ,]+", l)
+            if toks[0] == "s_nop":
+                left -= int(toks[1], 0) + 1
+            else:
+                wrote = toks[1] if len(toks) > 1 else ""
+                if wrote == "m0":
+                    raise RuntimeError(f"load into LDS directly after the write of m0:\n  {l}\n  {load}")
+                left -= 1
+            i -= 1
+
+    seen = 0
+    for i, l in enumerate(lines):
+        if l.startswith(("buffer_load", "global_load")) and re.search(r"\blds$", l):
+            seen += 1
+            walk(i - 1, 1, l)
+    return seen
+
+
+# what is checked on a source's generated assembly
+ASSEMBLY_CHECKS = {
+    "cholesky.hip": check_dpp_wait_states,
+    "hessian.hip": check_lds_dma_wait_states,
+    "layer_error.hip": check_lds_dma_wait_states,
+    "artifact.hip": check_lds_dma_wait_states,
+}
+
+
+def device_assembly(src: str) -> str:
+    extra = [] if src in NO_VGPR_FORM else VGPR_FORM
+    cmd = [_hipcc(), *[f for f in FLAGS if f not in ("-fPIC", "-Wall")], *extra, "-S", "--cuda-device-only",
+           os.path.join(CSRC, src), "-o", "-"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc -S failed for {src}:\n{r.stderr}")
+    return r.stdout
+
+
+def check_assembly(src: str) -> None:
+    if ASSEMBLY_CHECKS[src](device_assembly(src)) == 0:
+        raise RuntimeError(f"{src}: none of the checked instructions found in the generated assembly (check out of date?)")
+
+
 def build(verbose: bool = True) -> str:
     """Compiles every source (always, also when a library is already there) and links."""
     hipcc = _hipcc()
@@ -84,19 +151,11 @@ def build(verbose: bool = True) -> str:
             print("\n".join(errs), file=sys.stderr)
         return obj
 
-    def check_leaf_assembly():
-        cmd = [hipcc, *[f for f in FLAGS if f not in ("-fPIC", "-Wall")], *VGPR_FORM, "-S", "--cuda-device-only",
-               os.path.join(CSRC, "cholesky.hip"), "-o", "-"]
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc -S failed for cholesky.hip:\n{r.stderr}")
-        if check_dpp_wait_states(r.stdout) == 0:
-            raise RuntimeError("cholesky.hip: no DPP instruction found in the generated assembly (check out of date?)")
-
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
-        checked = ex.submit(check_leaf_assembly)
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        checked = [ex.submit(check_assembly, src) for src in ASSEMBLY_CHECKS]
         objs = list(ex.map(compile_one, SOURCES))
-        checked.result()
+        for c in checked:
+            c.result()
     r = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:

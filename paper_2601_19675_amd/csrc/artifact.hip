@@ -13,10 +13,9 @@
 // codes' stream from memory), more of them in tiles on the 16-bit matrix cores.
 #include <algorithm>
 #include <cmath>
-#include <type_traits>
-#include <utility>
 
 #include "common.h"
+#include "lds_dma.h"
 #include "rotation.h"
 
 namespace ptq {
@@ -840,37 +839,6 @@ constexpr int kYPitch = 40;   // bfloat16 elements per staged row of 32 ranks
 
 __device__ __forceinline__ int tile_key(int token) { return (token >> 1) & 7; }
 
-typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
-
-// 64 lanes x 16, 4 or 1 bytes from descriptor base + voff + soff to LDS address ldsaddr + 16 or 4 lane; lanes past the
-// descriptor's end deliver zeros
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-template <int BYTES>
-__device__ __forceinline__ void request_to_lds(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t ldsaddr) {
-  if constexpr (BYTES == 16)
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-  else if constexpr (BYTES == 4)
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ubyte %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-template <int N>
-__device__ __forceinline__ void wait_requests() {   // until N requests to memory are on their way; other counters: no wait
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
-
-// a buffer of `bytes` at p; p and bytes the same for a wave
-__device__ __forceinline__ i32x4 buffer_at(const void* p, int64_t bytes) {
-  const uint64_t a = (uint64_t)p;
-  return i32x4{(int)__builtin_amdgcn_readfirstlane((uint32_t)a), (int)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
-               (int)__builtin_amdgcn_readfirstlane((uint32_t)(bytes > 0 ? bytes : 0)), 0x00020000};
-}
 __device__ __forceinline__ void buffer_advance(i32x4& b, uint64_t bytes) {
   const uint64_t a = (((uint64_t)(uint32_t)b[1] << 32) | (uint32_t)b[0]) + bytes;
   b[0] = (int)__builtin_amdgcn_readfirstlane((uint32_t)a);
@@ -883,16 +851,6 @@ struct TileLds {
   static constexpr int kX = 32 * TT * kTileRow, kW = 256 * 4 * BITS, kGrid = 256 * 4;   // of one chunk
   static constexpr int w = kTileRing * kX, scale = w + kTileRing * kW, zero = scale + kTileRing * kGrid, all = zero + kTileRing * kGrid;
 };
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 struct TilePlan {
   int token_blocks, row_blocks, splits, chunks_per_part;   // splits x KG parts

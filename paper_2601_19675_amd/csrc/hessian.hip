@@ -19,10 +19,8 @@
 //
 // float32 activations: hessian_f32.hip (float64 matrix cores, 64 x 64 or 128 x 128 tiles), same
 // partial scheme with float64 partial tiles.
-#include <type_traits>
-#include <utility>
-
 #include "common.h"
+#include "lds_dma.h"
 
 namespace ptq {
 namespace {
@@ -167,8 +165,7 @@ __global__ __launch_bounds__(256) void hessian_bf16_kernel(const uint16_t* __res
 // only) fetch some valid channel instead; the outputs they feed lie outside the matrix and
 // are dropped by the reduction.
 //
-// The DMA requests are issued by inline assembly and tracked with explicit vmcnt waits:
-// the compiler would otherwise wait for every outstanding request before each LDS read.
+// The DMA requests are those of lds_dma.h.
 constexpr int kBT = 256;
 constexpr int kBKS = 32;                          // tokens per stage
 constexpr int kBRing = 4;                         // stages in LDS
@@ -177,49 +174,12 @@ constexpr int kBPart = kBKS * kBRow;              // A part: 16 KB
 constexpr size_t kBigLdsBytes = (size_t)kBRing * 2 * kBPart;  // 128 KB
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
-typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 
 __device__ __forceinline__ int swz(int row) { return ((row & 1) * 10) | ((row & 2) * 2); }
-
-// One request: 64 lanes x 16 bytes from (descriptor base + voff) to LDS address ldsaddr + 16 * lane.
-// (m0 is not otherwise used in this kernel: no indirect register indexing, no other LDS DMA.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t ldsaddr) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc)
-               : "memory", "m0");
-}
-
-// The same with the LDS address as a scalar base plus a compile-time offset: one scalar instruction per request
-// instead of an add into a temporary and a move.
-template <uint32_t OFFSET>
-__device__ __forceinline__ void dma16_at(i32x4 rsrc, uint32_t voff, uint32_t ldsbase) {
-  asm volatile("s_add_u32 m0, %0, %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(ldsbase), "v"(voff), "s"(rsrc),
-               "n"(OFFSET)
-               : "memory", "m0", "scc");
-}
-
-#pragma clang diagnostic pop
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  // s_waitcnt vmcnt(N); the other counters at their maximum (no wait)
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
 
 // rows of MFMA tiles that a wave of big_tile has in this role
 template <int ROLE>
 constexpr int role_rows = ROLE == 2 ? 2 : (ROLE == 3 ? 0 : 4);
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // A wave's tile is 128 x 32 NB: NB = 4, the 256 x 256 tile; NB = 2, one half (`half_tile`, 128 columns) of an
 // off-diagonal 256 x 256 tile, with a B part of half the size.  On a diagonal tile both operands come from the A part;
@@ -259,11 +219,7 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
     constexpr int L = diag ? 4 : 4 + NB;  // DMA instructions per stage and wave
 
     // descriptor over the chunk's tokens (uniform, kept in scalar registers)
-    const uint64_t gb0 = (uint64_t)(X + kbeg * ldx);
-    i32x4 rs = {(int)__builtin_amdgcn_readfirstlane((uint32_t)gb0),
-                (int)__builtin_amdgcn_readfirstlane((uint32_t)(gb0 >> 32)),
-                (int)__builtin_amdgcn_readfirstlane((uint32_t)(len * ldx * 2)),  // bytes, < 2^32 (host)
-                0x00020000};
+    i32x4 rs = buffer_at(X + kbeg * ldx, len * ldx * 2);   // bytes, < 2^32 (host)
     const uint32_t stage_step = __builtin_amdgcn_readfirstlane((uint32_t)(kBKS * ldx * 2));
 
     // per-lane byte offsets of the DMA instructions of a part, inside a stage (the descriptor advances): one brings
@@ -309,8 +265,8 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
     };
     // DMA instruction q of a stage (A rows first, then B rows) into the slot at dst
     auto dma_q = [&](int q, uint32_t dst) {
-      if (q < 4) dma16(rs, voA[q], dst + q * 4096);
-      else dma16(rs, voB[q - 4], dst + kBPart + (q - 4) * 4096);
+      if (q < 4) request_to_lds(rs, voA[q], dst + q * 4096);
+      else request_to_lds(rs, voB[q - 4], dst + kBPart + (q - 4) * 4096);
     };
     // One stage on: the descriptor moves (base up, extent down, never below zero -- past the end of the chunk every
     // lane is out of range and delivers zeros), the per-lane offsets stay.  Scalar work, where advancing the
@@ -370,7 +326,7 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
     }
 #pragma unroll
     for (int q = 0; q < L / 2; ++q) dma_q(q, lbase + (kBRing - 1) * kBStage + wave * 1024);
-    wait_vmcnt<2 * L + L / 2>();
+    wait_requests<2 * L + L / 2>();
     __builtin_amdgcn_s_barrier();
 
     // Iteration s: tokens 0..15 of stage s | barrier | tokens 16..31.  At the barrier every wave
@@ -418,8 +374,8 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
         constexpr int at = L == 8 ? g : (L == 6 ? (g < 3 ? g : -1) : (g & 1 ? g >> 1 : -1));
         if constexpr (at >= 0) {
           constexpr int q = Q0 + at;
-          if constexpr (q < 4) dma16_at<DST + q * 4096>(rs, voA[q], wbase);
-          else dma16_at<DST + kBPart + (q - 4) * 4096>(rs, voB[q - 4], wbase);
+          if constexpr (q < 4) request_to_lds_at<DST + q * 4096>(rs, voA[q], wbase);
+          else request_to_lds_at<DST + kBPart + (q - 4) * 4096>(rs, voB[q - 4], wbase);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -448,7 +404,7 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
                 integral_constant<uint32_t, pend_off>{}, fa0, fb0, fa1, fb1);
         dma_advance();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wait_vmcnt<2 * L>();
+        wait_requests<2 * L>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         half_at(role, integral_constant<uint32_t, next_off>{}, std::false_type{}, integral_constant<int, 0>{},
@@ -468,7 +424,7 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
         half(role, fa0, fb0, fa1, fb1, slot_off + 16 * kBRow, slot_off + 16 * kBRowB, L / 2, lbase + pend_off + wave * 1024);
         dma_advance();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wait_vmcnt<2 * L>();
+        wait_requests<2 * L>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         half(role, fa1, fb1, fa0, fb0, next_off, next_off, 0, lbase + slot_off + wave * 1024);
@@ -484,7 +440,7 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
       else if (wave == 2) main_loop(std::integral_constant<int, 3>{});
       else main_loop(std::integral_constant<int, 1>{});
     }
-    wait_vmcnt<0>();  // nothing may still be landing in LDS when the workgroup ends
+    wait_requests<0>();  // nothing may still be landing in LDS when the workgroup ends
   }
 
   // register r of MFMA tile (a, b): row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32

@@ -16,9 +16,7 @@
 // out over the m n terms of the trace: measured against the float64 definition the two traces
 // differ by a few parts in 10^9.
 #include "dgemm.h"
-
-#include <type_traits>
-#include <utility>
+#include "lds_dma.h"
 
 namespace ptq {
 namespace {
@@ -130,27 +128,6 @@ struct SplitArgs {
 constexpr int kWideM = 256;   // rows of a tile of the wide form
 constexpr int64_t kWideFrom = 384;   // tiles
 constexpr int kSlab = 16;            // rows of tiles that are worked on together; a multiple of 8
-
-typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
-
-// 64 lanes x 16 bytes from descriptor base + voff + soff to LDS address ldsaddr + 16 lane; lanes past the end deliver zeros
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void request_to_lds(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t ldsaddr) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(ldsaddr), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // D and W as bfloat16 pieces, four consecutive k per thread
 template <int DT, int P>
@@ -450,14 +427,12 @@ __global__ __launch_bounds__(512, 2) void quad_form_wide_kernel(SplitArgs a) {
     const uint16_t* plane = is_a ? (p < ND ? first + p * planeA : a.W + (p - ND) * planeA) : a.HuT + p * planeB;
     const int at = is_a ? i0 + row : j0 + row;
     const bool there = !is_a || at < a.mp;
-    const uint64_t base = (uint64_t)(plane + (int64_t)(there ? at : 0) * a.np);
-    src[r] = i32x4{(int)__builtin_amdgcn_readfirstlane((uint32_t)base), (int)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)),
-                   (int)__builtin_amdgcn_readfirstlane(there ? (uint32_t)a.np * 32u : 0u), 0x00020000};
+    src[r] = buffer_at(plane + (int64_t)(there ? at : 0) * a.np, there ? (int64_t)a.np * 32 : 0);
     dst[r] = (uint32_t)__builtin_amdgcn_readfirstlane(lbase + (is_a ? p * kPieceA : NA * kPieceA + p * kPieceB) + row * kRow);
   }
   auto request = [&](auto r_, auto stage_, int tile) {
     constexpr int r = decltype(r_)::value;
-    request_to_lds(src[r], voff, (uint32_t)min(tile, ktiles - 1) * (kSK * 2), dst[r] + decltype(stage_)::value * kStage);
+    request_to_lds<16>(src[r], voff, (uint32_t)min(tile, ktiles - 1) * (kSK * 2), dst[r] + decltype(stage_)::value * kStage);
   };
 
   f32x16 acc[1 + (NW > 0)][2][2];
@@ -527,7 +502,7 @@ __global__ __launch_bounds__(512, 2) void quad_form_wide_kernel(SplitArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     });
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): tile + 1, requested a step ago
+    wait_requests<0>();   // tile + 1, requested a step ago
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -541,7 +516,7 @@ __global__ __launch_bounds__(512, 2) void quad_form_wide_kernel(SplitArgs a) {
   };
   static_for<kOwn>([&](auto r) { request(r, Zero{}, 0); });
   static_for<kOwn>([&](auto r) { request(r, One{}, 1); });
-  __builtin_amdgcn_s_waitcnt((kOwn & 15) | ((kOwn >> 4) << 14) | 0x0f70);
+  wait_requests<kOwn>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   static_for<kReads>([&](auto i) { read(Zero{}, Zero{}, i); });
@@ -549,7 +524,7 @@ __global__ __launch_bounds__(512, 2) void quad_form_wide_kernel(SplitArgs a) {
     step(Zero{}, tile);
     step(One{}, tile + 1);
   }
-  __builtin_amdgcn_s_waitcnt(0x0f70);   // nothing may still be landing in LDS when the workgroup ends
+  wait_requests<0>();   // nothing may still be landing in LDS when the workgroup ends
 
   // sum_ij A_ij T_ij of the tile in float64; accumulator r of a lane is row (r / 4) * 8 + (lane / 32) * 4 + r % 4,
   // column lane % 32 of its 32 x 32 tile; rows and columns beyond m x n hold zeros, rows beyond mp are not there
