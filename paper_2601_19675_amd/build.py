@@ -68,10 +68,18 @@ def check_dpp_wait_states(asm_text: str) -> int:
 
 
 def check_lds_dma_wait_states(asm_text: str) -> int:
-    """lds_dma.h issues its loads into LDS from inline assembly, where the compiler does not count wait states: such a
-    load needs one after a scalar instruction wrote m0.  Walks the generated assembly back from every such load, into all predecessors at a label, and raises if
-    something stands closer.  Returns the number of loads seen."""
+    """lds_dma.h issues its loads into LDS from inline assembly, where the compiler does not count wait states: such a load
+    needs one after a scalar instruction wrote m0, and five after a vector instruction wrote a scalar register of its
+    operands.  Walks the generated assembly back from every such load, into all predecessors at a label, and raises
+    if something stands closer.  Returns the number of loads seen."""
     import re
+
+    def sgprs(tok):
+        m = re.match(r"s\[(\d+):(\d+)\]$", tok)
+        if m:
+            return set(range(int(m.group(1)), int(m.group(2)) + 1))
+        m = re.match(r"s(\d+)$", tok)
+        return {int(m.group(1))} if m else ({"vcc"} if tok == "vcc" else set())
 
     lines = [l.split(";")[0].strip() for l in asm_text.splitlines()]
     lines = [l for l in lines if l and (not l.startswith(".") or re.match(r"\.\w+:$", l))]
@@ -81,13 +89,13 @@ def check_lds_dma_wait_states(asm_text: str) -> int:
         if m:
             jumps.setdefault(m.group(1), []).append(i)
 
-    def walk(i, left, load):
+    def walk(i, left, load, operands, adjacent):
         """From line i back while `left` wait states are missing."""
         while left > 0 and i >= 0:
             l = lines[i]
             if l.endswith(":"):
                 for j in jumps.get(l[:-1], []):
-                    walk(j, left, load)
+                    walk(j, left, load, operands, adjacent)
                 if i > 0 and re.match(r"s_(branch|endpgm|setpc)", lines[i - 1]):
                     return
                 i -= 1
@@ -95,18 +103,22 @@ def check_lds_dma_wait_states(asm_text: str) -> int:
             toks = re.split(r"[ ,]+", l)
             if toks[0] == "s_nop":
                 left -= int(toks[1], 0) + 1
+                adjacent = False
             else:
                 wrote = toks[1] if len(toks) > 1 else ""
-                if wrote == "m0":
+                if adjacent and wrote == "m0":
                     raise RuntimeError(f"load into LDS directly after the write of m0:\n  {l}\n  {load}")
+                if toks[0].startswith("v_") and sgprs(wrote) & operands:
+                    raise RuntimeError(f"load into LDS too close to the write of its scalar operand:\n  {l}\n  {load}")
                 left -= 1
+                adjacent = False
             i -= 1
 
     seen = 0
     for i, l in enumerate(lines):
         if l.startswith(("buffer_load", "global_load")) and re.search(r"\blds$", l):
             seen += 1
-            walk(i - 1, 1, l)
+            walk(i - 1, 5, l, set().union(*(sgprs(t) for t in re.split(r"[ ,]+", l)[1:])), True)
     return seen
 
 

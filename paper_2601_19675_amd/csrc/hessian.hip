@@ -273,12 +273,13 @@ __device__ __forceinline__ void big_tile(const uint16_t* __restrict__ X, int64_t
     // eight per-lane offsets costs the wave eight vector instructions per stage.
     auto dma_advance = [&]() {
       const uint64_t base = (((uint64_t)(uint32_t)rs[1] << 32) | (uint32_t)rs[0]) + stage_step;
-      const uint32_t extent = (uint32_t)rs[2];
-      // (readfirstlane: the compiler forms the saturating difference in a vector register, and the descriptor
-      // operand of the requests has to be scalar)
+      uint32_t left;
+      // (the compiler would form the saturating difference in a vector register, and a request has to wait five states
+      // for a descriptor that comes out of one)
+      asm("s_sub_u32 %0, %1, %2\n\ts_cselect_b32 %0, 0, %0" : "=s"(left) : "s"(rs[2]), "s"(stage_step) : "scc");
       rs[0] = (int)__builtin_amdgcn_readfirstlane((uint32_t)base);
       rs[1] = (int)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-      rs[2] = (int)__builtin_amdgcn_readfirstlane(extent > stage_step ? extent - stage_step : 0u);
+      rs[2] = (int)left;
     };
     // The MFMAs of 16 tokens on (fa, fb) while the next fragments (na, nb) are read, `soA` / `soB` bytes on.  L/2 DMA
     // instructions, q0 onwards, go between the four groups of MFMAs: issued in one burst they fill the

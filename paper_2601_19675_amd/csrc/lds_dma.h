@@ -2,8 +2,9 @@
 // by count: for its own the compiler waits for all of them before each LDS read.  Not part of the C ABI.
 //
 // The compiler does not look into inline assembly for the wait states that an instruction needs after the one that
-// wrote its scalar operands, so one stands here: between a scalar write of m0 and the request that takes its LDS
-// address from it.  build.py checks it on the generated assembly.
+// wrote its scalar operands, so they stand here: one between a scalar write of m0 and the request that takes its LDS
+// address from it, five between a vector instruction that writes a scalar register (readfirstlane) and a request that has it
+// in its descriptor or offset.  build.py checks both on the generated assembly.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -17,8 +18,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 // a buffer of `bytes` (below 2^32) at p; p and bytes the same for a wave
 __device__ __forceinline__ i32x4 buffer_at(const void* p, int64_t bytes) {
   const uint64_t a = (uint64_t)p;
-  return i32x4{(int)__builtin_amdgcn_readfirstlane((uint32_t)a), (int)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
-               (int)__builtin_amdgcn_readfirstlane((uint32_t)(bytes > 0 ? bytes : 0)), 0x00020000};
+  i32x4 b{(int)__builtin_amdgcn_readfirstlane((uint32_t)a), (int)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
+          (int)__builtin_amdgcn_readfirstlane((uint32_t)(bytes > 0 ? bytes : 0)), 0x00020000};
+  asm volatile("s_nop 4" : "+s"(b));   // behind the readfirstlanes
+  return b;
 }
 
 // 64 lanes x 16, 4 or 1 bytes from descriptor base + voff + soff to LDS address ldsaddr + 16 or 4 lane; lanes past the

@@ -11,7 +11,9 @@ LOAD = "\tbuffer_load_dwordx4 v1, s[0:3], s9 offen lds"
 @pytest.mark.parametrize("text", [
     "\ts_mov_b32 m0, s4\n" + LOAD,                                       # the address in m0
     "\ts_add_u32 m0, s4, 0x400\n\t;;#ASMEND\n" + LOAD,
-    ".LBB0_1:\n" + LOAD + "\n\ts_mov_b32 m0, s4\n.LBB0_2:\n" + LOAD,       # by way of a label
+    "\tv_readfirstlane_b32 s2, v3\n\ts_mov_b32 m0, s4\n\ts_nop 0\n" + LOAD,  # a word of the descriptor
+    "\tv_readlane_b32 s9, v3, 1\n\ts_nop 3\n" + LOAD,                   # the offset
+    ".LBB0_1:\n" + LOAD + "\n\tv_readfirstlane_b32 s1, v3\n\ts_cbranch_scc1 .LBB0_1",   # round a loop
 ])
 def test_a_load_into_lds_too_close_is_found(text):
     with pytest.raises(RuntimeError):
@@ -20,7 +22,9 @@ def test_a_load_into_lds_too_close_is_found(text):
 
 @pytest.mark.parametrize("text", [
     "\ts_mov_b32 m0, s4\n\ts_nop 0\n" + LOAD,
-    "\ts_mov_b32 m0, s4\n\ts_branch .LBB0_2\n.LBB0_1:\n" + LOAD,         # another path
+    "\tv_readfirstlane_b32 s2, v3\n\ts_nop 4\n" + LOAD,
+    "\tv_readfirstlane_b32 s4, v3\n\ts_mov_b32 s2, s4\n" + LOAD,          # by way of a scalar instruction
+    "\tv_readfirstlane_b32 s2, v3\n\ts_branch .LBB0_2\n.LBB0_1:\n" + LOAD,   # another path
 ])
 def test_a_load_into_lds_far_enough_passes(text):
     assert build.check_lds_dma_wait_states(text) == 1
