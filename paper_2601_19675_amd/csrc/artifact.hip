@@ -1412,17 +1412,14 @@ ptq_status linear_forward_launch(const void* X, ptq_dtype xdt, int64_t ldx, int6
   float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(y) +
                                             align_up((size_t)tokens * (r > 0 ? r : 1) * sizeof(float), 256));
   // behind the partial sums, which leave a split's room: the tokens' exponents, where X~ is in pieces.  A layer of
-  // a few rows and more tokens than its workspace has exponents for goes by runs of tokens.
+  // a few rows and more tokens than its workspace has exponents for goes by runs of tokens, each with its exponents at
+  // the very end: the last run may be short enough to split its columns.
   const size_t behind = forward_partial_bytes(m, n) + forward_tail_bytes(m);
-  int64_t run = tokens;
-  int* exponents = nullptr;
   const bool pieces = takes_tiles(tokens, n);
-  if (pieces) {
-    run = std::min<int64_t>(tokens, (int64_t)(behind / sizeof(int)));
-    exponents = reinterpret_cast<int*>(reinterpret_cast<char*>(partial) + behind) - run;
-  }
+  const int64_t run = pieces ? std::min<int64_t>(tokens, (int64_t)(behind / sizeof(int))) : tokens;
   for (int64_t t0 = 0; t0 < tokens; t0 += run) {
     const int part = (int)std::min(run, tokens - t0);
+    int* exponents = pieces ? reinterpret_cast<int*>(reinterpret_cast<char*>(partial) + behind) - part : nullptr;
     const char* x0 = static_cast<const char*>(X) + t0 * ldx * (xdt == PTQ_F64 ? 8 : (xdt == PTQ_F32 ? 4 : 2));
     const bool tiles = pieces && takes_tiles(part, n);
     PrepArgs prep{x0, ldx, part, (int)n, perm, b_I, V, sigma, s, r, xt, y, nullptr, 0, 1, 0, 1, 1, 0, exponents, false, 0, 1.0 / std::sqrt((double)b_H)};

@@ -58,7 +58,7 @@ int hipStreamWaitEvent(void* s, void* e, unsigned f) { return 0; }
 
 def record(calls, read=None, failing=""):
     """[(status, [{"kernel", "grid", **arguments}])] for every (function, arguments).  `read`: arguments to note,
-    {part of a kernel's name: {key: (position, "i" for 32 bits or "q" for 64)}}; `failing`: part of a kernel's name whose
+    {part of a kernel's name: {key: (position, "i" for 32 bits or "q" for 64[, bytes into a struct argument])}}; `failing`: part of a kernel's name whose
     hipFuncSetAttribute fails."""
     if not os.path.exists(LIB):
         sys.path.insert(0, ROOT)
@@ -86,8 +86,8 @@ def _child():
         entry = dict(kernel=name.decode(), grid=[x, y, z])
         for part, wanted in job["read"].items():
             if part in entry["kernel"]:
-                for key, (at, kind) in wanted.items():
-                    entry[key] = c.cast(args[at], c.POINTER(c.c_int32 if kind == "i" else c.c_int64))[0]
+                for key, (at, kind, *into) in wanted.items():
+                    entry[key] = c.cast(args[at] + sum(into), c.POINTER(c.c_int32 if kind == "i" else c.c_int64))[0]
         launches.append(entry)
 
     callback = c.CFUNCTYPE(None, c.c_char_p, c.c_uint, c.c_uint, c.c_uint, c.POINTER(c.c_void_p))(on_launch)

@@ -75,6 +75,13 @@ def test_edges_of_what_the_launches_share_out(bits, tokens, m, n, group, r, dtyp
     _check(_apply(layer, bits, group), layer, bits, group)
 
 
+# tokens in runs, the last of which splits its columns over several workgroups
+@pytest.mark.parametrize("bits,tokens,m,n,r", [(4, 133, 1, 512, 0), (3, 585, 1, 4096, 16), (8, 395, 3, 544, 2)])
+def test_a_last_run_that_splits(bits, tokens, m, n, r):
+    layer = _random_layer(11 * bits + tokens, bits, tokens, m, n, 32, r, torch.float32)
+    _check(_apply(layer, bits, 32), layer, bits, 32)
+
+
 # quotients x / s whose reciprocal alone would not do: s beyond 2^500 and below 2^-500, beside ordinary ones
 def test_coefficients_of_extreme_scales():
     layer = list(_random_layer(5, 4, 200, 64, 1024, 64, 16, torch.float32))
