@@ -262,7 +262,9 @@ __device__ __host__ __forceinline__ int align16(int bytes) { return (bytes + 15)
 __device__ __forceinline__ uint32_t pair_low(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t pair_high(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
-// A number below 2^15 as the sum of two float16: each rounded to nearest, the second of what the first leaves
+// A number below 2^15 as the sum of a float16 and 2^-kSecond of another: each rounded to nearest, the second of what the
+// first leaves, which is at most 2^3
+constexpr int kSecond = 12;
 __device__ __forceinline__ uint32_t split2(double x) {
   // by way of float32, kept apart: as one conversion from float64 it is some forty instructions
   auto narrow = [](double v) {
@@ -271,7 +273,7 @@ __device__ __forceinline__ uint32_t split2(double x) {
     return (_Float16)f;
   };
   const _Float16 first = narrow(x);
-  const _Float16 second = narrow(x - (double)first);
+  const _Float16 second = narrow((x - (double)first) * (double)(1 << kSecond));
   return (uint32_t)__builtin_bit_cast(uint16_t, second) << 16 | __builtin_bit_cast(uint16_t, first);
 }
 
@@ -715,8 +717,11 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int co
 
 // ---- many tokens: 16-bit matrix cores -----------------------------------------------------------
 // O = X~ Dequant^T as a GEMM on the float16 matrix instruction.  code - zero is an integer of at most eight bits and a
-// sign: exact in float16.  X~ comes from float64 as the sum of two float16, each rounded to nearest, of a token's own power
-// of two: it is off by at most 2^-23 of itself, or 2^-35 of the token's largest |x| where that is more.  The products are exact
+// sign: exact in float16.  X~ comes from float64 as the sum of a float16 and 2^-12 of another, each rounded to nearest, of a
+// token's own power of two: it is off by at most 2^-23 of itself, or 2^-47 of the token's largest |x| where that is more (an
+// entry 2^23 times the others leaves them theirs).  The second pieces meet codes times 2^-12, which are raised to the codes
+// themselves for the first pieces by a multiplication per pair: without it the second bound would be
+// 2^-35, and a massive entry that meets a zero weight would cost its row the bits of all others.  The products are exact
 // in float32 and only its sums round; with two of them per weight fewer do than with the three truncated bfloat16
 // pieces that hold a float32 exactly, and the distance from the float64 product is smaller everywhere it was measured
 // (512 to 11008 columns, groups of 64 and 128, 2 to 8 bits: 0.63 to 1.35e-7 of its norm, 0.65 to 1.50e-7 with three
@@ -758,14 +763,13 @@ constexpr uint64_t code_order() {
   return o;
 }
 
-// Two codes at bit S of a word's halves, minus the zero, as float16: put into the mantissa of 1024 (unit 2^-S of it), then one
-// multiply-add; every value on the way is exact.  offset = -(2^(10 - S) + zero).
+// Two codes at bit S of a word's halves, minus the zero, as float16 and in the second pieces' unit: put into the mantissa
+// of 1024 (unit 2^-S of it), then one multiply-add; every value on the way is exact.  offset = -(2^(10 - S) + zero) 2^-kSecond.
 template <int S, int BITS>
 __device__ __forceinline__ f16x2 code_pair(uint32_t w, uint32_t magic, f16x2 offset) {
   constexpr uint32_t one = ((1u << BITS) - 1u) << S, both = one | one << 16;
   const f16x2 v = __builtin_bit_cast(f16x2, (w & both) | magic);
-  if constexpr (S == 0) return v + offset;
-  constexpr _Float16 unit = (_Float16)(1.0f / (1 << S));
+  constexpr _Float16 unit = (_Float16)(1.0f / (1 << (S + kSecond)));
   return __builtin_elementwise_fma(v, f16x2{unit, unit}, offset);
 }
 
@@ -790,17 +794,19 @@ __device__ __forceinline__ Offsets<BITS> code_offsets(uint32_t zero) {
   Offsets<BITS> out;
 #pragma unroll
   for (int i = 0; i < kCount; ++i) {
-    const _Float16 base = (_Float16)(float)(1 << (10 - kStep * i));
-    out.o[i] = -(f16x2{base, base} + z);
+    const _Float16 base = (_Float16)(float)(1 << (10 - kStep * i)), unit = (_Float16)(-1.0f / (1 << kSecond));
+    out.o[i] = (f16x2{base, base} + z) * unit;
   }
   return out;
 }
 
-// pair q of a half chunk's codes in their order, minus the zero
+// pair q of a half chunk's codes in their order, minus the zero, times 2^-kSecond
 template <int BITS, int Q>
 __device__ __forceinline__ f16x2 widen_pair(const HalfWords<BITS>& v, uint32_t magic, const Offsets<BITS>& o) {
   if constexpr (BITS == 8) {   // bytes 2 (q % 2) and the next of a word, 0x64 above each
-    return __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(magic, v.w[Q >> 1], Q & 1 ? 0x05030502u : 0x05010500u)) + o.o[0];
+    constexpr _Float16 unit = (_Float16)(1.0f / (1 << kSecond));
+    return __builtin_elementwise_fma(
+        __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(magic, v.w[Q >> 1], Q & 1 ? 0x05030502u : 0x05010500u)), f16x2{unit, unit}, o.o[0]);
   } else if constexpr (BITS == 4) {
     constexpr int k = Q >> 2, i = Q & 3;
     return code_pair<4 * (i & 1), 4>(i & 2 ? v.w[k] >> 8 : v.w[k], magic, o.o[i & 1]);
@@ -1001,12 +1007,19 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
       to.scale[rt] = r.scale[rt];
     }
   };
+  auto kept = [](f16x2 v) {   // formed here, not where a later step uses it
+    uint32_t bits = __builtin_bit_cast(uint32_t, v);
+    asm volatile("" : "+v"(bits));
+    return __builtin_bit_cast(f16x2, bits);
+  };
   auto widen = [&](Raw& r, Codes& to, auto index) {   // pair by pair, index < 8 RT
     constexpr int I = decltype(index)::value, q = I / RT, rt = I % RT;
-    to.pair[rt][q] = widen_pair<BITS, q>(r.w[rt], magic, off[rt]);
-    uint32_t bits = __builtin_bit_cast(uint32_t, to.pair[rt][q]);
-    asm volatile("" : "+v"(bits));   // here, not where the next step uses it
-    to.pair[rt][q] = __builtin_bit_cast(f16x2, bits);
+    to.pair[rt][q] = kept(widen_pair<BITS, q>(r.w[rt], magic, off[rt]));
+  };
+  auto raise = [&](Codes& to, auto step_, auto index) {   // from the second pieces' unit to the first's: four pairs of a step, index < 4 RT
+    constexpr int q = 4 * decltype(step_)::value + decltype(index)::value / RT, rt = decltype(index)::value % RT;
+    constexpr _Float16 unit = (_Float16)(float)(1 << kSecond);
+    to.pair[rt][q] = kept(to.pair[rt][q] * f16x2{unit, unit});
   };
   auto read_x = [&](auto slot_, auto piece, auto index) {   // index < 2 TT
     constexpr int p = decltype(piece)::value, ks = decltype(index)::value / TT, tt = decltype(index)::value % TT;
@@ -1061,12 +1074,15 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
     typedef integral_constant<int, (Q + 1) % kTileRing> Next;
     typedef integral_constant<int, (Q + 2) % kTileRing> After;
     constexpr int kPairs = 8 * RT / (2 * kHalf);   // widened per MFMA
+    constexpr int kRaised = 8 * RT / kHalf;        // raised per MFMA: a step's pairs while the other step's MFMAs go
     start_codes(raw[P ^ 1], codes[P ^ 1]);
     static_for<kHalf>([&](auto i_) {
       constexpr int i = decltype(i_)::value;
       mfma(codes[P], One{}, i_);
       if constexpr (i < 2 * TT) read_x(Here{}, Zero{}, i_);
       static_for<kPairs>([&](auto k) { widen(raw[P ^ 1], codes[P ^ 1], integral_constant<int, kPairs * i + decltype(k)::value>{}); });
+      if constexpr (i >= kHalf / 2)
+        static_for<kRaised>([&](auto k) { raise(codes[P], Zero{}, integral_constant<int, kRaised * (i - kHalf / 2) + decltype(k)::value>{}); });
       __builtin_amdgcn_sched_barrier(0);
     });
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1080,6 +1096,8 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
       if constexpr (i < 2 * TT) read_x(Next{}, One{}, i_);
       if constexpr (i < RT) read_raw(raw[P], After{}, After::value * Lds::kW, i_);
       static_for<kPairs>([&](auto k) { widen(raw[P ^ 1], codes[P ^ 1], integral_constant<int, kPairs * (kHalf + i) + decltype(k)::value>{}); });
+      if constexpr (i < kHalf / 2)
+        static_for<kRaised>([&](auto k) { raise(codes[P], One{}, integral_constant<int, kRaised * i + decltype(k)::value>{}); });
       static_for<(kBatch + kHalf - 1) / kHalf>([&](auto k) {
         constexpr int r = i * ((kBatch + kHalf - 1) / kHalf) + decltype(k)::value;
         if constexpr (r < kBatch) request(integral_constant<int, r>{}, Here{}, Next{}, Next::value * Lds::kW);
