@@ -11,6 +11,8 @@
 //
 // The product with the packed residual takes two forms: a few tokens row by row on the vector unit (bound by the
 // codes' stream from memory), more of them in tiles on the 16-bit matrix cores.
+#include <limits.h>
+
 #include <algorithm>
 #include <cmath>
 
@@ -163,13 +165,15 @@ struct PrepArgs {
   int coeff_tiles, coeff_splits;
   int run_lg, segments, segment;   // 2^run_lg tokens a rotating workgroup; workgroups per token (run_lg = 0) and chunks of each
   uint64_t order;   // 0: X~ as float32; otherwise as two float16 pieces, position p of 16 holds column (order >> 4 p) & 15
-  int* exponents;   // tokens: X~ is 2^exponents[token] times the pieces' sum
-  bool roomy;       // LDS beyond the row: kPrepWaves x 256 words
+  int* exponents;   // tokens: X~ is 2^exponents[token] times the pieces' sum; kPlain: X~ as float32
+  bool roomy;       // LDS beyond the row: kPrepExtra bytes
   int lg;           // b_H = 2^lg
   double scale;     // 1 / sqrt(b_H)
 };
 
 constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
+constexpr int kPrepExtra = kPrepWaves * (3 + 256) * (int)sizeof(uint32_t);
+constexpr int kPlain = INT_MIN;
 // From here on 16 tokens share a wave's quotients and conversions (whole call, 16 ranks: 200 x 4096 x 11008 75 us, 76 without;
 // 512 x 4096 x 11008 120 and 139; 1000 x 777 x 512 27 and 37).  Below it the chip is not full that way (128 x 4096 x 11008 57
 // and 52 us, 160 x 11008 x 4096 91 and 87).
@@ -370,6 +374,20 @@ __device__ __forceinline__ uint32_t magnitude(typename StoredType<DT>::type v) {
   else return ((uint32_t)v << 16) & 0x7fffffffu;
 }
 
+// ... and powers of two among them
+template <int DT>
+struct Magnitudes {
+  static constexpr int kMantissa = DT == PTQ_F64 ? 20 : 23, kBias = DT == PTQ_F64 ? 1023 : 127;
+  static __device__ bool finite(uint32_t v) { return (int)(v >> kMantissa) != 2 * kBias + 1; }
+  static __device__ int exponent(uint32_t v) {   // 2^exponent <= v < 2^(exponent + 1); v > 0
+    const int field = (int)(v >> kMantissa);
+    return field ? field - kBias : 31 - __clz((int)v) - kMantissa - (kBias - 1);
+  }
+  static __device__ uint32_t power(int e) {   // 2^e, at most the largest; 0 below the smallest
+    return e > -kBias ? (uint32_t)(e + kBias) << kMantissa : (e + kBias - 1 + kMantissa >= 0 ? 1u << (e + kBias - 1 + kMantissa) : 0u);
+  }
+};
+
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   auto with = [&](auto ctrl) { v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, false)); };
   with(std::integral_constant<int, kDppSwapPairs>{});
@@ -399,9 +417,9 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
   const int token0 = unit << run_lg, seg = item - unit * a.segments;
   const int run = min(1 << run_lg, a.tokens - token0);
   const int row = align16(a.n * (int)sizeof(ST));
-  // A wave stages a share of one token's row and keeps its largest magnitude
+  // A wave stages a share of one token's row and keeps its largest magnitude, and its smallest but zero, less one
   const int my = wave & ((1 << run_lg) - 1), shares = kPrepWaves >> run_lg;
-  uint32_t top = 0;
+  uint32_t top = 0, bottom = ~0u;
   if (my < run) {
     const ST* src = static_cast<const ST*>(a.X) + (int64_t)(token0 + my) * a.ldx;
     ST* dst = reinterpret_cast<ST*>(prep_lds + my * row);
@@ -412,15 +430,23 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
       *reinterpret_cast<Piece*>(dst + c) = p;
       if constexpr (PIECES) {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) top = max(top, magnitude<DT>(p.e[i]));
+        for (int i = 0; i < kPer; ++i) {
+          const uint32_t v = magnitude<DT>(p.e[i]);
+          top = max(top, v);
+          bottom = min(bottom, v - 1);
+        }
       }
     }
   }
   uint32_t* tops = reinterpret_cast<uint32_t*>(prep_lds + (row << run_lg));   // with pieces and where there is room: of each wave
-  uint32_t* swap = tops + kPrepWaves + 256 * wave;                            // ... and a wave's own 256 words
+  uint32_t* swap = tops + 3 * kPrepWaves + 256 * wave;                        // ... and a wave's own 256 words
   if (PIECES && a.roomy) {
     top = wave_max(top);
-    if (lane == 0) tops[wave] = top;
+    bottom = ~wave_max(~bottom);
+    if (lane == 0) {
+      tops[wave] = top;
+      tops[kPrepWaves + wave] = bottom;
+    }
   }
   const int nchunk_id = (a.b_I + 255) / 256;                   // chunks of the identity part
   const int nchunk = nchunk_id + (a.n - a.b_I + 255) / 256;    // ... plus those of the rotated part
@@ -438,27 +464,63 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
   };
   int4 next = places(min(wave, items - 1));
   __syncthreads();
-  // X~ 2^up stays below 2^15: 2^e <= max |x| < 2^(e + 1) (numbers below the normal range, rows of zeros and rows with an
-  // infinity or a NaN, whose outputs are NaN, go as they are), and a rotation makes it sqrt(b_H) times as large at most.
-  // Lane tl holds token tl's.
+  // X~ 2^up stays below 2^15: 2^e <= max |x| < 2^(e + 1) (rows of zeros and rows with an infinity or a NaN, whose outputs are
+  // NaN, go as they are), and a rotation makes it sqrt(b_H) times as large at most.  Lane tl holds token tl's.
+  // The pieces hold 23 bits of what is no smaller than 2^-kSpan of the largest; a token with more than one entry in 256
+  // below that goes as float32, and the product takes it by itself.  (Up to there, what they lack of a few entries is far below
+  // the rounding of the others.)
   int ups = 0;
   uint32_t from[4];   // where a lane's four positions of 16 come from
   if constexpr (PIECES) {
-    uint32_t largest = 0;
+    using M = Magnitudes<DT>;
+    constexpr int kSpan = 24;
+    const auto of_token = [&](int w) { return ((w ^ lane) & ((1 << run_lg) - 1)) == 0; };   // wave w's share and lane's token
+    uint32_t largest = 0, smallest = ~0u;
     if (a.roomy) {
-      static_assert(kPrepWaves == 8, "two reads");
-      const uint4 lo = reinterpret_cast<const uint4*>(tops)[0], hi = reinterpret_cast<const uint4*>(tops)[1];
-      const uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      static_assert(kPrepWaves == 8, "two reads each");
+      const uint4* read = reinterpret_cast<const uint4*>(tops);
+      const uint4 lo = read[0], hi = read[1], lo2 = read[2], hi2 = read[3];
+      const uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, b[8] = {lo2.x, lo2.y, lo2.z, lo2.w, hi2.x, hi2.y, hi2.z, hi2.w};
 #pragma unroll
-      for (int w = 0; w < 8; ++w) largest = max(largest, ((w ^ lane) & ((1 << run_lg) - 1)) == 0 ? t[w] : 0u);
+      for (int w = 0; w < 8; ++w) {
+        largest = max(largest, of_token(w) ? t[w] : 0u);
+        smallest = min(smallest, of_token(w) ? b[w] : ~0u);
+      }
     } else {   // one row
-      for (int q = lane; q < a.n; q += 64) largest = max(largest, magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]));
+      for (int q = lane; q < a.n; q += 64) {
+        const uint32_t v = magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]);
+        largest = max(largest, v);
+        smallest = min(smallest, v - 1);
+      }
       largest = wave_max(largest);
+      smallest = ~wave_max(~smallest);
     }
-    constexpr int kMantissa = DT == PTQ_F64 ? 20 : 23, kBias = DT == PTQ_F64 ? 1023 : 127;
-    const int field = (int)(largest >> kMantissa);
-    ups = field == 0 || field == 2 * kBias + 1 ? 0 : min(14 - (field - kBias) - (lg + 1) / 2, 1000);
-    if (seg == 0 && tid < run) a.exponents[token0 + tid] = -ups;
+    const bool ordinary = largest != 0 && M::finite(largest);
+    const int e = ordinary ? M::exponent(largest) : 0;
+    ups = ordinary ? min(14 - e - (lg + 1) / 2, 1000) : 0;
+    const uint32_t limit = ordinary ? M::power(e - kSpan) : 0u, below = limit ? limit - 1 : 0u;   // v - 1 < below: 0 < v < limit
+    if (__ballot(smallest < below)) {   // the same for all waves
+      int count = 0;
+      if (a.roomy) {
+        const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)below, my);
+        const ST* src = reinterpret_cast<const ST*>(prep_lds + my * row);
+        if (my < run)
+          for (int q = (wave >> run_lg) * 64 + lane; q < a.n; q += shares * 64) count += magnitude<DT>(src[q]) - 1 < mine;
+      } else {
+        for (int q = lane; q < a.n; q += 64) count += magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]) - 1 < below;
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off);
+      if (a.roomy) {
+        if (lane == 0) tops[2 * kPrepWaves + wave] = (uint32_t)count;
+        __syncthreads();
+        count = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) count += of_token(w) ? (int)tops[2 * kPrepWaves + w] : 0;
+      }
+      if (count > a.n / 256) ups = kPlain;
+    }
+    if (seg == 0 && tid < run) a.exponents[token0 + tid] = ups == kPlain ? kPlain : -ups;
     const uint32_t mine = (uint32_t)(a.order >> (16 * (lane & 3)));
 #pragma unroll
     for (int q = 0; q < 4; ++q) from[q] = 4 * (lane & ~3) + ((mine >> (4 * q)) & 15);
@@ -480,15 +542,16 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
       v[3] = stored_to_f64<DT>(buf[p.w]);
     }
     if (ch.rotated) fwht_chunk(v, lg, lane);
+    const int up = PIECES ? __builtin_amdgcn_readlane(ups, tl) : kPlain;
     if (PIECES || ch.rotated) {
-      const double factor = ch.rotated ? a.scale : 1.0, unit = PIECES ? ldexp(factor, __builtin_amdgcn_readlane(ups, tl)) : factor;
+      const double factor = ch.rotated ? a.scale : 1.0, unit = up != kPlain ? ldexp(factor, up) : factor;
 #pragma unroll
       for (int q = 0; q < 4; ++q) v[q] *= unit;
     }
     // of the token's 128 bytes in each of the 32-column pieces c / 32; c is a multiple of 4
     char* const base = reinterpret_cast<char*>(a.xt) + (int64_t)token * (kChunk * 4);
     const uint32_t at = (uint32_t)(c >> 5) * ((uint32_t)a.tokens * (kChunk * 4));
-    if constexpr (!PIECES) {
+    if (!PIECES || up == kPlain) {
       if (live) *reinterpret_cast<float4*>(base + (at + 4 * (c & 31))) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
       continue;
     }
@@ -531,17 +594,16 @@ ptq_status launch_forward_prep(PrepArgs a, hipStream_t st) {
   // tokens go several to a workgroup, until its waves have two chunks each.
   a.segments = (int)std::min<int64_t>(ceil_div(nchunk, kPrepWaves), ceil_div(256, a.tokens));
   a.segment = (int)ceil_div(nchunk, a.segments);
-  constexpr size_t extra = (kPrepWaves + (size_t)kPrepWaves * 256) * sizeof(uint32_t);   // behind the rows, with pieces
   a.run_lg = 0;
   while (a.run_lg < 3 && a.segments == 1 && (nchunk << a.run_lg) < 2 * kPrepWaves && a.tokens >> (a.run_lg + 1) >= 512 &&
          2 * row << a.run_lg <= 32 * 1024)
     ++a.run_lg;
   const size_t rows = (size_t)align16((int)row) << a.run_lg;
-  a.roomy = rows + extra <= 160 * 1024;
+  a.roomy = rows + kPrepExtra <= 160 * 1024;
   const auto off = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16; };
   const bool aligned = off(a.X) == 0 && (a.ldx * sizeof(ST)) % 16 == 0 && (a.r == 0 || (off(a.V) % 4 == 0 && off(a.s) == 0));
   const size_t coeff = many ? (size_t)kPrepWaves * 256 * sizeof(double) : (size_t)kPrepWaves * 4 * sizeof(double);
-  const size_t lds = std::max(a.order && a.roomy ? rows + extra : std::max(rows, row), a.r ? coeff : 0);
+  const size_t lds = std::max(a.order && a.roomy ? rows + kPrepExtra : std::max(rows, row), a.r ? coeff : 0);
   const unsigned grid = (unsigned)(a.coeff_tiles + ceil_div(a.tokens, (int64_t)1 << a.run_lg) * a.segments);
   const auto launch = [&](auto is_aligned, auto pieces) {
     constexpr auto kernel = forward_prep_kernel<DT, decltype(is_aligned)::value, decltype(pieces)::value>;
@@ -566,7 +628,7 @@ struct ForwardArgs {
   const uint16_t* sigma;
   const uint8_t* U;         // r x m, e4m3
   int r;
-  const int* exponents;     // tokens: with pieces, X~ is 2^exponent times their sum
+  const int* exponents;     // tokens: with pieces, X~ is 2^exponent times their sum; kPlain: X~ as float32
   float* partial;           // (splits - 1) x tokens x m: the first split's sums go to O
   float* O;                 // tokens x m
   int64_t ldo;
@@ -858,6 +920,40 @@ struct TileLds {
   static constexpr int w = kTileRing * kX, scale = w + kTileRing * kW, zero = scale + kTileRing * kGrid, all = zero + kTileRing * kGrid;
 };
 
+// One token, whose X~ is in float32, and a row of the weight over chunks [c_begin, c_end): for the few tokens that the pieces do
+// not hold.  Bound by the way to memory, chunk by chunk.  The arguments are fetched anew: kept for this, they would fill
+// the scalar registers of the loop before it.
+template <int BITS>
+__device__ __forceinline__ float plain_product(int token, int row, int c_begin, int c_end) {
+  auto args = (const __attribute__((address_space(4))) ForwardArgs*)__builtin_amdgcn_kernarg_segment_ptr();   // the first argument
+  asm volatile("" : "+s"(args));
+  const struct { const uint32_t* packed; const float* scales; const uint8_t* zeros; const float* xt; int m, xt_tokens; } a{
+      args->packed, args->scales, args->zeros, args->xt, args->m, args->xt_tokens};
+  const int gpc = args->group / kChunk;
+  float total = 0.f, acc = 0.f;
+#pragma unroll 1
+  for (int c = c_begin; c < c_end; ++c) {
+    const Words<BITS> words = *reinterpret_cast<const Words<BITS>*>(a.packed + ((int64_t)c * a.m + row) * BITS);
+    const int64_t grid = (int64_t)(c / gpc) * a.m + row;
+    const float zero = (float)a.zeros[grid];
+    const float* x = a.xt + ((int64_t)c * a.xt_tokens + token) * kChunk;
+    float sum = 0.f;
+    static_for<4>([&](auto quarter) {
+      constexpr int Q = decltype(quarter)::value;
+      float f[8];
+      codes_to_float<BITS, Q>(words, f);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) sum = fmaf(f[j] - zero, x[8 * Q + j], sum);
+    });
+    acc += sum;
+    if ((c + 1) % gpc == 0 || c + 1 == c_end) {
+      total = fmaf(a.scales[grid], acc, total);
+      acc = 0.f;
+    }
+  }
+  return total;
+}
+
 struct TilePlan {
   int token_blocks, row_blocks, splits, chunks_per_part;   // splits x KG parts
 };
@@ -1136,6 +1232,26 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) total[tt][rt][r] = ldexpf(total[tt][rt][r], e);
     }
+
+  // tokens whose X~ is not in pieces
+  const int there = min(kTokens, tokens - tb * kTokens);
+  const uint64_t plain = __ballot(exponent == kPlain) & (~0ull >> (64 - there));
+#pragma unroll 1
+  for (uint64_t rest = plain; rest; rest &= rest - 1) {
+    const int t = __builtin_ctzll(rest);
+    const float sum = plain_product<BITS>(tb * kTokens + t, min(row0 + lane, m - 1), c_begin, c_end);   // a row per lane
+    float mine[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) mine[rt] = __shfl(sum, rt * 32 + (lane & 31));
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool here = t == tt * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) total[tt][rt][r] = here ? mine[rt] : total[tt][rt][r];
+      }
+  }
 
   // The low-rank part, once: coefficients y (tokens x r) against the e4m3 codes of U, 32 ranks at a time; e4m3
   // is exact in bfloat16, y goes through three pieces of it (exact in float32, and their range is its range).
