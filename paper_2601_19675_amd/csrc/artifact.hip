@@ -172,7 +172,7 @@ struct PrepArgs {
 };
 
 constexpr int kPrepThreads = 512, kPrepWaves = kPrepThreads / 64;
-constexpr int kPrepExtra = kPrepWaves * (3 + 256) * (int)sizeof(uint32_t);
+constexpr int kPrepExtra = kPrepWaves * (2 + 256) * (int)sizeof(uint32_t);
 constexpr int kPlain = INT_MIN;
 // From here on 16 tokens share a wave's quotients and conversions (whole call, 16 ranks: 200 x 4096 x 11008 75 us, 76 without;
 // 512 x 4096 x 11008 120 and 139; 1000 x 777 x 512 27 and 37).  Below it the chip is not full that way (128 x 4096 x 11008 57
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
   const int token0 = unit << run_lg, seg = item - unit * a.segments;
   const int run = min(1 << run_lg, a.tokens - token0);
   const int row = align16(a.n * (int)sizeof(ST));
-  // A wave stages a share of one token's row and keeps its largest magnitude, and its smallest but zero, less one
+  // A wave stages a share of one token's row and keeps its largest magnitude, a lane of its entries the smallest but zero, less one
   const int my = wave & ((1 << run_lg) - 1), shares = kPrepWaves >> run_lg;
   uint32_t top = 0, bottom = ~0u;
   if (my < run) {
@@ -439,14 +439,10 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
     }
   }
   uint32_t* tops = reinterpret_cast<uint32_t*>(prep_lds + (row << run_lg));   // with pieces and where there is room: of each wave
-  uint32_t* swap = tops + 3 * kPrepWaves + 256 * wave;                        // ... and a wave's own 256 words
+  uint32_t* swap = tops + 2 * kPrepWaves + 256 * wave;                        // ... and a wave's own 256 words
   if (PIECES && a.roomy) {
     top = wave_max(top);
-    bottom = ~wave_max(~bottom);
-    if (lane == 0) {
-      tops[wave] = top;
-      tops[kPrepWaves + wave] = bottom;
-    }
+    if (lane == 0) tops[wave] = top;
   }
   const int nchunk_id = (a.b_I + 255) / 256;                   // chunks of the identity part
   const int nchunk = nchunk_id + (a.n - a.b_I + 255) / 256;    // ... plus those of the rotated part
@@ -466,64 +462,59 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
   __syncthreads();
   // X~ 2^up stays below 2^15: 2^e <= max |x| < 2^(e + 1) (rows of zeros and rows with an infinity or a NaN, whose outputs are
   // NaN, go as they are), and a rotation makes it sqrt(b_H) times as large at most.  Lane tl holds token tl's.
-  // The pieces hold 23 bits of what is no smaller than 2^-kSpan of the largest; a token with more than one entry in 256
+  // The pieces hold 23 bits of what is no smaller than 2^-kSpan of the largest; a token with more than one entry in 64
   // below that goes as float32, and the product takes it by itself.  (Up to there, what they lack of a few entries is far below
-  // the rounding of the others.)
+  // the rounding of the others.)  Most tokens of heavy-tailed activations have such entries, but few: only the lanes that have
+  // staged one look at theirs again.
   int ups = 0;
   uint32_t from[4];   // where a lane's four positions of 16 come from
   if constexpr (PIECES) {
     using M = Magnitudes<DT>;
     constexpr int kSpan = 24;
     const auto of_token = [&](int w) { return ((w ^ lane) & ((1 << run_lg) - 1)) == 0; };   // wave w's share and lane's token
-    uint32_t largest = 0, smallest = ~0u;
-    if (a.roomy) {
-      static_assert(kPrepWaves == 8, "two reads each");
-      const uint4* read = reinterpret_cast<const uint4*>(tops);
-      const uint4 lo = read[0], hi = read[1], lo2 = read[2], hi2 = read[3];
-      const uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, b[8] = {lo2.x, lo2.y, lo2.z, lo2.w, hi2.x, hi2.y, hi2.z, hi2.w};
+    static_assert(kPrepWaves == 8, "two reads");
+    const auto read8 = [&](int at, auto f) {   // the waves' words
+      const uint4 lo = reinterpret_cast<const uint4*>(tops + at)[0], hi = reinterpret_cast<const uint4*>(tops + at)[1];
+      const uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        largest = max(largest, of_token(w) ? t[w] : 0u);
-        smallest = min(smallest, of_token(w) ? b[w] : ~0u);
-      }
+      for (int w = 0; w < 8; ++w) f(of_token(w) ? t[w] : 0u);
+    };
+    uint32_t largest = 0;
+    if (a.roomy) {
+      read8(0, [&](uint32_t v) { largest = max(largest, v); });
     } else {   // one row
-      for (int q = lane; q < a.n; q += 64) {
-        const uint32_t v = magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]);
-        largest = max(largest, v);
-        smallest = min(smallest, v - 1);
-      }
+      for (int q = lane; q < a.n; q += 64) largest = max(largest, magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]));
       largest = wave_max(largest);
-      smallest = ~wave_max(~smallest);
     }
     const bool ordinary = largest != 0 && M::finite(largest);
     const int e = ordinary ? M::exponent(largest) : 0;
     ups = ordinary ? min(14 - e - (lg + 1) / 2, 1000) : 0;
     const uint32_t limit = ordinary ? M::power(e - kSpan) : 0u, below = limit ? limit - 1 : 0u;   // v - 1 < below: 0 < v < limit
-    if (__ballot(smallest < below)) {   // the same for all waves
-      int count = 0;
-      if (a.roomy) {
-        const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)below, my);
-        const ST* src = reinterpret_cast<const ST*>(prep_lds + my * row);
-        if (my < run)
-          for (int q = (wave >> run_lg) * 64 + lane; q < a.n; q += shares * 64) count += magnitude<DT>(src[q]) - 1 < mine;
-      } else {
-        for (int q = lane; q < a.n; q += 64) count += magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]) - 1 < below;
-      }
+    const uint32_t mine = a.roomy ? (uint32_t)__builtin_amdgcn_readlane((int)below, my) : below;
+    int count = 0;
+    if (!a.roomy) {
+      for (int q = lane; q < a.n; q += 64) count += magnitude<DT>(reinterpret_cast<const ST*>(prep_lds)[q]) - 1 < mine;
+    } else if (bottom < mine) {
+      constexpr int kPer = ALIGNED ? 16 / (int)sizeof(ST) : 1;
+      const ST* src = reinterpret_cast<const ST*>(prep_lds + my * row);
+      for (int c = ((wave >> run_lg) * 64 + lane) * kPer; c < a.n; c += shares * 64 * kPer)
+        for (int i = 0; i < kPer; ++i) count += magnitude<DT>(src[c + i]) - 1 < mine;
+    }
+    if (__ballot(count > 0)) {
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off);
-      if (a.roomy) {
-        if (lane == 0) tops[2 * kPrepWaves + wave] = (uint32_t)count;
-        __syncthreads();
-        count = 0;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) count += of_token(w) ? (int)tops[2 * kPrepWaves + w] : 0;
-      }
-      if (count > a.n / 256) ups = kPlain;
     }
+    if (a.roomy) {
+      if (lane == 0) tops[kPrepWaves + wave] = (uint32_t)count;
+      __syncthreads();
+      count = 0;
+      read8(kPrepWaves, [&](uint32_t v) { count += (int)v; });
+    }
+    if (count > a.n / 64) ups = kPlain;
     if (seg == 0 && tid < run) a.exponents[token0 + tid] = ups == kPlain ? kPlain : -ups;
-    const uint32_t mine = (uint32_t)(a.order >> (16 * (lane & 3)));
+    const uint32_t order = (uint32_t)(a.order >> (16 * (lane & 3)));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) from[q] = 4 * (lane & ~3) + ((mine >> (4 * q)) & 15);
+    for (int q = 0; q < 4; ++q) from[q] = 4 * (lane & ~3) + ((order >> (4 * q)) & 15);
   }
   for (int i = wave; i < items; i += kPrepWaves) {
     const int tl = i & ((1 << run_lg) - 1), token = token0 + tl;
