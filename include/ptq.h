@@ -396,9 +396,10 @@ ptq_status ptq_unpack_dequantize(const uint32_t* packed, int64_t m, int64_t n, i
  * packed, scales_t, zeros_t (group-major), bits, group: as above; group % 32 == 0.
  * U, V   r x m and r x n e4m3 codes, sigma r fp16 bit patterns, s n float64: the output of
  *        ptq_scaled_r1svd; r = 0 applies the residual alone (U, V, sigma, s may be NULL).
- * X~ and the low-rank coefficients are formed in float64 and rounded to float32 (X~, beyond a few
- * tokens, to the sum of two float16 pieces of a power of two of the token's own: to 2^-23 of an entry or
- * 2^-47 of the token's largest |x|); the products with the codes are exact and accumulate in float32.
+ * X~ and the low-rank coefficients are formed in float64 and rounded to float32; beyond a few tokens
+ * X~ is rounded to two float16 pieces of a power of two of the token's own: to 2^-23 of an entry, or 2^-47 of
+ * the token's largest |x| where that is more -- a token with more than one entry in 64 below 2^-24 of its
+ * largest is rounded to float32.  The pieces' products with the codes are exact; all sums are float32.
  * tokens <= 4096; the packed codes are read once per 64 tokens.
  * Workspace: PTQ_OP_LINEAR_FORWARD with m, n, t = tokens and block = r.
  */

@@ -816,6 +816,13 @@ constexpr uint64_t code_order() {
   return o;
 }
 
+template <int BITS>
+constexpr int position_of(int code) {
+  for (int p = 0; p < 16; ++p)
+    if ((int)(code_order<BITS>() >> (4 * p) & 15) == code) return p;
+  return -1;
+}
+
 // Two codes at bit S of a word's halves, minus the zero, as float16 and in the second pieces' unit: put into the mantissa
 // of 1024 (unit 2^-S of it), then one multiply-add; every value on the way is exact.  offset = -(2^(10 - S) + zero) 2^-kSecond.
 template <int S, int BITS>
@@ -911,11 +918,11 @@ struct TileLds {
   static constexpr int w = kTileRing * kX, scale = w + kTileRing * kW, zero = scale + kTileRing * kGrid, all = zero + kTileRing * kGrid;
 };
 
-// One token, whose X~ is in float32, and a row of the weight over chunks [c_begin, c_end): for the few tokens that the pieces do
-// not hold.  Bound by the way to memory, chunk by chunk.  The arguments are fetched anew: kept for this, they would fill
+// One token and a row of the weight over chunks [c_begin, c_end), in float32: for the few tokens that the pieces do
+// not hold (exponent kPlain), and for rows with scales past kScaleLimit.  Bound by the way to memory, chunk by chunk.  The arguments are fetched anew: kept for this, they would fill
 // the scalar registers of the loop before it.
 template <int BITS>
-__device__ __forceinline__ float plain_product(int token, int row, int c_begin, int c_end) {
+__device__ __forceinline__ float plain_product(int token, int exponent, int row, int c_begin, int c_end) {
   auto args = (const __attribute__((address_space(4))) ForwardArgs*)__builtin_amdgcn_kernarg_segment_ptr();   // the first argument
   asm volatile("" : "+s"(args));
   const struct { const uint32_t* packed; const float* scales; const uint8_t* zeros; const float* xt; int m, xt_tokens; } a{
@@ -928,13 +935,19 @@ __device__ __forceinline__ float plain_product(int token, int row, int c_begin, 
     const int64_t grid = (int64_t)(c / gpc) * a.m + row;
     const float zero = (float)a.zeros[grid];
     const float* x = a.xt + ((int64_t)c * a.xt_tokens + token) * kChunk;
+    const _Float16* pieces = reinterpret_cast<const _Float16*>(x);
     float sum = 0.f;
     static_for<4>([&](auto quarter) {
       constexpr int Q = decltype(quarter)::value;
-      float f[8];
+      float f[8], xv[8];
       codes_to_float<BITS, Q>(words, f);
+      static_for<8>([&](auto index) {
+        constexpr int j = decltype(index)::value, p = 16 * (Q / 2) + position_of<BITS>((8 * Q + j) & 15);
+        xv[j] = exponent == kPlain ? x[8 * Q + j]
+                                   : (float)ldexp((double)(float)pieces[p] + (double)(float)pieces[kChunk + p] * (1.0 / (1 << kSecond)), exponent);
+      });
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sum = fmaf(f[j] - zero, x[8 * Q + j], sum);
+      for (int j = 0; j < 8; ++j) sum = fmaf(f[j] - zero, xv[j], sum);
     });
     acc += sum;
     if ((c + 1) % gpc == 0 || c + 1 == c_end) {
@@ -944,6 +957,10 @@ __device__ __forceinline__ float plain_product(int token, int row, int c_begin, 
   }
   return total;
 }
+
+// Largest and, but for zero, smallest scale whose products with the accumulators stay in float32's normal range before a
+// token's power of two is taken off: the accumulators are multiples of 2^-37 below 2^40.
+constexpr uint32_t kScaleLimit[2] = {(127 - 80) << 23, (127 + 80) << 23};   // 2^-80, 2^80
 
 struct TilePlan {
   int token_blocks, row_blocks, splits, chunks_per_part;   // splits x KG parts
@@ -1067,6 +1084,7 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
 #pragma unroll
       for (int r = 0; r < 16; ++r) { acc[tt][rt][r] = 0.f; total[tt][rt][r] = 0.f; }
 
+  uint32_t least = ~0u, most = 0;   // scales of the lane's rows: magnitude less one, magnitude
   auto flush = [&](const float (&sc)[RT]) {
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
@@ -1193,7 +1211,16 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
     });
     advance_x();
     advance_w();
-    if (c < c_end && (--left == 0 || c + 1 == c_end)) { flush(codes[P].scale); left = gpc; }   // the same for a wave
+    if (c < c_end && (--left == 0 || c + 1 == c_end)) {   // the same for a wave
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const uint32_t v = __float_as_uint(codes[P].scale[rt]) & 0x7fffffffu;
+        least = min(least, v - 1);
+        most = max(most, v);
+      }
+      flush(codes[P].scale);
+      left = gpc;
+    }
   };
   // the same count for all waves; past c_end a part adds what is never used
   int c = c_begin;
@@ -1224,13 +1251,14 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
       for (int rt = 0; rt < RT; ++rt) total[tt][rt][r] = ldexpf(total[tt][rt][r], e);
     }
 
-  // tokens whose X~ is not in pieces
+  // tokens whose X~ is not in pieces; all, if a scale is too large or too small
   const int there = min(kTokens, tokens - tb * kTokens);
-  const uint64_t plain = __ballot(exponent == kPlain) & (~0ull >> (64 - there));
+  const bool extreme = least < kScaleLimit[0] - 1 || most > kScaleLimit[1];
+  const uint64_t plain = (__ballot(extreme) ? ~0ull : __ballot(exponent == kPlain)) & (~0ull >> (64 - there));
 #pragma unroll 1
   for (uint64_t rest = plain; rest; rest &= rest - 1) {
     const int t = __builtin_ctzll(rest);
-    const float sum = plain_product<BITS>(tb * kTokens + t, min(row0 + lane, m - 1), c_begin, c_end);   // a row per lane
+    const float sum = plain_product<BITS>(tb * kTokens + t, __builtin_amdgcn_readlane(exponent, t), min(row0 + lane, m - 1), c_begin, c_end);   // a row per lane
     float mine[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) mine[rt] = __shfl(sum, rt * 32 + (lane & 31));

@@ -130,6 +130,33 @@ def test_subnormal_tokens(bits, tokens, dtype):
     assert _rows_off(_apply(layer, bits, 32), layer, bits, 32, torch.arange(70)) <= _norm(torch.arange(70))
 
 
+# group scales far from those of a grid, with tokens whose size brings the outputs back: some rows, or some groups of all
+@pytest.mark.parametrize("power", [120, 90, -90, -140])
+@pytest.mark.parametrize("bits,tokens,m,n,group,dtype", [(4, 40, 70, 544, 32, torch.float32), (2, 7, 300, 2048, 128, torch.bfloat16),
+                                                         (3, 70, 600, 1024, 1024, torch.float64), (8, 193, 260, 96, 32, torch.float32)])
+def test_extreme_scales(bits, tokens, m, n, group, dtype, power):
+    layer = list(_random_layer(7 * bits + n, bits, tokens, m, n, group, 0, dtype))
+    scales, zeros, perm, X = layer[1:5]
+    X *= 2.0 ** (-power * 0.6)
+    scales[:, ::3] *= 2.0 ** power
+    if n // group > 3:
+        scales[1::2] *= 2.0 ** power if power < 0 else 1.0
+    X[1::5, perm[20]] *= 2.0 ** 30   # tokens of either kind
+    rows = torch.arange(0, m, 3)
+    assert _rows_off(_apply(layer, bits, group), layer, bits, group, rows) <= _norm(rows)
+
+
+# scales of zero are ordinary
+def test_scales_of_zero():
+    layer = list(_random_layer(3, 4, 40, 70, 544, 32, 0, torch.float32))
+    layer[1][::2, ::2] = 0.0
+    layer[1][:, 5] = 0.0
+    got = _apply(layer, 4, 32)
+    assert (got[:, 5] == 0).all()
+    rows = torch.arange(70)[torch.arange(70) != 5]
+    assert _rows_off(got, layer, 4, 32, rows) <= _norm(rows)
+
+
 # an infinity or a NaN stays in its own token
 def test_tokens_that_are_not_finite():
     layer = list(_random_layer(9, 4, 37, 130, 320, 64, 3, torch.float32))
