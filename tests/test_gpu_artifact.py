@@ -135,8 +135,8 @@ def test_forward_matches_oracle(bits, tokens, dtype, r):
 
 @pytest.mark.parametrize("bits,tokens,m,group", [(4, 19, 256, 128), (3, 32, 132, 32), (2, 45, 64, 512)])
 def test_forward_many_tokens_on_the_matrix_cores(bits, tokens, m, group):
-    """Eight or more tokens go through the float32 MFMA kernel, up to 32 per pass; groups of one chunk,
-    of four, and longer than a workgroup's run of columns; m a multiple of 4 (wide loads in the finish)."""
+    """Tiles of 32 tokens, and one of 64, on the float16 matrix cores; groups of one chunk, of four, and longer than a
+    workgroup's run of columns."""
     rng = np.random.default_rng(1000 + tokens)
     n, bI, bH, r = 1024, 256, 128, 6
     layer = _random_layer(rng, m, n, r, bits, group)
@@ -157,7 +157,7 @@ def test_forward_without_rotation_or_low_rank_is_a_plain_dequantized_product():
     assert np.allclose(got, ref, rtol=0, atol=_gamma(n) * np.max(np.abs(ref)) * 100)
 
 
-@pytest.mark.parametrize("tokens", [4, 45])   # 45 = a matrix-core pass of 32, one of 13: both kernels at full size
+@pytest.mark.parametrize("tokens", [4, 45])   # row by row, and a tile of 64 tokens, at full size
 def test_forward_full_size_attention_projection(tokens):
     rng = np.random.default_rng(99)
     m = n = 4096

@@ -4,50 +4,30 @@ import pytest
 import torch
 
 import paper_2601_19675_amd as ptq
-from test_gpu_forward_tiles import _codes, _random_layer
+from test_gpu_forward_tiles import _apply, _check, _codes, _random_layer, _reference
 
 pytestmark = pytest.mark.gpu
 
 
-def _apply(layer, bits, group):
-    packed, scales, zeros, perm, X, U, V, sigma, s = layer
-    n, r, m = X.shape[1], U.shape[0], scales.shape[1]
-    d = lambda t: t.cuda()  # noqa: E731
-    low = (d(U), d(V), d(sigma), d(s)) if r else (None,) * 4
-    O = torch.full((X.shape[0], m), float("nan"), device="cuda")
-    ptq.ptq_lopro_linear_forward(d(X), d(packed), bits, d(scales), d(zeros), group, d(perm), n, 16, *low, O)
-    torch.cuda.synchronize()
-    return O.cpu().double()
+# tokens of very different sizes, one of zeros, one with an entry 2^20 times the others, which meets a zero weight in some rows,
+# one of equal entries, which a rotation makes sqrt(b_H) times as large (b_H of even and odd powers)
+ANY_SIZE = [(4, 40, 70, 544, torch.float32), (2, 7, 300, 4096, torch.bfloat16), (8, 65, 33, 96, torch.float64), (3, 6, 33, 1152, torch.bfloat16)]
 
 
-def _check(got, layer, bits, group):
-    packed, scales, zeros, perm, X, U, V, sigma, s = layer
-    n, r = X.shape[1], U.shape[0]
-    X64 = X.double()
-    Wt = scales.double().repeat_interleave(group, 0) * (_codes(packed, n, bits) - zeros.double().repeat_interleave(group, 0))
-    Xt = X64[:, perm.long()]
-    want, mag = Xt @ Wt, Xt.abs() @ Wt.abs()
-    if r:
-        u, v = U.view(torch.float8_e4m3fn).double(), V.view(torch.float8_e4m3fn).double()
-        want = want + (((X64 / s) @ v.T) * sigma.double()) @ u
-        mag = mag + (((X64 / s).abs() @ v.abs().T) * sigma.double()) @ u.abs()
-    # the pieces: 2^-23 of an entry or 2^-47 of the token's largest; every sum of float32 rounds once (two products a column, three a
-    # rank, one per group and per split), one after the other at worst
-    bound = (2 * n + 3 * r + 2 * (n // group) + n // 256 + 10) * 2.0 ** -24
-    floor = 2.0 ** -47 * X64.abs().amax(1, keepdim=True) * Wt.abs().sum(0, keepdim=True)
-    err = (got - want).abs()
-    assert (err <= bound * mag + floor + 1e-37).all(), float((err / (bound * mag + floor + 1e-37)).max())
-
-
-# tokens of very different sizes, one of zeros, one with an entry 2^20 times the others, which meets a zero weight in some rows
-@pytest.mark.parametrize("bits,tokens,m,n,dtype", [(4, 40, 70, 544, torch.float32), (2, 7, 300, 4096, torch.bfloat16), (8, 65, 33, 96, torch.float64)])
-def test_tokens_of_any_size(bits, tokens, m, n, dtype):
+def _layer_of_any_size(bits, tokens, m, n, dtype):
     layer = list(_random_layer(bits + n, bits, tokens, m, n, 32, 0, dtype))
     X = layer[4]
     for t in range(tokens):
         X[t] *= 2.0 ** ((t * 11) % 120 - 60)
     X[2] = 0.0
     X[3, 5] = X[3].abs().amax() * 2.0 ** 20
+    X[4] = 255 / 128
+    return layer
+
+
+@pytest.mark.parametrize("bits,tokens,m,n,dtype", ANY_SIZE)
+def test_tokens_of_any_size(bits, tokens, m, n, dtype):
+    layer = _layer_of_any_size(bits, tokens, m, n, dtype)
     _check(_apply(layer, bits, 32), layer, bits, 32)
 
 
@@ -65,12 +45,9 @@ def _zero_weight(layer, bits, group, column, rows):
 
 
 def _rows_off(got, layer, bits, group, rows):
-    """Largest error of a token's outputs in these rows, relative to the norm that they would have with random signs;
-    unrotated, without a low-rank part."""
-    packed, scales, zeros, perm, X = layer[:5]
-    Wt = scales.double().repeat_interleave(group, 0) * (_codes(packed, X.shape[1], bits) - zeros.double().repeat_interleave(group, 0))
-    Xt, Wt = X.double()[:, perm.long()], Wt[:, rows]
-    return float(((got[:, rows] - Xt @ Wt).norm(dim=1) / (Xt.square() @ Wt.square()).sum(1).sqrt()).max())
+    """Largest error of a token's outputs in these rows, relative to the norm that they would have with random signs."""
+    want, _, size = _reference(layer, bits, group)
+    return float(((got - want)[:, rows].norm(dim=1) / size[:, rows].norm(dim=1)).max())
 
 
 def _norm(rows):
@@ -171,18 +148,26 @@ def test_tokens_that_are_not_finite():
 
 # a row that leaves no room in LDS behind it; tokens whose exponents the workspace of a tiny layer cannot hold at once (two whole
 # runs and one token); coefficients by several workgroups, with ranks and tokens past their tiles, and without room for that;
-# several narrow tokens to a workgroup; parts of 1, 2 and 3 chunks past a multiple of four
-@pytest.mark.parametrize("bits,tokens,m,n,group,r,dtype", [
+# two, four and eight narrow tokens to a workgroup, the last run of them whole or not; parts of 1, 2 and 3 chunks past a multiple of
+# four
+EDGES = [
     (4, 2, 9, 20448, 32, 0, torch.float64), (3, 193, 1, 32, 32, 2, torch.float32), (4, 200, 300, 2048, 128, 17, torch.bfloat16),
     (2, 223, 64, 4096, 64, 16, torch.float32), (8, 192, 8, 4096, 4096, 40, torch.bfloat16), (4, 1027, 40, 352, 32, 5, torch.float32),
-    (8, 70, 20, 1120, 32, 0, torch.bfloat16), (3, 5, 257, 864, 96, 16, torch.bfloat16), (2, 33, 4100, 1184, 32, 1, torch.float32)])
+    (8, 70, 20, 1120, 32, 0, torch.bfloat16), (3, 5, 257, 864, 96, 16, torch.bfloat16), (2, 33, 4100, 1184, 32, 1, torch.float32),
+    (4, 2050, 33, 288, 32, 3, torch.float32), (2, 4090, 20, 256, 64, 16, torch.bfloat16), (8, 4096, 9, 96, 32, 0, torch.float64)]
+
+
+@pytest.mark.parametrize("bits,tokens,m,n,group,r,dtype", EDGES)
 def test_edges_of_what_the_launches_share_out(bits, tokens, m, n, group, r, dtype):
     layer = _random_layer(7 * bits + tokens, bits, tokens, m, n, group, r, dtype)
     _check(_apply(layer, bits, group), layer, bits, group)
 
 
 # tokens in runs, the last of which splits its columns over several workgroups
-@pytest.mark.parametrize("bits,tokens,m,n,r", [(4, 133, 1, 512, 0), (3, 585, 1, 4096, 16), (8, 395, 3, 544, 2)])
+LAST_RUNS = [(4, 133, 1, 512, 0), (3, 585, 1, 4096, 16), (8, 395, 3, 544, 2)]
+
+
+@pytest.mark.parametrize("bits,tokens,m,n,r", LAST_RUNS)
 def test_a_last_run_that_splits(bits, tokens, m, n, r):
     layer = _random_layer(11 * bits + tokens, bits, tokens, m, n, 32, r, torch.float32)
     _check(_apply(layer, bits, 32), layer, bits, 32)
