@@ -1449,8 +1449,8 @@ ptq_status launch_forward_tile(const ForwardArgs& a, int tokens, hipStream_t st)
   s = std::min<int64_t>(s, ceil_div(chunks, kFwdRun) * kPartialTokens / tokens);
   s = std::max<int64_t>(1, std::min<int64_t>(s, chunks / kFwdRun));
   p.splits = (int)s;
-  const bool halves = TT == 2 && !many && chunks / s >= 2;
-  if (TT == 1) return halves ? launch_forward_tile_as<BITS, 1, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 1, 1>(a, tokens, p, st);
+  if (TT == 1) return launch_forward_tile_as<BITS, 1, 1>(a, tokens, p, st);
+  const bool halves = !many && chunks / s >= 2;
   return halves ? launch_forward_tile_as<BITS, 2, 2>(a, tokens, p, st) : launch_forward_tile_as<BITS, 2, 1>(a, tokens, p, st);
 }
 
