@@ -10,11 +10,10 @@
 //
 // Two forms of the same sum.  Weights stored in float64 take the float64 MFMA GEMM.  Weights
 // stored in float32 or bfloat16 take the bfloat16-split one: D, W and Hu are rounded to float32
-// once (W in bfloat16 is exact) and kept as three bfloat16 pieces each, the piece products and
-// the running sums over k are float32 on the matrix cores, and everything from the tile's
-// sum_ij A_ij T_ij on is float64.  The roundings are unbiased and independent, so they average
-// out over the m n terms of the trace: measured against the float64 definition the two traces
-// differ by a few parts in 10^9.
+// once (W in bfloat16 is exact) and kept as three bfloat16 pieces each, two in large layers (kTwoPiecesFrom);
+// the piece products and the running sums over k are float32 on the matrix cores, and everything
+// from the tile's sum_ij A_ij T_ij on is float64.  The roundings are unbiased and independent, so they
+// average out over the m n terms of the trace.  Two pieces go in tiles of 256 x 128 where there are enough of them.
 #include "dgemm.h"
 #include "lds_dma.h"
 
@@ -126,7 +125,6 @@ struct SplitArgs {
 };
 
 constexpr int kWideM = 256;   // rows of a tile of the wide form
-constexpr int64_t kWideFrom = 384;   // tiles
 constexpr int kSlab = 16;            // rows of tiles that are worked on together; a multiple of 8
 
 // D and W as bfloat16 pieces, four consecutive k per thread
@@ -659,11 +657,18 @@ static ptq_status launch_split_form(const void* W, ptq_dtype wdt, int64_t ldw, c
   const dim3 gh((unsigned)(np / 32), (unsigned)(np / 32));
   int tiles = (int)((mp / kT) * (np / kT));
   SplitArgs a{Dp, Wp, HuT, (int)mp, (int)np, partial};
-  // 256 x 128 tiles where they fill the chip one and a half times and little of them lies past the last row (whole call, 128 x 128
-  // and 256 x 128: bfloat16 11008 x 4096 1187 and 967 us, 4096 x 4096 429 and 384, 1100 x 6000 (235 tiles) 312 and 406;
-  // float32 4096 x 11008 3548 and 3091, 1100 x 6000 403 and 387, 2048 x 2048 (256) 91 and 100, 300 x 11008 (344) 660 and 752)
-  const int64_t wide_tiles = ceil_div(mp, kWideM) * (np / kT);
-  const bool wide = m * n >= kTwoPiecesFrom && wide_tiles * (wdt == PTQ_BF16 ? 1 : 2) >= kWideFrom && (mp % kWideM == 0 || mp > 4 * kWideM);
+  // 256 x 128 tiles where there are enough for 256 workgroups to end together: the widest take 512 / tiles of the average
+  // workgroup's time.  In bfloat16 from 448 on (whole call, 128 x 128 and 256 x 128 tiles: 2048 x 7168 626 and 596 us, 2304 x 7168
+  // 698 and 638, 4096 x 4096 420 and 382, 11008 x 4096 1187 and 967; below, 2048 x 6144 (384) 487 and 560, 2304 x 6144 (432) 536
+  // and 562, 2560 x 5120 (400) 422 and 426), from 384 where the rows of tiles are twelve or more, whose strips of D and W
+  // neighbours share (3072 x 4096 325 and 315, 3328 x 4096 377 and 340, 5120 x 2560 228 and 209; 2560 x 4096 (320) 296 and 292,
+  // 4096 x 2560 (320) 182 and 184).  In float32 both traces' tiles count: from 384 on (4096 x 11008 3548 and 3091, 1024 x 8192
+  // 720 and 605, 640 x 8192 549 and 513, 3072 x 2048 136 and 132; 640 x 7168 (336) 392 and 420, 2048 x 2048 (256) 89 and 98; a loss
+  // only near 6144 columns, 1408 to 2048 rows, 3 to 7 %).  Seven rows of tiles, whose strips go round the XCDs and are few, lose in
+  // either type (1792 x 4096 in float32 272 and 299, 1792 x 11008 in bfloat16 1410 and 1504).
+  const int64_t wide_rows = ceil_div(mp, kWideM), wide_tiles = wide_rows * (np / kT);
+  const bool wide = m * n >= kTwoPiecesFrom && wide_rows != 7 &&
+                    (wdt == PTQ_BF16 ? wide_tiles >= (wide_rows >= 12 ? 384 : 448) : 2 * wide_tiles >= 384);
   if (wide) tiles = (int)wide_tiles;
   auto run = [&](auto pieces) -> bool {
     constexpr int P = decltype(pieces)::value;

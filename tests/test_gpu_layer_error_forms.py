@@ -7,10 +7,12 @@ import paper_2601_19675_amd as ptq
 pytestmark = pytest.mark.gpu
 
 
-# just enough tiles for the form, a last row of tiles that is half there, rows of tiles past two groups of sixteen, columns past
-# the last tile; and just too few tiles
+# just enough tiles for the form, in each type and number of rows, a last row of tiles that is half there, rows of tiles past two
+# groups of sixteen, columns past the last tile; just too few tiles, and seven rows of them
 @pytest.mark.parametrize("m,n,dtype", [(3100, 3900, torch.bfloat16), (1409, 4100, torch.float32), (6144, 2050, torch.bfloat16),
-                                       (11000, 1155, torch.bfloat16), (2048, 3072, torch.float32), (3072, 3968, torch.bfloat16)])
+                                       (11000, 1155, torch.bfloat16), (2048, 3072, torch.float32), (3072, 3968, torch.bfloat16),
+                                       (2200, 6399, torch.bfloat16), (2304, 6200, torch.bfloat16), (600, 8190, torch.float32),
+                                       (1700, 4100, torch.float32)])
 def test_traces_of_the_wide_form(m, n, dtype):
     g = torch.Generator(device="cuda").manual_seed(m)
     W = (0.02 * torch.randn((m, n), generator=g, device="cuda")).to(dtype)
