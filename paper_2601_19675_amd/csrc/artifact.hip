@@ -1198,7 +1198,7 @@ __global__ __launch_bounds__(256 * KG, 2) void forward_tile_kernel(ForwardArgs a
     static_for<kHalf>([&](auto i_) {
       constexpr int i = decltype(i_)::value;
       mfma(codes[P], Zero{}, i_);
-      if constexpr (i < 2 * TT) read_x(Next{}, One{}, i_);
+      if constexpr (i >= kHalf / 2) read_x(Next{}, One{}, integral_constant<int, i - kHalf / 2>{});   // kHalf / 2 = 2 TT
       if constexpr (i < RT) read_raw(raw[P], After{}, After::value * Lds::kW, i_);
       static_for<kPairs>([&](auto k) { widen(raw[P ^ 1], codes[P ^ 1], integral_constant<int, kPairs * (kHalf + i) + decltype(k)::value>{}); });
       if constexpr (i < kHalf / 2)
