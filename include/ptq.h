@@ -398,8 +398,8 @@ ptq_status ptq_unpack_dequantize(const uint32_t* packed, int64_t m, int64_t n, i
  *        ptq_scaled_r1svd; r = 0 applies the residual alone (U, V, sigma, s may be NULL).
  * X~ and the low-rank coefficients are formed in float64 and rounded to float32; beyond a few tokens
  * X~ is rounded to two float16 pieces of a power of two of the token's own: to 2^-23 of an entry, or 2^-47 of
- * the token's largest |x| where that is more -- a token with more than one entry in 64 below 2^-24 of its
- * largest is rounded to float32.  The pieces' products with the codes are exact; all sums are float32.
+ * the token's largest |x| where that is more -- a token with more than a quarter of its entries below 2^-24
+ * of its largest is rounded to float32.  The pieces' products with the codes are exact and summed in float32.
  * tokens <= 4096; the packed codes are read once per 64 tokens.
  * Workspace: PTQ_OP_LINEAR_FORWARD with m, n, t = tokens and block = r.
  */

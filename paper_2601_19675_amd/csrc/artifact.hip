@@ -462,10 +462,11 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
   __syncthreads();
   // X~ 2^up stays below 2^15: 2^e <= max |x| < 2^(e + 1) (rows of zeros and rows with an infinity or a NaN, whose outputs are
   // NaN, go as they are), and a rotation makes it sqrt(b_H) times as large at most.  Lane tl holds token tl's.
-  // The pieces hold 23 bits of what is no smaller than 2^-kSpan of the largest; a token with more than one entry in 64
-  // below that goes as float32, and the product takes it by itself.  (Up to there, what they lack of a few entries is far below
-  // the rounding of the others.)  Most tokens of heavy-tailed activations have such entries, but few: only the lanes that have
-  // staged one look at theirs again.
+  // The pieces hold 23 bits of what is no smaller than 2^-kSpan of the largest, and 2^-47 of the largest of anything.  That is
+  // below the rounding of the float32 sums unless most of what a row sees is smaller: a token with more than a quarter of its entries
+  // below the line goes as float32, and the product takes it by itself, at some eighteen times the cost (64 x 4096 x 700: 24 us, 425 with
+  // all tokens of that kind; entries up to 2^22 times the others stay).  Most tokens of heavy-tailed activations have such
+  // entries, but few: only the lanes that have staged one look at theirs again.
   int ups = 0;
   uint32_t from[4];   // where a lane's four positions of 16 come from
   if constexpr (PIECES) {
@@ -510,7 +511,7 @@ __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs 
       count = 0;
       read8(kPrepWaves, [&](uint32_t v) { count += (int)v; });
     }
-    if (count > a.n / 64) ups = kPlain;
+    if (count > a.n / 4) ups = kPlain;
     if (seg == 0 && tid < run) a.exponents[token0 + tid] = ups == kPlain ? kPlain : -ups;
     const uint32_t order = (uint32_t)(a.order >> (16 * (lane & 3)));
 #pragma unroll
@@ -817,10 +818,10 @@ constexpr uint64_t code_order() {
 }
 
 template <int BITS>
-constexpr int position_of(int code) {
-  for (int p = 0; p < 16; ++p)
-    if ((int)(code_order<BITS>() >> (4 * p) & 15) == code) return p;
-  return -1;
+constexpr uint64_t code_place() {   // the other way round: code j is at position (place >> 4 j) & 15
+  uint64_t o = 0;
+  for (int p = 0; p < 16; ++p) o |= (uint64_t)p << (4 * (code_order<BITS>() >> (4 * p) & 15));
+  return o;
 }
 
 // Two codes at bit S of a word's halves, minus the zero, as float16 and in the second pieces' unit: put into the mantissa
@@ -918,8 +919,8 @@ struct TileLds {
   static constexpr int w = kTileRing * kX, scale = w + kTileRing * kW, zero = scale + kTileRing * kGrid, all = zero + kTileRing * kGrid;
 };
 
-// One token and a row of the weight over chunks [c_begin, c_end), in float32: for the few tokens that the pieces do
-// not hold (exponent kPlain), and for rows with scales past kScaleLimit.  Bound by the way to memory, chunk by chunk.  The arguments are fetched anew: kept for this, they would fill
+// One token and a row of the weight over chunks [c_begin, c_end), X~ in float32, the sums of eight products in float32 and all
+// others in float64: for the few tokens that the pieces do not hold (exponent kPlain), and for rows with scales past kScaleLimit.  The arguments are fetched anew: kept for this, they would fill
 // the scalar registers of the loop before it.
 template <int BITS>
 __device__ __forceinline__ float plain_product(int token, int exponent, int row, int c_begin, int c_end) {
@@ -928,34 +929,47 @@ __device__ __forceinline__ float plain_product(int token, int exponent, int row,
   const struct { const uint32_t* packed; const float* scales; const uint8_t* zeros; const float* xt; int m, xt_tokens; } a{
       args->packed, args->scales, args->zeros, args->xt, args->m, args->xt_tokens};
   const int gpc = args->group / kChunk;
-  float total = 0.f, acc = 0.f;
+  // four chunks on their way at a time; lane j (and j + 32) holds x of a chunk's column j
+  constexpr int kAhead = 4;
+  constexpr uint64_t place = code_place<BITS>();
+  const int lane = threadIdx.x & 63, column = lane & 31;
+  const int at = (column & 16) + (int)((place >> (4 * (lane & 15))) & 15);
+  double total = 0.0, acc = 0.0;
 #pragma unroll 1
-  for (int c = c_begin; c < c_end; ++c) {
-    const Words<BITS> words = *reinterpret_cast<const Words<BITS>*>(a.packed + ((int64_t)c * a.m + row) * BITS);
-    const int64_t grid = (int64_t)(c / gpc) * a.m + row;
-    const float zero = (float)a.zeros[grid];
-    const float* x = a.xt + ((int64_t)c * a.xt_tokens + token) * kChunk;
-    const _Float16* pieces = reinterpret_cast<const _Float16*>(x);
-    float sum = 0.f;
-    static_for<4>([&](auto quarter) {
-      constexpr int Q = decltype(quarter)::value;
-      float f[8], xv[8];
-      codes_to_float<BITS, Q>(words, f);
-      static_for<8>([&](auto index) {
-        constexpr int j = decltype(index)::value, p = 16 * (Q / 2) + position_of<BITS>((8 * Q + j) & 15);
-        xv[j] = exponent == kPlain ? x[8 * Q + j]
-                                   : (float)ldexp((double)(float)pieces[p] + (double)(float)pieces[kChunk + p] * (1.0 / (1 << kSecond)), exponent);
-      });
+  for (int c0 = c_begin; c0 < c_end; c0 += kAhead) {
+    Words<BITS> words[kAhead];
+    float zero[kAhead], scale[kAhead], xv[kAhead];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sum = fmaf(f[j] - zero, xv[j], sum);
-    });
-    acc += sum;
-    if ((c + 1) % gpc == 0 || c + 1 == c_end) {
-      total = fmaf(a.scales[grid], acc, total);
-      acc = 0.f;
+    for (int i = 0; i < kAhead; ++i) {
+      const int c = min(c0 + i, c_end - 1);
+      const int64_t grid = (int64_t)(c / gpc) * a.m + row;
+      words[i] = *reinterpret_cast<const Words<BITS>*>(a.packed + ((int64_t)c * a.m + row) * BITS);
+      zero[i] = (float)a.zeros[grid];
+      scale[i] = a.scales[grid];
+      const float* x = a.xt + ((int64_t)c * a.xt_tokens + token) * kChunk;
+      const _Float16* pieces = reinterpret_cast<const _Float16*>(x) + at;
+      xv[i] = exponent == kPlain ? x[column]
+                                 : (float)ldexp((double)(float)pieces[0] + (double)(float)pieces[kChunk] * (1.0 / (1 << kSecond)), exponent);
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      if (c0 + i >= c_end) break;
+      static_for<4>([&](auto quarter) {
+        constexpr int Q = decltype(quarter)::value;
+        float f[8], sum = 0.f;
+        codes_to_float<BITS, Q>(words[i], f);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          sum = fmaf(f[j] - zero[i], __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(xv[i]), 8 * Q + j)), sum);
+        acc += (double)sum;
+      });
+      if ((c0 + i + 1) % gpc == 0 || c0 + i + 1 == c_end) {
+        total = fma((double)scale[i], acc, total);
+        acc = 0.0;
+      }
     }
   }
-  return total;
+  return (float)total;
 }
 
 // Largest and, but for zero, smallest scale whose products with the accumulators stay in float32's normal range before a

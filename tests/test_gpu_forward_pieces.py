@@ -89,10 +89,11 @@ def test_tokens_past_the_pieces(bits, tokens, m, n, group, dtype):
     assert _rows_off(got, layer, bits, group, torch.arange(m)) <= _norm(torch.arange(m))
 
 
-# a few entries in a row of 2^-40 times the others are left to the pieces
-def test_a_few_small_entries():
+# some entries of a row 2^-40 times the others are left to the pieces
+@pytest.mark.parametrize("every", [300, 5])
+def test_some_small_entries(every):
     layer = list(_random_layer(77, 4, 40, 70, 2048, 32, 0, torch.float32))
-    layer[4][:, ::300] *= 2.0 ** -40
+    layer[4][:, ::every] *= 2.0 ** -40
     assert _rows_off(_apply(layer, 4, 32), layer, 4, 32, torch.arange(70)) <= _norm(torch.arange(70))
 
 
