@@ -141,14 +141,14 @@ __device__ __forceinline__ float fp16_bits_to_float(uint16_t h) {
 
 // ---- what the products read: X~ and the low-rank coefficients, one launch -------------------------
 // X~ = X P Q in float64, written as float32 (xt[chunk][token][32]) for the few-token product, as two float16 pieces
-// ([2][32] in the same place) for the tiles, and, in float64,
+// ([2][32] in the same place) for the tiles (but for tokens that these do not hold), and, in float64,
 //   y[t][k] = sigma_k * sum_j V[k][j] x[t][j] / s[j].
 // The first workgroups take y: a token and four ranks each, or 16 tokens x 16 ranks on the float64 matrix instruction from
 // kPrepMany tokens on.  The others rotate: a workgroup stages the rows of a token (several, where they are narrow and many)
 // in LDS and transforms 256-column chunks, a wave each (a row goes to several workgroups while there are few tokens).
 // For a few tokens both parts are chains of latencies; for many the rotation is vector instructions (some 200 per
 // chunk).  512 tokens x 11008 columns, 16 ranks: 30 us as float32 with 2 tokens x 16 ranks of y per workgroup on the vector
-// unit (the rotation alone 15), now 24 with the pieces (18); 4000 x 1024 34 -> 22.
+// unit (the rotation alone 15), now 26 with the pieces and the look at each token's small entries (24 without it); 4000 x 1024 34 -> 22.
 struct PrepArgs {
   const void* X;
   int64_t ldx;
@@ -403,7 +403,8 @@ template <int DT, bool ALIGNED, bool PIECES>
 __global__ __launch_bounds__(kPrepThreads, 4) void forward_prep_kernel(PrepArgs a) {
   extern __shared__ __attribute__((aligned(16))) char prep_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = (int)__builtin_amdgcn_readfirstlane(tid >> 6);
-  // all arguments at once: fetched where they are used, one after the other, they cost a few tokens' launch half a microsecond
+  // all arguments at once: fetched where they are used they are a chain of trips to memory (with those of the product for a few
+  // tokens, 2 x 4096 x 4096 14.4 -> 13.8 us, 3 x 4096 x 4096 17.1 -> 16.6; the forms with pieces spill 52 scalar registers for it and are no slower)
   asm volatile("" ::"s"(a.X), "s"(a.ldx), "s"(a.tokens), "s"(a.n), "s"(a.perm), "s"(a.b_I), "s"(a.xt), "s"(a.run_lg), "s"(a.segments),
                "s"(a.segment), "s"(a.order), "s"((int)a.roomy), "s"(a.lg), "s"(a.scale), "s"(a.V), "s"(a.s), "s"(a.r), "s"(a.y), "s"(a.coeff_tiles));
   if ((int)blockIdx.x < a.coeff_tiles) {
@@ -775,11 +776,12 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int co
 // token's own power of two: it is off by at most 2^-23 of itself, or 2^-47 of the token's largest |x| where that is more (an
 // entry 2^23 times the others leaves them theirs).  The second pieces meet codes times 2^-12, which are raised to the codes
 // themselves for the first pieces by a multiplication per pair: without it the second bound would be
-// 2^-35, and a massive entry that meets a zero weight would cost its row the bits of all others.  The products are exact
+// 2^-35, and a massive entry that meets a zero weight would cost its row the bits of all others (the tile kernel 3 % faster).  What
+// two pieces do not hold, and scales that would leave float32's range in the token's unit, take plain_product.  The products are exact
 // in float32 and only its sums round; with two of them per weight fewer do than with the three truncated bfloat16
 // pieces that hold a float32 exactly, and the distance from the float64 product is smaller everywhere it was measured
-// (512 to 11008 columns, groups of 64 and 128, 2 to 8 bits: 0.63 to 1.35e-7 of its norm, 0.65 to 1.50e-7 with three
-// pieces): the second pieces' products, 2^-11 of the others, go first.  The group's scale is applied to the
+// (512 to 11008 columns, 5 to 4000 tokens, groups of 64 and 128, 2 to 8 bits, 110 sizes: 0.62 to 1.83e-7 of its norm, 0.66 to
+// 1.93e-7 with three pieces): the second pieces' products, 2^-11 of the others, go first.  The group's scale is applied to the
 // accumulators where a group ends, the token's power of two at the end.
 //
 // A workgroup takes 32 TT tokens x 128 RT rows of the weight, a wave 32 TT x 32 RT, and walks over chunks of
@@ -789,10 +791,11 @@ __global__ __launch_bounds__(256) void forward_rows_kernel(ForwardArgs a, int co
 // One barrier per chunk, in the middle of its MFMAs; what a chunk needs was requested four chunks before, straight into LDS.
 // Between two MFMAs a wave issues a pair or two of the next chunk's codes, a fragment read or a request, in the order
 // written down: 2 waves per SIMD, 64 tokens, at most 250 registers.
-// Bound: MFMA and what a wave issues beside it (16 MFMAs, about 65 other instructions and, every group, 128).
-// Kernel alone, 512 tokens x 4096 x 11008, 4 bits: 92 us (three bfloat16 pieces, split where they were staged: 150).
-// Whole calls with 16 ranks, three pieces -> now: 512 x 4096 x 11008 171 -> 119 us, 2048 x 11008 x 4096 564 -> 363,
-// 4000 x 999 x 1024 71 -> 50, 128 x 4096 x 4096 45 -> 37, 32 x 11008 x 4096 45 -> 28, 8 x 4096 x 4096 21 -> 18.4.
+// Bound: MFMA and what a wave issues beside it (per chunk 16 MFMAs, some 70 other vector and 80 scalar instructions, 12 LDS reads;
+// every group, 128 multiply-adds).  Kernel alone, 512 tokens x 4096 x 11008, 3 bits: 100 us (three bfloat16 pieces, split where
+// they were staged: 150).
+// Whole calls with 16 ranks, 4 bits, three pieces -> now: 512 x 4096 x 11008 166 -> 121 us, 2048 x 11008 x 4096 562 -> 378,
+// 4000 x 999 x 1024 71 -> 50, 128 x 4096 x 4096 46 -> 38, 32 x 11008 x 4096 45 -> 29, 8 x 4096 x 4096 21 -> 19.3.
 template <int BITS> struct HalfWords { uint32_t w[BITS == 2 ? 1 : (BITS == 8 ? 4 : 2)]; };
 
 // two bfloat16 numbers from floats whose low halves are zero (or are to be dropped)
