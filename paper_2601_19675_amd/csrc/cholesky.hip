@@ -7,7 +7,7 @@
 // through the reversal.  Both are done by one recursion on the diagonal block
 // [o, o+s) of G, which returns X = L^{-1} of that block:
 //
-//     split s = s1 + s2
+//     s up to kStepsMax: 128 columns at a time (run_steps);  above, split s = s1 + s2
 //     X11           = rec(G11)
 //     L21           = G21 X11^T                       (GEMM, X11 triangular)
 //     G22          -= L21 L21^T                       (SYRK, lower tiles)  } one launch
@@ -15,8 +15,8 @@
 //     X22           = rec(G22)
 //     X21           = -X22 T
 //
-// Every off-diagonal step is a float64 MFMA GEMM; only blocks of at most 128
-// columns are factored and inverted inside one workgroup (in LDS).  L itself
+// Every off-diagonal step is a float64 MFMA GEMM; blocks of 128 columns are
+// factored and inverted inside one workgroup (in LDS).  L itself
 // is never needed again, so only X is kept: it is stored directly in U through
 // the reversal, X(i,j) = U[n-1-i][n-1-j].  L21^T is parked in the (otherwise
 // unused) upper triangle of the work matrix, L21 X11 in the dead G21 block.
@@ -57,25 +57,23 @@ __global__ __launch_bounds__(1024) void diag_stats_kernel(const double* __restri
   }
 }
 
-// G = J H_d J (lower triangle, zeros above), and U cleared.
+// G = J H_d J (lower triangle) and U's lower triangle cleared; the other halves are written before they are read.
 __global__ __launch_bounds__(256) void build_work_kernel(const double* __restrict__ H, int64_t ldh,
                                                          int n, const double* __restrict__ scal,
                                                          double* __restrict__ G, double* __restrict__ U,
                                                          int64_t ldu) {
   const int i = blockIdx.y;
   const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  double g = 0.0;
-  if (j <= i) {
-    const int hi = n - 1 - i, hj = n - 1 - j;  // hi <= hj: upper triangle of H
-    g = H[(int64_t)hi * ldh + hj];
-    if (i == j) {
-      if (g == 0.0) g = 1.0;
-      g += scal[0];
-    }
+  if (j > i) return;
+  const int hi = n - 1 - i, hj = n - 1 - j;  // hi <= hj: upper triangle of H
+  double g = H[(int64_t)hi * ldh + hj];
+  if (i == j) {
+    if (g == 0.0) g = 1.0;
+    g += scal[0];
+  } else {
+    U[(int64_t)i * ldu + j] = 0.0;
   }
   G[(int64_t)i * n + j] = g;
-  U[(int64_t)i * ldu + j] = 0.0;
 }
 
 // ---- leaf: X = inverse of the Cholesky factor of G[o:o+s, o:o+s], s <= 128 ---
@@ -227,9 +225,8 @@ __device__ __forceinline__ void panel_stage(PanelRegs& R, double nc, double& rl,
 }
 #undef PTQ_CHAIN
 
-__global__ __launch_bounds__(kLeafThreads) void leaf_kernel(const double* __restrict__ G, int n, int o, int s,
-                                                            double* __restrict__ U, int64_t ldu, int32_t* info) {
-  extern __shared__ double lds[];
+__device__ __forceinline__ void leaf_block(const double* __restrict__ G, int n, int o, int s, double* __restrict__ U,
+                                           int64_t ldu, int32_t* info, double* lds) {
   double* S = lds;                                    // [128][129]
   double* XD = lds + kLeaf * kLeafP;                  // [16][129]: X_kk(i, j) at XD[i * 129 + 16 k + j]
   double* DUMP = XD + 16 * kLeafP;                    // [256]
@@ -488,6 +485,386 @@ __global__ __launch_bounds__(kLeafThreads) void leaf_kernel(const double* __rest
   store_rows(nb >= 2 ? 16 * (nb - 2) : 0, sp, tid, kLeafThreads);
 }
 
+// ---- a diagonal block of up to kStepsMax columns, 128 columns at a time -----------------
+// What the leaf does with sub-blocks of 16, once more with blocks of 128.  Per block column k, in three launches:
+//
+//   step      workgroup 0: the leaf of block k.  All others: the update with block column k-1 of every block
+//             below row k-1,  G_ij -= L_i,k-1 L_j,k-1^T  (i >= j >= k, without (k, k))  and
+//             T'_ij -= L_i,k-1 X_k-1,j  (i >= k, j < k; T' = -T starts at j = k-1)
+//   panel     L_ik = G_ik X_kk^T for i > k;  X_kj = X_kk T'_kj for j < k
+//   diagonal  G_k+1,k+1 -= L_k+1,k L_k+1,k^T
+//
+// The leaf is a chain of pivots on one compute unit (33 us); the flops of a step run beside it on the others, so up to
+// a few thousand columns a step costs little more than its leaf.  The recursion below took a leaf and one to seven small
+// latency-bound launches per 128 columns in turn: n = 4096 2553 -> 1850 us, n = 512 in a layer's calls 212 -> 172.
+// The storage is the recursion's: L^T in the mirror block of G, T' in the dead block of G, X in U through the
+// reversal.  T' is subtracted from once per step after a sum of 128 terms that starts from zero, so what rounds at the
+// size of the entry is n / 128 operations (distance from the float64 product of torch at n = 4096: 1.6e-15, the
+// recursion 2.5e-15).
+struct Steps {
+  double* G;      // work matrix, n x n, ld = n
+  double* U;      // output, X reversed: X(i, j) = U[n-1-i][n-1-j]
+  int ldu, n, o, s;
+  int32_t* info;
+  __device__ __forceinline__ double* g(int i, int j) const { return G + (int64_t)(o + i) * n + o + j; }
+  __device__ __forceinline__ double* x(int i, int j) const {
+    return U + (int64_t)(n - 1 - o - i) * ldu + (n - 1 - o - j);
+  }
+};
+
+typedef double f64x2u __attribute__((vector_size(16), aligned(8)));   // 16-byte global access at 8-byte alignment
+typedef double f64x2 __attribute__((vector_size(16)));
+
+// The update's tiles: 128 x 64 per workgroup of eight waves (4 x 2, 32 x 32 each), 32 columns of the contraction per
+// k-tile, two LDS stages.  Bound by the float64 matrix pipe at the clock the power limit leaves (12 us a tile of 128
+// columns with all compute units busy, 10.2 at 2.05 GHz).  128 x 128 tiles are as fast per flop, but a step of a
+// 4096-column block has 1.2 to 4 tiles of 128 x 64 per compute unit, and half of the larger ones is lost in the last
+// round more often (n = 4096: 1861 us; 1913).
+constexpr int kUpBK = 32, kUpN = 64;
+constexpr int kUpPA = kLeaf + 2, kUpPB = kUpN + 2;                  // LDS pitches of a k row
+constexpr int kUpStage = kUpBK * (kUpPA + kUpPB);                   // doubles
+static_assert(2 * kUpStage * sizeof(double) <= kLeafLdsBytes, "the update's stages live in the leaf's LDS");
+
+// (one k-step: the next one's fragment reads, then MM MFMAs with one request or one LDS store after each of the first ones)
+template <int I, int MM, int NV, int NW>
+__device__ __forceinline__ void update_order() {
+  if constexpr (I < MM) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if constexpr (I < NV) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    if constexpr (I < NW) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+    update_order<I + 1, MM, NV, NW>();
+  }
+}
+
+// C(i, j) -= sum over the 128 columns of block column kp of L(i, k) * B(k, j) on the tiles first, first + stride, ... of
+// the block rows kp + 1, kp + 2, ... (block row bi has columns up to its diagonal block, the first without that one):
+// C = G and B = L^T right of block column kp, C = T' and B = X up to it (in it T' starts from zero).
+__device__ __forceinline__ void update_tiles(const Steps& st, int kp, int first, int stride, int total, double* lds) {
+  constexpr int TM = 2, BN = kUpN, PA = kUpPA, PB = kUpPB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int p0 = kp * kLeaf;
+  const int n8 = st.n * 8, u8 = st.ldu * 8;            // bytes of a row
+  // Buffer loads: the tile in the descriptor, the k-tile in the scalar offset.  Operands lie inside their matrix whole
+  // (columns past the block are the next row's entries: at most n - 1 + 127 in row n - 2); C may not in a ragged tile,
+  // so its rows are in the checked offset and read as zero behind the matrix.
+  // A thread has a pair of columns in every 8th (A, 128 columns) or 16th (B, 64) k row.
+  constexpr int RA = 8, NA = kUpBK / RA, RB = 16, NB = kUpBK / RB;
+  const int pra = tid & 63, kra = tid >> 6, prb = tid & 31, krb = tid >> 5;
+  const int offa = kra * n8 + 16 * pra, fwd = krb * n8 + 16 * prb, bwd = (RB - 1 - krb) * u8 + 16 * prb;
+  const int offc = lq * n8 + 8 * l16;
+  auto rest_of_g = [&](const double* p) {
+    const int64_t left = ((int64_t)st.n * st.n - (p - st.G)) * 8;   // (a wave's part of a ragged tile may begin behind the end)
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), 0, (int)(left < 0 ? 0 : left < 0x7fffffff ? left : 0x7fffffff),
+                                             0x00020000);
+  };
+  struct Tile {
+    int i0, j0;
+    bool back;              // B rows run backwards in memory
+    __amdgpu_buffer_rsrc_t a, b;
+  };
+  auto tile_at = [&](int q) {
+    constexpr int per = kLeaf / BN;
+    int bi = kp + 1, c = per * (kp + 1);
+    while (q >= c) {
+      q -= c;
+      ++bi;
+      c = per * (bi + 1);
+    }
+    const int i0 = __builtin_amdgcn_readfirstlane(bi * kLeaf), j0 = __builtin_amdgcn_readfirstlane(q * BN);
+    Tile x{i0, j0, j0 < p0 + kLeaf, rest_of_g(st.g(p0, i0)), rest_of_g(st.g(p0, j0))};   // A(i, k) = A[k n + i]
+    // X(p0 .. p0 + 127, j0 .. j0 + BN - 1) lies in U whole; its lowest address is that of its last entry
+    if (x.back)
+      x.b = __builtin_amdgcn_make_buffer_rsrc(st.x(p0 + kLeaf - 1, j0 + BN - 1), 0, (kLeaf - 1) * u8 + 8 * BN, 0x00020000);
+    return x;
+  };
+  f64x2 ra[NA], rb[NB];
+  auto request = [&](const Tile& x, int t) {
+#pragma unroll
+    for (int q = 0; q < NA; ++q)
+      ra[q] = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(x.a, offa, (kUpBK * t + RA * q) * n8, 0));
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int k0 = kUpBK * t + RB * q;
+      rb[q] = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(x.b, x.back ? bwd : fwd,
+                                                                            x.back ? (kLeaf - RB - k0) * u8 : k0 * n8, 0));
+    }
+  };
+  auto park = [&](int stage) {   // (in the order of memory; the reader knows which way B runs)
+    double* s = lds + stage * kUpStage;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) *reinterpret_cast<f64x2*>(s + (kra + RA * q) * PA + 2 * pra) = ra[q];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) *reinterpret_cast<f64x2*>(s + kUpBK * PA + (krb + RB * q) * PB + 2 * prb) = rb[q];
+  };
+  if (first >= total) return;
+  Tile cur = tile_at(first);
+  request(cur, 0);
+  park(0);
+  request(cur, 1);
+  __syncthreads();
+  constexpr int kTiles = kLeaf / kUpBK, kSteps = kUpBK / 4;
+  for (int q = first; q < total; q += stride) {
+    const Tile nxt = q + stride < total ? tile_at(q + stride) : cur;
+    const int rows = min(kLeaf, st.s - cur.i0) - wm * 16 * TM, cols = min(BN, st.s - cur.j0) - wn * 32;
+    const __amdgpu_buffer_rsrc_t C = rest_of_g(st.g(cur.i0, cur.j0) + (int64_t)wm * 16 * TM * st.n + wn * 32);
+    const int frag_a = lq * PA + wm * 16 * TM + l16;
+    const int j = wn * 32 + l16;
+    const int frag_b0 = kUpBK * PA + lq * PB + (cur.back ? BN - 1 - j : j), frag_b1 = cur.back ? frag_b0 - 16 : frag_b0 + 16;
+    f64x4 acc[TM][2];
+    double c[TM][4][2];
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[m][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) {
+      // k-tile t is in LDS stage t & 1, t + 1 in registers
+      const double* s = lds + (t & 1) * kUpStage;
+      double a[2][TM], b[2][2];
+      auto frags = [&](int ks, int slot) {
+#pragma unroll
+        for (int m = 0; m < TM; ++m) a[slot][m] = s[frag_a + 4 * ks * PA + 16 * m];
+        b[slot][0] = s[frag_b0 + 4 * ks * PB];
+        b[slot][1] = s[frag_b1 + 4 * ks * PB];
+      };
+      frags(0, 0);
+#pragma unroll
+      for (int ks = 0; ks < kSteps; ++ks) {
+        const int slot = ks & 1;
+        if (ks + 1 < kSteps) frags(ks + 1, slot ^ 1);
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+          for (int b2 = 0; b2 < 2; ++b2)
+            acc[m][b2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[slot][m], b[slot][b2], acc[m][b2], 0, 0, 0);
+        if (ks == 1) park((t + 1) & 1);
+        if (ks == 3) {
+          if (t + 2 < kTiles) request(cur, t + 2);
+          else request(nxt, t + 2 - kTiles);
+        }
+        // (the stores, requests and loads of C take two k-steps each: ks = 1, 2; 3, 4; 5, 6)
+        if (ks == 5) {   // a quarter of C
+#pragma unroll
+          for (int r = 0; r < TM; ++r) {
+            const int e = t * TM + r, m = e >> 2, rr = e & 3;
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2)
+              c[m][rr][b2] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(C, offc + (16 * m + 4 * rr) * n8 + 128 * b2, 0, 0));
+          }
+        }
+      }
+      constexpr int MM = 2 * TM, E = NA + NB;
+      static_assert(E <= 2 * MM && 2 * TM <= MM, "");
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, 0, 0>();                                  // ks = 0
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, 0, (E < MM ? E : MM)>();                  // 1
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, 0, (E < MM ? 0 : E - MM)>();              // 2
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, (E < MM ? E : MM), 0>();                  // 3
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, (E < MM ? 0 : E - MM), 0>();              // 4
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, MM, 0>();                                 // 5
+      __builtin_amdgcn_sched_group_barrier(0x100, TM + 2, 0);
+      update_order<0, MM, 0, 0>();                                  // 6
+      update_order<0, MM, 0, 0>();                                  // 7
+      __syncthreads();
+    }
+    const bool diag = cur.i0 <= cur.j0, fresh = cur.j0 >= p0 && cur.back;
+    const int below = cur.i0 + wm * 16 * TM + lq - (cur.j0 + wn * 32 + l16);   // row minus column of the lane's first entry
+    double* out = st.g(cur.i0 + wm * 16 * TM + lq, cur.j0 + wn * 32 + l16);
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * m + 4 * r;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const bool ok = i + lq < rows && 16 * b + l16 < cols && (!diag || below + i - 16 * b >= 0);
+          if (ok) out[(int64_t)i * st.n + 16 * b] = (fresh ? 0.0 : c[m][r][b]) - acc[m][b][r];
+        }
+      }
+    cur = nxt;
+  }
+}
+
+// Workgroup 0: the leaf of block k.  The others: the update with block column k - 1 of everything but the
+// leaf's block.
+__global__ __launch_bounds__(kLeafThreads) void step_kernel(Steps st, int k, int tiles) {
+  extern __shared__ double lds[];
+  if (blockIdx.x == 0) {
+    leaf_block(st.G, st.n, st.o + k * kLeaf, min(kLeaf, st.s - k * kLeaf), st.U, st.ldu, st.info, lds);
+    return;
+  }
+  // consecutive workgroups go to the eight dies in turn: where all 256 are there, a die takes neighbouring tiles
+  const int b = blockIdx.x, x = b & 7;
+  const int first = gridDim.x == 256 ? (x == 0 ? (b >> 3) - 1 : 32 * x - 1 + (b >> 3)) : b - 1;
+  update_tiles(st, k - 1, first, (int)gridDim.x - 1, tiles, lds);
+}
+
+// 32 x 32 tile of a product over at most 128 terms, both operands whole in LDS, one memory latency.
+// element(o, k) = p[o so + k sk]; o clamped to `count`, terms from kvalid on are zero.
+constexpr int kStripKP = kLeaf + 2, kStripOP = 34;
+constexpr int kStripDoubles = kLeaf * kStripOP;        // (the larger of the two layouts)
+static_assert(32 * kStripKP <= kStripDoubles, "");
+// A thread has eight pairs of neighbours in memory: terms (KFAST; BACK: they run backwards) or rows.
+enum class Strip { kTerms, kTermsBack, kRows };
+template <Strip S>
+__device__ __forceinline__ void strip_load(const double* p, int64_t so, int64_t sk, int count, int kvalid, int kmax, f64x2 (&v)[8]) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int e = tid + 256 * u;
+    if constexpr (S == Strip::kRows) {
+      const int k = e >> 4, o = 2 * (e & 15);
+      if (k < kmax) v[u] = *reinterpret_cast<const f64x2u*>(p + o + (int64_t)min(k, kvalid - 1) * sk);
+    } else {
+      const int o = min(e >> 6, count - 1), k = 2 * (e & 63);
+      const double* q = p + (int64_t)o * so;
+      if (k < kmax) {
+        if (kvalid < kmax) {         // (the last block of a width that is no multiple of 32: a pair may straddle its end)
+          v[u][0] = q[(int64_t)min(k, kvalid - 1) * sk];
+          v[u][1] = q[(int64_t)min(k + 1, kvalid - 1) * sk];
+        } else if constexpr (S == Strip::kTerms) {
+          v[u] = *reinterpret_cast<const f64x2u*>(q + k);
+        } else {
+          const f64x2 w = *reinterpret_cast<const f64x2u*>(q - k - 1);
+          v[u] = f64x2{w[1], w[0]};
+        }
+      }
+    }
+  }
+}
+template <Strip S>
+__device__ __forceinline__ void strip_park(const f64x2 (&v)[8], int kvalid, int kmax, double* lds) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int e = tid + 256 * u;
+    const bool rows = S == Strip::kRows;
+    const int o = rows ? 2 * (e & 15) : e >> 6, k = rows ? e >> 4 : 2 * (e & 63);
+    const f64x2 w = {k < kvalid ? v[u][0] : 0.0, (rows ? k : k + 1) < kvalid ? v[u][1] : 0.0};
+    if (k < kmax) *reinterpret_cast<f64x2*>(lds + (rows ? k * kStripOP + o : o * kStripKP + k)) = w;
+  }
+}
+template <Strip SA, Strip SB>
+__device__ __forceinline__ f64x4 strip_product(const double* pa, int64_t soa, int64_t ska, int counta, const double* pb,
+                                               int64_t sob, int64_t skb, int countb, int kvalid, int kmax, double* lds) {
+  double* la = lds;
+  double* lb = lds + kStripDoubles;
+  {
+    f64x2 va[8], vb[8];
+    strip_load<SA>(pa, soa, ska, counta, kvalid, kmax, va);
+    strip_load<SB>(pb, sob, skb, countb, kvalid, kmax, vb);
+    strip_park<SA>(va, kvalid, kmax, la);
+    strip_park<SB>(vb, kvalid, kmax, lb);
+  }
+  __syncthreads();
+  constexpr bool AK = SA != Strip::kRows, BK = SB != Strip::kRows;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
+  const double* fa = la + (AK ? (wm * 16 + l16) * kStripKP + lq : lq * kStripOP + wm * 16 + l16);
+  const double* fb = lb + (BK ? (wn * 16 + l16) * kStripKP + lq : lq * kStripOP + wn * 16 + l16);
+  constexpr int da = AK ? 4 : 4 * kStripOP, db = BK ? 4 : 4 * kStripOP;
+  f64x4 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int k = 0; k < kmax; k += 32) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      acc[q & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[q * da], fb[q * db], acc[q & 3], 0, 0, 0);
+    fa += 8 * da;
+    fb += 8 * db;
+  }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// After the leaf of block k: L_ik^T = X_kk G_ik^T for the rows i below it, X_kj = X_kk T'_kj for j < k.
+__global__ __launch_bounds__(256) void panel_kernel(Steps st, int k, int strips_l) {
+  extern __shared__ double lds[];
+  const int d0 = k * kLeaf;
+  const int w = min(kLeaf, st.s - d0);
+  const int b = blockIdx.x;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
+  // consecutive workgroups go to the eight dies in turn: the four that share a strip of G or T' meet in one L2
+  const int strip = (b >> 5) * 8 + (b & 7);
+  const int m0 = 32 * (3 - ((b >> 3) & 3));            // the longest first
+  const int mi = wm * 16 + lq, nj = wn * 16 + l16;
+  if (strip < strips_l) {
+    const int r0 = d0 + kLeaf + 32 * strip;            // rows of G
+    const int count = min(32, st.s - r0);
+    const f64x4 acc = strip_product<Strip::kTermsBack, Strip::kTerms>(st.x(d0 + m0, d0), -(int64_t)st.ldu, -1, 32, st.g(r0, d0),
+                                                                      st.n, 1, count, kLeaf, m0 + 32, lds);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (nj < count) *st.g(d0 + m0 + mi + 4 * r, r0 + nj) = acc[r];
+  } else {
+    const int c0 = 32 * (strip - strips_l);
+    if (m0 >= w || c0 >= d0) return;
+    const int count = min(32, w - m0);
+    const f64x4 acc = strip_product<Strip::kTermsBack, Strip::kRows>(st.x(d0 + m0, d0), -(int64_t)st.ldu, -1, count, st.g(d0, c0),
+                                                                     1, st.n, 32, min(w, m0 + 32), m0 + 32, lds);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (mi + 4 * r < count) *st.x(d0 + m0 + mi + 4 * r, c0 + nj) = acc[r];
+  }
+}
+
+// G_dd -= L_dk L_dk^T (lower triangle), d = k + 1: what the next leaf waits for.
+__global__ __launch_bounds__(256) void diagonal_kernel(Steps st, int k) {
+  extern __shared__ double lds[];
+  const int d0 = k * kLeaf, e0 = d0 + kLeaf;
+  const int w = min(kLeaf, st.s - e0);
+  int bi = 0, bj = blockIdx.x;
+  while (bj > bi) bj -= ++bi;
+  const int i0 = 32 * bi, j0 = 32 * bj;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
+  const int i = i0 + wm * 16 + lq, j = j0 + wn * 16 + l16;
+  double c[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c[r] = *st.g(e0 + min(i + 4 * r, w - 1), e0 + min(j, w - 1));
+  const f64x4 acc = strip_product<Strip::kRows, Strip::kRows>(st.g(d0, e0 + i0), 1, st.n, 32, st.g(d0, e0 + j0), 1, st.n, 32,
+                                                              kLeaf, kLeaf, lds);
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (i + 4 * r < w && j <= i + 4 * r) *st.g(e0 + i + 4 * r, e0 + j) = c[r] - acc[r];
+}
+
+// Above this many columns the steps' updates outgrow the leaf (an update with 128 columns moves 16 bytes of C per 256
+// flops) and the recursion's products over thousands of columns are the better ones.  Whole call in steps / halves by
+// the recursion: 4100 columns 1888 / 2328 us, 5000 2956 / 3290, 6016 4329 / 4363, 8192 9275 / 8309.
+constexpr int kStepsMax = 5120;
+bool run_steps(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t stream) {
+  const Steps st{G, U, ldu, n, o, s, info};
+  constexpr int strip_lds = 2 * kStripDoubles * (int)sizeof(double);
+  if (!lds_opt_in<step_kernel>((int)kLeafLdsBytes) || !lds_opt_in<panel_kernel>(strip_lds) ||
+      !lds_opt_in<diagonal_kernel>(strip_lds))
+    return false;
+  const int N = (int)ceil_div(s, kLeaf);
+  for (int k = 0; k < N; ++k) {
+    // block rows k .. N-1 of the lower triangle, without the block (k, k)
+    const int blocks = k ? (N - k) * (N + k + 1) / 2 - 1 : 0;
+    const int tiles = kLeaf / kUpN * blocks;
+    step_kernel<<<1 + (tiles < 255 ? tiles : 255), kLeafThreads, kLeafLdsBytes, stream>>>(st, k, tiles);
+    const int below = s - (k + 1) * kLeaf;
+    const int strips_l = below > 0 ? (int)ceil_div(below, 32) : 0, strips = strips_l + 4 * k;
+    if (strips > 0) panel_kernel<<<32 * (int)ceil_div(strips, 8), 256, strip_lds, stream>>>(st, k, strips_l);
+    if (below > 0) {
+      const int t = (int)ceil_div(below < kLeaf ? below : kLeaf, 32);
+      diagonal_kernel<<<t * (t + 1) / 2, 256, strip_lds, stream>>>(st, k);
+    }
+  }
+  return true;
+}
+
 // ---- the four GEMM steps of one recursion node -------------------------------
 // Each step describes its operands as strided views for the tile at (i0, j0):
 // A(i, k) and B(k, j) with i, j tile-local and k counted from the block start.
@@ -703,33 +1080,20 @@ bool launch_tiles2(const Op1& op1, int M1, int N1, const Op2& op2, int M2, int N
   return true;
 }
 
-// Tile shape by problem size, as measured: 128 x 128 once there are enough tiles to fill the
-// chip twice over; up to about a 1500-wide node 32 x 32 tiles (there the k loops are short and
-// bound by the latency of their loads, whatever the tile: many small workgroups hide it best);
-// 64 x 64 between.
-inline int tile_class(int M, int N) {
-  if (ceil_div(M, 128) * ceil_div(N, 128) >= 512) return 2;
-  if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return 0;
-  return 1;
-}
+// Tile shape by problem size, as measured: 128 x 128 once there are enough tiles to fill the chip twice over, 64 x 64
+// below (the halves of a recursion node have more than 2500 rows).
+inline bool large_tiles(int M, int N) { return ceil_div(M, 128) * ceil_div(N, 128) >= 512; }
 
 template <class Op>
 bool launch_node(const Op& op, int M, int N, hipStream_t st, int max_cus = 0) {
-  switch (tile_class(M, N)) {
-    case 2: return launch_tiles<4, 4, Op>(op, M, N, st, max_cus);          // one workgroup per compute unit
-    case 1: return launch_tiles<2, 2, Op>(op, M, N, st, 3 * max_cus);      // three
-    default: return launch_tiles<1, 1, Op>(op, M, N, st, 4 * max_cus);
-  }
+  if (large_tiles(M, N)) return launch_tiles<4, 4, Op>(op, M, N, st, max_cus);   // one workgroup per compute unit
+  return launch_tiles<2, 2, Op>(op, M, N, st, 3 * max_cus);                      // three
 }
 
 template <class Op1, class Op2>
 bool launch_node2(const Op1& op1, int M1, int N1, const Op2& op2, int M2, int N2, hipStream_t st) {
-  const int c1 = tile_class(M1, N1), c2 = tile_class(M2, N2);
-  switch (c1 < c2 ? c1 : c2) {
-    case 2: return launch_tiles2<4, 4, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
-    case 1: return launch_tiles2<2, 2, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
-    default: return launch_tiles2<1, 1, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
-  }
+  if (large_tiles(M1, N1) && large_tiles(M2, N2)) return launch_tiles2<4, 4, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
+  return launch_tiles2<2, 2, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
 }
 
 // ---- helper streams for work that is off the critical chain -----------------------------------
@@ -792,17 +1156,14 @@ inline int first_part(int s) { return ((int)ceil_div(s, kLeaf) / 2) * kLeaf; }
 // this block have been enqueued on st.
 bool recurse(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t st, Side* side, int depth,
              const std::function<bool()>* on_first_half = nullptr) {
-  if (s <= kLeaf) {
-    leaf_kernel<<<1, kLeafThreads, kLeafLdsBytes, st>>>(G, n, o, s, U, ldu, info);
-    return true;
-  }
+  if (s <= kStepsMax) return run_steps(G, U, ldu, n, o, s, info, st);
   const int s1 = first_part(s);
   const int s2 = s - s1;
   const Node nd{G, U, ldu, n, o, s1, s2, o + s1};
-  if (side && depth < kMaxDepth && tile_class(s2, s1) == 2) {
+  if (side && depth < kMaxDepth && large_tiles(s2, s1)) {
     // a large node.  Early part: beside the second half of the first child's recursion
     const int sA = s1 > kLeaf ? first_part(s1) : 0;
-    const bool early = sA > 0 && tile_class(s2, sA) == 2;
+    const bool early = s1 > kStepsMax && large_tiles(s2, sA);
     const std::function<bool()> start_early = [&]() -> bool {
       const Node part{G, U, ldu, n, o, sA, s2, o + s1};
       return hipEventRecord(side->early_fork[depth], st) == hipSuccess &&
@@ -852,7 +1213,6 @@ ptq_status cholesky_launch(const double* H, int64_t ldh, int64_t n, double damp,
   double* G = static_cast<double*>(ws);
   double* scal = reinterpret_cast<double*>(static_cast<char*>(ws) +
                                            align_up((size_t)n * (size_t)n * sizeof(double), 256));
-  if (!lds_opt_in<leaf_kernel>((int)kLeafLdsBytes)) return PTQ_ERR_HIP;
   diag_stats_kernel<<<1, 1024, 0, st>>>(H, ldh, (int)n, damp, dead_mask, scal, info);
   PTQ_HIP_CHECK_LAUNCH();
   dim3 g((unsigned)ceil_div(n, 256), (unsigned)n);
@@ -860,7 +1220,7 @@ ptq_status cholesky_launch(const double* H, int64_t ldh, int64_t n, double damp,
   PTQ_HIP_CHECK_LAUNCH();
   // the helper stream only where a node is large enough to use it (the top node is the largest)
   const int top1 = first_part((int)n);
-  Side* side = (n > kLeaf && tile_class((int)n - top1, top1) == 2) ? side_for_device() : nullptr;
+  Side* side = (n > kStepsMax && large_tiles((int)n - top1, top1)) ? side_for_device() : nullptr;
   bool ok;
   if (side) {
     std::lock_guard<std::mutex> hold(side->lock);
