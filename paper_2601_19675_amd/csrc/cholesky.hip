@@ -555,6 +555,7 @@ __device__ __forceinline__ void update_tiles(const Steps& st, int kp, int first,
   const int pra = tid & 63, kra = tid >> 6, prb = tid & 31, krb = tid >> 5;
   const int offa = kra * n8 + 16 * pra, fwd = krb * n8 + 16 * prb, bwd = (RB - 1 - krb) * u8 + 16 * prb;
   const int offc = lq * n8 + 8 * l16;
+  const int blocks = (st.s + kLeaf - 1) / kLeaf;
   auto rest_of_g = [&](const double* p) {
     const int64_t left = ((int64_t)st.n * st.n - (p - st.G)) * 8;   // (a wave's part of a ragged tile may begin behind the end)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), 0, (int)(left < 0 ? 0 : left < 0x7fffffff ? left : 0x7fffffff),
@@ -566,12 +567,32 @@ __device__ __forceinline__ void update_tiles(const Steps& st, int kp, int first,
     __amdgpu_buffer_rsrc_t a, b;
   };
   auto tile_at = [&](int q) {
+    // The first block row, then groups of four: down the group before the next column, so that the 32 neighbouring tiles
+    // of a die are 4 x 8 and share their operands in its L2.  Where a group's rows are longer than its first: row by row.
     constexpr int per = kLeaf / BN;
-    int bi = kp + 1, c = per * (kp + 1);
-    while (q >= c) {
-      q -= c;
+    int bi = kp + 1;
+    if (q >= per * bi) {
+      q -= per * bi;
       ++bi;
-      c = per * (bi + 1);
+      int h, c;
+      for (;;) {
+        h = min(4, blocks - bi);
+        c = per * (bi + 1);
+        const int all = h * c + per * (h * (h - 1) / 2);
+        if (q < all) break;
+        q -= all;
+        bi += 4;
+      }
+      if (q < h * c) {
+        bi += q % h;
+        q /= h;
+      } else {
+        q -= h * c;
+        int u = 1;
+        while (q >= per * u) q -= per * u++;
+        bi += u;
+        q += c;
+      }
     }
     const int i0 = __builtin_amdgcn_readfirstlane(bi * kLeaf), j0 = __builtin_amdgcn_readfirstlane(q * BN);
     Tile x{i0, j0, j0 < p0 + kLeaf, rest_of_g(st.g(p0, i0)), rest_of_g(st.g(p0, j0))};   // A(i, k) = A[k n + i]
