@@ -64,17 +64,19 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
   const double* __restrict__ U = a.U;
 
   // LDS carve-up: partial sums of four waves at a time (reused as the state tile),
-  // the mini-block errors, the mini-block's 16 x 16 diagonal block of U and its
-  // reciprocal pivots (double-buffered), group min / max, and the code tile.
+  // the mini-block's errors and integers, its 16 x 16 diagonal block of U and its
+  // reciprocal pivots (double-buffered), group min / max and grids, and the code tile.
   double* P = lds;                                  // MT = 1: [4][16][bw]; else [rows][bw]
   double* S = lds;                                  // [rows][bw + 1]   (aliases P)
-  double* Em = lds + state_doubles(MT, a.bw);       // [16 k][rows]
-  double* Qm = Em + 16 * kRows;                     // [16 k][rows + 1]: the mini-block's dequantized values
-  double* Ud = Qm + 16 * (kRows + 1);               // [2][16][16]
+  double* Em = lds + state_doubles(MT, a.bw);       // [2][16 k][rows]
+  double* Km = Em + 32 * kRows;                     // [2][16 k][rows + 1]: code minus zero-point
+  double* Ud = Km + 32 * (kRows + 1);               // [2][16][16]
   double* Id = Ud + 512;                            // [2][16]
   double* gmin = Id + 32;                           // [rows]
   double* gmax = gmin + kRows;                      // [rows]
-  uint8_t* Ct = reinterpret_cast<uint8_t*>(gmax + kRows);  // [rows][bw]
+  double* Gs = gmax + kRows;                        // [2][rows]: scale of the last two groups
+  double* Gz = Gs + 2 * kRows;                      // [2][rows]: their zero-points
+  uint8_t* Ct = reinterpret_cast<uint8_t*>(Gz + 2 * kRows);  // [rows][bw]
 
   if constexpr (MT == 1) {
   // ---- phase 1: acc = E[rows, 0:i1] * U[0:i1, block], k split over the waves
@@ -358,33 +360,116 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
   }
   __syncthreads();
 
-  // ---- phase 2: 16-column mini-blocks
+  // ---- phase 2: 16-column mini-blocks.  Bound by the walk's dependent chain.  One wave walks and does nothing else; what
+  // the others do for it -- the next diagonal block, the errors pushed onto the tiles to come -- and what becomes of its
+  // results -- codes, dequantized values, errors for the later blocks, row sums -- runs beside the walk, one mini-block
+  // later where it needs the results.  A mini-block in cycles, 512 x 512, with all of it in the walking wave's own
+  // stream and now: requests and the group's start of its grid 630 / 290, state and pivots from LDS 390 / 150, the walk
+  // 3350 / 2480, push 600 - 860 / 620, stores and barriers 600 / 420.  Whole calls 512 x 512 114 -> 92 us, 4096 x 4096
+  // 1804 -> 1692, 11008 x 4096 4098 -> 3859, 4096 x 11008 9760 -> 9492; the same bits.  (Raised priority of the walking
+  // wave and of the push that it waits for: 9554.)
+  typedef double f64x2 __attribute__((vector_size(16)));
   const double maxq = (double)((1 << a.bits) - 1);
   const int ng = a.n / a.group;
-  double scale = 1.0, rscale = 1.0, zero = 0.0, klo = 0.0, khi = 0.0, err2 = 0.0;  // lanes 0..15 of wave 0
-  constexpr int kUpd = (NT + kWaves - 1) / kWaves;  // tiles one wave may have to update per mini-block
+  const int role = __builtin_amdgcn_readfirstlane(wave);
+  double scale = 1.0, rscale = 1.0, zero = 0.0, klo = 0.0, khi = 0.0;   // lanes 0 .. rows - 1 of wave 0
+  double err2 = 0.0;                                                    // ... of wave 1
+  // Up to eight tiles: wave t pushes the errors of every mini-block before it onto tile t of the state, which it keeps in
+  // registers until it is walked (one row tile; with more the registers run out: 8192 x 4096 2970 -> 3210 us).  Only the
+  // tile that is walked next has to be done before the walk goes on; the others follow beside it.  More tiles than
+  // waves: all waves push, tile by tile, between the walks.
+  constexpr bool kOwn = NT <= kWaves, kKeep = kOwn && MT == 1;
+  constexpr int kUpd = kOwn ? 1 : (NT - 1 + kWaves - 1) / kWaves;  // tiles one wave may have to update per mini-block
+  double idr[16], sd[15];   // reciprocal pivots of the next mini-block to walk, its entries of U right of the diagonal
+  auto fetch_pivots = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) idr[j] = Id[buf * 16 + j];
+#pragma unroll
+    for (int j = 0; j < 15; ++j) sd[j] = Ud[buf * 256 + j * 16 + j + 1];
+  };
+  // results of mini-block mbp (grid gp) leave: errors and values 128 contiguous bytes per 16 lanes
+  auto finish_mini_block = [&](int mbp, int gp) {
+    const int c0 = 16 * mbp, gcol = a.i1 + c0;
+    const double* em = Em + (mbp & 1) * 16 * kRows;
+    const double* km = Km + (mbp & 1) * 16 * (kRows + 1);
+    if (tid >= 256) {
+#pragma unroll
+      for (int pass = 0; pass < MT; ++pass) {
+        const int e = tid - 256 + 256 * pass;          // Em is [16 k][rows]: e = k * rows + row
+        const int k = e / kRows, rr = e - k * kRows;
+        a.errT[(int64_t)(gcol + k) * a.mpad + row0 + rr] = em[e];
+        const int r = e >> 4, j = e & 15;
+        const double kv = km[j * (kRows + 1) + r];
+        Ct[r * a.bw + c0 + j] = (uint8_t)(kv + Gz[gp * kRows + r]);
+        if (a.Wq && row0 + r < a.m) a.Wq[(int64_t)(row0 + r) * a.n + gcol + j] = Gs[gp * kRows + r] * kv;
+      }
+    } else if (role == 1 && lane < kRows) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double e = em[j * kRows + lane];
+        err2 = fma(e, e, err2);
+      }
+    }
+  };
+  auto state_of = [&](int t, int mt, int r) -> double& {
+    return S[(kRowTile * mt + 4 * r + (lane >> 4)) * sp + 16 * t + (lane & 15)];
+  };
+  double sv[MT][4], ub[kUpd][4];
+  auto fetch_state = [&](int t) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sv[mt][r] = state_of(t, mt, r);
+  };
+  auto put_state = [&](int t) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) state_of(t, mt, r) = sv[mt][r];
+  };
+  // the rows of U that push a mini-block's errors onto this wave's tiles
+  auto fetch_push = [&](int mb) {
+#pragma unroll
+    for (int q = 0; q < kUpd; ++q) {
+      const int t = kOwn ? role : mb + 1 + role + kWaves * q;
+      const int tc = t < nt ? t : nt - 1;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        ub[q][kk] = U[(int64_t)(a.i1 + 16 * mb + 4 * kk + (lane >> 4)) * a.ldu + a.i1 + 16 * tc + (lane & 15)];
+    }
+  };
+  auto push = [&](int mb, int q, int t, bool last) {   // the errors of mini-block mb onto tile t, which goes back to LDS
+    if constexpr (!kKeep) fetch_state(t);
+    const double* em = Em + (mb & 1) * 16 * kRows;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const double av = em[(4 * kk + (lane >> 4)) * kRows + kRowTile * mt + (lane & 15)];
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(av, ub[q][kk], d, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sv[mt][r] -= d[r];
+    }
+    if (!kKeep || last) put_state(t);
+  };
+  if (role == 0) fetch_pivots(0);
+  else if (kKeep && role < nt) fetch_state(role);
+  int gp = 0;
+  int group_left = 0, group_at = a.i1 / a.group;   // columns to the next group start, groups before it (blocks begin with one)
   for (int mb = 0; mb < nt; ++mb) {
     const int c0 = 16 * mb;           // first column of the mini-block inside the block
     const int gcol = a.i1 + c0;       // ... and in the layer
     const int buf = mb & 1;
-    const bool gstart = (gcol % a.group) == 0;
-    // operands that do not depend on this mini-block's results: the next diagonal
-    // block and the rows of U that push this mini-block's errors onto later tiles
-    double ud_next = 0.0, id_next = 0.0;
-    if (mb + 1 < nt) {
-      if (tid < 256) ud_next = U[(int64_t)(gcol + 16 + (tid >> 4)) * a.ldu + gcol + 16 + (tid & 15)];
-      // (the reciprocals by a wave that does not walk, not by a kernel of their own: 512 x 512 115 -> 114 us)
-      if (tid >= 256 && tid < 272) id_next = 1.0 / U[(int64_t)(gcol + 16 + tid - 256) * (a.ldu + 1)];
+    const bool gstart = group_left == 0;
+    const int gp_before = gp, g_now = group_at;
+    if (gstart) {
+      if (mb > 0) gp ^= 1;
+      group_left = a.group;
+      ++group_at;
     }
-    double ub[kUpd][4];
-#pragma unroll
-    for (int q = 0; q < kUpd; ++q) {
-      const int t = mb + 1 + wave + kWaves * q;
-      const int tc = t < nt ? t : nt - 1;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        ub[q][kk] = U[(int64_t)(gcol + 4 * kk + (lane >> 4)) * a.ldu + a.i1 + 16 * tc + (lane & 15)];
-    }
+    group_left -= 16;
     if (gstart && !a.static_groups) {
       // min / max of the group's current values: 16 lanes per row, 16 rows per pass of the first four waves
       if (tid < 256) {
@@ -410,16 +495,14 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
       }
       __syncthreads();
     }
-    if (tid < kRows) {
-      const int r = tid;
+    if (role == 0 && lane < kRows) {
+      const int r = lane;
       const bool rlive = row0 + r < a.m;
       if (gstart && a.static_groups) {
-        const int64_t at = (int64_t)(rlive ? row0 + r : 0) * ng + gcol / a.group;
+        const int64_t at = (int64_t)(rlive ? row0 + r : 0) * ng + g_now;
         scale = (double)a.scales[at];
         rscale = 1.0 / scale;
         zero = (double)a.zeros[at];
-        klo = -zero;
-        khi = maxq - zero;
       } else if (gstart) {
         double lo = gmin[r], hi = gmax[r];
         if (lo == hi) {
@@ -430,12 +513,16 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
         scale = (double)sf;
         rscale = 1.0 / scale;
         zero = rint(-lo / scale);
+        if (rlive) {
+          a.scales[(int64_t)(row0 + r) * ng + g_now] = sf;
+          a.zeros[(int64_t)(row0 + r) * ng + g_now] = (uint8_t)zero;
+        }
+      }
+      if (gstart) {
         klo = -zero;
         khi = maxq - zero;
-        if (rlive) {
-          a.scales[(int64_t)(row0 + r) * ng + gcol / a.group] = sf;
-          a.zeros[(int64_t)(row0 + r) * ng + gcol / a.group] = (uint8_t)zero;
-        }
+        Gs[gp * kRows + r] = scale;
+        Gz[gp * kRows + r] = zero;
       }
       // The walk is one dependent chain of float64 operations per column; everything that does not
       // depend on it is taken out of its way: the reciprocal pivots and the entries of U that carry
@@ -443,21 +530,24 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
       // effect on the columns further on is applied one step later, next to the following column's
       // chain, as independent operations that fill its latency (left to itself the compiler gathers
       // them in front of each column as one more chain; the scheduling barrier keeps a step's
-      // instructions in their step); and the results go to LDS only -- other waves write them out.
-      double w[16], idr[16], sd[15], rp[16], rc[16];
+      // instructions in their step); and of the results only the error and the integer go to LDS.
+      double w[16], rp[16], rc[16];
       const double* ud = Ud + buf * 256;
+      double* em = Em + buf * 16 * kRows + r;
+      double* km = Km + buf * 16 * (kRows + 1) + r;
 #pragma unroll
       for (int j = 0; j < 16; ++j) w[j] = S[r * sp + c0 + j];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) idr[j] = Id[buf * 16 + j];
-#pragma unroll
-      for (int j = 0; j < 15; ++j) sd[j] = ud[j * 16 + j + 1];
       double ep = 0.0;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        // the rest of row j of U, for the next step
+        // the rest of row j of U, for the next step (pairs at 16 bytes: the offset of an 8-byte pair read ends at 2 KB,
+        // and an address of its own for every read costs the walk two issue slots each)
 #pragma unroll
-        for (int c = j + 2; c < 16; ++c) rc[c] = ud[j * 16 + c];
+        for (int c = (j + 2) & ~1; c < 16; c += 2) {
+          const f64x2 two = *reinterpret_cast<const f64x2*>(ud + j * 16 + c);
+          rc[c] = two[0];
+          rc[c + 1] = two[1];
+        }
         // column j - 1 onto the columns after this one: nothing below waits for these
         if (j > 0) {
 #pragma unroll
@@ -473,67 +563,59 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
         const double k = fmin(fmax(rint(x), klo), khi);
         const double e = fma(-scale, k, w[j]) * idr[j];
         if (j < 15) w[j + 1] = fma(-e, sd[j], w[j + 1]);
-        err2 = fma(e, e, err2);
-        Ct[r * a.bw + c0 + j] = (uint8_t)(k + zero);
-        Em[j * kRows + r] = e;
-        Qm[j * (kRows + 1) + r] = scale * k;
+        em[j * kRows] = e;
+        km[j * (kRows + 1)] = k;
         ep = e;
 #pragma unroll
         for (int c = j + 2; c < 16; ++c) rp[c] = rc[c];
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    if (role != 0) {
+      if (kOwn && mb > 0 && !gstart && role > mb && role < nt) push(mb - 1, 0, role, false);   // (what the next walk did not wait for)
+      double ud_next = 0.0, id_next = 0.0;
+      if (mb + 1 < nt) {   // the next diagonal block and its reciprocal pivots
+        if (tid >= 256) ud_next = U[(int64_t)(gcol + 16 + ((tid - 256) >> 4)) * a.ldu + gcol + 16 + (tid & 15)];
+        if (role == 3 && lane < 16) id_next = U[(int64_t)(gcol + 16 + lane) * (a.ldu + 1)];
+      }
+      if (!kOwn || (role > mb && role < nt)) fetch_push(mb);
+      if (mb > 0) finish_mini_block(mb - 1, gp_before);
+      if (mb + 1 < nt) {
+        if (tid >= 256) Ud[(buf ^ 1) * 256 + tid - 256] = ud_next;
+        if (role == 3 && lane < 16) Id[(buf ^ 1) * 16 + lane] = 1.0 / id_next;
+      }
+    } else if (!kOwn) {
+      fetch_push(mb);
+    }
     __syncthreads();
-    // push the 16 new errors onto the later tiles of the block
+    if constexpr (kOwn) {
+      // onto the tile that is walked next; onto all of them if the next walk begins with a look at its group
+      if (role == mb + 1 || (group_left == 0 && role > mb)) {
+        if (role < nt) push(mb, 0, role, true);
+      }
+    } else {
 #pragma unroll
-    for (int q = 0; q < kUpd; ++q) {
-      const int t = mb + 1 + wave + kWaves * q;
-      if (t < nt) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          f64x4 d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            const double av = Em[(4 * kk + (lane >> 4)) * kRows + kRowTile * mt + (lane & 15)];
-            d = __builtin_amdgcn_mfma_f64_16x16x4f64(av, ub[q][kk], d, 0, 0, 0);
-          }
-          double sv[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sv[r] = S[(kRowTile * mt + 4 * r + (lane >> 4)) * sp + 16 * t + (lane & 15)];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) S[(kRowTile * mt + 4 * r + (lane >> 4)) * sp + 16 * t + (lane & 15)] = sv[r] - d[r];
-        }
+      for (int q = 0; q < kUpd; ++q) {
+        const int t = mb + 1 + role + kWaves * q;
+        if (t < nt) push(mb, q, t, true);
       }
     }
-    // the mini-block's errors (for the later blocks) and dequantized values leave through the
-    // upper four waves, 128 contiguous bytes per 16 lanes
-    if (tid >= 256) {
-#pragma unroll
-      for (int pass = 0; pass < MT; ++pass) {
-        const int e = tid - 256 + 256 * pass;          // Em is [16 k][rows]: e = k * rows + row
-        const int k = e / kRows, rr = e - k * kRows;
-        a.errT[(int64_t)(gcol + k) * a.mpad + row0 + rr] = Em[e];
-        const int r = e >> 4, j = e & 15;
-        if (a.Wq && row0 + r < a.m) a.Wq[(int64_t)(row0 + r) * a.n + gcol + j] = Qm[j * (kRows + 1) + r];
-      }
-    }
-    if (mb + 1 < nt) {
-      if (tid < 256) Ud[(buf ^ 1) * 256 + tid] = ud_next;
-      if (tid >= 256 && tid < 272) Id[(buf ^ 1) * 16 + tid - 256] = id_next;
-    }
+    if (role == 0 && mb + 1 < nt) fetch_pivots(buf ^ 1);
     __syncthreads();
   }
+  finish_mini_block(nt - 1, gp);
+  __syncthreads();
 
   // ---- outputs of the block
   for (int e = tid; e < kRows * a.bw; e += kThreads) {
     const int r = e / a.bw, c = e - r * a.bw;
     if (row0 + r < a.m) a.codes[(int64_t)(row0 + r) * a.n + a.i1 + c] = Ct[r * a.bw + c];
   }
-  if (a.row_err2 && tid < kRows && row0 + tid < a.m) {
+  if (a.row_err2 && role == 1 && lane < kRows && row0 + lane < a.m) {
     if (a.i1 == 0)
-      a.row_err2[row0 + tid] = err2;
+      a.row_err2[row0 + lane] = err2;
     else
-      a.row_err2[row0 + tid] += err2;
+      a.row_err2[row0 + lane] += err2;
   }
 }
 
@@ -569,7 +651,7 @@ __global__ __launch_bounds__(kThreads) void quant_layer_kernel(QuantArgs a, int 
 
 size_t block_lds_bytes(int mt, int bw) {
   const int rows = kRowTile * mt;
-  return (size_t)(state_doubles(mt, bw) + 16 * rows + 16 * (rows + 1) + 512 + 32 + 2 * rows) * sizeof(double) +
+  return (size_t)(state_doubles(mt, bw) + 32 * rows + 32 * (rows + 1) + 512 + 32 + 6 * rows) * sizeof(double) +
          (size_t)rows * bw;
 }
 
