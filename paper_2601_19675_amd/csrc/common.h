@@ -67,12 +67,13 @@ inline bool lds_opt_in(int bytes) {
 // Lane exchanges inside a row of 16 lanes by data-parallel primitives: register moves, no trip
 // through the LDS crossbar (which a shuffle of a float64 makes twice).  Applied in this order --
 // pairs, half quads, half mirror, mirror -- with an associative, commutative operation after
-// each, every lane ends up with the result over 2, 4, 8, 16 lanes.
+// each, every lane ends up with the result over 2, 4, 8, 16 lanes.  (All these patterns read lanes of the row itself;
+// saying that lanes outside it read as zero spares setting the destination first.)
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
   const unsigned long long bits = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)bits, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(bits >> 32), CTRL, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)bits, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(bits >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 constexpr int kDppSwapPairs = 0xB1;      // quad_perm [1, 0, 3, 2]

@@ -14,14 +14,17 @@
 // codebook in LDS.  Every lane then knows the group's errors and applies them to the later columns of the
 // mini-block itself, so the eight waves walk their two rows each without a barrier between groups.
 // Bound: float64 vector instructions of the losses (18 and a selection per entry of 4 weights) and the
-// chain from a group's losses to the next group's values.  4096 x 4096, 256 x 4: 4.13 -> 3.39 ms; 64 x 2: 4.12 -> 2.49
-// (before: lane permutes through the LDS crossbar, the entry taken out of registers, conditional loads, and room for 256
-// entries in every lane whatever K).
+// chain from a group's losses to the next group's values.  4096 x 4096, 256 x 4: 4.13 -> 3.39 -> 3.11 ms; 64 x 2: 4.12 ->
+// 2.62 -> 2.49 (first: lane permutes through the LDS crossbar, the entry taken out of registers, conditional loads, and
+// room for 256 entries in every lane whatever K; then: U and addresses spilled over the walk, an address for every
+// pair read of U, entries tested against K one by one).  A group of the former now takes 1800 cycles.
 #include "lazy_update.h"
 #include "rotation.h"
 
 namespace ptq {
 namespace {
+
+typedef double f64x2 __attribute__((vector_size(16)));
 
 constexpr int kRows = 16;       // rows per workgroup
 constexpr int kThreads = 512;
@@ -62,13 +65,32 @@ __device__ __forceinline__ double half_wave_min(double v) {
   return fmin(even, odd);
 }
 __device__ __forceinline__ int half_wave_min(int v) {
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppSwapPairs, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppSwapHalfQuads, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppSwapPairs, 0xf, 0xf, true));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppSwapHalfQuads, 0xf, 0xf, true));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xf, 0xf, true));
+  v = min(v, __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xf, 0xf, true));
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
   const u32x2 p = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
   return min((int)p[0], (int)p[1]);
+}
+
+// Blocks of up to 128 columns: the block of U itself, upper tiles of 16 x 16, is staged in LDS before the walk.  Fetched
+// per mini-block it had to be held in registers that the walk does not have: spilled, every request waited for
+// the one before, 5000 cycles before and 2500 after the 7400 of a mini-block's walk at 4096 x 4096, 256 x 4.
+// (Where a lane holds fewer entries nothing spills and the staging costs more than it gives: 64 x 2 2490 us, staged 2604.)
+template <int NT, int D, int SLOTS, bool RAGGED>
+constexpr bool vq_staged() { return NT <= 8 && SLOTS * D >= 32 && !RAGGED; }
+// tile (r, c), r <= c, in row order; their number; the r and c of number i
+__host__ __device__ constexpr int upper_tile(int nt, int r, int c) { return r * nt - r * (r - 1) / 2 + c - r; }
+__host__ __device__ constexpr int upper_tiles(int nt) { return nt * (nt + 1) / 2; }
+__device__ constexpr int upper_tile_row(int nt, int i) {
+  int r = 0;
+  while (i >= nt - r) i -= nt - r++;
+  return r;
+}
+__device__ constexpr int upper_tile_column(int nt, int i) {
+  const int r = upper_tile_row(nt, i);
+  return i - upper_tile(nt, r, r) + r;
 }
 
 // RAGGED: a last block whose width is no multiple of 16 (n need only be one of D).  Its last mini-block is walked as far as the
@@ -95,7 +117,10 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   double* Ud = Qm + 272;                            // [2][16][16] diagonal block of U
   double* Id = Ud + 512;                            // [2][16] reciprocal pivots
   double* Cb = Id + 32;                             // [32 SLOTS][D] the codebook
-  uint8_t* It = reinterpret_cast<uint8_t*>(Cb + kMaxEntries * D);  // [16][bw / D] indices of the block
+  constexpr bool kStaged = vq_staged<NT, D, SLOTS, RAGGED>();
+  double* Ut = Cb + kMaxEntries * D;                // kStaged: [tiles][16][16] the block's upper tiles of U
+  double* Ia = Ut + (kStaged ? 256 * upper_tiles(NT) : 0);                 // kStaged: [16 NT] reciprocal pivots
+  uint8_t* It = reinterpret_cast<uint8_t*>(Ia + (kStaged ? 16 * NT : 0));  // [16][bw / D] indices of the block
 
   // ---- phase 1: acc = E[rows, 0:i1] * U[0:i1, block], k split over the waves
   f64x4 acc[NT];
@@ -130,6 +155,25 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
     typename StoredType<DT>::type wraw[NP];
     uint8_t draw[NP];
     int at[NP];   // row * 256 + column of the block
+    // (256 threads to a tile of U, two tiles at a time)
+    constexpr int NU = kStaged ? (upper_tiles(NT) + 1) / 2 : 1;
+    double uraw[NU];
+    const int half = __builtin_amdgcn_readfirstlane(tid >> 8);
+    auto tile_of = [&](int p, int& tr, int& tc) {
+      const int last = upper_tiles(NT) - 1, i1 = 2 * p + 1 < last ? 2 * p + 1 : last;
+      tr = half ? upper_tile_row(NT, i1) : upper_tile_row(NT, 2 * p);
+      tc = half ? upper_tile_column(NT, i1) : upper_tile_column(NT, 2 * p);
+    };
+    if constexpr (kStaged) {
+#pragma unroll
+      for (int p = 0; p < NU; ++p) {
+        int tr, tc;
+        tile_of(p, tr, tc);
+        tr = min(tr, nt - 1);   // (a narrower block: a tile that it has, not stored)
+        tc = min(tc, nt - 1);
+        uraw[p] = U[(int64_t)(a.i1 + 16 * tr + ((tid >> 4) & 15)) * a.ldu + a.i1 + 16 * tc + (tid & 15)];
+      }
+    }
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int e = min(tid + kThreads * p, kRows * a.bw - 1);
@@ -151,8 +195,18 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
 #pragma unroll
     for (int p = 0; p < NP; ++p)
       if (tid + kThreads * p < kRows * a.bw) S[(at[p] >> 8) * sp + (at[p] & 255)] = sv[p];
-    if (tid < 256) Ud[tid] = U[(int64_t)in_layer(a.i1 + (tid >> 4)) * a.ldu + in_layer(a.i1 + (tid & 15))];
-    if (tid < 16) Id[tid] = invd[in_layer(a.i1 + tid)];
+    if constexpr (kStaged) {
+#pragma unroll
+      for (int p = 0; p < NU; ++p) {
+        int tr, tc;
+        tile_of(p, tr, tc);
+        if (tc < nt) Ut[256 * upper_tile(NT, tr, tc) + (tid & 255)] = uraw[p];
+      }
+      if (tid < a.bw) Ia[tid] = invd[a.i1 + tid];
+    } else {
+      if (tid < 256) Ud[tid] = U[(int64_t)in_layer(a.i1 + (tid >> 4)) * a.ldu + in_layer(a.i1 + (tid & 15))];
+      if (tid < 16) Id[tid] = invd[in_layer(a.i1 + tid)];
+    }
     for (int e = tid; e < 32 * SLOTS * D; e += kThreads) Cb[e] = e < a.K * D ? (double)a.codebook[e] : 0.0;
   }
   __syncthreads();
@@ -161,11 +215,12 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   // this lane's codebook entries, k = l32 + 32 s, in registers from here on (after the lazy update, whose
   // accumulators need the room)
   const int l32 = lane & 31;
+  // (one that does not exist is infinitely far away: its loss is no smaller than any)
   double cb[SLOTS][D];
 #pragma unroll
   for (int s = 0; s < SLOTS; ++s)
 #pragma unroll
-    for (int i = 0; i < D; ++i) cb[s][i] = Cb[(l32 + 32 * s) * D + i];
+    for (int i = 0; i < D; ++i) cb[s][i] = l32 + 32 * s < a.K ? Cb[(l32 + 32 * s) * D + i] : __builtin_inf();
   const int r = 2 * wave + (lane >> 5);   // the row of this half-wave
   double err2 = 0.0;
   constexpr int kUpd = (NT + kWaves - 1) / kWaves;
@@ -175,21 +230,39 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
     const int gcol = a.i1 + c0;
     const int buf = mb & 1;
     double ud_next = 0.0, id_next = 0.0;
-    if (mb + 1 < nt) {
-      if (tid < 256) ud_next = U[(int64_t)in_layer(gcol + 16 + (tid >> 4)) * a.ldu + in_layer(gcol + 16 + (tid & 15))];
-      if (tid < 16) id_next = invd[in_layer(gcol + 16 + tid)];
-    }
     double ub[kUpd][4];
+    if constexpr (!kStaged) {
+      if (mb + 1 < nt) {
+        if (tid < 256) ud_next = U[(int64_t)in_layer(gcol + 16 + (tid >> 4)) * a.ldu + in_layer(gcol + 16 + (tid & 15))];
+        if (tid < 16) id_next = invd[in_layer(gcol + 16 + tid)];
+      }
 #pragma unroll
-    for (int q = 0; q < kUpd; ++q) {
-      const int t = mb + 1 + wave + kWaves * q;
-      const int tc = t < nt ? t : nt - 1;
+      for (int q = 0; q < kUpd; ++q) {
+        const int t = mb + 1 + wave + kWaves * q;
+        const int tc = t < nt ? t : nt - 1;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        ub[q][kk] = U[(int64_t)in_layer(gcol + 4 * kk + (lane >> 4)) * a.ldu + in_layer(a.i1 + 16 * tc + (lane & 15))];
+        for (int kk = 0; kk < 4; ++kk)
+          ub[q][kk] = U[(int64_t)in_layer(gcol + 4 * kk + (lane >> 4)) * a.ldu + in_layer(a.i1 + 16 * tc + (lane & 15))];
+      }
     }
     {
-      const double* ud = Ud + buf * 256;
+      const double* ud = kStaged ? Ut + 256 * upper_tile(NT, mb, mb) : Ud + buf * 256;
+      const double* id = kStaged ? Ia + 16 * mb : Id + buf * 16;
+      // entries [from, to) right of column c of row `row` of the block into x[from ..], 16 bytes at a time: the offset of an
+      // 8-byte pair read ends at 2 KB, and most of the rows would take an address of their own
+      auto fetch_row = [&](double* x, int from, int to, int row, int c) {
+        if constexpr (D % 2 == 0) {
+#pragma unroll
+          for (int k = from & ~1; k < to; k += 2) {
+            const f64x2 two = *reinterpret_cast<const f64x2*>(ud + row * 16 + c + k);
+            if (k >= from) x[k] = two[0];
+            x[k + 1] = two[1];
+          }
+        } else {
+#pragma unroll
+          for (int k = from; k < to; ++k) x[k] = ud[row * 16 + c + k];
+        }
+      };
       double w[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) w[j] = S[r * sp + c0 + j];
@@ -201,9 +274,8 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
         double T[D][D], inv[D];
 #pragma unroll
         for (int i = 0; i < D; ++i) {
-          inv[i] = Id[buf * 16 + g * D + i];
-#pragma unroll
-          for (int k = i + 1; k < D; ++k) T[i][k] = ud[(g * D + i) * 16 + g * D + k];
+          inv[i] = id[g * D + i];
+          fetch_row(T[i], i + 1, D, g * D + i, g * D);
         }
         // losses of this lane's entries, ascending index: a later entry wins only if strictly smaller
         double best = __builtin_inf();
@@ -221,7 +293,7 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
             for (int kx = i + 1; kx < D; ++kx) rem[kx] = fma(-e, T[i][kx], rem[kx]);
             loss = fma(e, e, loss);
           }
-          const bool take = k < a.K && loss < best;
+          const bool take = loss < best;
           best = take ? loss : best;
           bidx = take ? k : bidx;
         }
@@ -248,10 +320,14 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
           }
         }
         // the group's errors onto the later columns of the mini-block
+        {
+          double u[16];
 #pragma unroll
-        for (int c = (g + 1) * D; c < 16; ++c) {
+          for (int i = 0; i < D; ++i) {   // (per column the rows in order)
+            fetch_row(u, (g + 1) * D, 16, g * D + i, 0);
 #pragma unroll
-          for (int i = 0; i < D; ++i) w[c] = fma(-e[i], ud[(g * D + i) * 16 + c], w[c]);
+            for (int c = (g + 1) * D; c < 16; ++c) w[c] = fma(-e[i], u[c], w[c]);
+          }
         }
         if (l32 == 0) {
 #pragma unroll
@@ -264,6 +340,18 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
         }
       }
     }
+    // (what follows computes its addresses anew: kept over the walk they are spilled, and a reload waits for the stores
+    // of the mini-block before)
+    int ln = lane, tl = tid;
+    if constexpr (kStaged) asm volatile("" : "+v"(ln), "+v"(tl));
+    if constexpr (kStaged) {
+#pragma unroll
+      for (int q = 0; q < kUpd; ++q) {
+        const int t = min(mb + 1 + wave + kWaves * q, nt - 1);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) ub[q][kk] = Ut[256 * upper_tile(NT, mb, t) + (4 * kk + (ln >> 4)) * 16 + (ln & 15)];
+      }
+    }
     __syncthreads();
     // push the 16 new errors onto the later tiles of the block
 #pragma unroll
@@ -273,23 +361,23 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
         f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-          const double av = Em[(4 * kk + (lane >> 4)) * kRows + (lane & 15)];
+          const double av = Em[(4 * kk + (ln >> 4)) * kRows + (ln & 15)];
           d = __builtin_amdgcn_mfma_f64_16x16x4f64(av, ub[q][kk], d, 0, 0, 0);
         }
         double sv[4];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) sv[rr] = S[(4 * rr + (lane >> 4)) * sp + 16 * t + (lane & 15)];
+        for (int rr = 0; rr < 4; ++rr) sv[rr] = S[(4 * rr + (ln >> 4)) * sp + 16 * t + (ln & 15)];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) S[(4 * rr + (lane >> 4)) * sp + 16 * t + (lane & 15)] = sv[rr] - d[rr];
+        for (int rr = 0; rr < 4; ++rr) S[(4 * rr + (ln >> 4)) * sp + 16 * t + (ln & 15)] = sv[rr] - d[rr];
       }
     }
-    if (tid >= 256) {
-      const int e = tid - 256;
+    if (tl >= 256) {
+      const int e = tl - 256;
       if (!RAGGED || gcol + (e >> 4) < a.n) a.errT[(int64_t)(gcol + (e >> 4)) * a.mpad + row0 + (e & 15)] = Em[e];
       const int rr = e >> 4, j = e & 15;
       if (a.Wq && row0 + rr < a.m && (!RAGGED || gcol + j < a.n)) a.Wq[(int64_t)(row0 + rr) * a.n + gcol + j] = Qm[j * 17 + rr];
     }
-    if (mb + 1 < nt) {
+    if (!kStaged && mb + 1 < nt) {
       if (tid < 256) Ud[(buf ^ 1) * 256 + tid] = ud_next;
       if (tid < 16) Id[(buf ^ 1) * 16 + tid] = id_next;
     }
@@ -310,14 +398,16 @@ __global__ __launch_bounds__(kThreads) void vq_block_kernel(VqArgs a) {
   }
 }
 
-size_t vq_lds_bytes(int bw, int d) {
-  return (size_t)(4 * kRows * bw + 256 + 272 + 512 + 32 + kMaxEntries * d) * sizeof(double) + (size_t)kRows * bw;
+// (staged: the block of U, for blocks of nt tiles at most)
+size_t vq_lds_bytes(int bw, int d, int staged_nt) {
+  const int staged = staged_nt ? 256 * upper_tiles(staged_nt) + 16 * staged_nt : 0;
+  return (size_t)(4 * kRows * bw + 256 + 272 + 512 + 32 + kMaxEntries * d + staged) * sizeof(double) + (size_t)kRows * bw;
 }
 
 template <int DT, int NT, int D, int SLOTS, bool RAGGED = false>
 ptq_status vq_launch_block(const VqArgs& a, hipStream_t st) {
-  if (!lds_opt_in<vq_block_kernel<DT, NT, D, SLOTS, RAGGED>>((int)vq_lds_bytes(16 * NT, D))) return PTQ_ERR_HIP;
-  const size_t lds = vq_lds_bytes((a.bw + 15) / 16 * 16, D);
+  if (!lds_opt_in<vq_block_kernel<DT, NT, D, SLOTS, RAGGED>>((int)vq_lds_bytes(16 * NT, D, vq_staged<NT, D, SLOTS, RAGGED>() ? NT : 0))) return PTQ_ERR_HIP;
+  const size_t lds = vq_lds_bytes((a.bw + 15) / 16 * 16, D, vq_staged<NT, D, SLOTS, RAGGED>() ? NT : 0);
   vq_block_kernel<DT, NT, D, SLOTS, RAGGED><<<(unsigned)ceil_div(a.m, kRows), kThreads, lds, st>>>(a);
   return PTQ_OK;
 }
