@@ -496,7 +496,7 @@ __device__ __forceinline__ void leaf_block(const double* __restrict__ G, int n, 
 //
 // The leaf is a chain of pivots on one compute unit (33 us); the flops of a step run beside it on the others, so up to
 // a few thousand columns a step costs little more than its leaf.  The recursion below took a leaf and one to seven small
-// latency-bound launches per 128 columns in turn: n = 4096 2553 -> 1850 us, n = 512 in a layer's calls 212 -> 172.
+// latency-bound launches per 128 columns in turn: n = 4096 2553 -> 1680 us, a layer of 512 x 512 371 -> 341.
 // The storage is the recursion's: L^T in the mirror block of G, T' in the dead block of G, X in U through the
 // reversal.  T' is subtracted from once per step after a sum of 128 terms that starts from zero, so what rounds at the
 // size of the entry is n / 128 operations (distance from the float64 product of torch at n = 4096: 1.6e-15, the
@@ -863,6 +863,7 @@ __global__ __launch_bounds__(256) void diagonal_kernel(Steps st, int k) {
 // flops) and the recursion's products over thousands of columns are the better ones.  Whole call in steps / halves by
 // the recursion: 4100 columns 1888 / 2328 us, 5000 2956 / 3290, 6016 4329 / 4363, 8192 9275 / 8309.
 constexpr int kStepsMax = 5120;
+constexpr int kStepsLd = 1 << 20;   // the update's offsets into 128 rows of U are 32-bit bytes: longer rows go by the recursion
 bool run_steps(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t stream) {
   const Steps st{G, U, ldu, n, o, s, info};
   constexpr int strip_lds = 2 * kStripDoubles * (int)sizeof(double);
@@ -1177,7 +1178,7 @@ inline int first_part(int s) { return ((int)ceil_div(s, kLeaf) / 2) * kLeaf; }
 // this block have been enqueued on st.
 bool recurse(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t st, Side* side, int depth,
              const std::function<bool()>* on_first_half = nullptr) {
-  if (s <= kStepsMax) return run_steps(G, U, ldu, n, o, s, info, st);
+  if (s <= kLeaf || (s <= kStepsMax && ldu <= kStepsLd)) return run_steps(G, U, ldu, n, o, s, info, st);
   const int s1 = first_part(s);
   const int s2 = s - s1;
   const Node nd{G, U, ldu, n, o, s1, s2, o + s1};

@@ -1,0 +1,36 @@
+"""Which way a factor goes, read from the launches that the host would make: 128 columns at a time up to 5120 columns, halves
+of more by the recursion, and rows of U too long for the steps' 32-bit offsets by the recursion as well."""
+import pytest
+
+import paper_2601_19675_amd as ptq
+from launch_recorder import PTR, record
+from paper_2601_19675_amd import binding
+
+
+def _launches(n, ldu):
+    ws = ptq.ptq_workspace_bytes(binding.OP_CHOLESKY_INV, 0, n)
+    (rc, launches), = record([("ptq_damped_cholesky_inv", [PTR, n, n, 0.01, PTR, ldu, 0, PTR, PTR, ws, 0])])
+    assert rc == 0
+    return launches
+
+
+@pytest.mark.parametrize("n", [1, 128, 129, 512, 4096, 5120])
+def test_steps(n):
+    launches = _launches(n, n)
+    blocks = -(-n // 128)
+    steps = [l["grid"][0] for l in launches if "step_kernel" in l["kernel"]]
+    # the leaf, and for every block row below the half tiles up to its diagonal block (the leaf's own row without that)
+    tiles = [0] + [2 * ((blocks - k) * (blocks + k + 1) // 2 - 1) for k in range(1, blocks)]
+    assert steps == [1 + min(t, 255) for t in tiles]
+    assert sum("diagonal_kernel" in l["kernel"] for l in launches) == blocks - 1
+    assert not any("node_gemm" in l["kernel"] for l in launches)
+
+
+@pytest.mark.parametrize("n,ldu", [(5121, 5121), (11008, 11008), (1000, (1 << 20) + 1)])
+def test_recursion(n, ldu):
+    launches = _launches(n, ldu)
+    assert any("node_gemm" in l["kernel"] for l in launches)
+    # every block of 128 columns has its leaf
+    assert sum("step_kernel" in l["kernel"] for l in launches) == -(-n // 128)
+    if ldu > 1 << 20:
+        assert all(l["grid"][0] == 1 for l in launches if "step_kernel" in l["kernel"])
