@@ -1034,11 +1034,9 @@ __device__ __forceinline__ void node_gemm_tile(const Op& op, int lin, int gx, in
   const bool full = (i1 - i0 == T::BM) && (j1 - j0 == T::BN) && ke > kb && ((ke - kb) % kGemmBK == 0) &&
                     spana < ((int64_t)1 << 31) && spanb < ((int64_t)1 << 31);
   bool done = false;
-  if constexpr (TM * TN >= 4) {
-    if (full) {
-      dgemm_mainloop_pipelined<TM, TN, Op::A_KFAST, Op::B_KFAST>(acc, va, vb, kb, ke, smem);
-      done = true;
-    }
+  if (full) {
+    dgemm_mainloop_pipelined<TM, TN, Op::A_KFAST, Op::B_KFAST>(acc, va, vb, kb, ke, smem);
+    done = true;
   }
   if (!done)
     dgemm_mainloop<TM, TN, Op::A_KFAST, Op::B_KFAST>(acc, va, DgemmIdentity{}, vb, DgemmIdentity{}, i1 - i0, j1 - j0,
@@ -1134,7 +1132,8 @@ bool launch_node2(const Op1& op1, int M1, int N1, const Op2& op2, int M2, int N2
 //    (`on_first_half`), the early part runs on its stream, and after the child the node finishes
 //    the panel (columns [sA, s1)) and the update (k in [sA, s1)) on the caller's stream (cap
 //    kEarlyCus; n = 11008: 18.0 ms without, 17.9 / 17.4 / 17.5 / 17.6 ms with 128 / 160 / 192 / 224;
-//    n = 8192: 9.49 without, 9.04 / 8.95 with 128 / 192).
+//    only where the first half is itself halved: one that goes 128 columns at a time has no such point; n = 8192 in
+//    two blocks of steps takes 8.1 ms).
 // Smaller nodes gain nothing (measured) and keep one stream, with T in the update's launch.  The
 // streams and a few events per device are created on first use and kept for the life of the
 // process (default priority).
