@@ -1034,9 +1034,11 @@ __device__ __forceinline__ void node_gemm_tile(const Op& op, int lin, int gx, in
   const bool full = (i1 - i0 == T::BM) && (j1 - j0 == T::BN) && ke > kb && ((ke - kb) % kGemmBK == 0) &&
                     spana < ((int64_t)1 << 31) && spanb < ((int64_t)1 << 31);
   bool done = false;
-  if (full) {
-    dgemm_mainloop_pipelined<TM, TN, Op::A_KFAST, Op::B_KFAST>(acc, va, vb, kb, ke, smem);
-    done = true;
+  if constexpr (TM * TN >= 4) {
+    if (full) {
+      dgemm_mainloop_pipelined<TM, TN, Op::A_KFAST, Op::B_KFAST>(acc, va, vb, kb, ke, smem);
+      done = true;
+    }
   }
   if (!done)
     dgemm_mainloop<TM, TN, Op::A_KFAST, Op::B_KFAST>(acc, va, DgemmIdentity{}, vb, DgemmIdentity{}, i1 - i0, j1 - j0,
@@ -1100,20 +1102,33 @@ bool launch_tiles2(const Op1& op1, int M1, int N1, const Op2& op2, int M2, int N
   return true;
 }
 
-// Tile shape by problem size, as measured: 128 x 128 once there are enough tiles to fill the chip twice over, 64 x 64
-// below (the halves of a recursion node have more than 2500 rows).
-inline bool large_tiles(int M, int N) { return ceil_div(M, 128) * ceil_div(N, 128) >= 512; }
+// Tile shape by problem size, as measured: 128 x 128 once there are enough tiles to fill the chip twice over; up to about a
+// 1500-wide node 32 x 32 tiles (there the k loops are short and bound by the latency of their loads, whatever the tile:
+// many small workgroups hide it best); 64 x 64 between.  Nodes that narrow are left only where rows of U are too long for
+// the steps: rows of 2^20 + 1, whole call with 64 x 64 / 32 x 32 there, 300 columns 149 / 118 us, 1000 581 / 423, 3000 2198 / 1764.
+inline int tile_class(int M, int N) {
+  if (ceil_div(M, 128) * ceil_div(N, 128) >= 512) return 2;
+  if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return 0;
+  return 1;
+}
 
 template <class Op>
 bool launch_node(const Op& op, int M, int N, hipStream_t st, int max_cus = 0) {
-  if (large_tiles(M, N)) return launch_tiles<4, 4, Op>(op, M, N, st, max_cus);   // one workgroup per compute unit
-  return launch_tiles<2, 2, Op>(op, M, N, st, 3 * max_cus);                      // three
+  switch (tile_class(M, N)) {
+    case 2: return launch_tiles<4, 4, Op>(op, M, N, st, max_cus);          // one workgroup per compute unit
+    case 1: return launch_tiles<2, 2, Op>(op, M, N, st, 3 * max_cus);      // three
+    default: return launch_tiles<1, 1, Op>(op, M, N, st, 4 * max_cus);
+  }
 }
 
 template <class Op1, class Op2>
 bool launch_node2(const Op1& op1, int M1, int N1, const Op2& op2, int M2, int N2, hipStream_t st) {
-  if (large_tiles(M1, N1) && large_tiles(M2, N2)) return launch_tiles2<4, 4, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
-  return launch_tiles2<2, 2, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
+  const int c1 = tile_class(M1, N1), c2 = tile_class(M2, N2);
+  switch (c1 < c2 ? c1 : c2) {
+    case 2: return launch_tiles2<4, 4, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
+    case 1: return launch_tiles2<2, 2, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
+    default: return launch_tiles2<1, 1, Op1, Op2>(op1, M1, N1, op2, M2, N2, st);
+  }
 }
 
 // ---- helper streams for work that is off the critical chain -----------------------------------
@@ -1171,20 +1186,21 @@ Side* side_for_device() {
   return state[dev].load(std::memory_order_acquire) == 2 ? &sides[dev] : nullptr;
 }
 
+inline bool in_steps(int s, int ldu) { return s <= kLeaf || (s <= kStepsMax && ldu <= kStepsLd); }
 inline int first_part(int s) { return ((int)ceil_div(s, kLeaf) / 2) * kLeaf; }
 
 // `on_first_half`, if given, is called (on the host) right after the launches that invert the first half of
 // this block have been enqueued on st.
 bool recurse(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t st, Side* side, int depth,
              const std::function<bool()>* on_first_half = nullptr) {
-  if (s <= kLeaf || (s <= kStepsMax && ldu <= kStepsLd)) return run_steps(G, U, ldu, n, o, s, info, st);
+  if (in_steps(s, ldu)) return run_steps(G, U, ldu, n, o, s, info, st);
   const int s1 = first_part(s);
   const int s2 = s - s1;
   const Node nd{G, U, ldu, n, o, s1, s2, o + s1};
-  if (side && depth < kMaxDepth && large_tiles(s2, s1)) {
+  if (side && depth < kMaxDepth && tile_class(s2, s1) == 2) {
     // a large node.  Early part: beside the second half of the first child's recursion
-    const int sA = s1 > kLeaf ? first_part(s1) : 0;
-    const bool early = s1 > kStepsMax && large_tiles(s2, sA);
+    const int sA = first_part(s1);
+    const bool early = !in_steps(s1, ldu) && tile_class(s2, sA) == 2;
     const std::function<bool()> start_early = [&]() -> bool {
       const Node part{G, U, ldu, n, o, sA, s2, o + s1};
       return hipEventRecord(side->early_fork[depth], st) == hipSuccess &&
@@ -1241,7 +1257,7 @@ ptq_status cholesky_launch(const double* H, int64_t ldh, int64_t n, double damp,
   PTQ_HIP_CHECK_LAUNCH();
   // the helper stream only where a node is large enough to use it (the top node is the largest)
   const int top1 = first_part((int)n);
-  Side* side = (n > kStepsMax && large_tiles((int)n - top1, top1)) ? side_for_device() : nullptr;
+  Side* side = (n > kLeaf && tile_class((int)n - top1, top1) == 2) ? side_for_device() : nullptr;
   bool ok;
   if (side) {
     std::lock_guard<std::mutex> hold(side->lock);

@@ -84,27 +84,32 @@ __device__ __forceinline__ void dgemm_mainloop(f64x4 (&acc)[TM][TN], DView A, FA
   }
   const int stepa = kGemmBK * A.sk, stepb = kGemmBK * B.sk;
 
-  double ra[T::EA], rb[T::EB];
+  // Register sets for the k-tiles in flight.  The smallest tile has two loads per operand and thread and
+  // a k-tile of four MFMAs per wave: with one k-tile in flight every iteration waits out a whole memory
+  // latency (measured: 0.6 - 1.3 us per iteration where the MFMAs need 0.1), so it keeps four in flight.
+  constexpr int D = (TM * TN == 1) ? 4 : 1;
+  double ra[D][T::EA], rb[D][T::EB];
   // loads of the next k-tile in line (tiles are fetched in rising order; its offsets are the current
-  // ones); only the last tile can stick out of [kbeg, kend): there the k index is clamped
-  auto fetch = [&](int k0) {
+  // ones) into register set SET; only the last tile can stick out of [kbeg, kend): there the k index is clamped
+  auto fetch = [&](auto set, int k0) {
+    constexpr int SET = decltype(set)::value;
     if (k0 + kGemmBK <= kend) {
 #pragma unroll
-      for (int p = 0; p < T::EA; ++p) ra[p] = A.p[offa[p]];
+      for (int p = 0; p < T::EA; ++p) ra[SET][p] = A.p[offa[p]];
 #pragma unroll
-      for (int p = 0; p < T::EB; ++p) rb[p] = B.p[offb[p]];
+      for (int p = 0; p < T::EB; ++p) rb[SET][p] = B.p[offb[p]];
     } else {
 #pragma unroll
       for (int p = 0; p < T::EA; ++p) {
         const int k = A_KFAST ? (tid + 256 * p) % kGemmBK : (tid + 256 * p) / T::BM;
         const int over = k0 + k - (kend - 1);
-        ra[p] = A.p[offa[p] - (over > 0 ? over : 0) * A.sk];
+        ra[SET][p] = A.p[offa[p] - (over > 0 ? over : 0) * A.sk];
       }
 #pragma unroll
       for (int p = 0; p < T::EB; ++p) {
         const int k = B_KFAST ? (tid + 256 * p) % kGemmBK : (tid + 256 * p) / T::BN;
         const int over = k0 + k - (kend - 1);
-        rb[p] = B.p[offb[p] - (over > 0 ? over : 0) * B.sk];
+        rb[SET][p] = B.p[offb[p] - (over > 0 ? over : 0) * B.sk];
       }
     }
 #pragma unroll
@@ -112,7 +117,20 @@ __device__ __forceinline__ void dgemm_mainloop(f64x4 (&acc)[TM][TN], DView A, FA
 #pragma unroll
     for (int p = 0; p < T::EB; ++p) offb[p] += stepb;
   };
-  auto stash = [&](int k0, double* st) {
+  // the same for a tile known to lie inside [kbeg, kend): no branch
+  auto fetch_inner = [&](auto set) {
+    constexpr int SET = decltype(set)::value;
+#pragma unroll
+    for (int p = 0; p < T::EA; ++p) ra[SET][p] = A.p[offa[p]];
+#pragma unroll
+    for (int p = 0; p < T::EB; ++p) rb[SET][p] = B.p[offb[p]];
+#pragma unroll
+    for (int p = 0; p < T::EA; ++p) offa[p] += stepa;
+#pragma unroll
+    for (int p = 0; p < T::EB; ++p) offb[p] += stepb;
+  };
+  auto stash = [&](auto set, int k0, double* st) {
+    constexpr int SET = decltype(set)::value;
     double* sa = st;
     double* sb = st + kGemmBK * T::PA;
 #pragma unroll
@@ -121,7 +139,7 @@ __device__ __forceinline__ void dgemm_mainloop(f64x4 (&acc)[TM][TN], DView A, FA
       const int i = A_KFAST ? e / kGemmBK : e % T::BM;
       const int k = A_KFAST ? e % kGemmBK : e / T::BM;
       const bool ok = ((oka >> p) & 1u) && (k0 + k < kend);
-      const double v = fa(ra[p], i, k0 + k);
+      const double v = fa(ra[SET][p], i, k0 + k);
       sa[k * T::PA + i] = ok ? v : 0.0;
     }
 #pragma unroll
@@ -130,11 +148,24 @@ __device__ __forceinline__ void dgemm_mainloop(f64x4 (&acc)[TM][TN], DView A, FA
       const int j = B_KFAST ? e / kGemmBK : e % T::BN;
       const int k = B_KFAST ? e % kGemmBK : e / T::BN;
       const bool ok = ((okb >> p) & 1u) && (k0 + k < kend);
-      const double v = fb(rb[p], k0 + k, j);
+      const double v = fb(rb[SET][p], k0 + k, j);
       sb[k * T::PB + j] = ok ? v : 0.0;
     }
   };
 
+  // A tile with fewer than four MFMAs per k-step would run them as one dependent chain (an MFMA's
+  // result is ready only three instruction times later): the k-steps of a k-tile then go to NS
+  // separate accumulator sets, added up at the end.
+  constexpr int NS = (TM * TN >= 4) ? 1 : 4 / (TM * TN);
+  f64x4 part[NS][TM][TN];
+  if constexpr (NS > 1) {
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) part[q][tm][tn] = f64x4{0.0, 0.0, 0.0, 0.0};
+  }
   // the MFMAs of the k-tile in LDS stage `stage`
   auto compute = [&](int stage) {
     const double* sa = smem + stage * T::kStageDoubles;
@@ -157,26 +188,83 @@ __device__ __forceinline__ void dgemm_mainloop(f64x4 (&acc)[TM][TN], DView A, FA
 #pragma unroll
       for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-          acc[tm][tn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[slot][tm], b[slot][tn], acc[tm][tn], 0, 0, 0);
+        for (int tn = 0; tn < TN; ++tn) {
+          if constexpr (NS == 1)
+            acc[tm][tn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[slot][tm], b[slot][tn], acc[tm][tn], 0, 0, 0);
+          else
+            part[(kk >> 2) % NS][tm][tn] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[slot][tm], b[slot][tn],
+                                                                                part[(kk >> 2) % NS][tm][tn], 0, 0, 0);
+        }
       __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);   // the reads of the next k-step first
       __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);   // then this k-step's MFMAs
     }
   };
 
-  // Tile t is computed from LDS stage t % 2 while tile t + 1 goes from the registers to the other stage and tile t + 2 is
-  // requested into them.
-  const int ntile = (kend - kbeg + kGemmBK - 1) / kGemmBK;
+  // Tile t is computed from LDS stage t % 2 while tile t + 1 goes from register set (t + 1) % D to the
+  // other stage and tile t + 1 + D is requested into the set that has just been emptied.
+  const int ntile = (kend - kbeg + kGemmBK - 1) / kGemmBK, nfull = (kend - kbeg) / kGemmBK;
   auto k_of = [&](int t) { return kbeg + t * kGemmBK; };
-  fetch(k_of(0));
-  stash(k_of(0), smem);
-  if (ntile > 1) fetch(k_of(1));
+  using std::integral_constant;
+  // prologue: tile 0 into stage 0, tiles 1 .. D requested
+  fetch(integral_constant<int, 0>{}, k_of(0));
+  stash(integral_constant<int, 0>{}, k_of(0), smem);
+  {
+    auto request = [&](auto dc) {
+      constexpr int d = decltype(dc)::value;   // tile d + 1 into set (d + 1) % D
+      if (d + 1 < ntile) fetch(integral_constant<int, (d + 1) % D>{}, k_of(d + 1));
+    };
+    request(integral_constant<int, 0>{});
+    if constexpr (D > 1) request(integral_constant<int, 1>{});
+    if constexpr (D > 2) request(integral_constant<int, 2>{});
+    if constexpr (D > 3) request(integral_constant<int, 3>{});
+    static_assert(D <= 4, "the prologue is written out for up to four sets");
+  }
   __syncthreads();
-  for (int t = 0; t < ntile; ++t) {
-    if (t + 1 < ntile) stash(k_of(t + 1), smem + ((t + 1) & 1) * T::kStageDoubles);
-    if (t + 2 < ntile) fetch(k_of(t + 2));
-    compute(t & 1);
-    __syncthreads();
+  int t0 = 0;
+  // steady state, D iterations per round, no branch inside: every tile stashed and requested is a full one
+  // (the last request of a round is tile t0 + 2 D)
+  auto round = [&](auto inner) {
+    constexpr bool INNER = decltype(inner)::value;
+    auto iter = [&](auto dc) {
+      constexpr int d = decltype(dc)::value;
+      const int t = t0 + d;
+      using Set = integral_constant<int, (d + 1) % D>;
+      if constexpr (INNER) {
+        stash(Set{}, k_of(t + 1), smem + ((d + 1) & 1) * T::kStageDoubles);
+        fetch_inner(Set{});
+        compute(d & 1);
+        __syncthreads();
+      } else {
+        if (t < ntile) {
+          if (t + 1 < ntile) stash(Set{}, k_of(t + 1), smem + ((t + 1) & 1) * T::kStageDoubles);
+          if (t + 1 + D < ntile) fetch(Set{}, k_of(t + 1 + D));
+          compute(t & 1);
+          __syncthreads();
+        }
+      }
+    };
+    iter(integral_constant<int, 0>{});
+    if constexpr (D > 1) iter(integral_constant<int, 1>{});
+    if constexpr (D > 2) iter(integral_constant<int, 2>{});
+    if constexpr (D > 3) iter(integral_constant<int, 3>{});
+  };
+  if constexpr (D % 2 == 0) {   // (stage parity by d needs an even round)
+    for (; t0 + 2 * D < nfull; t0 += D) round(integral_constant<bool, true>{});
+  }
+  for (; t0 < ntile; t0 += D) round(integral_constant<bool, false>{});
+  if constexpr (NS > 1) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double sum = part[0][tm][tn][r];
+#pragma unroll
+          for (int q = 1; q < NS; ++q) sum += part[q][tm][tn][r];
+          acc[tm][tn][r] += sum;
+        }
+      }
   }
 }
 

@@ -34,3 +34,16 @@ def test_recursion(n, ldu):
     assert sum("step_kernel" in l["kernel"] for l in launches) == -(-n // 128)
     if ldu > 1 << 20:
         assert all(l["grid"][0] == 1 for l in launches if "step_kernel" in l["kernel"])
+
+
+@pytest.mark.parametrize("n", [129, 300, 2000])
+def test_narrow_nodes_of_long_rows(n):
+    # up to about 1500 columns a node's products are bound by latency: 32 x 32 tiles
+    nodes = [l["kernel"] for l in _launches(n, (1 << 20) + 1) if "node_gemm" in l["kernel"]]
+    assert nodes and all("ILi1ELi1E" in k for k in nodes)
+
+
+def test_wide_nodes_of_long_rows():
+    # a node of 128 x 128 tiles, halves that go on halving: the early part of panel and update beside the second half of the first child
+    capped = [l for l in _launches(8192, (1 << 20) + 1) if "ILi4ELi4ELb1E" in l["kernel"]]
+    assert sorted(l["grid"][0] for l in capped) == [128, 192, 192]   # T, and the early part's two

@@ -1,7 +1,7 @@
 """The factor of up to a few thousand columns goes 128 columns at a time: a leaf beside the update with the block column
 before it, the panel, the next leaf's block.  Sizes at the edges of the leaf, of the panel's strips of 32 and of the
-update's tiles, one to many block columns, an output with a longer row; and a width just past the largest block, whose
-halves go this way under one recursion."""
+update's tiles, one to many block columns, an output with a longer row; a width just past the largest block, whose
+halves go this way under one recursion; and rows too long for the steps."""
 import numpy as np
 import pytest
 import torch
@@ -33,9 +33,7 @@ def _gpu(H, extra, fill):
     return U, info.cpu().tolist()
 
 
-@pytest.mark.parametrize("n,extra", [(1, 0), (127, 0), (128, 0), (129, 0), (160, 1), (161, 0), (256, 0), (257, 3), (383, 0), (449, 0),
-                                     (640, 0), (1000, 1), (1601, 0)])
-def test_factor_in_steps(n, extra):
+def _check(n, extra):
     H = _case(n, n)
     Hd, _ = orc.damp(H, DAMP)
     U, info = _gpu(H, extra, 0xFF)   # (an all-ones workspace reads as NaN)
@@ -48,6 +46,18 @@ def test_factor_in_steps(n, extra):
     R = np.linalg.inv(orc.inverse_cholesky_upper(Hd))
     B = np.abs(U) @ np.abs(R)
     assert np.all(np.abs(U @ Hd @ U.T - np.eye(n)) <= 6 * (n + 1) * 2.0**-53 * (B @ B.T))
+
+
+@pytest.mark.parametrize("n,extra", [(1, 0), (127, 0), (128, 0), (129, 0), (160, 1), (161, 0), (256, 0), (257, 3), (383, 0), (449, 0),
+                                     (640, 0), (1000, 1), (1601, 0)])
+def test_factor_in_steps(n, extra):
+    _check(n, extra)
+
+
+@pytest.mark.parametrize("n", [129, 300, 700])
+def test_factor_of_long_rows(n):
+    """Rows of U past 2^20 entries: the recursion down to 128 columns, nodes of 1 to 316 rows, ragged ones among them."""
+    _check(n, (1 << 20) + 1 - n)
 
 
 def test_factor_of_halves_in_steps():
