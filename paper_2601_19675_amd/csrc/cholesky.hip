@@ -504,11 +504,12 @@ __device__ __forceinline__ void leaf_block(const double* __restrict__ G, int n, 
 struct Steps {
   double* G;      // work matrix, n x n, ld = n
   double* U;      // output, X reversed: X(i, j) = U[n-1-i][n-1-j]
-  int ldu, n, o, s;
+  int64_t ldu;    // (the update, which only a block of more than 128 columns has, needs it to be at most kStepsLd)
+  int n, o, s;
   int32_t* info;
   __device__ __forceinline__ double* g(int i, int j) const { return G + (int64_t)(o + i) * n + o + j; }
   __device__ __forceinline__ double* x(int i, int j) const {
-    return U + (int64_t)(n - 1 - o - i) * ldu + (n - 1 - o - j);
+    return U + (n - 1 - o - i) * ldu + (n - 1 - o - j);
   }
 };
 
@@ -546,7 +547,7 @@ __device__ __forceinline__ void update_tiles(const Steps& st, int kp, int first,
   const int wm = wave >> 1, wn = wave & 1;
   const int l16 = lane & 15, lq = lane >> 4;
   const int p0 = kp * kLeaf;
-  const int n8 = st.n * 8, u8 = st.ldu * 8;            // bytes of a row
+  const int n8 = st.n * 8, u8 = (int)st.ldu * 8;       // bytes of a row
   // Buffer loads: the tile in the descriptor, the k-tile in the scalar offset.  Operands lie inside their matrix whole
   // (columns past the block are the next row's entries: at most n - 1 + 127 in row n - 2); C may not in a ragged tile,
   // so its rows are in the checked offset and read as zero behind the matrix.
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(256) void panel_kernel(Steps st, int k, int strips_
   if (strip < strips_l) {
     const int r0 = d0 + kLeaf + 32 * strip;            // rows of G
     const int count = min(32, st.s - r0);
-    const f64x4 acc = strip_product<Strip::kTermsBack, Strip::kTerms>(st.x(d0 + m0, d0), -(int64_t)st.ldu, -1, 32, st.g(r0, d0),
+    const f64x4 acc = strip_product<Strip::kTermsBack, Strip::kTerms>(st.x(d0 + m0, d0), -st.ldu, -1, 32, st.g(r0, d0),
                                                                       st.n, 1, count, kLeaf, m0 + 32, lds);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -830,7 +831,7 @@ __global__ __launch_bounds__(256) void panel_kernel(Steps st, int k, int strips_
     const int c0 = 32 * (strip - strips_l);
     if (m0 >= w || c0 >= d0) return;
     const int count = min(32, w - m0);
-    const f64x4 acc = strip_product<Strip::kTermsBack, Strip::kRows>(st.x(d0 + m0, d0), -(int64_t)st.ldu, -1, count, st.g(d0, c0),
+    const f64x4 acc = strip_product<Strip::kTermsBack, Strip::kRows>(st.x(d0 + m0, d0), -st.ldu, -1, count, st.g(d0, c0),
                                                                      1, st.n, 32, min(w, m0 + 32), m0 + 32, lds);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -864,7 +865,7 @@ __global__ __launch_bounds__(256) void diagonal_kernel(Steps st, int k) {
 // the recursion: 4100 columns 1888 / 2328 us, 5000 2956 / 3290, 6016 4329 / 4363, 8192 9275 / 8309.
 constexpr int kStepsMax = 5120;
 constexpr int kStepsLd = 1 << 20;   // the update's offsets into 128 rows of U are 32-bit bytes: longer rows go by the recursion
-bool run_steps(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t stream) {
+bool run_steps(double* G, double* U, int64_t ldu, int n, int o, int s, int32_t* info, hipStream_t stream) {
   const Steps st{G, U, ldu, n, o, s, info};
   constexpr int strip_lds = 2 * kStripDoubles * (int)sizeof(double);
   if (!lds_opt_in<step_kernel>((int)kLeafLdsBytes) || !lds_opt_in<panel_kernel>(strip_lds) ||
@@ -893,13 +894,13 @@ bool run_steps(double* G, double* U, int ldu, int n, int o, int s, int32_t* info
 struct Node {
   double* G;      // work matrix, n x n, ld = n
   double* U;      // output, X reversed: X(i, j) = U[n-1-i][n-1-j]
-  int ldu;
+  int64_t ldu;
   int n, o, s1, s2;
   int r;          // first row of the second block: o + s1, except for the early part of a panel or an update
                   // (see recurse), whose k range [o, o + s1) ends before the second block begins
   __device__ __forceinline__ const double* g(int i, int j) const { return G + (int64_t)i * n + j; }
   __device__ __forceinline__ const double* x(int i, int j) const {
-    return U + (int64_t)(n - 1 - i) * ldu + (n - 1 - j);
+    return U + (n - 1 - i) * ldu + (n - 1 - j);
   }
 };
 
@@ -971,7 +972,7 @@ struct OpX21 {
   __device__ DView b(int j0) const { return DView{nd.g(nd.o + nd.s1, nd.o + j0), 1, nd.n}; }  // T(k, j)
   __device__ void store(int i, int j, double v) const {
     if (i < nd.s2 && j < nd.s1)
-      nd.U[(int64_t)(nd.n - 1 - (nd.o + nd.s1 + i)) * nd.ldu + (nd.n - 1 - (nd.o + j))] = -v;
+      nd.U[(nd.n - 1 - (nd.o + nd.s1 + i)) * nd.ldu + (nd.n - 1 - (nd.o + j))] = -v;
   }
 };
 
@@ -1029,8 +1030,8 @@ __device__ __forceinline__ void node_gemm_tile(const Op& op, int lin, int gx, in
   // a tile with no ragged edge takes the software-pipelined loop (same sums in the same order)
   // (its buffer loads address a tile's footprint with 32-bit byte offsets)
   const DView va = op.a(i0), vb = op.b(j0);
-  const int64_t spana = ((int64_t)T::BM * abs(va.so) + (int64_t)(ke - kb) * abs(va.sk)) * 8;
-  const int64_t spanb = ((int64_t)T::BN * abs(vb.so) + (int64_t)(ke - kb) * abs(vb.sk)) * 8;
+  const int64_t spana = (T::BM * std::abs(va.so) + (ke - kb) * std::abs(va.sk)) * 8;
+  const int64_t spanb = (T::BN * std::abs(vb.so) + (ke - kb) * std::abs(vb.sk)) * 8;
   const bool full = (i1 - i0 == T::BM) && (j1 - j0 == T::BN) && ke > kb && ((ke - kb) % kGemmBK == 0) &&
                     spana < ((int64_t)1 << 31) && spanb < ((int64_t)1 << 31);
   bool done = false;
@@ -1186,12 +1187,12 @@ Side* side_for_device() {
   return state[dev].load(std::memory_order_acquire) == 2 ? &sides[dev] : nullptr;
 }
 
-inline bool in_steps(int s, int ldu) { return s <= kLeaf || (s <= kStepsMax && ldu <= kStepsLd); }
+inline bool in_steps(int s, int64_t ldu) { return s <= kLeaf || (s <= kStepsMax && ldu <= kStepsLd); }
 inline int first_part(int s) { return ((int)ceil_div(s, kLeaf) / 2) * kLeaf; }
 
 // `on_first_half`, if given, is called (on the host) right after the launches that invert the first half of
 // this block have been enqueued on st.
-bool recurse(double* G, double* U, int ldu, int n, int o, int s, int32_t* info, hipStream_t st, Side* side, int depth,
+bool recurse(double* G, double* U, int64_t ldu, int n, int o, int s, int32_t* info, hipStream_t st, Side* side, int depth,
              const std::function<bool()>* on_first_half = nullptr) {
   if (in_steps(s, ldu)) return run_steps(G, U, ldu, n, o, s, info, st);
   const int s1 = first_part(s);
@@ -1261,9 +1262,9 @@ ptq_status cholesky_launch(const double* H, int64_t ldh, int64_t n, double damp,
   bool ok;
   if (side) {
     std::lock_guard<std::mutex> hold(side->lock);
-    ok = recurse(G, U, (int)ldu, (int)n, 0, (int)n, info, st, side, 0);
+    ok = recurse(G, U, ldu, (int)n, 0, (int)n, info, st, side, 0);
   } else {
-    ok = recurse(G, U, (int)ldu, (int)n, 0, (int)n, info, st, nullptr, 0);
+    ok = recurse(G, U, ldu, (int)n, 0, (int)n, info, st, nullptr, 0);
   }
   if (!ok) return PTQ_ERR_HIP;
   PTQ_HIP_CHECK_LAUNCH();

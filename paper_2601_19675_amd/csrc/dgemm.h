@@ -12,8 +12,8 @@
 // two doubles per lane per instruction, so plain 8-byte LDS reads keep it busy;
 // what has to be kept small is everything else a wave issues, because a wave
 // issues in order and with one wave per SIMD nothing else fills the gaps.
-// Hence: per-thread element offsets are computed once and advanced by one add
-// per k-tile, loads for tile t+2 are issued before the MFMAs of tile t, and
+// Hence: per-thread offsets are computed once and scalar bases
+// advanced per k-tile, loads for tile t+2 are issued before the MFMAs of tile t, and
 // LDS is double-buffered so that there is one barrier per k-tile.
 #pragma once
 #include <type_traits>
@@ -38,15 +38,57 @@ struct DgemmTile {
   static constexpr int EB = BN * kGemmBK / 256;
 };
 
-// element(o, k) = p[o * so + k * sk], o = row of A / column of B inside the tile.
-// All offsets of one tile fit in 31 bits.
+// element(o, k) = p[o * so + k * sk], o = row of A / column of B inside the tile; strides and offsets of any size
+// (a column of k goes down thousands of rows of U or H, whose length is the caller's).
 struct DView {
   const double* p;
-  int so, sk;
+  int64_t so, sk;
 };
 
 struct DgemmIdentity {
   __device__ __forceinline__ double operator()(double v, int, int) const { return v; }
+};
+
+// A thread's loads of an operand's k-tiles (EDGE rows or columns by kGemmBK): its elements sit at one offset from E
+// scalar bases, so that 64-bit offsets cost few registers (offsets of its own for every element spilled in the callers).
+template <int EDGE, bool KFAST>
+struct DgemmFetch {
+  static constexpr int E = EDGE * kGemmBK / 256;
+  static constexpr int kRows = 256 / kGemmBK, kSteps = 256 / EDGE;   // rows (KFAST) or steps of k from one element to the next
+  const double* next;   // the next k-tile in line
+  int64_t sk, off, off_last;
+  int64_t base[E];      // of every element, in bytes from `next`
+  int k, groups;        // k of the first element; groups of rows before the last one that has any
+
+  __device__ __forceinline__ DgemmFetch(DView V, int count, int kbeg) : next(V.p + kbeg * V.sk), sk(V.sk) {
+    const int tid = threadIdx.x;
+    const int o = KFAST ? tid / kGemmBK : tid % EDGE;
+    k = KFAST ? tid % kGemmBK : tid / EDGE;
+    // rows from `count` on read a row that is there
+    groups = KFAST ? (count - 1) / kRows : 0;
+    const int in_last = count - 1 - kRows * groups;
+    off_last = (o < in_last ? o : in_last) * V.so + k * sk;
+    off = KFAST ? o * V.so + k * sk : off_last;
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+      base[p] = 8 * (KFAST ? kRows * (p < groups ? p : groups) * V.so : kSteps * p * sk);
+      asm("" : "+r"(base[p]));   // (left to itself the compiler forms the addresses of a k-tile as one chain of vector adds)
+    }
+  }
+  // the first `left` steps of k of the next k-tile (there are no more), what is past them reads the last one
+  template <bool TAIL>
+  __device__ __forceinline__ void load(double (&r)[E], int left) {
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+      int64_t at = KFAST && p < groups ? off : off_last;
+      if constexpr (TAIL) {
+        const int over = k + (KFAST ? 0 : kSteps * p) - (left - 1);
+        at -= (over > 0 ? over : 0) * sk;
+      }
+      r[p] = reinterpret_cast<const double*>(reinterpret_cast<const char*>(next) + base[p])[at];
+    }
+    next += kGemmBK * sk;
+  }
 };
 
 // fa(v, i, k) / fb(v, k, j) may transform a loaded value (tile-local i / j,
@@ -63,71 +105,42 @@ __device__ __forceinline__ void dgemm_mainloop(f64x4 (&acc)[TM][TN], DView A, FA
   const int wm = wave >> 1, wn = wave & 1;
   if (kbeg >= kend) return;
 
-  // fixed per-thread element coordinates and running offsets (at k-tile 0)
-  int offa[T::EA], offb[T::EB];
   unsigned oka = 0, okb = 0;
 #pragma unroll
   for (int p = 0; p < T::EA; ++p) {
     const int e = tid + 256 * p;
-    const int i = A_KFAST ? e / kGemmBK : e % T::BM;
-    const int k = A_KFAST ? e % kGemmBK : e / T::BM;
-    oka |= (i < rows ? 1u : 0u) << p;
-    offa[p] = (i < rows ? i : rows - 1) * A.so + (kbeg + k) * A.sk;
+    oka |= ((A_KFAST ? e / kGemmBK : e % T::BM) < rows ? 1u : 0u) << p;
   }
 #pragma unroll
   for (int p = 0; p < T::EB; ++p) {
     const int e = tid + 256 * p;
-    const int j = B_KFAST ? e / kGemmBK : e % T::BN;
-    const int k = B_KFAST ? e % kGemmBK : e / T::BN;
-    okb |= (j < cols ? 1u : 0u) << p;
-    offb[p] = (j < cols ? j : cols - 1) * B.so + (kbeg + k) * B.sk;
+    okb |= ((B_KFAST ? e / kGemmBK : e % T::BN) < cols ? 1u : 0u) << p;
   }
-  const int stepa = kGemmBK * A.sk, stepb = kGemmBK * B.sk;
+  DgemmFetch<T::BM, A_KFAST> la(A, rows, kbeg);
+  DgemmFetch<T::BN, B_KFAST> lb(B, cols, kbeg);
 
   // Register sets for the k-tiles in flight.  The smallest tile has two loads per operand and thread and
   // a k-tile of four MFMAs per wave: with one k-tile in flight every iteration waits out a whole memory
   // latency (measured: 0.6 - 1.3 us per iteration where the MFMAs need 0.1), so it keeps four in flight.
   constexpr int D = (TM * TN == 1) ? 4 : 1;
   double ra[D][T::EA], rb[D][T::EB];
-  // loads of the next k-tile in line (tiles are fetched in rising order; its offsets are the current
-  // ones) into register set SET; only the last tile can stick out of [kbeg, kend): there the k index is clamped
+  // loads of the next k-tile in line (tiles are fetched in rising order) into register set SET; only the last tile can
+  // stick out of [kbeg, kend): there the k index is clamped
   auto fetch = [&](auto set, int k0) {
     constexpr int SET = decltype(set)::value;
     if (k0 + kGemmBK <= kend) {
-#pragma unroll
-      for (int p = 0; p < T::EA; ++p) ra[SET][p] = A.p[offa[p]];
-#pragma unroll
-      for (int p = 0; p < T::EB; ++p) rb[SET][p] = B.p[offb[p]];
+      la.template load<false>(ra[SET], kGemmBK);
+      lb.template load<false>(rb[SET], kGemmBK);
     } else {
-#pragma unroll
-      for (int p = 0; p < T::EA; ++p) {
-        const int k = A_KFAST ? (tid + 256 * p) % kGemmBK : (tid + 256 * p) / T::BM;
-        const int over = k0 + k - (kend - 1);
-        ra[SET][p] = A.p[offa[p] - (over > 0 ? over : 0) * A.sk];
-      }
-#pragma unroll
-      for (int p = 0; p < T::EB; ++p) {
-        const int k = B_KFAST ? (tid + 256 * p) % kGemmBK : (tid + 256 * p) / T::BN;
-        const int over = k0 + k - (kend - 1);
-        rb[SET][p] = B.p[offb[p] - (over > 0 ? over : 0) * B.sk];
-      }
+      la.template load<true>(ra[SET], kend - k0);
+      lb.template load<true>(rb[SET], kend - k0);
     }
-#pragma unroll
-    for (int p = 0; p < T::EA; ++p) offa[p] += stepa;
-#pragma unroll
-    for (int p = 0; p < T::EB; ++p) offb[p] += stepb;
   };
   // the same for a tile known to lie inside [kbeg, kend): no branch
   auto fetch_inner = [&](auto set) {
     constexpr int SET = decltype(set)::value;
-#pragma unroll
-    for (int p = 0; p < T::EA; ++p) ra[SET][p] = A.p[offa[p]];
-#pragma unroll
-    for (int p = 0; p < T::EB; ++p) rb[SET][p] = B.p[offb[p]];
-#pragma unroll
-    for (int p = 0; p < T::EA; ++p) offa[p] += stepa;
-#pragma unroll
-    for (int p = 0; p < T::EB; ++p) offb[p] += stepb;
+    la.template load<false>(ra[SET], kGemmBK);
+    lb.template load<false>(rb[SET], kGemmBK);
   };
   auto stash = [&](auto set, int k0, double* st) {
     constexpr int SET = decltype(set)::value;
@@ -296,6 +309,8 @@ __device__ __forceinline__ void dgemm_mainloop_pipelined(f64x4 (&acc)[TM][TN], D
                                                          double* smem) {
   using T = DgemmTile<TM, TN>;
   constexpr int EA = T::EA, EB = T::EB, E = EA + EB, MM = TM * TN;
+  // (the caller has seen that the tile's footprint in both operands is below 2^31 bytes)
+  const int aso = (int)A.so, ask = (int)A.sk, bso = (int)B.so, bsk = (int)B.sk;
   static_assert(E <= 2 * MM, "loads of a k-tile are spread over the MFMAs of its first two k-steps");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -306,19 +321,19 @@ __device__ __forceinline__ void dgemm_mainloop_pipelined(f64x4 (&acc)[TM][TN], D
   if (ntile <= 0) return;
 
   // buffer resources based at the lowest address the tile touches (strides may be negative)
-  const int64_t loa = (A.so < 0 ? (int64_t)(T::BM - 1) * A.so : 0) + (A.sk < 0 ? (int64_t)(K - 1) * A.sk : 0);
-  const int64_t lob = (B.so < 0 ? (int64_t)(T::BN - 1) * B.so : 0) + (B.sk < 0 ? (int64_t)(K - 1) * B.sk : 0);
+  const int64_t loa = (A.so < 0 ? (T::BM - 1) * A.so : 0) + (A.sk < 0 ? (K - 1) * A.sk : 0);
+  const int64_t lob = (B.so < 0 ? (T::BN - 1) * B.so : 0) + (B.sk < 0 ? (K - 1) * B.sk : 0);
   const __amdgpu_buffer_rsrc_t ra_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<double*>(A.p + (int64_t)kbeg * A.sk + loa), 0, (int)0xFFFFFFFFu, 0x00020000);
+      const_cast<double*>(A.p + kbeg * A.sk + loa), 0, (int)0xFFFFFFFFu, 0x00020000);
   const __amdgpu_buffer_rsrc_t rb_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<double*>(B.p + (int64_t)kbeg * B.sk + lob), 0, (int)0xFFFFFFFFu, 0x00020000);
+      const_cast<double*>(B.p + kbeg * B.sk + lob), 0, (int)0xFFFFFFFFu, 0x00020000);
   int voa[EA], vob[EB], lda[EA], ldb[EB];
 #pragma unroll
   for (int p = 0; p < EA; ++p) {
     const int e = tid + 256 * p;
     const int i = A_KFAST ? e / kGemmBK : e % T::BM;
     const int k = A_KFAST ? e % kGemmBK : e / T::BM;
-    voa[p] = (i * A.so + k * A.sk - (A.so < 0 ? (T::BM - 1) * A.so : 0) - (A.sk < 0 ? (kGemmBK - 1) * A.sk : 0)) * 8;
+    voa[p] = (i * aso + k * ask - (aso < 0 ? (T::BM - 1) * aso : 0) - (ask < 0 ? (kGemmBK - 1) * ask : 0)) * 8;
     lda[p] = k * T::PA + i;
   }
 #pragma unroll
@@ -326,12 +341,12 @@ __device__ __forceinline__ void dgemm_mainloop_pipelined(f64x4 (&acc)[TM][TN], D
     const int e = tid + 256 * p;
     const int j = B_KFAST ? e / kGemmBK : e % T::BN;
     const int k = B_KFAST ? e % kGemmBK : e / T::BN;
-    vob[p] = (j * B.so + k * B.sk - (B.so < 0 ? (T::BN - 1) * B.so : 0) - (B.sk < 0 ? (kGemmBK - 1) * B.sk : 0)) * 8;
+    vob[p] = (j * bso + k * bsk - (bso < 0 ? (T::BN - 1) * bso : 0) - (bsk < 0 ? (kGemmBK - 1) * bsk : 0)) * 8;
     ldb[p] = kGemmBK * T::PA + k * T::PB + j;
   }
   // scalar byte offset of the k-tile about to be requested
-  int soa = (A.sk < 0 ? -(K - kGemmBK) * A.sk : 0) * 8, sob = (B.sk < 0 ? -(K - kGemmBK) * B.sk : 0) * 8;
-  const int stepa = kGemmBK * A.sk * 8, stepb = kGemmBK * B.sk * 8;
+  int soa = (ask < 0 ? -(K - kGemmBK) * ask : 0) * 8, sob = (bsk < 0 ? -(K - kGemmBK) * bsk : 0) * 8;
+  const int stepa = kGemmBK * ask * 8, stepb = kGemmBK * bsk * 8;
 
   double ra[2][EA], rb[2][EB];
   auto request = [&](int set) {

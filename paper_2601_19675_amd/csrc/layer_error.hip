@@ -27,7 +27,7 @@ struct ErrArgs {
   const double* A2;  // [2][m][n]: D = W - Wq, then W, both widened to float64
   int m, n;
   const double* H;
-  int ldh;
+  int64_t ldh;
   double* partial;  // [2][tiles]
 };
 
@@ -700,7 +700,7 @@ ptq_status layer_error_launch(const void* W, ptq_dtype wdt, int64_t ldw, const d
   double* A2 = reinterpret_cast<double*>(static_cast<char*>(ws) + partial_bytes(m, n));
   const unsigned wg = (unsigned)ceil_div(m * n, 256);
   widen_kernel<<<wg, 256, 0, st>>>(static_cast<const double*>(W), ldw, Wq, (int)m, (int)n, A2);
-  ErrArgs a{A2, (int)m, (int)n, H, (int)ldh, partial};
+  ErrArgs a{A2, (int)m, (int)n, H, ldh, partial};
   dim3 g(2 * (unsigned)ceil_div(m, Tile::BM), (unsigned)ceil_div(n, Tile::BN));
   const int tiles = (int)(g.x / 2 * g.y);
   constexpr int lds = Tile::kSmemDoubles * (int)sizeof(double);

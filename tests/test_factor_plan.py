@@ -47,3 +47,14 @@ def test_wide_nodes_of_long_rows():
     # a node of 128 x 128 tiles, halves that go on halving: the early part of panel and update beside the second half of the first child
     capped = [l for l in _launches(8192, (1 << 20) + 1) if "ILi4ELi4ELb1E" in l["kernel"]]
     assert sorted(l["grid"][0] for l in capped) == [128, 192, 192]   # T, and the early part's two
+
+
+@pytest.mark.parametrize("n", [100, 129, 300])
+def test_row_length_past_31_bits(n):
+    ws = ptq.ptq_workspace_bytes(binding.OP_CHOLESKY_INV, 0, n)
+    ldu = (1 << 31) + 16
+    (rc, launches), = record([("ptq_damped_cholesky_inv", [PTR, n, n, 0.01, PTR, ldu, 0, PTR, PTR, ws, 0])],
+                             read={"step_kernel": dict(ldu=(0, "q", 16)), "node_gemm": dict(ldu=(0, "q", 16))})
+    assert rc == 0
+    rows = [l["ldu"] for l in launches if "ldu" in l]
+    assert rows and all(r == ldu for r in rows)

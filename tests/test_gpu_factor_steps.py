@@ -60,6 +60,12 @@ def test_factor_of_long_rows(n):
     _check(n, (1 << 20) + 1 - n)
 
 
+@pytest.mark.parametrize("n,ldu", [(140, (1 << 25) + 1), (4400, (1 << 20) + 1)])
+def test_factor_of_rows_past_31_bits(n, ldu):
+    """U of 37 GB: offsets across a tile's rows, and down the columns of a node, that 31 bits do not hold."""
+    _check(n, ldu - n)
+
+
 def test_factor_of_halves_in_steps():
     n = 5150
     H = _case(n, 5)
