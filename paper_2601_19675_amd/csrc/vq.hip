@@ -74,12 +74,14 @@ __device__ __forceinline__ int half_wave_min(int v) {
   return min((int)p[0], (int)p[1]);
 }
 
-// Blocks of up to 128 columns: the block of U itself, upper tiles of 16 x 16, is staged in LDS before the walk.  Fetched
+// Blocks of 48 to 128 columns: the block of U itself, upper tiles of 16 x 16, is staged in LDS before the walk.  Fetched
 // per mini-block it had to be held in registers that the walk does not have: spilled, every request waited for
 // the one before, 5000 cycles before and 2500 after the 7400 of a mini-block's walk at 4096 x 4096, 256 x 4.
-// (Where a lane holds fewer entries nothing spills and the staging costs more than it gives: 64 x 2 2490 us, staged 2604.)
+// (Where a lane holds fewer entries nothing spills and the staging costs more than it gives: 64 x 2 2490 us, staged 2604.
+// Nor does it pay for blocks of one or two tiles, which ask for the next mini-block's U once or not at all: in a form of
+// their own, 4096 x 1024, 256 x 4, blocks of 16 1067 us, staged 1726, and of 32 765, staged 1005; of 48 staged 833, 881.)
 template <int NT, int D, int SLOTS, bool RAGGED>
-constexpr bool vq_staged() { return NT <= 8 && SLOTS * D >= 32 && !RAGGED; }
+constexpr bool vq_staged() { return NT == 8 && SLOTS * D >= 32 && !RAGGED; }
 // tile (r, c), r <= c, in row order; their number; the r and c of number i
 __host__ __device__ constexpr int upper_tile(int nt, int r, int c) { return r * nt - r * (r - 1) / 2 + c - r; }
 __host__ __device__ constexpr int upper_tiles(int nt) { return nt * (nt + 1) / 2; }
@@ -418,6 +420,13 @@ ptq_status vq_run_blocks_with(VqArgs a, int block, hipStream_t st) {
     a.i1 = i1;
     a.bw = (a.n - i1 < block) ? a.n - i1 : block;
     // (one form of the ragged kernel, for all widths and codebooks: it takes a layer's last block only)
+    if constexpr (vq_staged<8, D, SLOTS, false>()) {
+      if (a.bw == 16 || a.bw == 32) {
+        const ptq_status rc = vq_launch_block<DT, 2, D, SLOTS>(a, st);
+        if (rc != PTQ_OK) return rc;
+        continue;
+      }
+    }
     const ptq_status rc = a.bw % 16 != 0 ? vq_launch_block<DT, 16, D, kMaxEntries / 32, true>(a, st)
                           : a.bw <= 128  ? vq_launch_block<DT, 8, D, SLOTS>(a, st)
                                          : vq_launch_block<DT, 16, D, SLOTS>(a, st);

@@ -1,5 +1,5 @@
-"""The vector walk with its block of U in LDS (codebooks of more than 64 entries of 4 weights, blocks of up to 128 columns):
-blocks of one to eight tiles, last blocks that are narrower, ragged rows, dead columns."""
+"""The vector walk of codebooks of more than 64 entries of 4 weights: the form that has its block of U in LDS (blocks of three to
+eight tiles), the one for one or two tiles, the one for more than eight; last blocks that are narrower, ragged rows, dead columns."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,n,block,entries", [(3, 16, 16, 65), (17, 112, 48, 100), (16, 240, 112, 256), (33, 208, 128, 200),
-                                               (20, 384, 128, 256), (18, 160, 256, 256)])
+                                               (20, 384, 128, 256), (18, 160, 256, 256),
+                                               (19, 96, 32, 256), (35, 160, 128, 90), (9, 176, 96, 256)])
 def test_staged_walk(m, n, block, entries):
     rng = np.random.default_rng(10 * n + entries)
     W = rng.normal(0, 0.02, (m, n))
