@@ -31,7 +31,7 @@ def _hipcc() -> str:
 
 
 def check_dpp_wait_states(asm_text: str) -> int:
-    """The leaf kernel of cholesky.hip issues DPP instructions from inline assembly, where the compiler
+    """The leaf of cholesky.hip's factor issues DPP instructions from inline assembly, where the compiler
     does not count wait states: a DPP read needs two (two instructions, or s_nop) after a vector
     instruction wrote the register it reads.  The source keeps that distance by construction; this walks
     the generated assembly and raises if the compiler has put something closer (a copy into an

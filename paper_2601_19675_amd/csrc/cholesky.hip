@@ -57,7 +57,9 @@ __global__ __launch_bounds__(1024) void diag_stats_kernel(const double* __restri
   }
 }
 
-// G = J H_d J (lower triangle) and U's lower triangle cleared; the other halves are written before they are read.
+// G = J H_d J (lower triangle) and U's lower triangle cleared.  Entries of the other halves (and of blocks beside a ragged
+// tile) may be read before they are written, as whatever the workspace holds, NaN included: only into entries of a product
+// that are not stored.  An entry of a product depends on its own row of A and column of B alone.
 __global__ __launch_bounds__(256) void build_work_kernel(const double* __restrict__ H, int64_t ldh,
                                                          int n, const double* __restrict__ scal,
                                                          double* __restrict__ G, double* __restrict__ U,
@@ -1134,20 +1136,22 @@ bool launch_node2(const Op1& op1, int M1, int N1, const Op2& op2, int M2, int N2
 
 // ---- helper streams for work that is off the critical chain -----------------------------------
 // The chain  leaf -> panel -> update -> leaf ...  of a half of a node is a sequence of small,
-// latency-bound launches that leaves most of the chip idle.  For the largest nodes (128 x 128 tiles)
-// two pieces of the node's own work run beside those chains, each on a stream of its own with a cap
-// on its workgroups, so that the chain's launches always find free compute units:
+// latency-bound launches that leaves most of the chip idle, or of steps whose update fills it only in part.  For the
+// largest nodes (128 x 128 tiles) two pieces of the node's own work run beside those chains, each on a stream of its own
+// with a cap on its workgroups, so that the chain finds compute units (a step's update asks for all of them and gets
+// what the cap leaves: under 11008 columns a full step takes 62 us, alone some 33):
 //  * beside the chain of the SECOND half:  T = L21 X11  (a quarter of the node's flops), which is
 //    needed only by the node's last step -- forked after the trailing update, joined before
-//    X21 = -X22 T  (cap kSideCus; measured at n = 11008: 128 gives the shortest total, 256 gains
-//    nothing, 64 makes T the longer path);
+//    X21 = -X22 T  (cap kSideCus; n = 11008 with 64 / 96 / 128 / 160 / 192 / 255: 21.4 / 17.8 / 16.18 / 16.34 / 16.22 /
+//    16.6 ms, the least of them makes T the longer path; n = 12288 31.7 / 26.0 / 23.5 / 21.9 / 22.1 / 22.9);
 //  * beside the second half of the FIRST half's recursion:  the early part of the node's panel and
 //    update.  Once the first half A = [o, o + sA) of the first child is inverted, the columns
 //    [0, sA) of L21 = G21 X11^T are computable (X11 is lower triangular: they need X_A only), and so
 //    is their share  G22 -= L21[:, :sA] L21[:, :sA]^T  of the update.  The child signals that point
 //    (`on_first_half`), the early part runs on its stream, and after the child the node finishes
 //    the panel (columns [sA, s1)) and the update (k in [sA, s1)) on the caller's stream (cap
-//    kEarlyCus; n = 11008: 18.0 ms without, 17.9 / 17.4 / 17.5 / 17.6 ms with 128 / 160 / 192 / 224;
+//    kEarlyCus; n = 11008 with 96 / 128 / 160 / 192 / 224: 17.9 / 16.8 / 16.0 / 16.2 / 16.3 ms, n = 12288 25.6 / 23.9 /
+//    23.3 / 23.5 / 23.4;
 //    only where the first half is itself halved: one that goes 128 columns at a time has no such point; n = 8192 in
 //    two blocks of steps takes 8.1 ms).
 // Smaller nodes gain nothing (measured) and keep one stream, with T in the update's launch.  The

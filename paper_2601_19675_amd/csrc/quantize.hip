@@ -365,9 +365,10 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
   // results -- codes, dequantized values, errors for the later blocks, row sums -- runs beside the walk, one mini-block
   // later where it needs the results.  A mini-block in cycles, 512 x 512, with all of it in the walking wave's own
   // stream and now: requests and the group's start of its grid 630 / 290, state and pivots from LDS 390 / 150, the walk
-  // 3350 / 2480, push 600 - 860 / 620, stores and barriers 600 / 420.  Whole calls 512 x 512 114 -> 92 us, 4096 x 4096
-  // 1804 -> 1692, 11008 x 4096 4098 -> 3859, 4096 x 11008 9760 -> 9492; the same bits.  (Raised priority of the walking
-  // wave and of the push that it waits for: 9554.)
+  // 3350 / 2480, push 600 - 860 / 620, stores and barriers 600 / 420.  Whole calls 512 x 512 110 -> 87 us, 4096 x 4096
+  // 1679 -> 1574, 8192 x 4096 2988 -> 2734, 11008 x 4096 3947 -> 3703, 4096 x 11008 9670 -> 9400; the same bits.  (Three row
+  // tiles with blocks of 16 or 32 columns are 1 to 2 % slower so: 9217 x 2048 6440 -> 6560, 3390 -> 3430.  Raised priority
+  // of the walking wave and of the push that it waits for: 0.7 % slower, 4096 x 11008.)
   typedef double f64x2 __attribute__((vector_size(16)));
   const double maxq = (double)((1 << a.bits) - 1);
   const int ng = a.n / a.group;
@@ -375,7 +376,7 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
   double scale = 1.0, rscale = 1.0, zero = 0.0, klo = 0.0, khi = 0.0;   // lanes 0 .. rows - 1 of wave 0
   double err2 = 0.0;                                                    // ... of wave 1
   // Up to eight tiles: wave t pushes the errors of every mini-block before it onto tile t of the state, which it keeps in
-  // registers until it is walked (one row tile; with more the registers run out: 8192 x 4096 2970 -> 3210 us).  Only the
+  // registers until it is walked (one row tile; with more the registers run out: 8192 x 4096 2925 -> 3209 us).  Only the
   // tile that is walked next has to be done before the walk goes on; the others follow beside it.  More tiles than
   // waves: all waves push, tile by tile, between the walks.
   constexpr bool kOwn = NT <= kWaves, kKeep = kOwn && MT == 1;
@@ -589,7 +590,8 @@ __device__ __forceinline__ void quant_block(const QuantArgs& a, double* lds) {
     }
     __syncthreads();
     if constexpr (kOwn) {
-      // onto the tile that is walked next; onto all of them if the next walk begins with a look at its group
+      // onto the tile that is walked next; onto all of them if a group begins with it (its grid is taken from them, unless
+      // it is given)
       if (role == mb + 1 || (group_left == 0 && role > mb)) {
         if (role < nt) push(mb, 0, role, true);
       }

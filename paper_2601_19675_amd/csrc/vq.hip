@@ -14,10 +14,10 @@
 // codebook in LDS.  Every lane then knows the group's errors and applies them to the later columns of the
 // mini-block itself, so the eight waves walk their two rows each without a barrier between groups.
 // Bound: float64 vector instructions of the losses (18 and a selection per entry of 4 weights) and the
-// chain from a group's losses to the next group's values.  4096 x 4096, 256 x 4: 4.13 -> 3.39 -> 3.11 ms; 64 x 2: 4.12 ->
-// 2.62 -> 2.49 (first: lane permutes through the LDS crossbar, the entry taken out of registers, conditional loads, and
-// room for 256 entries in every lane whatever K; then: U and addresses spilled over the walk, an address for every
-// pair read of U, entries tested against K one by one).  A group of the former now takes 1800 cycles.
+// chain from a group's losses to the next group's values.  4096 x 4096, both sides in one run: 256 x 4 3303 -> 2883 us, 64 x 2
+// 2441 -> 2276 (before: U and addresses spilled over the walk, an address for every pair read of U, entries tested
+// against K one by one; 4.1 ms both with lane permutes through the LDS crossbar, the entry taken out of registers,
+// conditional loads, and room for 256 entries in every lane whatever K).  A group of the former takes 1800 cycles.
 #include "lazy_update.h"
 #include "rotation.h"
 
@@ -77,7 +77,7 @@ __device__ __forceinline__ int half_wave_min(int v) {
 // Blocks of 48 to 128 columns: the block of U itself, upper tiles of 16 x 16, is staged in LDS before the walk.  Fetched
 // per mini-block it had to be held in registers that the walk does not have: spilled, every request waited for
 // the one before, 5000 cycles before and 2500 after the 7400 of a mini-block's walk at 4096 x 4096, 256 x 4.
-// (Where a lane holds fewer entries nothing spills and the staging costs more than it gives: 64 x 2 2490 us, staged 2604.
+// (Where a lane holds fewer entries nothing spills and the staging costs 5 % more than it gives, 64 x 2.
 // Nor does it pay for blocks of one or two tiles, which ask for the next mini-block's U once or not at all: in a form of
 // their own, 4096 x 1024, 256 x 4, blocks of 16 1067 us, staged 1726, and of 32 765, staged 1005; of 48 staged 833, 881.)
 template <int NT, int D, int SLOTS, bool RAGGED>
